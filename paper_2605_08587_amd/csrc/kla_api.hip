@@ -88,6 +88,10 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
 
 int scan_waves(int n_chains, int dv, int dt, const Tune& tune);
 
+// fp32 sweeps (kla_chunk_sweeps_f32.hip): column tiles per workgroup.  Four waves share a tile whatever the number; with
+// more tiles than CUs two per workgroup halve the LDS reads of every product, with fewer they would leave CUs idle.
+inline int f32_tiles(long n_tiles) { return n_tiles > 256 ? 2 : 1; }
+
 // Validates the size arguments shared by the chunk entry points and lays out the workspace.
 int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int32_t* cu_host, int n_seq, unsigned opts, Plan* p)
 {
@@ -143,6 +147,7 @@ int scan_waves(int n_chains, int dv, int dt, const Tune& tune)
 {
     int w;
     if (tune.scan_waves) w = tune.scan_waves;        // tuning field: 1, 2 or 4 waves (16 state columns each) per workgroup
+    else if (dt == KLA_F32) w = f32_tiles((long)n_chains * (dv / 16));
     else {
         // enough workgroups to cover the 256 CUs, else the widest slice that still gives >= 2 waves of loaders
         // workgroups for w waves: chains8 * dv / (16 w).  Wide slices halve the operand re-reads but need
@@ -151,7 +156,7 @@ int scan_waves(int n_chains, int dv, int dt, const Tune& tune)
         const long wg1 = chains8 * (dv / 16);
         w = (wg1 / 4 >= 512) ? 4 : ((wg1 / 2 >= 192) ? 2 : 1);
     }
-    if (dt == KLA_F32 && w > 2) w = 2;            // fp32 operands take twice the LDS
+    if (dt == KLA_F32 && w > 2) w = 2;            // fp32: column tiles per workgroup, 1 or 2
     while (16 * w > dv) w >>= 1;
     return w;
 }
@@ -232,8 +237,8 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
         if (!pl.tune.generic_scan)                       // else the element-type-generic kernel (A/B testing)
             return kla::launch_scan_bf16(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
-    if (kla::launch_scan<E>(sa, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
-    return KLA_OK;
+    if constexpr (sizeof(E) == 4) return kla::launch_scan_f32(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+    else                          return kla::launch_scan(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
 }
 
 // ---- backward pass ---------------------------------------------------------------------------------
@@ -357,8 +362,14 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    if (kla::launch_bwd_states<E>(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
-    if (kla::launch_bwd_scan<E>(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
+    if constexpr (sizeof(E) == 4) {
+        const int tiles = f32_tiles((long)pl.base.n_states * H * (dv / 16));
+        if (kla::launch_bwd_states_f32(ba, dk, tiles, st) != hipSuccess) return KLA_ERR_HIP;
+        if (kla::launch_bwd_scan_f32(ba, dk, tiles, st) != hipSuccess) return KLA_ERR_HIP;
+    } else {
+        if (kla::launch_bwd_states(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
+        if (kla::launch_bwd_scan(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
+    }
     if (kla::launch_bwd_assemble<E>(ba, dk, pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     return KLA_OK;
 }
@@ -419,7 +430,10 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
         if (!pl.base.tune.generic_scan)                  // else the element-type-generic kernel (A/B testing)
             return kla::launch_scan_bf16_diag(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
-    return kla::launch_scan_diag<E>(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+    if constexpr (sizeof(E) == 4)
+        return kla::launch_scan_f32(sa, dk, f32_tiles((long)pl.base.n_states * H * (dv / 16)), st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+    else
+        return kla::launch_scan_diag(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
 }
 
 // ---- scratch of the entry point that allocates nothing (kla_chunk_fwd_static) --------------------------

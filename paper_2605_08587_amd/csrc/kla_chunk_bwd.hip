@@ -19,6 +19,8 @@
 //   bwd_states_kernel    forward over the chunks of a (sequence, head, column slice): S_c, X, U        -> workspace
 //   bwd_scan_kernel      backward over the same chunks: dS'_c, Y -> workspace, dv and dh0 -> outputs
 //   bwd_assemble_kernel  per chunk-head: the contractions over d_v and over the chunk -> dq, dk, dlog_alpha, deta
+// These two are the plain form of the sweeps, kept for bf16 as the A/B reference (KLA_TUNE_GENERIC_BWD); fp32 runs those of
+// kla_chunk_sweeps_f32.hip and shares the third kernel.
 // The two sweeps treat state columns independently (as the forward does); everything that contracts over d_v is
 // left to the third kernel, so no atomics are needed and the result is run-to-run deterministic.
 #include "kla_common.hpp"
@@ -789,36 +791,30 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
 // =================================================================================================
 // launchers
 // =================================================================================================
-template <typename E, int DK>
-static hipError_t launch_states_dk(const BwdArgs<E>& a, int waves, hipStream_t st)
+template <int DK>
+static hipError_t launch_sweep_dk(const BwdArgs<bf16_t>& a, int waves, bool reverse, hipStream_t st)
 {
     const int n_chains = (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
     if (n_chains == 0) return hipSuccess;
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
-    if (waves == 1) hipLaunchKernelGGL((bwd_states_kernel<E, DK, 1>), grid, dim3(64), 0, st, a);
-    else            hipLaunchKernelGGL((bwd_states_kernel<E, DK, 2>), grid, dim3(128), 0, st, a);
+    if (reverse) {
+        if (waves == 1) hipLaunchKernelGGL((bwd_scan_kernel<bf16_t, DK, 1>), grid, dim3(64), 0, st, a);
+        else            hipLaunchKernelGGL((bwd_scan_kernel<bf16_t, DK, 2>), grid, dim3(128), 0, st, a);
+    } else {
+        if (waves == 1) hipLaunchKernelGGL((bwd_states_kernel<bf16_t, DK, 1>), grid, dim3(64), 0, st, a);
+        else            hipLaunchKernelGGL((bwd_states_kernel<bf16_t, DK, 2>), grid, dim3(128), 0, st, a);
+    }
     return hipGetLastError();
 }
-template <typename E, int DK>
-static hipError_t launch_scan_dk(const BwdArgs<E>& a, int waves, hipStream_t st)
-{
-    const int n_chains = (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
-    if (n_chains == 0) return hipSuccess;
-    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
-    if (waves == 1) hipLaunchKernelGGL((bwd_scan_kernel<E, DK, 1>), grid, dim3(64), 0, st, a);
-    else            hipLaunchKernelGGL((bwd_scan_kernel<E, DK, 2>), grid, dim3(128), 0, st, a);
-    return hipGetLastError();
-}
-
-template <typename E> hipError_t launch_bwd_states(const BwdArgs<E>& a, int dk, int waves, hipStream_t st)
+hipError_t launch_bwd_states(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
     if (waves != 1 && waves != 2) return hipErrorInvalidValue;
-    return dk == 64 ? launch_states_dk<E, 64>(a, waves, st) : launch_states_dk<E, 128>(a, waves, st);
+    return dk == 64 ? launch_sweep_dk<64>(a, waves, false, st) : launch_sweep_dk<128>(a, waves, false, st);
 }
-template <typename E> hipError_t launch_bwd_scan(const BwdArgs<E>& a, int dk, int waves, hipStream_t st)
+hipError_t launch_bwd_scan(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
     if (waves != 1 && waves != 2) return hipErrorInvalidValue;
-    return dk == 64 ? launch_scan_dk<E, 64>(a, waves, st) : launch_scan_dk<E, 128>(a, waves, st);
+    return dk == 64 ? launch_sweep_dk<64>(a, waves, true, st) : launch_sweep_dk<128>(a, waves, true, st);
 }
 template <typename E> hipError_t launch_bwd_assemble(const BwdArgs<E>& a, int dk, long n_chunks, hipStream_t st)
 {
@@ -828,10 +824,6 @@ template <typename E> hipError_t launch_bwd_assemble(const BwdArgs<E>& a, int dk
     else          hipLaunchKernelGGL((bwd_assemble_kernel<E, 128>), grid, block, 0, st, a);
     return hipGetLastError();
 }
-template hipError_t launch_bwd_states<float>(const BwdArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_bwd_states<bf16_t>(const BwdArgs<bf16_t>&, int, int, hipStream_t);
-template hipError_t launch_bwd_scan<float>(const BwdArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_bwd_scan<bf16_t>(const BwdArgs<bf16_t>&, int, int, hipStream_t);
 template hipError_t launch_bwd_assemble<float>(const BwdArgs<float>&, int, long, hipStream_t);
 template hipError_t launch_bwd_assemble<bf16_t>(const BwdArgs<bf16_t>&, int, long, hipStream_t);
 

@@ -17,8 +17,11 @@
 //
 // The chunk loop is the only serial dependency of the whole forward, so its latency is what
 // counts: the next chunk's operands are fetched from global memory into registers before the
-// current chunk's products are issued, and (bf16) written to the other half of a double-buffered
+// current chunk's products are issued, and written to the other half of a double-buffered
 // LDS area afterwards, leaving one barrier per chunk.
+//
+// This is the plain form, kept for bf16 as the A/B reference (KLA_TUNE_GENERIC_SCAN) of the specialised kernel in
+// kla_chunk_scan_bf16.hip; fp32 inputs run kla_chunk_sweeps_f32.hip.
 #include "kla_common.hpp"
 #include "kla_kernels.hpp"
 #include "kla_mma.hpp"
@@ -51,8 +54,7 @@ struct ScanCfg {
     static constexpr int OFF_Q = OPB, OFF_KT = 2 * OPB, OFF_T = 3 * OPB, OFF_P = OFF_T + TPB, OFF_V = OFF_P + TPB,
                          OFF_EG = OFF_V + VB, OFF_ED = OFF_EG + 256, OFF_EQ = OFF_ED + 256, OFF_GC = OFF_EQ + 256,
                          STAGE = OFF_GC + 512;        // OFF_GC: gamma_C per channel (diagonal gating only)
-    static constexpr int STAGES = sizeof(E) == 2 ? 2 : 1;      // fp32 operands take twice the LDS: single buffer
-    static constexpr int LDS = STAGES * (STAGE + OSB);
+    static constexpr int LDS = 2 * (STAGE + OSB);               // double buffer
     static constexpr int UK = (16 * PPR + NTH - 1) / NTH;       // (4-row group, piece) units of K/Q per thread
     static constexpr int UV = (16 * VPP + NTH - 1) / NTH;
     static constexpr int TP16 = TPB / 16;                       // 16-byte pieces of a T'/P area
@@ -304,40 +306,26 @@ __global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
     };
 
     Prefetch<E, DK, NW, DIAG> pf;
-    if constexpr (C::STAGES == 2) {
-        char* stage0 = lds;
-        char* stage1 = lds + C::STAGE;
-        E* ost0 = reinterpret_cast<E*>(lds + 2 * C::STAGE);
-        E* ost1 = reinterpret_cast<E*>(lds + 2 * C::STAGE + C::OSB);
-        if (nch > 0) { fetch(0, pf); stash(pf, stage0); }
+    char* stage0 = lds;
+    char* stage1 = lds + C::STAGE;
+    E* ost0 = reinterpret_cast<E*>(lds + 2 * C::STAGE);
+    E* ost1 = reinterpret_cast<E*>(lds + 2 * C::STAGE + C::OSB);
+    if (nch > 0) { fetch(0, pf); stash(pf, stage0); }
+    __syncthreads();
+    for (int c = 0; c < nch; ++c) {
+        char* cur = (c & 1) ? stage1 : stage0;
+        char* nxt = (c & 1) ? stage0 : stage1;
+        E* ost = (c & 1) ? ost1 : ost0;
+        const bool more = c + 1 < nch;
+        if (more) fetch(c + 1, pf);                      // in flight while this chunk's products run
+        compute(cur, ost);
+        if (more) stash(pf, nxt);
+        // One barrier per chunk.  It orders (i) this chunk's staged outputs before their write-out,
+        // (ii) the next chunk's operands before their use, (iii) all reads of `cur` before it is
+        // overwritten one iteration later, and (iv) the write-out of chunk c-1 (done by every wave
+        // before it arrives here) before `ost` of that parity is staged again in chunk c+1.
         __syncthreads();
-        for (int c = 0; c < nch; ++c) {
-            char* cur = (c & 1) ? stage1 : stage0;
-            char* nxt = (c & 1) ? stage0 : stage1;
-            E* ost = (c & 1) ? ost1 : ost0;
-            const bool more = c + 1 < nch;
-            if (more) fetch(c + 1, pf);                  // in flight while this chunk's products run
-            compute(cur, ost);
-            if (more) stash(pf, nxt);
-            // One barrier per chunk.  It orders (i) this chunk's staged outputs before their write-out,
-            // (ii) the next chunk's operands before their use, (iii) all reads of `cur` before it is
-            // overwritten one iteration later, and (iv) the write-out of chunk c-1 (done by every wave
-            // before it arrives here) before `ost` of that parity is staged again in chunk c+1.
-            __syncthreads();
-            write_out(c, ost);
-        }
-    } else {
-        char* stage0 = lds;
-        E* ost = reinterpret_cast<E*>(lds + C::STAGE);
-        for (int c = 0; c < nch; ++c) {
-            __syncthreads();                             // previous chunk's operands and staging tile are free
-            fetch(c, pf);
-            stash(pf, stage0);
-            __syncthreads();
-            compute(stage0, ost);
-            __syncthreads();
-            write_out(c, ost);
-        }
+        write_out(c, ost);
     }
 
     if (a.hT) {
@@ -349,8 +337,8 @@ __global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
     }
 }
 
-template <typename E, int DK, bool DIAG>
-static hipError_t launch_scan_dk(const ScanArgs<E>& a, int waves, hipStream_t st)
+template <int DK, bool DIAG>
+static hipError_t launch_scan_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st)
 {
     const int n_states = a.n_seq > 0 ? a.n_seq : a.N;
     const int n_chains = n_states * a.H;
@@ -358,31 +346,25 @@ static hipError_t launch_scan_dk(const ScanArgs<E>& a, int waves, hipStream_t st
     const int nsl = a.dv / (16 * waves);
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * nsl));
     switch (waves) {
-        case 1: hipLaunchKernelGGL((scan_kernel<E, DK, 1, DIAG>), grid, dim3(64), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((scan_kernel<E, DK, 2, DIAG>), grid, dim3(128), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 1, DIAG>), grid, dim3(64), 0, st, a); break;
+        case 2: hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 2, DIAG>), grid, dim3(128), 0, st, a); break;
         default:
-            if constexpr (sizeof(E) == 2 && !DIAG) { hipLaunchKernelGGL((scan_kernel<E, DK, 4, false>), grid, dim3(256), 0, st, a); break; }
+            if constexpr (!DIAG) { hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 4, false>), grid, dim3(256), 0, st, a); break; }
             else return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template <typename E> hipError_t launch_scan(const ScanArgs<E>& a, int dk, int waves, hipStream_t st)
+hipError_t launch_scan(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (dk == 64) return launch_scan_dk<E, 64, false>(a, waves, st);
-    return launch_scan_dk<E, 128, false>(a, waves, st);
+    return dk == 64 ? launch_scan_dk<64, false>(a, waves, st) : launch_scan_dk<128, false>(a, waves, st);
 }
-template hipError_t launch_scan<float>(const ScanArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_scan<bf16_t>(const ScanArgs<bf16_t>&, int, int, hipStream_t);
 
 // diagonal gating: waves = 1 or 2
-template <typename E> hipError_t launch_scan_diag(const ScanArgs<E>& a, int dk, int waves, hipStream_t st)
+hipError_t launch_scan_diag(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
     if (waves != 1 && waves != 2) return hipErrorInvalidValue;
-    if (dk == 64) return launch_scan_dk<E, 64, true>(a, waves, st);
-    return launch_scan_dk<E, 128, true>(a, waves, st);
+    return dk == 64 ? launch_scan_dk<64, true>(a, waves, st) : launch_scan_dk<128, true>(a, waves, st);
 }
-template hipError_t launch_scan_diag<float>(const ScanArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_scan_diag<bf16_t>(const ScanArgs<bf16_t>&, int, int, hipStream_t);
 
 }  // namespace kla

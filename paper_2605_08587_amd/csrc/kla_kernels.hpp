@@ -66,15 +66,18 @@ template <typename E> struct ScanArgs {
     // sequence s / seg_G, seg_Lc chunks long (the last one of a sequence takes what is left), and h0 / hT are
     // indexed by segment.
     int seg_G, seg_Lc;
-    // Diagonal gating (generic kernel only): the transposed K operand of the state update comes from kt_src instead of
+    // Diagonal gating: the transposed K operand of the state update comes from kt_src instead of
     // k, and the state decays per row by gc_vec[chunk-head][dk] instead of by gamma_C.  Both NULL otherwise.
     const E* kt_src; const float* gc_vec;
     // Fused bf16 scan only (the stage forms T', P and the decay vectors itself; wsT, wsP, wsG unused): the gates.
     const float* log_alpha = nullptr; const float* eta = nullptr; float eps = 0.f;
 };
-// waves = 1, 2 or 4: each wave of a workgroup carries 16 state columns through the whole sequence
-template <typename E> hipError_t launch_scan(const ScanArgs<E>& a, int dk, int waves, hipStream_t st);
-template <typename E> hipError_t launch_scan_diag(const ScanArgs<E>& a, int dk, int waves, hipStream_t st);
+// bf16, plain form (A/B reference of the specialised kernel below): waves = 1, 2 or 4, each wave of a workgroup carries 16
+// state columns through the whole sequence
+hipError_t launch_scan(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
+hipError_t launch_scan_diag(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
+// fp32: tiles = 1 or 2 column tiles (16 state columns, shared by four waves) per workgroup; diagonal gating when a.kt_src is set
+hipError_t launch_scan_f32(const ScanArgs<float>& a, int dk, int tiles, hipStream_t st);
 
 // bf16 specialisations (direct global->LDS copies, swizzled token-major staging, transposing LDS reads)
 hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);
@@ -124,8 +127,10 @@ template <typename E> struct BwdArgs {
     // segment, [N * seg_G][H][dk][dv].
     int seg_G, seg_Lc;
 };
-template <typename E> hipError_t launch_bwd_states(const BwdArgs<E>& a, int dk, int waves, hipStream_t st);
-template <typename E> hipError_t launch_bwd_scan(const BwdArgs<E>& a, int dk, int waves, hipStream_t st);
+hipError_t launch_bwd_states(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);   // bf16, plain form
+hipError_t launch_bwd_scan(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
+hipError_t launch_bwd_states_f32(const BwdArgs<float>& a, int dk, int tiles, hipStream_t st);
+hipError_t launch_bwd_scan_f32(const BwdArgs<float>& a, int dk, int tiles, hipStream_t st);
 // bf16 specialisations of the two sweeps (copy wave, LDS ring, transposing reads: see kla_chunk_bwd_bf16.hip)
 hipError_t launch_intra_bwd_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);
 hipError_t launch_bwd_states_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
