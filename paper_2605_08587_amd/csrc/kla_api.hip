@@ -195,14 +195,18 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     }
     if (intra && n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, st) != hipSuccess) return KLA_ERR_HIP;
     if (intra) {
-        bool done = false;
+        [[maybe_unused]] bool done = false;
         if constexpr (sizeof(E) == 2) {
             if (!pl.tune.generic_intra) {                // else the element-type-generic kernel (A/B testing)
                 if (kla::launch_intra_bf16(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
                 done = true;
             }
         }
-        if (!done && kla::launch_intra<E>(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+        if constexpr (sizeof(E) == 4) {
+            if (kla::launch_intra_f32(ia, dk, false, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+        } else {
+            if (!done && kla::launch_intra(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+        }
     }
     if (unpack && kla::launch_unpack<E>(wsT, wsP, wsG, Tb_out, P_out, g_out, pl.n_chunks * H, st) != hipSuccess)
         return KLA_ERR_HIP;
@@ -300,7 +304,11 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     if constexpr (sizeof(E) == 2) {
         if (fast && kla::launch_intra_bwd_bf16(ia, dk, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     }
-    if (!fast && kla::launch_intra_bwd<E>(ia, dk, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+    if constexpr (sizeof(E) == 4) {
+        if (kla::launch_intra_f32(ia, dk, true, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+    } else {
+        if (!fast && kla::launch_intra_bwd(ia, dk, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+    }
 
     kla::BwdArgs<E> ba;
     ba.q = ia.q; ba.k = ia.k; ba.v = static_cast<const E*>(v);

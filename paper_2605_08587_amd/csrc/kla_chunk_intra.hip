@@ -14,6 +14,9 @@
 // (I + L)^{-1} is built in fp32: the four 16x16 diagonal blocks by forward substitution in LDS,
 // then the off-diagonal blocks by two levels of block products on fp32 MFMA,
 //   [T11 0; T21 T22] with T21 = -T22 (L21 T11).
+//
+// intra_kernel is the plain form, kept for bf16 as the A/B reference (KLA_TUNE_GENERIC_INTRA) of kla_chunk_intra_bf16.hip;
+// fp32 inputs run kla_chunk_intra_f32.hip.  The diagonal-gating stage below serves both element types.
 #include "kla_common.hpp"
 #include "kla_kernels.hpp"
 #include "kla_mma.hpp"
@@ -308,31 +311,25 @@ __global__ __launch_bounds__(256) void intra_kernel(IntraArgs<E> a)
     invert_and_store<E, BWD>(Lm, Tm, Pm, beta_s, reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC, tid);
 }
 
-template <typename E>
-hipError_t launch_intra(const IntraArgs<E>& a, int dk, int n_chunks, hipStream_t st)
+hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st)
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_kernel<E, 64, false>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_kernel<E, 128, false>), grid, block, 0, st, a);
+    if (dk == 64) hipLaunchKernelGGL((intra_kernel<bf16_t, 64, false>), grid, block, 0, st, a);
+    else          hipLaunchKernelGGL((intra_kernel<bf16_t, 128, false>), grid, block, 0, st, a);
     return hipGetLastError();
 }
-template hipError_t launch_intra<float>(const IntraArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_intra<bf16_t>(const IntraArgs<bf16_t>&, int, int, hipStream_t);
 
 // The records of the backward pass: a.wsT points at them, a.wsP and a.wsG are not used.  kOptGdnBeta: beta = eta, and
 // the record's fourth vector, d beta / d eta, is 1; kOptNormalizeQ: P^T carries 1/||q_i||, which is also the fifth vector.
-template <typename E>
-hipError_t launch_intra_bwd(const IntraArgs<E>& a, int dk, int n_chunks, hipStream_t st)
+hipError_t launch_intra_bwd(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st)
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_kernel<E, 64, true>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_kernel<E, 128, true>), grid, block, 0, st, a);
+    if (dk == 64) hipLaunchKernelGGL((intra_kernel<bf16_t, 64, true>), grid, block, 0, st, a);
+    else          hipLaunchKernelGGL((intra_kernel<bf16_t, 128, true>), grid, block, 0, st, a);
     return hipGetLastError();
 }
-template hipError_t launch_intra_bwd<float>(const IntraArgs<float>&, int, int, hipStream_t);
-template hipError_t launch_intra_bwd<bf16_t>(const IntraArgs<bf16_t>&, int, int, hipStream_t);
 
 // ---- diagonal gating (App. B, "Extension to diagonal gating") -----------------------------------------------
 // log_alpha holds d_k values per token and head; gamma_i is a vector and every decay ratio acts inside the inner

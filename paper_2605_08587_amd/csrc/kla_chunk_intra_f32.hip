@@ -1,0 +1,262 @@
+// Intra-chunk stage for single-precision inputs (eqs. (3), (6), (7) per chunk and head; the algebra and the record are
+// those of kla_chunk_intra.hip), all products on v_mfma_f32_16x16x4_f32, one workgroup of four waves per chunk-head.
+//
+// What bounds it: latency.  A chunk-head is 20 Gram tiles - 2.1 us of one CU's matrix cores at d_k = 128 - behind a trip to
+// memory and in front of the serial 16-row substitutions and block products of (I + L)^{-1}, so the only way to a busy
+// chip is several chunk-heads per CU.  The footprint is therefore one K tile (32 KB at d_k = 128; the matrices of the
+// inverse overlay it): four workgroups per CU.
+//   * Wave w forms the Q K^T tiles of row tile w and the K K^T tiles of row tile 3 - w: five tiles for every wave, and a
+//     wave needs the Q rows of one row tile only, which go from memory straight into its registers.
+//   * The Gram tiles of P come out of the product in the orientation in which an accumulator tile is the operand quad
+//     that the record stores (K Q^T for P, Q K^T for the backward's P^T), so P never passes through LDS.
+//   * ||k_i||^2 is the diagonal of K K^T, ||q_i||^2 a sum over the registers of the lanes that hold row i.
+// Measured, K and Q staged as operand slots (101 KB, one workgroup per CU) -> this kernel: 1024 chunk-heads of d_k = 128
+// 79 -> 34 us (36 us with three workgroups per CU and no spilled register), 64 chunk-heads of d_k = 64 13.3 -> 9.7 us.
+#include "kla_common.hpp"
+#include "kla_kernels.hpp"
+#include "kla_f32_ops.hpp"
+
+namespace kla {
+
+namespace {
+
+constexpr int kLdm = 68;   // row stride (floats) of the fp32 64x64 matrices in LDS: 16-byte aligned rows
+
+__device__ __forceinline__ float4 bquad(const float* m, int row0, int col0, int r, int g)   // rows 4g..4g+3 of column r
+{
+    const float* p = m + (row0 + 4 * g) * kLdm + col0 + r;
+    return make_float4(p[0], p[kLdm], p[2 * kLdm], p[3 * kLdm]);
+}
+__device__ __forceinline__ float4 aquad(const float* m, int row0, int col0, int r, int g)   // columns 4g..4g+3 of row r
+{
+    return ldf4(m + (row0 + r) * kLdm + col0 + 4 * g);
+}
+
+}  // namespace
+
+// BWD = false: the forward's records [T' | P | three vectors].  BWD = true: those of the backward pass,
+// [T' | M^T | P^T | five vectors] (see bwd_record_bytes in kla_mma.hpp).
+template <int DK, bool BWD>
+__global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
+{
+    typedef F32<DK> C;
+    constexpr int KB = C::KB, REC = BWD ? bwd_record_bytes<float>() : ws_record_bytes<float>(), HALF = ws_half_bytes<float>();
+    constexpr int MB = 64 * kLdm * 4;
+    __shared__ __attribute__((aligned(1024))) char area[C::TILE > 2 * MB ? C::TILE : 2 * MB];
+    __shared__ __attribute__((aligned(16))) float g_s[4][64];        // running sums of log alpha, one copy per wave
+    __shared__ __attribute__((aligned(16))) float beta_s[64];
+    float* Lm = reinterpret_cast<float*>(area);                      // these two overlay the K tile once the Gram products are done
+    float* Tm = reinterpret_cast<float*>(area + MB);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int h = blockIdx.x % a.H;
+    const ChunkPos cp = chunk_pos(a.cu_seqlens, a.chunk_off, a.n_seq, a.T, a.NT, blockIdx.x / a.H);
+    const int clen = cp.clen;
+    const size_t ks = (size_t)a.H * DK;
+    char* rec = reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC;
+    float* vec = reinterpret_cast<float*>(rec + (BWD ? 3 : 2) * HALF);
+    const bool gdn = (a.opts & kOptGdnBeta) != 0;
+
+    // ---- everything the workgroup reads, requested at once (rows beyond a short chunk: its last row, zeroed below)
+    TileRegs<DK> kr;
+    kr.load(a.k + (size_t)cp.tok0 * ks + (size_t)h * DK, ks, clen, tid);
+    float4 qf[KB];
+    {
+        const float* q = a.q + (size_t)(cp.tok0 + min(16 * wave + r, clen - 1)) * ks + (size_t)h * DK + 4 * g;
+#pragma unroll
+        for (int b = 0; b < KB; ++b) qf[b] = ldf4(q + 16 * b);
+    }
+    const size_t gate = (size_t)(cp.tok0 + min(lane, clen - 1)) * a.H + h;
+    float x = a.log_alpha[gate];
+    float et = a.eta[gate];
+    x = lane < clen ? x : 0.f;
+    et = lane < clen ? et : 0.f;
+
+    // ---- g_i = log gamma_i; the decay vectors of the record
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_up(x, off, kWave); if (lane >= off) x += y; }
+    g_s[wave][lane] = x;
+    if (wave == 0) {
+        vec[lane] = expf(x);
+        vec[64 + lane] = expf(__shfl(x, 63, kWave) - x);
+        if constexpr (!BWD) a.wsG[(size_t)blockIdx.x * 128 + lane] = x;
+    }
+    kr.template stash<true>(area, tid, clen);
+    // ---- 1/||q_i|| of row 16 w + r (1 when the read-out is not normalised; 0 for a zero query)
+    float rq = 1.f;
+    {
+        const bool live = 16 * wave + r < clen;
+        float ss = 0.f;
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            if (!live) qf[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+            ss += qf[b].x * qf[b].x; ss += qf[b].y * qf[b].y; ss += qf[b].z * qf[b].z; ss += qf[b].w * qf[b].w;
+        }
+        ss += __shfl_xor(ss, 16, kWave);
+        ss += __shfl_xor(ss, 32, kWave);
+        if (a.opts & kOptNormalizeQ) rq = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+        if (g == 0) {
+            if constexpr (BWD) vec[256 + 16 * wave + r] = rq;
+            else {
+                vec[128 + 16 * wave + r] = expf(g_s[wave][16 * wave + r]) * rq;
+                a.wsG[(size_t)blockIdx.x * 128 + 64 + 16 * wave + r] = rq;
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- Gram tiles, P to the record, L and beta to LDS.  One instance per wave: every tile index is a constant.
+    auto gram = [&](auto wc) {
+        constexpr int W = wc, A = 3 - W, NT = (A > W ? A : W) + 1;
+        TileOps<DK> ops;
+        ops.init(A, r, g);
+        int boff[4];                                     // row operand of any tile: that of tile 0 + 16 rows per tile
+#pragma unroll
+        for (int y = 0; y < 4; ++y) boff[y] = ops.row_off[y] - 16 * A * C::RB;
+        floatx4 kk[A + 1], qk[W + 1];
+#pragma unroll
+        for (int t = 0; t <= A; ++t) kk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            const float4 ka = ops.row_quad(area, b);
+            static_for<NT>([&](auto tc) {
+                constexpr int t = tc;
+                const float4 kb = t == A ? ka : ldf4(area + boff[b & 3] + 16 * t * C::RB + 256 * (b >> 2));
+                if constexpr (t <= A) mma16(kk[t], ka, kb);                  // rows: token of tile A, column: token of tile t
+                if constexpr (t <= W) {
+                    if constexpr (BWD) mma16(qk[t], qf[b], kb);              // rows: query of tile W, column: key of tile t
+                    else               mma16(qk[t], kb, qf[b]);              // rows: key of tile t, column: query of tile W
+                }
+            });
+        }
+        const float* gw = g_s[W];
+        // ---- P (or P^T): decay, mask, 1/||q||; straight into the record
+        const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
+        auto put = [&](char* half, int pair, int blk, floatx4 v) {
+            *reinterpret_cast<float4*>(half + ((size_t)pair * 64 + lane) * 32 + 16 * blk) = quad(v);
+        };
+        static_for<W + 1>([&](auto tc) {
+            constexpr int t = tc;
+            floatx4 v;
+            if constexpr (BWD) {                         // lane: P[16 W + 4 g + e][16 t + r], the quad of row 16 t + r of P^T
+                const float gj = gw[16 * t + r];
+                const floatx4 gi = lda4(gw + 16 * W + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float rqi = __shfl(rq, 4 * g + e, kWave);
+                    v[e] = (t < W || r <= 4 * g + e) ? expf(gi[e] - gj) * qk[t][e] * rqi : 0.f;
+                }
+                put(rec + 2 * HALF, triu_pair(t, W >> 1), W & 1, v);
+            } else {                                     // lane: P[16 W + r][16 t + 4 g + e]
+                const float gi = gw[16 * W + r];
+                const floatx4 gj = lda4(gw + 16 * t + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (t < W || 4 * g + e <= r) ? expf(gi - gj[e]) * qk[t][e] * rq : 0.f;
+                put(rec + HALF, tri_pair(W, t >> 1), t & 1, v);
+            }
+        });
+        // the tile of a stored pair that lies on the other side of the diagonal
+        if constexpr (BWD) { if constexpr ((W & 1) == 1) put(rec + 2 * HALF, triu_pair(W, W >> 1), 0, z4); }
+        else               { if constexpr ((W & 1) == 0) put(rec + HALF, tri_pair(W, W >> 1), 1, z4); }
+        // ---- beta of the rows of tile A: ||k_i||^2 sits on the diagonal, row 4 g + e in lane 20 g + e
+        floatx4 be;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float ss = __shfl(kk[A][e], 20 * g + e, kWave), eta = __shfl(et, 16 * A + 4 * g + e, kWave);
+            be[e] = gdn ? eta : kaczmarz_beta(eta, ss, a.eps);
+            if (r == 4 * g + e) {
+                beta_s[16 * A + r] = be[e];
+                if constexpr (BWD) {
+                    vec[128 + 16 * A + r] = be[e];
+                    vec[192 + 16 * A + r] = gdn ? 1.f : ((ss + a.eps == 0.f) ? 0.f : 1.0f / (ss + a.eps));
+                }
+            }
+        }
+        __syncthreads();                                 // the K tile is dead from here on
+        static_for<A + 1>([&](auto tc) {
+            constexpr int t = tc;
+            const float gj = gw[16 * t + r];
+            const floatx4 gi = lda4(gw + 16 * A + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                Lm[(16 * A + 4 * g + e) * kLdm + 16 * t + r] = (t < A || r < 4 * g + e) ? be[e] * expf(gi[e] - gj) * kk[t][e] : 0.f;
+        });
+        if constexpr ((W & 1) == 0) {                    // tiles (0, 1) and (2, 3) of (I + L)^{-1}: stored, and zero
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Tm[(16 * W + 4 * g + e) * kLdm + 16 * (W + 1) + r] = 0.f;
+        }
+    };
+    if (wave == 0) gram(IntC<0>()); else if (wave == 1) gram(IntC<1>()); else if (wave == 2) gram(IntC<2>()); else gram(IntC<3>());
+    __syncthreads();
+
+    // ---- (I + L)^{-1}: the diagonal 16x16 blocks by forward substitution (wave w: block w, lane r: column r; the rows
+    //      of L are read ahead, they do not depend on the result)
+    {
+        const float* Lb = Lm + 16 * wave * kLdm + 16 * wave;
+        float xs[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            float s0 = (i == r) ? 1.f : 0.f, s1 = 0.f;
+            floatx4 row[4];
+#pragma unroll
+            for (int c4 = 0; c4 < (i + 3) / 4; ++c4) row[c4] = lda4(Lb + i * kLdm + 4 * c4);
+#pragma unroll
+            for (int j = 0; j < i; ++j) { if (j & 1) s1 -= row[j >> 2][j & 3] * xs[j]; else s0 -= row[j >> 2][j & 3] * xs[j]; }
+            xs[i] = s0 + s1;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if ((i >> 2) == g) Tm[(16 * wave + i) * kLdm + 16 * wave + r] = xs[i];
+    }
+    __syncthreads();
+    // ---- 32x32 level, waves 0 and 1: T_ba = -D_b (L_ba D_a)
+    if (wave < 2) {
+        const int ra = 32 * wave, rb = ra + 16;
+        floatx4 y = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
+        mma16(y, aquad(Lm, rb, ra, r, g), bquad(Tm, ra, ra, r, g));
+        mma16(z, aquad(Tm, rb, rb, r, g), quad(y));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Tm[(rb + 4 * g + e) * kLdm + ra + r] = -z[e];
+    }
+    __syncthreads();
+    // ---- 64x64 level: T[32:64, 0:32] = -T22 (L21 T11); wave = (row tile ti, column tile tj)
+    {
+        const int ti = wave >> 1, tj = wave & 1;
+        floatx4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            const float4 b = bquad(Tm, 16 * tm, 16 * tj, r, g);
+            mma16(y0, aquad(Lm, 32, 16 * tm, r, g), b);
+            mma16(y1, aquad(Lm, 48, 16 * tm, r, g), b);
+        }
+        mma16(z, aquad(Tm, 32 + 16 * ti, 32, r, g), quad(y0));
+        mma16(z, aquad(Tm, 32 + 16 * ti, 48, r, g), quad(y1));
+        // the block written below is read by no wave in this phase, so no barrier is needed here
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Tm[(32 + 16 * ti + 4 * g + e) * kLdm + 16 * tj + r] = -z[e];
+    }
+    __syncthreads();
+    // ---- T' = (I + L)^{-1} diag(beta) (and, for the backward, M^T) -> record, in operand order
+    write_tri_f32<false, true>(rec, Tm, beta_s, tid);
+    if constexpr (BWD) write_tri_f32<true, false>(rec + HALF, Tm, nullptr, tid);
+}
+
+template <int DK>
+static hipError_t launch_dk(const IntraArgs<float>& a, bool bwd, int n_chunks, hipStream_t st)
+{
+    if (n_chunks == 0) return hipSuccess;
+    const dim3 grid((unsigned)n_chunks * a.H), block(256);
+    if (bwd) hipLaunchKernelGGL((intra_f32_kernel<DK, true>), grid, block, 0, st, a);
+    else     hipLaunchKernelGGL((intra_f32_kernel<DK, false>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
+hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, bool bwd, int n_chunks, hipStream_t st)
+{
+    return dk == 64 ? launch_dk<64>(a, bwd, n_chunks, st) : launch_dk<128>(a, bwd, n_chunks, st);
+}
+
+}  // namespace kla

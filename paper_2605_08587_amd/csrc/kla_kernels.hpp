@@ -36,9 +36,11 @@ template <typename E> struct IntraArgs {
     E* wsT; E* wsP; float* wsG;
     unsigned opts;                               // kOptNormalizeQ | kOptGdnBeta
 };
-template <typename E> hipError_t launch_intra(const IntraArgs<E>& a, int dk, int n_chunks, hipStream_t st);
+hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);       // bf16, plain form
 // the records of the backward pass (see bwd_record_bytes in kla_mma.hpp) at a.wsT; a.wsP, a.wsG unused; a.opts: kOptNormalizeQ | kOptGdnBeta
-template <typename E> hipError_t launch_intra_bwd(const IntraArgs<E>& a, int dk, int n_chunks, hipStream_t st);
+hipError_t launch_intra_bwd(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);   // bf16, plain form
+// fp32: the forward's records, or (bwd) those of the backward pass
+hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, bool bwd, int n_chunks, hipStream_t st);
 
 // Diagonal gating (App. B): log_alpha is [tokens, H, dk].  Besides the records (with unit decay vectors) the stage
 // writes the operands the scan is then given in place of k and q - kplus = K o Gamma, qplus = Q o Gamma (rows of the
