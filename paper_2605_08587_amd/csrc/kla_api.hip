@@ -122,7 +122,7 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     p->off_P = half;
     p->off_G = round256((size_t)n_chunks * H * (2 * half + 768));   // + three vectors of 64 fp32 (see kla_mma.hpp)
     p->off_C = round256(p->off_G + (size_t)n_chunks * H * 128 * sizeof(float));      // g and 1/||q||
-    p->off_M = round256(p->off_C + (size_t)(n_seq + 1) * sizeof(int32_t));
+    p->off_M = round256(p->off_C + (size_t)(2 * n_seq + 1) * sizeof(int32_t));       // chunk offsets, scan order of the sequences
     p->seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->tune, &p->seg_Lc);
     // per (sequence, head): G - 1 maps [N | M] and G incoming states, fp32
     const size_t maps = p->seg_G > 1 ? (size_t)N * (p->seg_G - 1) * H * dk * (dv + dk) * sizeof(float) : 0;
@@ -130,7 +130,8 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     p->off_S = round256(p->off_M + maps);
     p->total = round256(p->off_S + states);
     p->waves = scan_waves(p->n_states * H, dv, dt, p->tune);
-    // bf16, a plain scan of two compute waves per workgroup (512 .. 2047 sixteen-column chains, e.g. 8 x 8 heads of 128
+    if (p->tune.fused && !p->tune.scan_waves && p->waves > 2) p->waves = 2;
+    // bf16, a plain scan of two compute waves per workgroup (257 .. 512 sixteen-column chains, e.g. 8 x 8 heads of 128
     // columns): the fused kernel, which keeps the per-chunk objects on chip and needs nothing of the workspace (a token
     // size is still reported and asked for).  Measured: 0.116 against 0.124 ms on 8 x 8 heads x 4096 tokens; with one
     // compute wave per workgroup (few chains) its helper waves redo the per-chunk work once per 16 columns and the
@@ -149,12 +150,19 @@ int scan_waves(int n_chains, int dv, int dt, const Tune& tune)
     if (tune.scan_waves) w = tune.scan_waves;        // tuning field: 1, 2 or 4 waves (16 state columns each) per workgroup
     else if (dt == KLA_F32) w = f32_tiles((long)n_chains * (dv / 16));
     else {
-        // enough workgroups to cover the 256 CUs, else the widest slice that still gives >= 2 waves of loaders
-        // workgroups for w waves: chains8 * dv / (16 w).  Wide slices halve the operand re-reads but need
-        // enough workgroups to cover the 256 CUs; a lone long sequence is latency-bound and runs best narrow.
+        // bf16: a workgroup fills a CU (LDS), so the scan runs in ceil(workgroups / 256) rounds of a length that depends on
+        // the waves of a workgroup.  Relative lengths of a chunk step with 1, 2, 4 and 8 waves, measured with the chip
+        // full (8 x 2048 tokens, 8 heads, d_v = 256: 174, 107, 85 us per call for 4, 2, 1 rounds of 1, 2, 4 waves; 16 x
+        // 2048, 16 heads, d_v = 256: 361 us for 4 rounds of 4 waves, 305 us for 2 of 8; 20 x 1024, 8 heads, d_v = 256: 117
+        // us for 3 of 4, 125 us for 2 of 8).  The cheapest wins; between equals the narrower, which uses more CUs.
         const long chains8 = ((long)n_chains + 7) / 8 * 8;
-        const long wg1 = chains8 * (dv / 16);
-        w = (wg1 / 4 >= 512) ? 4 : ((wg1 / 2 >= 192) ? 2 : 1);
+        const int step[4] = {100, 100, 136, 215};
+        long best = 0;
+        w = 1;
+        for (int i = 0; i < 4 && 16 << i <= dv; ++i) {
+            const long cost = (chains8 * (dv / (16 << i)) + 255) / 256 * step[i];
+            if (i == 0 || cost < best) { best = cost; w = 1 << i; }
+        }
     }
     if (dt == KLA_F32 && w > 2) w = 2;            // fp32: column tiles per workgroup, 1 or 2
     while (16 * w > dv) w >>= 1;
@@ -193,7 +201,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_scan_fused_bf16(fa, dk, pl.waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    if (intra && n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, st) != hipSuccess) return KLA_ERR_HIP;
+    if (intra && n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
     if (intra) {
         [[maybe_unused]] bool done = false;
         if constexpr (sizeof(E) == 2) {
@@ -215,6 +223,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     sa.q = static_cast<const E*>(q); sa.k = static_cast<const E*>(k); sa.v = static_cast<const E*>(v);
     sa.h0 = h0; sa.o = static_cast<E*>(o); sa.hT = hT;
     sa.cu_seqlens = ia.cu_seqlens; sa.chunk_off = chunk_off; sa.n_seq = n_seq;
+    sa.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
     sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
     sa.wsT = wsT; sa.wsP = wsP; sa.wsG = wsG; sa.opts = opts;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = nullptr; sa.gc_vec = nullptr;
@@ -242,7 +251,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_scan_bf16(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4) return kla::launch_scan_f32(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
-    else                          return kla::launch_scan(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+    else                          return kla::launch_scan(sa, dk, waves > 4 ? 4 : waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
 }
 
 // ---- backward pass ---------------------------------------------------------------------------------
@@ -265,7 +274,7 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     const size_t rows = (size_t)N * T * H * dv * elem_bytes(dt);
     p->off_rec = 0;                                              // [T' | M^T | P^T | five vectors] per chunk-head
     p->off_C = round256(ch * (3 * half + 1280));
-    p->off_S = round256(p->off_C + (size_t)(n_seq + 1) * sizeof(int32_t));
+    p->off_S = round256(p->off_C + (size_t)(2 * n_seq + 1) * sizeof(int32_t));
     p->off_dS = round256(p->off_S + states);
     // the bf16 kernels do not keep U (their assembly forms it again from T' and X); the generic ones do
     const size_t rows_u = (dt == KLA_BF16 && !p->base.tune.generic_bwd) ? 0 : rows;
@@ -291,7 +300,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
 {
     int* chunk_off = reinterpret_cast<int*>(ws + pl.off_C);
     const int NT = (T + 63) / 64;
-    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, st) != hipSuccess) return KLA_ERR_HIP;
+    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
 
     kla::IntraArgs<E> ia;
     ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
@@ -317,6 +326,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     ba.dq = static_cast<E*>(dq); ba.dk = static_cast<E*>(dk_); ba.dv = static_cast<E*>(dv_);
     ba.dlog_alpha = dlog_alpha; ba.deta = deta; ba.dh0 = dh0;
     ba.cu_seqlens = ia.cu_seqlens; ba.chunk_off = chunk_off; ba.n_seq = n_seq;
+    ba.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
     ba.N = N; ba.T = T; ba.NT = NT; ba.H = H; ba.dv_dim = dv;
     ba.rec = ws + pl.off_rec;
     ba.s_chk = reinterpret_cast<E*>(ws + pl.off_S); ba.ds_chk = reinterpret_cast<E*>(ws + pl.off_dS);
@@ -413,7 +423,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
 {
     int* chunk_off = reinterpret_cast<int*>(ws + pl.base.off_C);
     const int NT = (T + 63) / 64;
-    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, st) != hipSuccess) return KLA_ERR_HIP;
+    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
     kla::IntraDiagArgs<E> ia;
     ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
     ia.log_alpha = log_alpha; ia.eta = eta; ia.eps = eps;
@@ -429,6 +439,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     sa.q = ia.qplus; sa.k = ia.kplus; sa.v = static_cast<const E*>(v);
     sa.h0 = h0; sa.o = static_cast<E*>(o); sa.hT = hT;
     sa.cu_seqlens = ia.cu_seqlens; sa.chunk_off = chunk_off; sa.n_seq = n_seq;
+    sa.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
     sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
     sa.wsT = ia.wsT; sa.wsP = reinterpret_cast<E*>(ws + pl.base.off_P); sa.wsG = ia.wsG; sa.opts = 0u;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = ia.ktilde; sa.gc_vec = ia.gc;

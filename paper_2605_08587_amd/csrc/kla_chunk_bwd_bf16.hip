@@ -74,9 +74,11 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
     const int nsl = a.dv_dim / SLW;
     const int n_states = a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N);
     const int xcd = blockIdx.x & 7, pidx = blockIdx.x >> 3;
-    const int chain = (pidx / nsl) * 8 + xcd, slice = pidx % nsl;
-    if (chain >= n_states * a.H) return;
-    const int s = chain / a.H, h = chain % a.H;
+    const int rank = (pidx / nsl) * 8 + xcd, slice = pidx % nsl;
+    if (rank >= n_states * a.H) return;
+    const int h = rank % a.H;
+    const int s = a.seq_order ? a.seq_order[rank / a.H] : rank / a.H;
+    const int chain = s * a.H + h;
     long t0; int len, ch0;
     if (a.cu_seqlens) { t0 = a.cu_seqlens[s]; len = a.cu_seqlens[s + 1] - (int)t0; ch0 = a.chunk_off[s]; }
     else if (a.seg_G > 0) {                              // segment sg of sequence n: chunks [sg Lc, (sg + 1) Lc)

@@ -684,21 +684,43 @@ hipError_t launch_intra_diag(const IntraDiagArgs<E>& a, int dk, int n_chunks, hi
 template hipError_t launch_intra_diag<float>(const IntraDiagArgs<float>&, int, int, hipStream_t);
 template hipError_t launch_intra_diag<bf16_t>(const IntraDiagArgs<bf16_t>&, int, int, hipStream_t);
 
-// ---- chunk offsets of a packed batch: chunk_off[s] = sum_{s'<s} ceil(len_s'/64) --------------
-__global__ void chunk_offsets_kernel(const int* __restrict__ cu_seqlens, int n_seq, int* __restrict__ chunk_off)
+// ---- chunk offsets of a packed batch: chunk_off[s] = sum_{s'<s} ceil(len_s'/64), and the order in which the sweeps take
+//      the sequences: most chunks first, so that the workgroups that run longest start first and the short ones fill
+//      the CUs that become free (up to kOrderMax sequences; more of them balance by number, and keep their order).
+constexpr int kOrderMax = 256;
+__global__ __launch_bounds__(256) void chunk_offsets_kernel(const int* __restrict__ cu_seqlens, int n_seq, int* __restrict__ chunk_off,
+                                                            int* __restrict__ order)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        int acc = 0;
-        for (int s = 0; s < n_seq; ++s) {
-            chunk_off[s] = acc;
-            acc += (cu_seqlens[s + 1] - cu_seqlens[s] + 63) / 64;
+    __shared__ int nc_s[256];
+    __shared__ int wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int carry = 0;
+    for (int s0 = 0; s0 < n_seq; s0 += 256) {            // 256 sequences at a time: prefix sum in each wave, then over the waves
+        const int s = s0 + tid;
+        const int nc = s < n_seq ? (cu_seqlens[s + 1] - cu_seqlens[s] + 63) / 64 : 0;
+        int x = nc;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { const int y = __shfl_up(x, off, kWave); if (lane >= off) x += y; }
+        if (lane == 63) wsum[wave] = x;
+        nc_s[tid] = nc;
+        __syncthreads();
+        int base = carry;
+        for (int w = 0; w < wave; ++w) base += wsum[w];
+        if (s < n_seq) chunk_off[s] = base + x - nc;
+        carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        if (n_seq > kOrderMax) { if (s < n_seq) order[s] = s; }
+        else if (s < n_seq) {
+            int rank = 0;
+            for (int j = 0; j < n_seq; ++j) rank += (nc_s[j] > nc || (nc_s[j] == nc && j < s)) ? 1 : 0;
+            order[rank] = s;
         }
-        chunk_off[n_seq] = acc;
+        __syncthreads();
     }
+    if (tid == 0) chunk_off[n_seq] = carry;
 }
-hipError_t launch_chunk_offsets(const int* cu_seqlens, int n_seq, int* chunk_off, hipStream_t st)
+hipError_t launch_chunk_offsets(const int* cu_seqlens, int n_seq, int* chunk_off, int* order, hipStream_t st)
 {
-    hipLaunchKernelGGL(chunk_offsets_kernel, dim3(1), dim3(64), 0, st, cu_seqlens, n_seq, chunk_off);
+    hipLaunchKernelGGL(chunk_offsets_kernel, dim3(1), dim3(256), 0, st, cu_seqlens, n_seq, chunk_off, order);
     return hipGetLastError();
 }
 

@@ -29,6 +29,12 @@
 //     the chunks two and one steps ahead, straight into two LDS record buffers, so K and Q are read from memory
 //     once and the per-chunk objects never leave the CU (see the helper section below).  A seventh wave, otherwise
 //     idle, writes the staged outputs to memory.
+//   * Eight compute waves (SELF; batches of more than 1024 sixteen-column chains): a workgroup takes 128 columns, two
+//     waves per SIMD cover each other's latencies, and K, Q, T', P are copied once per 128 columns instead of once per
+//     64. There is no copy or write-out wave then (a ninth wave would cap the registers at 168 and the products spill):
+//     every wave issues an eighth of the copies a step ahead and writes an eighth of the previous outputs. What bounds
+//     it is memory: 16 packed sequences of 512..4096 tokens, 16 heads, d_v = 256 move about 1 GB through the scan:
+//     265 us with four waves, 220 us with eight (4.5 TB/s; a large copy reaches 4.9).
 //   * A short last chunk is handled without zero filling: rows beyond it re-read the last valid row;
 //     their T' rows and columns are zero (beta = 0 there), so they contribute nothing to U, to the
 //     state or to any stored output.
@@ -67,9 +73,14 @@ struct Cfg {
     static constexpr int R_T = FU ? 0 : OFF_T, R_P = FU ? TPB : OFF_P, R_EG = FU ? 2 * TPB : OFF_EG;
     static constexpr int RECB = 2 * TPB + 1024;          // bytes of a record buffer: [T-area | P | four vectors of 64 fp32]
     static constexpr int HSCR_T = 4096 + 6 * 256, HSCR_P = 6 * 256;   // private LDS of a T-side / P-side helper wave
-    // row stride of the output staging tile: 24 (NW <= 2) or 40 (NW = 4) dwords, so that the 8-dword spans which
-    // one wave writes into 8 consecutive rows fall into disjoint banks
-    static constexpr int ORB = NW <= 2 ? 96 : 160;
+    // row stride of the output staging tile: 24 (NW <= 2), 40 (NW = 4) or 72 (NW = 8) dwords, so that the 8-dword spans
+    // which one wave writes into 8 consecutive rows fall into disjoint banks
+    static constexpr int ORB = NW <= 2 ? 96 : (NW == 4 ? 160 : 288);
+    // Swizzle of the V slice: the transposing read of a wave takes its 32 bytes of eight rows per cycle, and the rows of
+    // a slice 128 (NW = 4) or 256 bytes wide repeat the banks every second row or every row; the index of a row's
+    // 16-byte piece is XORed with twice this function of the row (period 8), on the global side of the copy.
+    __host__ __device__ static constexpr int vswz(int row) { return NW == 8 ? 2 * (row & 7) : (NW == 4 ? 2 * ((row >> 1) & 3) : 0); }
+    static constexpr int NGV = RPV >= 8 ? 1 : 8 / RPV;   // copy blocks after which the swizzle repeats
     static constexpr int OSB = 64 * ORB;
     static constexpr int EXTRA = FU ? 2 * RECB + 2 * HSCR_T + 2 * HSCR_P : 0;
     static constexpr int NST = (3 * STAGE + 2 * OSB + EXTRA <= 160 * 1024) ? 3 : 2;   // LDS ring depth
@@ -86,7 +97,11 @@ struct Cfg {
     // waves of a workgroup: compute waves, then the copy wave and the wave that writes the outputs; fused: compute
     // waves, two T-side helpers, the copy wave, the write-out wave - placed so that the two P-side helpers after it land
     // on the SIMDs of the T-side ones - and those two
-    static constexpr int NWAVES = NW + (FU ? 6 : 2);
+    // With eight compute waves (two per SIMD) there is no wave of either kind: a ninth would cap every wave at 168
+    // registers, and a partner on the same SIMD covers what a compute wave spends on copies and stores.
+    static constexpr bool SELF = NW == 8;
+    static_assert(!SELF || (!DG && !FU), "plain scan only");
+    static constexpr int NWAVES = NW + (FU ? 6 : (SELF ? 0 : 2));
     static constexpr int W_COPY = FU ? NW + 2 : NW;
     static constexpr int W_P = NW + 4, W_IDLE = FU ? NW + 3 : NW + 1;
     static_assert(LDS <= 160 * 1024 && (NST != 3 || NDMA < 64), "LDS budget of a gfx950 CU; 6-bit vmcnt (counted waits only with three stages)");
@@ -608,9 +623,11 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     const int n_states = a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N);
     const int n_chains = n_states * a.H;
     const int xcd = blockIdx.x & 7, pidx = blockIdx.x >> 3;
-    const int chain = (pidx / nsl) * 8 + xcd, slice = pidx % nsl;
-    if (chain >= n_chains) return;
-    const int s = chain / a.H, h = chain % a.H;
+    const int rank = (pidx / nsl) * 8 + xcd, slice = pidx % nsl;
+    if (rank >= n_chains) return;
+    const int h = rank % a.H;
+    const int s = (!FU && a.seq_order) ? a.seq_order[rank / a.H] : rank / a.H;
+    const int chain = s * a.H + h;
     long t0; int len, ch0;
     if (a.cu_seqlens) { t0 = a.cu_seqlens[s]; len = a.cu_seqlens[s + 1] - (int)t0; ch0 = FU ? 0 : a.chunk_off[s]; }
     else if (a.seg_G > 0) {                              // segment sg of sequence n: chunks [sg Lc, (sg + 1) Lc)
@@ -653,7 +670,10 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 #pragma unroll
     for (int j = 0; j < NGK; ++j)
         gk[j] = lrow * (int)kq_row + ((pcol ^ swz_piece<DK>(RPB * j + lrow)) * 16);
-    const int gv = (lane / VPP) * (int)v_row + (lane % VPP) * 16;
+    int gv[C::NGV];
+#pragma unroll
+    for (int j = 0; j < C::NGV; ++j)
+        gv[j] = (lane / VPP) * (int)v_row + (((lane % VPP) ^ C::vswz(RPV * j + lane / VPP)) * 16);
     // LDS reads.  K/Q row slots: token row 16 it + r, logical column 4 kp + g:
     int oK[KP];
 #pragma unroll
@@ -664,7 +684,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     int oKT[KP];
 #pragma unroll
     for (int kp = 0; kp < KP; ++kp) oKT[kp] = (4 * g + a4) * RB + (((4 * kp + c4) ^ swz_piece<DK>(4 * g + a4)) * 16);
-    const int oV = (4 * g + a4) * VRW + (16 * wave + 4 * c4) * 2;      // V tile rows 4 g + a4 (+ 16 it)
+    const int oV = (4 * g + a4) * VRW + (((2 * wave + (c4 >> 1)) ^ C::vswz(4 * g + a4)) * 16) + (c4 & 1) * 8;   // V tile rows 4 g + a4 (+ 16 it)
     // staging tile: after the 4x4 transposition below lane (r, g) holds row 4 g + (r & 3) (+ 16 it), columns
     // 4 (r >> 2) .. + 3 of this wave's 16
     const int oO = (4 * g + (r & 3)) * ORB + (16 * wave + 4 * (r >> 2)) * 2;
@@ -701,13 +721,13 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             if (clen == 64) {
                 static_for<C::NVB>([&](auto i) {
                     const int b = i;
-                    dma16(vc + (size_t)(b * RPV) * v_row, gv, st + C::OFF_V + b * 1024);
+                    dma16(vc + (size_t)(b * RPV) * v_row, gv[b % C::NGV], st + C::OFF_V + b * 1024);
                 });
             } else {
                 static_for<C::NVB>([&](auto i) {
                     const int b = i;
                     const int row = b * RPV + lane / VPP;
-                    dma16(vc, min(row, clen - 1) * (int)v_row + (lane % VPP) * 16, st + C::OFF_V + b * 1024);
+                    dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + b * 1024);
                 });
             }
             if constexpr (!FU) {
@@ -919,6 +939,17 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         }
     };
 
+    auto store_final = [&]() {
+        if (!a.hT) return;
+#pragma unroll
+        for (int kt = 0; kt < KB; ++kt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int f = 32 * (kt >> 1) + 8 * g + 4 * (kt & 1) + e;
+                a.hT[((size_t)chain * DK + f) * a.dv + col] = S[kt][e];
+            }
+    };
+
     char* ost0 = lds + NST * C::STAGE;
     char* ost1 = ost0 + C::OSB;
 
@@ -1053,6 +1084,52 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         }
     }
 
+    if constexpr (C::SELF) {
+        // ---- eight compute waves, two stages.  At the start of step c each wave issues its eighth of the copies of chunk
+        // c + 1 (into the stage chunk c - 1 left) and writes its eighth of the outputs of chunk c - 1; both have the
+        // whole step to complete.
+        auto issue_part = [&](int c, char* st) {
+            const int clen = min(64, len - 64 * c);
+            const char* kc = kbase + (size_t)(64 * c) * kq_row;
+            const char* qc = qbase + (size_t)(64 * c) * kq_row;
+            const char* vc = vbase + (size_t)(64 * c) * v_row;
+            const char* tc = tpbase + (size_t)c * a.H * REC;
+            constexpr int NK = C::NKB / 8, NV = C::NVB / 8;          // blocks of K (and Q), V per wave
+            static_assert(C::NKB % 8 == 0 && C::NVB == 16 && C::NTB == 12, "shares of the copy blocks");
+            const int bk = wave * NK, bv = wave * NV;
+            static_for<NK>([&](auto i) {
+                const int row = (bk + i) * RPB + lrow;
+                const int off = clen == 64 ? gk[(NK == 1 ? bk : (int)i) % NGK] + (bk + i) * RPB * (int)kq_row
+                                           : min(row, clen - 1) * (int)kq_row + ((pcol ^ swz_piece<DK>(row)) * 16);
+                dma16(kc, off, st + (bk + i) * 1024);
+                dma16(qc, off, st + C::OFF_Q + (bk + i) * 1024);
+            });
+            static_for<NV>([&](auto i) {
+                const int row = (bv + i) * RPV + lane / VPP;
+                dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + (bv + i) * 1024);
+            });
+            if (wave < 6) {
+                dma16(tc + wave * 2048, lane * 16, st + C::OFF_T + wave * 2048);
+                dma16(tc + wave * 2048 + 1024, lane * 16, st + C::OFF_T + wave * 2048 + 1024);
+            } else if (wave == 6 && lane < 48) {
+                dma16(tc + 2 * C::TPB, lane * 16, st + C::OFF_EG);
+            }
+        };
+        if (nch > 0) issue_part(0, lds);
+        wait_vmcnt<0>();
+        __syncthreads();
+        for (int c = 0; c < nch; ++c) {
+            char* st = lds + (c & 1) * C::STAGE;
+            if (c + 1 < nch) issue_part(c + 1, lds + ((c + 1) & 1) * C::STAGE);
+            if (c > 0) write_out(c - 1, (c & 1) ? ost0 : ost1, tid, IntC<512>());
+            compute(st, st, (c & 1) ? ost1 : ost0);
+            wait_vmcnt<0>();                             // this wave's copies (and stores); the barrier covers the others'
+            __syncthreads();
+        }
+        if (nch > 0) write_out(nch - 1, (nch & 1) ? ost0 : ost1, tid, IntC<512>());
+        store_final();
+        return;
+    }
     // ---- compute waves ---------------------------------------------------------------------------------
     if constexpr (FU) __syncthreads();                   // step -2
     __syncthreads();                                     // chunk 0 is in stage 0 (and its record in buffer 0)
@@ -1067,15 +1144,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         scur = (scur + 1 == NST) ? 0 : scur + 1;
     }
 
-    if (a.hT) {
-#pragma unroll
-        for (int kt = 0; kt < KB; ++kt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int f = 32 * (kt >> 1) + 8 * g + 4 * (kt & 1) + e;
-                a.hT[((size_t)chain * DK + f) * a.dv + col] = S[kt][e];
-            }
-    }
+    store_final();
 }
 
 template <int DK>
@@ -1096,9 +1165,13 @@ static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st
             if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 2, true>), grid, dim3(64 * 4), 0, st, a);
             else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 2, false>), grid, dim3(64 * 4), 0, st, a);
             break;
-        default:
+        case 4:
             if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 4, true>), grid, dim3(64 * 6), 0, st, a);
             else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 4, false>), grid, dim3(64 * 6), 0, st, a);
+            break;
+        default:
+            if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 8, true>), grid, dim3(64 * 8), 0, st, a);
+            else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 8, false>), grid, dim3(64 * 8), 0, st, a);
             break;
     }
     return hipGetLastError();

@@ -85,10 +85,12 @@ template <typename A> __device__ __forceinline__ Pos sweep_pos(const A& a, int d
 {
     Pos p;
     const int nsl = dv / slw, xcd = blockIdx.x & 7, pidx = blockIdx.x >> 3;
-    p.chain = (pidx / nsl) * 8 + xcd; p.slice = pidx % nsl;
-    p.valid = p.chain < (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
-    const int s = p.valid ? p.chain / a.H : 0;
-    p.h = p.chain % a.H;
+    const int rank = (pidx / nsl) * 8 + xcd;
+    p.slice = pidx % nsl;
+    p.valid = rank < (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
+    const int s = !p.valid ? 0 : (a.seq_order ? a.seq_order[rank / a.H] : rank / a.H);
+    p.h = rank % a.H;
+    p.chain = s * a.H + p.h;
     if (a.cu_seqlens) { p.t0 = a.cu_seqlens[s]; p.len = a.cu_seqlens[s + 1] - (int)p.t0; p.ch0 = a.chunk_off[s]; }
     else              { p.t0 = (long)s * a.T;   p.len = a.T;                             p.ch0 = s * a.NT; }
     p.nch = (p.len + 63) / 64;

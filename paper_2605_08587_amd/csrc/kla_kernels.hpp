@@ -71,6 +71,8 @@ template <typename E> struct ScanArgs {
     // Diagonal gating: the transposed K operand of the state update comes from kt_src instead of
     // k, and the state decays per row by gc_vec[chunk-head][dk] instead of by gamma_C.  Both NULL otherwise.
     const E* kt_src; const float* gc_vec;
+    // Packed batches: the order in which workgroups take the sequences, most chunks first (NULL: as they come)
+    const int* seq_order = nullptr;
     // Fused bf16 scan only (the stage forms T', P and the decay vectors itself; wsT, wsP, wsG unused): the gates.
     const float* log_alpha = nullptr; const float* eta = nullptr; float eps = 0.f;
 };
@@ -128,6 +130,7 @@ template <typename E> struct BwdArgs {
     // Segmented sweeps (seg_G > 0, fixed-length bf16 batches only; see ScanArgs): h0, d_hT and dh0 are then indexed by
     // segment, [N * seg_G][H][dk][dv].
     int seg_G, seg_Lc;
+    const int* seq_order = nullptr;  // packed batches, see ScanArgs
 };
 hipError_t launch_bwd_states(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);   // bf16, plain form
 hipError_t launch_bwd_scan(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
@@ -143,7 +146,8 @@ template <typename E> hipError_t launch_bwd_assemble(const BwdArgs<E>& a, int dk
 // measurement probes (kla_probe.hip)
 hipError_t launch_probe(int kind, void* buf, void* aux, size_t bytes, int iters, hipStream_t st);
 
-hipError_t launch_chunk_offsets(const int* cu_seqlens, int n_seq, int* chunk_off, hipStream_t st);
+// chunk_off[n_seq + 1]: chunks before every sequence; order[n_seq]: the sequences, most chunks first (see ScanArgs::seq_order)
+hipError_t launch_chunk_offsets(const int* cu_seqlens, int n_seq, int* chunk_off, int* order, hipStream_t st);
 template <typename E>
 hipError_t launch_unpack(const E* wsT, const E* wsP, const float* wsG, float* Tb, float* P, float* gout, long n_ch,
                          hipStream_t st);
