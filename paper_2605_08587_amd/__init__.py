@@ -3,10 +3,16 @@
 Argument marshalling only: every step of the path runs in the HIP kernels.  PyTorch supplies
 device memory and the current stream.  There is no CPU fallback: if the compiled library is
 missing, or a tensor is not on the GPU, the call raises.
+
+Calls with plain GPU tensors that fit each other are checked, given memory and launched by kla_binding.so
+(csrc/kla_binding.cpp), which hands back None for anything else; the code here then takes the same call step by step and
+raises what there is to raise.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import threading
 
@@ -15,12 +21,14 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # KLA_LIBRARY names another build of the same library (the host-sanitizer run of tests/host_sanitizers.py uses it)
 LIB_PATH = os.environ.get("KLA_LIBRARY") or os.path.join(_HERE, "libkla.so")
+BINDING_PATH = os.path.join(_HERE, "kla_binding.so")
 HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "kla.h")
 
 KLA_F32, KLA_BF16 = 0, 1
 KLA_OPT_NORMALIZE_Q, KLA_OPT_GDN_BETA = 1, 2
 _lock = threading.Lock()
 _lib = None
+_native = None      # the module kla_binding, bound to _lib
 
 _vp, _fp, _ip = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p
 _SIGNATURES = {
@@ -70,18 +78,32 @@ class KlaError(RuntimeError):
 
 def lib():
     """The loaded C library; raises if it has not been built (python -m paper_2605_08587_amd.build)."""
-    global _lib
+    global _lib, _native
     with _lock:
         if _lib is None:
-            if not os.path.exists(LIB_PATH):
-                raise RuntimeError("libkla.so is not built: run `python -m paper_2605_08587_amd.build` "
-                                   "(there is no CPU fallback)")
+            for path in (LIB_PATH, BINDING_PATH):
+                if not os.path.exists(path):
+                    raise RuntimeError("%s is not built: run `python -m paper_2605_08587_amd.build` "
+                                       "(there is no CPU fallback)" % os.path.basename(path))
             l = ctypes.CDLL(LIB_PATH)
             for name, (res, args) in _SIGNATURES.items():
                 fn = getattr(l, name)
                 fn.restype, fn.argtypes = res, args
-            _lib = l
+            loader = importlib.machinery.ExtensionFileLoader("kla_binding", BINDING_PATH)
+            m = importlib.util.module_from_spec(importlib.util.spec_from_loader("kla_binding", loader))
+            loader.exec_module(m)
+            m.bind(*(ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in (
+                "kla_decode_step_opts", "kla_decode_step_diag_opts", "kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_fwd_opts",
+                "kla_chunk_fwd_diag_workspace_bytes", "kla_chunk_fwd_diag_opts", "kla_chunk_bwd_workspace_bytes_opts",
+                "kla_chunk_bwd_opts")))
+            _native, _lib = m, l
     return _lib
+
+
+def _binding():
+    if _native is None:
+        lib()
+    return _native
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -203,6 +225,17 @@ def _ws_bytes(t):
     return 0 if t is None else t.numel() * t.element_size()
 
 
+def _fast_fwd(diag, q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, want_hT, workspace, out, hT, chunk, bits):
+    """(out, hT) through the native half of the binding, or None if it does not take the call."""
+    if cu_seqlens is not None and cu_seqlens_host is None:
+        cu_seqlens_host = _host_cu(cu_seqlens)[0]
+    r = _binding().chunk_fwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else cu_seqlens_host,
+                             bool(want_hT), workspace, out, hT, chunk, bits, diag)
+    if type(r) is int:
+        raise KlaError(r, "kla_chunk_fwd_diag" if diag else "kla_chunk_fwd")
+    return r
+
+
 def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_hT=True, workspace=None,
                   out=None, hT=None, chunk=64, _stage=None, normalize_q=False, gdn_beta=False, cu_seqlens_host=None,
                   tune=None):
@@ -214,6 +247,11 @@ def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_h
     normalize_q: o_t = S_t^T q_t / ||q_t||;  gdn_beta: beta_t = eta_t (kla_chunk_fwd_opts of the C ABI).
     tune: tuning fields (see tune()); None = DEFAULT_TUNE.
     """
+    if _stage is None:
+        r = _fast_fwd(False, q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, want_hT, workspace, out, hT, chunk,
+                      _opts(normalize_q, gdn_beta) | _tune(tune))
+        if r is not None:
+            return r
     cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
     n_states = n_seq if n_seq > 0 else q.shape[0]
     N, T, H, dk, dv = _check_chunk(q, k, v, log_alpha, eta, h0, n_states,
@@ -275,6 +313,10 @@ def kla_chunk_fwd_diag(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, w
                        out=None, hT=None, chunk=64, cu_seqlens_host=None, normalize_q=False, gdn_beta=False, tune=None):
     """Chunkwise forward with diagonal gating: log_alpha is [N,T,H,dk] fp32 (one decay per key channel).
     Everything else, the options included, as kla_chunk_fwd; returns (o, hT)."""
+    r = _fast_fwd(True, q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, want_hT, workspace, out, hT, chunk,
+                  _opts(normalize_q, gdn_beta) | _tune(tune))
+    if r is not None:
+        return r
     cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
     n_states = n_seq if n_seq > 0 else q.shape[0]
     N, T, H, dk, dv = _check_chunk(q, k, v, log_alpha, eta, h0, n_states, la_shape=tuple(q.shape),
@@ -301,13 +343,18 @@ def kla_chunk_fwd_diag(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, w
 
 def kla_decode_step_diag(q, k, v, log_alpha, eta, eps, S, out=None, normalize_q=False, gdn_beta=False, tune=None):
     """One decode step with diagonal gating: log_alpha is [B,H,dk]; S [B,H,dk,dv] fp32 is updated in place."""
+    bits = _opts(normalize_q, gdn_beta) | _tune(tune)
+    r = _binding().decode(q, k, v, log_alpha, eta, eps, S, out, bits, True)
+    if r is not None:
+        if type(r) is int:
+            raise KlaError(r, "kla_decode_step_diag")
+        return r
     B, H, dk, dv = _check_decode(q, k, v, log_alpha, eta, S, out, la_shape=tuple(q.shape))
     _dev(q, k, v, log_alpha, eta, S, out)
     if out is None:
         out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
     args = (_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(eta), float(eps), _ptr(S), _ptr(out), B, H, dk, dv, _dt(q),
             _stream())
-    bits = _opts(normalize_q, gdn_beta) | _tune(tune)
     rc = lib().kla_decode_step_diag_opts(*args, bits) if bits else lib().kla_decode_step_diag(*args)
     if rc != 0:
         raise KlaError(rc, "kla_decode_step_diag")
@@ -329,6 +376,14 @@ def kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=None, d_hT=None, cu_seql
     Returns a dict: dq, dk, dv (dtype of q), dlog_alpha, deta (fp32 [N,T,H]), dh0 (fp32, or None).
     `out` may hold preallocated tensors under the same names; `workspace` a uint8 buffer.
     """
+    if not out and workspace is None:
+        host = _host_cu(cu_seqlens)[0] if cu_seqlens is not None and cu_seqlens_host is None else cu_seqlens_host
+        r = _binding().chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else host, d_o, d_hT,
+                                 bool(want_dh0), chunk, _opts(normalize_q, gdn_beta) | _tune(tune))
+        if r is not None:
+            if type(r) is int:
+                raise KlaError(r, "kla_chunk_bwd")
+            return dict(zip(("dq", "dk", "dv", "dlog_alpha", "deta", "dh0"), r))
     cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
     n_states = n_seq if n_seq > 0 else q.shape[0]
     out = dict(out or {})
@@ -372,13 +427,18 @@ def kla_debug_chunk_stage(stage, q, k, v, log_alpha, eta, eps, workspace, out, h
 
 def kla_decode_step(q, k, v, log_alpha, eta, eps, S, out=None, normalize_q=False, gdn_beta=False, tune=None):
     """One decode step; S [B,H,dk,dv] fp32 is updated in place; returns o [B,H,dv].  Options as in kla_chunk_fwd."""
+    bits = _opts(normalize_q, gdn_beta) | _tune(tune)
+    r = _binding().decode(q, k, v, log_alpha, eta, eps, S, out, bits, False)
+    if r is not None:
+        if type(r) is int:
+            raise KlaError(r, "kla_decode_step")
+        return r
     B, H, dk, dv = _check_decode(q, k, v, log_alpha, eta, S, out)
     _dev(q, k, v, log_alpha, eta, S, out)
     if out is None:
         out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
     args = (_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(eta), float(eps), _ptr(S), _ptr(out),
             B, H, dk, dv, _dt(q), _stream())
-    bits = _opts(normalize_q, gdn_beta) | _tune(tune)
     rc = lib().kla_decode_step_opts(*args, bits) if bits else lib().kla_decode_step(*args)
     if rc != 0:
         raise KlaError(rc, "kla_decode_step")
@@ -452,18 +512,19 @@ class _KlaChunk(torch.autograd.Function):
     def forward(ctx, q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta):
         o, hT = kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
                               normalize_q=normalize_q, gdn_beta=gdn_beta)
-        ctx.save_for_backward(q, k, v, log_alpha, eta, h0 if h0 is not None else q.new_empty(0))
-        ctx.misc = (eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, h0 is not None)
+        ctx.save_for_backward(q, k, v, log_alpha, eta, h0)
+        ctx.set_materialize_grads(False)     # the library takes a missing d_hT for zeros: no buffer of them is filled and read
+        ctx.misc = (eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta)
         return o, hT
 
     @staticmethod
     def backward(ctx, d_o, d_hT):
         q, k, v, log_alpha, eta, h0 = ctx.saved_tensors
-        eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, has_h0 = ctx.misc
-        g = kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o.contiguous(), h0=h0 if has_h0 else None,
-                          d_hT=None if d_hT is None else d_hT.contiguous(), cu_seqlens=cu_seqlens,
-                          cu_seqlens_host=cu_seqlens_host, want_dh0=has_h0 and ctx.needs_input_grad[5],
-                          normalize_q=normalize_q, gdn_beta=gdn_beta)
+        eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta = ctx.misc
+        d_o = q.new_zeros(v.shape) if d_o is None else d_o.contiguous()
+        g = kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=h0, d_hT=None if d_hT is None else d_hT.contiguous(),
+                          cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
+                          want_dh0=h0 is not None and ctx.needs_input_grad[5], normalize_q=normalize_q, gdn_beta=gdn_beta)
         return (g["dq"], g["dk"], g["dv"], g["dlog_alpha"], g["deta"], g["dh0"], None, None, None, None, None)
 
 

@@ -1,4 +1,5 @@
-"""Build step: compiles the HIP sources under csrc/ into libkla.so (gfx950 only), in-tree.
+"""Build step: compiles the HIP sources under csrc/ into libkla.so (gfx950 only) and the native half of the Python binding
+into kla_binding.so, in-tree.
 
     python -m paper_2605_08587_amd.build
 """
@@ -11,6 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkla.so")
+BINDING = os.path.join(HERE, "kla_binding.so")
 SOURCES = ["kla_api.hip", "kla_decode.hip", "kla_chunk_intra.hip", "kla_chunk_intra_bf16.hip", "kla_chunk_intra_f32.hip", "kla_chunk_scan.hip", "kla_chunk_sweeps_f32.hip",
            "kla_chunk_scan_bf16.hip", "kla_chunk_segments.hip", "kla_chunk_bwd.hip", "kla_chunk_bwd_bf16.hip", "kla_probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -47,5 +49,25 @@ def build_lib(verbose: bool = False, extra=(), jobs: int = 8) -> str:
     return LIB
 
 
+def build_binding(verbose: bool = False) -> str:
+    """Compiles csrc/kla_binding.cpp (host code only) against the installed PyTorch."""
+    import sysconfig
+    import torch
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    root = os.path.dirname(torch.__file__)
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = [hipcc, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "kla_binding.cpp"), "-o", tmp,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 if __name__ == "__main__":
+    print(build_binding(verbose=True))
     print(build_lib(verbose=True, extra=sys.argv[1:]))

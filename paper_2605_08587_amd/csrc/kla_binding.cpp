@@ -1,0 +1,285 @@
+// The launching half of the Python binding: checks the tensors of a call, allocates what the caller did not pass, and
+// calls the C ABI on the current stream, without going through Python objects for every pointer and extent.  A decode step
+// of one sequence is 4 us of kernel; marshalled in Python its call cost the host 13 us.
+//
+// Every entry returns None for arguments it does not take (wrong extents or types, tensors that are not plain dense GPU
+// tensors, subclasses): the Python code then goes through the same call step by step and raises what there is to raise.
+// A refusal by the library itself comes back as its status code (an int).  The functions are called through the addresses
+// that bind() was given, so that they are those of the library the package has loaded.
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <climits>
+#include <initializer_list>
+#include <optional>
+
+#include "../../include/kla.h"
+
+namespace {
+
+struct Api {
+    decltype(&kla_decode_step_opts) decode;
+    decltype(&kla_decode_step_diag_opts) decode_diag;
+    decltype(&kla_chunk_fwd_workspace_bytes_opts) fwd_bytes;
+    decltype(&kla_chunk_fwd_opts) fwd;
+    decltype(&kla_chunk_fwd_diag_workspace_bytes) fwd_diag_bytes;
+    decltype(&kla_chunk_fwd_diag_opts) fwd_diag;
+    decltype(&kla_chunk_bwd_workspace_bytes_opts) bwd_bytes;
+    decltype(&kla_chunk_bwd_opts) bwd;
+} api = {};
+
+// A plain, dense tensor: torch.Tensor or Parameter itself, strided and contiguous, with memory of its own.  (What
+// function transforms and fake modes pass around is not.)
+const at::Tensor* dense(PyObject* o)
+{
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.defined() || t.layout() != at::kStrided) return nullptr;
+    const c10::TensorImpl* impl = t.unsafeGetTensorImpl();
+    const c10::DispatchKeySet ks = impl->key_set();
+    if (!impl->has_storage() || impl->is_python_dispatch() || ks.has(c10::DispatchKey::FuncTorchBatched) ||
+        ks.has(c10::DispatchKey::FuncTorchGradWrapper) || ks.has(c10::DispatchKey::Functionalize))
+        return nullptr;
+    return t.is_contiguous() ? &t : nullptr;
+}
+const at::Tensor* on_gpu(PyObject* o)
+{
+    const at::Tensor* t = dense(o);
+    return t && t->is_cuda() ? t : nullptr;
+}
+// GPU tensor of this element type and these extents
+const at::Tensor* gpu(PyObject* o, at::ScalarType type, at::IntArrayRef shape)
+{
+    const at::Tensor* t = on_gpu(o);
+    return t && t->scalar_type() == type && t->sizes() == shape ? t : nullptr;
+}
+// the same, or None (then *t stays null); false: neither
+bool gpu_or_none(PyObject* o, at::ScalarType type, at::IntArrayRef shape, const at::Tensor** t)
+{
+    *t = nullptr;
+    if (o == Py_None) return true;
+    *t = gpu(o, type, shape);
+    return *t != nullptr;
+}
+void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
+float* fptr(const at::Tensor* t) { return static_cast<float*>(ptr(t)); }
+
+bool type_of(const at::Tensor& q, kla_dtype* dt)
+{
+    if (q.scalar_type() == at::kBFloat16) *dt = KLA_BF16;
+    else if (q.scalar_type() == at::kFloat) *dt = KLA_F32;
+    else return false;
+    return true;
+}
+bool number(PyObject* o, double* x)
+{
+    *x = PyFloat_AsDouble(o);
+    if (*x == -1.0 && PyErr_Occurred()) { PyErr_Clear(); return false; }
+    return true;
+}
+bool integer(PyObject* o, long lo, long hi, long* x)
+{
+    *x = PyLong_AsLong(o);
+    if (*x == -1 && PyErr_Occurred()) { PyErr_Clear(); return false; }
+    return *x >= lo && *x <= hi;
+}
+bool ints(std::initializer_list<int64_t> xs)
+{
+    for (const int64_t x : xs) if (x > INT_MAX) return false;
+    return true;
+}
+void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// Other threads run while a call allocates and launches (and get their turn back if it throws).
+struct NoGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+PyObject* wrap(const std::optional<at::Tensor>& t)
+{
+    if (t) return THPVariable_Wrap(*t);
+    Py_RETURN_NONE;
+}
+
+// What the chunk entry points share.
+struct Chunk {
+    const at::Tensor *q, *k, *v, *la, *eta, *h0, *cu;
+    const int32_t* cu_host;
+    int64_t N, T, H, dk, dv, n_states;
+    int n_seq;
+    double eps;
+    kla_dtype dt;
+    at::ScalarType type;
+
+    // args: q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host
+    bool take(PyObject* const* a, bool diag)
+    {
+        q = on_gpu(a[0]); v = on_gpu(a[2]);
+        if (!q || !v || q->dim() != 4 || v->dim() != 4 || !type_of(*q, &dt)) return false;
+        type = q->scalar_type();
+        N = q->size(0); T = q->size(1); H = q->size(2); dk = q->size(3); dv = v->size(3);
+        if (!ints({N, T, H, dk, dv}) || v->scalar_type() != type || v->sizes() != at::IntArrayRef({N, T, H, dv})) return false;
+        k = gpu(a[1], type, q->sizes());
+        la = diag ? gpu(a[3], at::kFloat, q->sizes()) : gpu(a[3], at::kFloat, {N, T, H});
+        eta = gpu(a[4], at::kFloat, {N, T, H});
+        if (!k || !la || !eta || !number(a[5], &eps)) return false;
+        cu = nullptr; cu_host = nullptr; n_seq = 0; n_states = N;
+        if (a[7] != Py_None) {
+            cu = on_gpu(a[7]);
+            const at::Tensor* c = dense(a[8]);
+            if (!cu || !c || !c->is_cpu() || cu->scalar_type() != at::kInt || c->scalar_type() != at::kInt || cu->dim() != 1 ||
+                c->dim() != 1 || cu->numel() != c->numel() || cu->numel() < 2 || cu->numel() > INT_MAX)
+                return false;
+            cu_host = static_cast<const int32_t*>(c->data_ptr());
+            n_seq = (int)cu->numel() - 1;
+            n_states = n_seq;
+        } else if (a[8] != Py_None) return false;
+        return gpu_or_none(a[6], at::kFloat, {n_states, H, dk, dv}, &h0);
+    }
+    at::Tensor empty(at::IntArrayRef shape, at::ScalarType t) const { return at::empty(shape, q->options().dtype(t).requires_grad(false)); }
+};
+
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    if (n != 8) { PyErr_SetString(PyExc_TypeError, "bind takes eight addresses"); return nullptr; }
+    void* p[8];
+    for (int i = 0; i < 8; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[i]);
+        if (!p[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address"); return nullptr; }
+    }
+    api.decode = reinterpret_cast<decltype(api.decode)>(p[0]);
+    api.decode_diag = reinterpret_cast<decltype(api.decode_diag)>(p[1]);
+    api.fwd_bytes = reinterpret_cast<decltype(api.fwd_bytes)>(p[2]);
+    api.fwd = reinterpret_cast<decltype(api.fwd)>(p[3]);
+    api.fwd_diag_bytes = reinterpret_cast<decltype(api.fwd_diag_bytes)>(p[4]);
+    api.fwd_diag = reinterpret_cast<decltype(api.fwd_diag)>(p[5]);
+    api.bwd_bytes = reinterpret_cast<decltype(api.bwd_bytes)>(p[6]);
+    api.bwd = reinterpret_cast<decltype(api.bwd)>(p[7]);
+    Py_RETURN_NONE;
+}
+
+// decode(q, k, v, log_alpha, eta, eps, S, out, opts, diag) -> out
+PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 10 || !api.decode) Py_RETURN_NONE;
+    const bool diag = a[9] == Py_True;
+    const at::Tensor *q = on_gpu(a[0]), *v = on_gpu(a[2]);
+    kla_dtype dt;
+    double eps;
+    long opts;
+    if (!q || !v || q->dim() != 3 || v->dim() != 3 || !type_of(*q, &dt) || !number(a[5], &eps) || !integer(a[8], 0, UINT_MAX, &opts))
+        Py_RETURN_NONE;
+    const int64_t B = q->size(0), H = q->size(1), dk = q->size(2), dv = v->size(2);
+    const at::ScalarType type = q->scalar_type();
+    const at::Tensor *k = gpu(a[1], type, q->sizes()), *eta = gpu(a[4], at::kFloat, {B, H}), *S = gpu(a[6], at::kFloat, {B, H, dk, dv});
+    const at::Tensor* la = diag ? gpu(a[3], at::kFloat, q->sizes()) : gpu(a[3], at::kFloat, {B, H});
+    const at::Tensor* out = nullptr;
+    if (!ints({B, H, dk, dv}) || !k || !eta || !S || !la || v->scalar_type() != type || v->sizes() != at::IntArrayRef({B, H, dv}) ||
+        !gpu_or_none(a[7], type, {B, H, dv}, &out))
+        Py_RETURN_NONE;
+    at::Tensor o;
+    int rc;
+    {
+        const NoGil no_gil;
+        o = out ? *out : at::empty({B, H, dv}, q->options().requires_grad(false));
+        rc = (diag ? api.decode_diag : api.decode)(ptr(q), ptr(k), ptr(v), fptr(la), fptr(eta), (float)eps, fptr(S), o.data_ptr(), (int)B,
+                                                   (int)H, (int)dk, (int)dv, dt, stream(), (unsigned)opts);
+    }
+    if (rc != KLA_OK) return PyLong_FromLong(rc);
+    return THPVariable_Wrap(o);
+    END_HANDLE_TH_ERRORS
+}
+
+// chunk_fwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, want_hT, workspace, out, hT, chunk, opts, diag)
+// -> (out, hT)
+PyObject* chunk_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 16 || !api.fwd) Py_RETURN_NONE;
+    const bool diag = a[15] == Py_True, want_hT = a[9] == Py_True;
+    Chunk c;
+    long chunk, opts;
+    if (!c.take(a, diag) || !integer(a[13], INT_MIN, INT_MAX, &chunk) || !integer(a[14], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
+    const at::Tensor *out_ = nullptr, *hT_ = nullptr, *ws_ = nullptr;
+    if (!gpu_or_none(a[11], c.type, {c.N, c.T, c.H, c.dv}, &out_) || !gpu_or_none(a[12], at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &hT_))
+        Py_RETURN_NONE;
+    if (a[10] != Py_None && !(ws_ = on_gpu(a[10]))) Py_RETURN_NONE;
+    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk = (int)c.dk, dv = (int)c.dv;
+    std::optional<at::Tensor> out, hT;
+    at::Tensor ws;
+    int rc;
+    {
+        const NoGil no_gil;
+        if (ws_) ws = *ws_;
+        else {
+            const size_t need = diag ? api.fwd_diag_bytes(N, T, H, dk, dv, (int)chunk, c.dt, c.cu_host, c.n_seq)
+                                     : api.fwd_bytes(N, T, H, dk, dv, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
+            ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
+    }
+    out = out_ ? *out_ : c.empty({c.N, c.T, c.H, c.dv}, c.type);
+    if (hT_) hT = *hT_;
+    else if (want_hT) hT = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
+    rc = (diag ? api.fwd_diag : api.fwd)(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0),
+                                         out->data_ptr(), hT ? static_cast<float*>(hT->data_ptr()) : nullptr,
+                                         static_cast<const int32_t*>(ptr(c.cu)), c.cu_host, c.n_seq, N, T, H, dk, dv, (int)chunk,
+                                         c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+    }
+    if (rc != KLA_OK) return PyLong_FromLong(rc);
+    PyObject* r = PyTuple_New(2);
+    if (!r) return nullptr;
+    PyTuple_SET_ITEM(r, 0, wrap(out));
+    PyTuple_SET_ITEM(r, 1, wrap(hT));
+    return r;
+    END_HANDLE_TH_ERRORS
+}
+
+// chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, d_o, d_hT, want_dh0, chunk, opts)
+// -> (dq, dk, dv, dlog_alpha, deta, dh0), all of them new
+PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 14 || !api.bwd) Py_RETURN_NONE;
+    const bool want_dh0 = a[11] == Py_True;
+    Chunk c;
+    long chunk, opts;
+    if (!c.take(a, false) || !integer(a[12], INT_MIN, INT_MAX, &chunk) || !integer(a[13], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
+    const at::Tensor *d_o = gpu(a[9], c.type, {c.N, c.T, c.H, c.dv}), *d_hT = nullptr;
+    if (!d_o || !gpu_or_none(a[10], at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &d_hT)) Py_RETURN_NONE;
+    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk_ = (int)c.dk, dv_ = (int)c.dv;
+    std::optional<at::Tensor> dq, dk, dv, dla, deta, dh0;
+    int rc;
+    {
+        const NoGil no_gil;
+        const size_t need = api.bwd_bytes(N, T, H, dk_, dv_, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
+        const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
+        dq = c.empty(c.q->sizes(), c.type);
+        dk = c.empty(c.q->sizes(), c.type);
+        dv = c.empty(c.v->sizes(), c.type);
+        dla = c.empty({c.N, c.T, c.H}, at::kFloat);
+        deta = c.empty({c.N, c.T, c.H}, at::kFloat);
+        if (want_dh0) dh0 = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
+        rc = api.bwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT), dq->data_ptr(),
+                     dk->data_ptr(), dv->data_ptr(), static_cast<float*>(dla->data_ptr()), static_cast<float*>(deta->data_ptr()),
+                     dh0 ? static_cast<float*>(dh0->data_ptr()) : nullptr, static_cast<const int32_t*>(ptr(c.cu)), c.cu_host, c.n_seq, N, T,
+                     H, dk_, dv_, (int)chunk, c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+    }
+    if (rc != KLA_OK) return PyLong_FromLong(rc);
+    PyObject* r = PyTuple_New(6);
+    if (!r) return nullptr;
+    const std::optional<at::Tensor>* g[6] = {&dq, &dk, &dv, &dla, &deta, &dh0};
+    for (int i = 0; i < 6; ++i) PyTuple_SET_ITEM(r, i, wrap(*g[i]));
+    return r;
+    END_HANDLE_TH_ERRORS
+}
+
+#define KLA_FASTCALL(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {KLA_FASTCALL(bind), KLA_FASTCALL(decode), KLA_FASTCALL(chunk_fwd), KLA_FASTCALL(chunk_bwd), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "kla_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_kla_binding() { return PyModule_Create(&module); }
