@@ -54,6 +54,7 @@ struct Plan {
     long n_chunks;       // over all sequences
     int n_states;        // sequences
     size_t off_T, off_P, off_G, off_C, off_M, off_S, total;
+    size_t order_bytes;  // of these, what the scan order of a packed batch adds
     int seg_G, seg_Lc;   // segment-parallel scan: segments per sequence (1 = off) and chunks per segment
     int waves;           // compute waves per scan workgroup (of the unsegmented scan)
     bool fused;          // bf16 only: one kernel, no intra-chunk stage, nothing in the workspace
@@ -61,10 +62,14 @@ struct Plan {
 };
 
 // Segments per sequence for the scan stage.  A small fixed-length bf16 batch of long sequences (at most 128
-// sixteen-column chains, at least 64 chunks) is cut so that about 256 workgroups of two chains run (measured
-// on one 65K-token sequence of 8 heads: 1.24 ms unsegmented, 0.70 ms with 4 segments, 0.57 ms with 8, 0.71 ms
-// with 16); the tuning field KLA_TUNE_SCAN_SEGMENTS(n) forces n (1 = never).  Returns the number of non-empty segments and sets the chunks per segment.
-int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& tune, int* Lc)
+// sixteen-column chains, at least 64 chunks) is cut until max_chains sixteen-column chains run, into segments of at least
+// 16 chunks.  Forward: 1024 of them, 256 workgroups of four compute waves; 512, workgroups of two, where the value head
+// is narrow and the maps' d_k more columns weigh most (one 65K sequence of 8 heads 345 against 414 us, 8192 tokens of
+// d_v = 256 84 against 98 us; 2 x 16K tokens of d_v = 64 154 against 137 us).  Backward: 512, its sweeps have two compute
+// waves at most.  Beyond 16 segments their serial composition outweighs the shorter scans (32K tokens of 4 heads: 139 us
+// with 32, 128 us with 16).  The tuning field KLA_TUNE_SCAN_SEGMENTS(n) forces n (1 = never).  Returns the number of
+// non-empty segments and sets the chunks per segment.
+int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& tune, int max_chains, int* Lc)
 {
     *Lc = NT;
     if (dt != KLA_BF16 || n_seq > 0 || N <= 0 || NT < 2) return 1;
@@ -73,9 +78,7 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
     int want = 1;
     if (tune.segments >= 1) want = tune.segments;
     else if (groups <= 128 && NT >= 64) {
-        // up to 512 sixteen-column chains (256 workgroups of two compute waves), segments of at least 16 chunks
-        want = 1;
-        while (want < 16 && (long)want * 2 * groups <= 512 && NT / (want * 2) >= 16) want *= 2;
+        while (want < 16 && (long)want * 2 * groups <= max_chains && NT / (want * 2) >= 16) want *= 2;
     }
     if (want > NT) want = NT;
     if (want <= 1) return 1;
@@ -123,12 +126,23 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     p->off_G = round256((size_t)n_chunks * H * (2 * half + 768));   // + three vectors of 64 fp32 (see kla_mma.hpp)
     p->off_C = round256(p->off_G + (size_t)n_chunks * H * 128 * sizeof(float));      // g and 1/||q||
     p->off_M = round256(p->off_C + (size_t)(2 * n_seq + 1) * sizeof(int32_t));       // chunk offsets, scan order of the sequences
-    p->seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->tune, &p->seg_Lc);
-    // per (sequence, head): G - 1 maps [N | M] and G incoming states, fp32
-    const size_t maps = p->seg_G > 1 ? (size_t)N * (p->seg_G - 1) * H * dk * (dv + dk) * sizeof(float) : 0;
-    const size_t states = p->seg_G > 1 ? (size_t)N * p->seg_G * H * dk * dv * sizeof(float) : 0;
-    p->off_S = round256(p->off_M + maps);
-    p->total = round256(p->off_S + states);
+    p->order_bytes = p->off_M - round256(p->off_C + (size_t)(n_seq + 1) * sizeof(int32_t));
+    auto segments = [&](int max_chains) {
+        p->seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->tune, max_chains, &p->seg_Lc);
+        // per (sequence, head): G - 1 maps [N | M] and G incoming states, fp32
+        const size_t maps = p->seg_G > 1 ? (size_t)N * (p->seg_G - 1) * H * dk * (dv + dk) * sizeof(float) : 0;
+        const size_t states = p->seg_G > 1 ? (size_t)N * p->seg_G * H * dk * dv * sizeof(float) : 0;
+        p->off_S = round256(p->off_M + maps);
+        p->total = round256(p->off_S + states);
+    };
+    segments(dv >= 128 ? 1024 : 512);
+    if (p->total > (size_t)KLA_STATIC_SCRATCH_BYTES && p->seg_G > 1) {
+        // the larger number of segments is not to put a batch out of reach of the entry point with the fixed scratch, nor
+        // to make that entry point's results differ from this one's
+        const size_t all = p->total;
+        segments(512);
+        if (p->total > (size_t)KLA_STATIC_SCRATCH_BYTES && p->total != all) segments(dv >= 128 ? 1024 : 512);
+    }
     p->waves = scan_waves(p->n_states * H, dv, dt, p->tune);
     if (p->tune.fused && !p->tune.scan_waves && p->waves > 2) p->waves = 2;
     // bf16, a plain scan of two compute waves per workgroup (257 .. 512 sixteen-column chains, e.g. 8 x 8 heads of 128
@@ -140,7 +154,7 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     // wherever it can run (one or two compute waves, no segments).
     p->fused = dt == KLA_BF16 && p->seg_G <= 1 && !p->tune.unfused && !p->tune.generic_scan && !p->tune.generic_intra &&
                (p->tune.fused ? p->waves <= 2 : (p->waves == 2 && dv <= 128));
-    if (p->fused) p->total = 256;
+    if (p->fused) { p->total = 256; p->order_bytes = 0; }
     return KLA_OK;
 }
 
@@ -237,12 +251,9 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             sa.seg_G = pl.seg_G; sa.seg_Lc = pl.seg_Lc;
             if (kla::launch_segment_maps_bf16(sa, dk, maps, st) != hipSuccess) return KLA_ERR_HIP;
             if (kla::launch_segment_combine(h0, maps, seg_state, N, H, dk, dv, pl.seg_G, st) != hipSuccess) return KLA_ERR_HIP;
-            sa.h0 = seg_state; sa.hT = seg_state;
+            sa.h0 = seg_state;
             const int wseg = scan_waves(pl.n_states * pl.seg_G * H, dv, KLA_BF16, pl.tune);
-            if (kla::launch_scan_bf16(sa, dk, wseg, st) != hipSuccess) return KLA_ERR_HIP;
-            if (hT && kla::launch_segment_gather(seg_state, hT, N, H, dk, dv, pl.seg_G, pl.seg_G - 1, st) != hipSuccess)
-                return KLA_ERR_HIP;
-            return KLA_OK;
+            return kla::launch_scan_bf16(sa, dk, wseg, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
     const int waves = pl.waves;
@@ -268,6 +279,7 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
 {
     const int rc = make_plan(N, T, H, dk, dv, chunk, dt, cu_host, n_seq, opts, &p->base);
     if (rc != KLA_OK) return rc;
+    p->base.seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->base.tune, 512, &p->base.seg_Lc);
     const size_t half = (size_t)384 * 8 * elem_bytes(dt);
     const size_t ch = (size_t)p->base.n_chunks * H;
     const size_t states = ch * dk * dv * elem_bytes(dt);          // checkpoints are kept in the element type
@@ -459,7 +471,9 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
 // A file-scope device array: every GPU the library runs on holds its own copy at its own address until the
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the address that
 // kernels receive is looked up once per device, with that device current, and kept.
-constexpr size_t kStaticScratchBytes = (size_t)KLA_STATIC_SCRATCH_BYTES;
+// The bound that callers know, KLA_STATIC_SCRATCH_BYTES, does not count the scan order of a packed batch: it has room of
+// its own behind.
+constexpr size_t kStaticScratchBytes = (size_t)KLA_STATIC_SCRATCH_BYTES + (1u << 20);
 constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 std::mutex scratch_mutex;
@@ -590,7 +604,8 @@ int kla_chunk_fwd_static(const void* q, const void* k, const void* v, const floa
     const int rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N,
                                       T, H, dk, dv, chunk, dt, 0u, &pl);
     if (rc != KLA_OK) return rc;
-    if (pl.total > kStaticScratchBytes) return KLA_ERR_WORKSPACE;      // refused before any HIP call
+    if (pl.total - pl.order_bytes > (size_t)KLA_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
+        return KLA_ERR_WORKSPACE;                                       // refused before any HIP call
     if (pl.n_states == 0) return KLA_OK;
     void* ws = static_scratch();
     if (!ws) return KLA_ERR_HIP;

@@ -941,12 +941,17 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 
     auto store_final = [&]() {
         if (!a.hT) return;
+        size_t fc = chain;
+        if (!FU && a.seg_G > 0) {                        // h_T is the state the last segment of a sequence leaves
+            if (s % a.seg_G != a.seg_G - 1) return;
+            fc = (size_t)(s / a.seg_G) * a.H + h;
+        }
 #pragma unroll
         for (int kt = 0; kt < KB; ++kt)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int f = 32 * (kt >> 1) + 8 * g + 4 * (kt & 1) + e;
-                a.hT[((size_t)chain * DK + f) * a.dv + col] = S[kt][e];
+                a.hT[(fc * DK + f) * a.dv + col] = S[kt][e];
             }
     };
 

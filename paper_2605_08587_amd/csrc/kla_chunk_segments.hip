@@ -9,7 +9,7 @@
 //   1. scan_maps_bf16_kernel: for every segment but the last of a sequence, M and N at once, by running the
 //      recurrence on d_v + d_k columns: the value columns from S = 0 with the real V, the "phi" columns from
 //      S = I with V = 0.  No outputs, no Q, no P: only the chain part of a chunk (K S, X, U = T'X, state
-//      update), 32 columns per workgroup.
+//      update), 32 or 64 columns per workgroup.
 //   2. segment_combine_kernel: S_in(0) = h0, S_in(g+1) = M_g S_in(g) + N_g, in fp32 (G - 1 small products).
 //   3. the ordinary scan kernel over all N x G segments at once, each starting from its S_in (the kernel's
 //      segmented mode), which also produces the outputs; segment_gather_kernel then copies the last segment's
@@ -25,33 +25,40 @@ namespace kla {
 
 namespace {
 
-template <int DK>
-struct MapCfg {
-    static constexpr int NW = 2;                         // compute waves, 16 columns each
+template <int DK, int NW>
+struct MapCfg {                                          // NW: compute waves, 16 columns each
     static constexpr int KB = DK / 16, KP = DK / 32;
     static constexpr int SLW = 16 * NW;
     static constexpr int RB = DK * 2, PPR = DK / 8, RPB = 1024 / RB, NKB = 64 / RPB;
     static constexpr int VRW = SLW * 2, VPP = VRW / 16, RPV = 64 / VPP, NVB = 64 / RPV;
     static constexpr int TPB = kTriPairs * 64 * 16, NTB = TPB / 1024;
     static constexpr int OFF_T = 64 * RB, OFF_V = OFF_T + TPB, OFF_EG = OFF_V + 64 * VRW, STAGE = OFF_EG + 512;
-    static constexpr int NST = 3;
-    static constexpr int LDS = NST * STAGE;
+    // Two compute waves: a copy wave keeps a ring of three stages filled.  Four: every wave copies its share of the next
+    // chunk into the other of two stages at the start of a step, and a second workgroup on the CU covers what the first
+    // one waits for (two compute waves per SIMD).
+    static constexpr bool SELF = NW > 2;
+    static constexpr int NST = SELF ? 2 : 3;
+    static constexpr int LDS = NST * STAGE, NTHR = 64 * NW + (SELF ? 0 : 64);
     static constexpr int NDMA_V = NKB + NTB + NVB + 1;   // copy instructions per chunk, value columns
     static constexpr int NDMA_P = NKB + NTB + 1;         // ... phi columns (no V)
-    static_assert(LDS <= 160 * 1024 && NDMA_V < 32, "LDS budget; two chunks of copies within the 6-bit vmcnt");
+    // swizzle of the V slice, as in the scan kernel
+    __host__ __device__ static constexpr int vswz(int row) { return NW == 4 ? 2 * ((row >> 1) & 3) : 0; }
+    static_assert(NW == 2 || NW == 4, "compute waves");
+    static_assert(2 * LDS <= 160 * 1024 && NDMA_V < 32, "two workgroups per CU; two chunks of copies within the 6-bit vmcnt");
+    static_assert(!SELF || (NKB % NW == 0 && NVB == 2 * NW), "shares of the copy blocks");
 };
 
 }  // namespace
 
-// grid: (map chains rounded up to 8) x (d_v + d_k) / 32 workgroups of 2 compute waves + 1 copy wave.
+// grid: (map chains rounded up to 8) x (d_v + d_k) / (16 NW) workgroups.
 // Map chain = ((n (G-1) + sg) H + h): segment sg < G-1 of sequence n, head h.
 // maps: per map chain [N: DK x dv | M: DK x DK] fp32.
 // BREC: the records are those of the backward pass ([T' | M^T | P^T | vectors], see bwd_record_bytes).
-template <int DK, bool BREC = false>
-__global__ __launch_bounds__(192) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a, float* __restrict__ maps)
+template <int DK, int NW, bool BREC>
+__global__ __launch_bounds__((MapCfg<DK, NW>::NTHR), 2) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a, float* __restrict__ maps)
 {
-    typedef MapCfg<DK> C;
-    constexpr int NW = C::NW, KB = C::KB, KP = C::KP, SLW = C::SLW, RB = C::RB, PPR = C::PPR, RPB = C::RPB,
+    typedef MapCfg<DK, NW> C;
+    constexpr int KB = C::KB, KP = C::KP, SLW = C::SLW, RB = C::RB, PPR = C::PPR, RPB = C::RPB,
                   VRW = C::VRW, VPP = C::VPP, RPV = C::RPV, NST = C::NST;
 
     __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
@@ -91,7 +98,7 @@ __global__ __launch_bounds__(192) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a,
     constexpr int VEC = (BREC ? 3 : 2) * C::TPB;         // offset of gamma_i | gamma_C/gamma_i in a record
     const char* tpbase = reinterpret_cast<const char*>(a.wsT) + ((size_t)ch0 * a.H + h) * REC;
 
-    if (wave == NW) {
+    if constexpr (!C::SELF) if (wave == NW) {
         // ---- the copy wave ---------------------------------------------------------------------------
         const int lrow = lane / PPR, pcol = lane % PPR;
         constexpr int NGK = 8 / RPB;                    // the swizzle has period 8 rows
@@ -149,12 +156,35 @@ __global__ __launch_bounds__(192) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a,
         oK[kp] = r * RB + (((4 * kp + g) ^ swz_piece<DK>(r)) * 16);
         oKT[kp] = (4 * g + a4) * RB + (((4 * kp + c4) ^ swz_piece<DK>(4 * g + a4)) * 16);
     }
-    const int oV = (4 * g + a4) * VRW + (16 * wave + 4 * c4) * 2;
+    const int oV = (4 * g + a4) * VRW + (((2 * wave + (c4 >> 1)) ^ C::vswz(4 * g + a4)) * 16) + (c4 & 1) * 8;
 
+    auto issue_part = [&](int c, char* st) {             // this wave's share of the copies of chunk c (SELF; every chunk is full)
+        constexpr int NK = C::NKB / NW, NGK = 8 / RPB;
+        const int lrow = lane / PPR, pcol = lane % PPR;
+        const char* kc = kbase + (size_t)(64 * c) * kq_row;
+        const char* tc = tpbase + (size_t)c * a.H * REC;
+        const int bk = wave * NK, bv = wave * 2;
+        static_for<NK>([&](auto i) {
+            const int lo = lrow * (int)kq_row + ((pcol ^ swz_piece<DK>(RPB * (i % NGK) + lrow)) * 16);
+            dma16(kc + (size_t)((bk + i) * RPB) * kq_row, lo, st + (bk + i) * 1024);
+        });
+        if (wave < 3) {                                  // T': six blocks
+            static_for<2>([&](auto i) { dma16(tc + (2 * wave + i) * 1024, lane * 16, st + C::OFF_T + (2 * wave + i) * 1024); });
+        } else if (lane < 32) dma16(tc + VEC, lane * 16, st + C::OFF_EG);   // gamma_i | gamma_C/gamma_i
+        if (!phi) {
+            const char* vc = vbase + (size_t)(64 * c) * v_row;
+            static_for<2>([&](auto i) {
+                const int lo = (lane / VPP) * (int)v_row + (((lane % VPP) ^ C::vswz(RPV * i + lane / VPP)) * 16);
+                dma16(vc + (size_t)((bv + i) * RPV) * v_row, lo, st + C::OFF_V + (bv + i) * 1024);
+            });
+        }
+    };
+    if constexpr (C::SELF) { issue_part(0, lds); wait_vmcnt<0>(); }
     __syncthreads();                                     // chunk 0 is in stage 0
     int scur = 0;
     for (int c = 0; c < nch; ++c) {
         const char* st = lds + scur * C::STAGE;
+        if constexpr (C::SELF) { if (c + 1 < nch) issue_part(c + 1, lds + (scur ^ 1) * C::STAGE); }   // the stage chunk c-1 was read from
         const char* pG = st + C::OFF_EG + 16 * g;
         const float gC = *reinterpret_cast<const float*>(st + C::OFF_EG + 63 * 4);
         u32x2 Sq[KB];
@@ -205,6 +235,7 @@ __global__ __launch_bounds__(192) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a,
                 const char* p = st + oKT[kp] + 32 * jp * RB + 8 * b;
                 mma_bf16(S[t], lds_read_tr(p), lds_read_tr(p + 16 * RB), Udq[2 * jp], Udq[2 * jp + 1]);
             }
+        if constexpr (C::SELF) wait_vmcnt<0>();          // this wave's copies; the barrier covers the others'
         __syncthreads();   // chunk c+1's operands before their use; all reads of this stage before its refill
         scur = (scur + 1 == NST) ? 0 : scur + 1;
     }
@@ -220,39 +251,71 @@ __global__ __launch_bounds__(192) void scan_maps_bf16_kernel(ScanArgs<bf16_t> a,
         }
 }
 
-// S_in(0) = h0 (or 0), S_in(g+1) = M_g S_in(g) + N_g, in fp32.  The G - 1 steps are serial, so the work of a step
-// is spread wide: one workgroup per (sequence, head, 8 state columns), thread t owns row t/2 and 4 of the
-// columns, reads its row of M_g with all loads in flight at once, and takes S_in(g) from LDS.
+// S_in(0) = h0 (or 0), S_in(g+1) = M_g S_in(g) + N_g, in fp32.  The G - 1 steps are serial, so what counts is the length
+// of one: a workgroup of four waves owns 16 state columns of a (sequence, head), each wave DK / 4 rows, on fp32 MFMA
+// (0.85 us of the CU's matrix cores per step at d_k = 128).  The state goes round through one of two LDS images: one
+// barrier per step.  The rows of M and N of the next step (72 KB per workgroup) and the stores of S_in are issued a few at
+// a time between the products: a wave that issues them in one piece stands in the memory queue for longer than the
+// products take.  Measured, 16 segments of 8 heads: 74 -> 35 us (one thread per row and four
+// columns, nothing fetched ahead -> this).
 template <int DK>
-__global__ __launch_bounds__(2 * DK) void segment_combine_kernel(const float* __restrict__ h0, const float* __restrict__ maps,
-                                                                float* __restrict__ seg_state, int H, int dv, int G)
+__global__ __launch_bounds__(256, 1) void segment_combine_kernel(const float* __restrict__ h0, const float* __restrict__ maps,
+                                                                 float* __restrict__ seg_state, int H, int dv, int G)
 {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    __shared__ __attribute__((aligned(16))) f4 Ss[DK][2];
-    const int nh = blockIdx.x, c0 = blockIdx.y * 8;      // nh = n H + h
+    constexpr int KB = DK / 16, RT = DK / 64;            // blocks of the contraction; row tiles of a wave
+    __shared__ __attribute__((aligned(16))) floatx4 Ss[2][KB * 64];      // accumulator tile t of all rows = B quads of block t
+    const int nh = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, g = lane >> 4;
     const int n = nh / H, h = nh % H;
-    const int row = threadIdx.x >> 1, half = threadIdx.x & 1;
-    const int col = c0 + 4 * half;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (h0) acc = *reinterpret_cast<const f4*>(h0 + ((size_t)nh * DK + row) * dv + col);
-    for (int sg = 0; sg < G; ++sg) {
-        *reinterpret_cast<f4*>(seg_state + ((size_t)((n * G + sg) * H + h) * DK + row) * dv + col) = acc;
-        if (sg + 1 == G) break;
-        const float* mp = maps + (size_t)((n * (G - 1) + sg) * H + h) * DK * (dv + DK);
-        const f4* Mrow = reinterpret_cast<const f4*>(mp + (size_t)DK * dv + (size_t)row * DK);
-        f4 m[DK / 4];
+    const int col = blockIdx.y * 16 + r, row0 = 16 * RT * wave;
+    const int orow = (row0 + 4 * g) * dv + col;          // element (t = 0, e = 0) of this lane in N and in a state
+    floatx4 acc[RT], m[2][RT][KB], nn[2][RT];
+    auto map_of = [&](int sg) { return maps + (size_t)((n * (G - 1) + min(sg, G - 2)) * H + h) * DK * (dv + DK); };   // past the end: the last one again
+    // the part of a map that goes with block b of the contraction: M[rows][16 b ..], and element b of N (RT x 4 = KB of them)
+    auto fetch = [&](const float* mp, int b, floatx4 (&md)[RT][KB], floatx4 (&nd)[RT]) {
 #pragma unroll
-        for (int i = 0; i < DK / 4; ++i) m[i] = Mrow[i];
-        const f4 nn = *reinterpret_cast<const f4*>(mp + (size_t)row * dv + col);
-        Ss[row][half] = acc;
-        __syncthreads();
-        acc = nn;
+        for (int t = 0; t < RT; ++t)
+            md[t][b] = *reinterpret_cast<const floatx4*>(mp + (size_t)DK * dv + (row0 + 16 * t + r) * DK + 16 * b + 4 * g);
+        nd[b >> 2][b & 3] = mp[orow + (16 * (b >> 2) + (b & 3)) * dv];
+    };
+    auto step = [&](int sg, auto cur) {                  // map sg is in set sg & 1
+        constexpr int C = cur;
+        floatx4 old[RT], s[KB];
 #pragma unroll
-        for (int i = 0; i < DK / 4; ++i)
+        for (int t = 0; t < RT; ++t) {
+            Ss[C][(RT * wave + t) * 64 + lane] = acc[t];
+            old[t] = acc[t];
+            acc[t] = nn[C][t];
+        }
+        const float* mp = map_of(sg + 1);
+        float* out = seg_state + (size_t)((n * G + sg) * H + h) * DK * dv + orow;
+        __syncthreads();                                 // the other image is written in the next step only
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acc += m[i][kk] * Ss[4 * i + kk][half];
-        __syncthreads();                                 // every thread has read Ss before it is overwritten
-    }
+        for (int b = 0; b < KB; ++b) s[b] = Ss[C][b * 64 + lane];
+#pragma unroll
+        for (int b = 0; b < KB; ++b) {
+            fetch(mp, b, m[C ^ 1], nn[C ^ 1]);
+            out[(16 * (b >> 2) + (b & 3)) * dv] = old[b >> 2][b & 3];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < RT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[C][t][b][e], s[b][e], acc[t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][e] = h0 ? h0[(size_t)nh * DK * dv + orow + (16 * t + e) * dv] : 0.f;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) fetch(map_of(0), b, m[0], nn[0]);
+    int sg = 0;
+    for (; sg + 2 < G; sg += 2) { step(sg, IntC<0>()); step(sg + 1, IntC<1>()); }
+    if (sg + 1 < G) step(sg++, IntC<0>());
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) seg_state[(size_t)((n * G + sg) * H + h) * DK * dv + orow + (16 * t + e) * dv] = acc[t][e];
 }
 
 // The backward counterpart: g(s-1) = M_s^T g(s) + b(s) down the segments (see launch_segment_combine_rev).  Same
@@ -304,33 +367,40 @@ __global__ void segment_gather_kernel(const float* __restrict__ seg_state, float
     hT[i] = seg_state[((n * G + g_last) * H + h) * per_head + e];
 }
 
-hipError_t launch_segment_maps_bf16(const ScanArgs<bf16_t>& a, int dk, float* maps, hipStream_t st)
+template <int DK, int NW, bool BREC>
+static void maps_launch(const ScanArgs<bf16_t>& a, int n_chains, float* maps, hipStream_t st)
+{
+    typedef MapCfg<DK, NW> C;
+    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * ((a.dv + DK) / C::SLW)));
+    hipLaunchKernelGGL((scan_maps_bf16_kernel<DK, NW, BREC>), grid, dim3(C::NTHR), 0, st, a, maps);
+}
+template <bool BREC>
+static hipError_t maps_waves(const ScanArgs<bf16_t>& a, int dk, float* maps, hipStream_t st)
 {
     const int n_chains = a.N * (a.seg_G - 1) * a.H;
     if (n_chains <= 0) return hipSuccess;
-    const int nsl = (a.dv + dk) / 32;
-    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * nsl));
-    if (dk == 64) hipLaunchKernelGGL((scan_maps_bf16_kernel<64>), grid, dim3(192), 0, st, a, maps);
-    else          hipLaunchKernelGGL((scan_maps_bf16_kernel<128>), grid, dim3(192), 0, st, a, maps);
+    // Four compute waves once that still gives most CUs a workgroup: 15 x 8 maps of 64 chunks and 256 columns 170 -> 133 us,
+    // 3 x 8 maps of 16 chunks (96 workgroups) the wrong way, 54 -> 57 us per call.
+    const bool wide = (long)((n_chains + 7) / 8 * 8) * ((a.dv + dk) / 64) >= 192;
+    if (dk == 64) { if (wide) maps_launch<64, 4, BREC>(a, n_chains, maps, st); else maps_launch<64, 2, BREC>(a, n_chains, maps, st); }
+    else          { if (wide) maps_launch<128, 4, BREC>(a, n_chains, maps, st); else maps_launch<128, 2, BREC>(a, n_chains, maps, st); }
     return hipGetLastError();
 }
-
+hipError_t launch_segment_maps_bf16(const ScanArgs<bf16_t>& a, int dk, float* maps, hipStream_t st)
+{
+    return maps_waves<false>(a, dk, maps, st);
+}
 hipError_t launch_segment_maps_bwdrec_bf16(const ScanArgs<bf16_t>& a, int dk, float* maps, hipStream_t st)
 {
-    const int n_chains = a.N * (a.seg_G - 1) * a.H;
-    if (n_chains <= 0) return hipSuccess;
-    const int nsl = (a.dv + dk) / 32;
-    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * nsl));
-    if (dk == 64) hipLaunchKernelGGL((scan_maps_bf16_kernel<64, true>), grid, dim3(192), 0, st, a, maps);
-    else          hipLaunchKernelGGL((scan_maps_bf16_kernel<128, true>), grid, dim3(192), 0, st, a, maps);
-    return hipGetLastError();
+    return maps_waves<true>(a, dk, maps, st);
 }
 
 hipError_t launch_segment_combine(const float* h0, const float* maps, float* seg_state, int N, int H, int dk, int dv,
                                   int G, hipStream_t st)
 {
-    const dim3 grid((unsigned)(N * H), (unsigned)(dv / 8));
-    if (dk == 64) hipLaunchKernelGGL((segment_combine_kernel<64>), grid, dim3(128), 0, st, h0, maps, seg_state, H, dv, G);
+    if (G < 2) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(N * H), (unsigned)(dv / 16));
+    if (dk == 64) hipLaunchKernelGGL((segment_combine_kernel<64>), grid, dim3(256), 0, st, h0, maps, seg_state, H, dv, G);
     else          hipLaunchKernelGGL((segment_combine_kernel<128>), grid, dim3(256), 0, st, h0, maps, seg_state, H, dv, G);
     return hipGetLastError();
 }

@@ -65,8 +65,8 @@ template <typename E> struct ScanArgs {
     const E* wsT; const E* wsP; const float* wsG;
     unsigned opts;
     // Segmented mode (seg_G > 0, fixed-length batches only): "sequence" s of the kernel is segment s % seg_G of
-    // sequence s / seg_G, seg_Lc chunks long (the last one of a sequence takes what is left), and h0 / hT are
-    // indexed by segment.
+    // sequence s / seg_G, seg_Lc chunks long (the last one of a sequence takes what is left), h0 is indexed by segment,
+    // and hT, by sequence, is written by the last segment.
     int seg_G, seg_Lc;
     // Diagonal gating: the transposed K operand of the state update comes from kt_src instead of
     // k, and the state decays per row by gc_vec[chunk-head][dk] instead of by gamma_C.  Both NULL otherwise.
