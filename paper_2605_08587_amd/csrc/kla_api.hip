@@ -202,6 +202,13 @@ int scan_waves(int n_chains, int dv, int dt, const Tune& tune, long* cost_out)
     return w;
 }
 
+// Whether the intra-chunk stage finds its chunks by itself and leaves the offsets and the scan order of a packed batch to the
+// kernels behind it; a batch without a single chunk has no such stage.
+bool intra_places(int n_seq, long n_chunks, bool generic)
+{
+    return n_seq > 0 && n_seq <= kla::kPosScanMax && n_chunks > 0 && !generic;
+}
+
 template <typename E>
 int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
                    const float* h0, void* o, float* hT, const int32_t* cu_dev, int n_seq, int N, int T, int H, int dk,
@@ -234,7 +241,10 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_scan_fused_bf16(fa, dk, pl.waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    if (intra && n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    const bool generic_intra = sizeof(E) == 2 && pl.tune.generic_intra;
+    if (intra && !intra_places(n_seq, pl.n_chunks, generic_intra)) {
+        if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    } else if (intra) ia.pos_out = chunk_off;
     if (intra) {
         [[maybe_unused]] bool done = false;
         if constexpr (sizeof(E) == 2) {
@@ -331,9 +341,11 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
 {
     int* chunk_off = reinterpret_cast<int*>(ws + pl.off_C);
     const int NT = (T + 63) / 64;
-    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    const bool placed = intra_places(n_seq, pl.base.n_chunks, sizeof(E) == 2 && pl.base.tune.generic_bwd);
+    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
 
     kla::IntraArgs<E> ia;
+    if (placed) ia.pos_out = chunk_off;
     ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
     ia.log_alpha = log_alpha; ia.eta = eta; ia.eps = eps;
     ia.cu_seqlens = n_seq > 0 ? cu_dev : nullptr; ia.chunk_off = chunk_off; ia.n_seq = n_seq;
@@ -454,8 +466,10 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
 {
     int* chunk_off = reinterpret_cast<int*>(ws + pl.base.off_C);
     const int NT = (T + 63) / 64;
-    if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    const bool placed = intra_places(n_seq, pl.base.n_chunks, false);
+    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
     kla::IntraDiagArgs<E> ia;
+    if (placed) ia.pos_out = chunk_off;
     ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
     ia.log_alpha = log_alpha; ia.eta = eta; ia.eps = eps;
     ia.cu_seqlens = n_seq > 0 ? cu_dev : nullptr; ia.chunk_off = chunk_off; ia.n_seq = n_seq;

@@ -370,7 +370,8 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = blockIdx.x % a.H;
     const int cg = blockIdx.x / a.H;
-    const ChunkPos cp = chunk_pos(a.cu_seqlens, a.chunk_off, a.n_seq, a.T, a.NT, cg);
+    const ChunkPos cp = a.pos_out ? chunk_pos_scan(a.cu_seqlens, a.n_seq, cg, lane, tid < 64 && blockIdx.x == 0 ? a.pos_out : nullptr)
+                                  : chunk_pos(a.cu_seqlens, a.chunk_off, a.n_seq, a.T, a.NT, cg);
     const long tok0 = cp.tok0;
     const int clen = cp.clen;
     const size_t row_stride = (size_t)a.H * DK;

@@ -11,7 +11,8 @@
 //     that the record stores (K Q^T for P, Q K^T for the backward's P^T), so P never passes through LDS.
 //   * ||k_i||^2 is the diagonal of K K^T, ||q_i||^2 a sum over the registers of the lanes that hold row i.
 // Measured, K and Q staged as operand slots (101 KB, one workgroup per CU) -> this kernel: 1024 chunk-heads of d_k = 128
-// 79 -> 34 us (36 us with three workgroups per CU and no spilled register), 64 chunk-heads of d_k = 64 13.3 -> 9.7 us.
+// 79 -> 34 us, 64 chunk-heads of d_k = 64 13.3 -> 9.7 us; with the rows of the substitutions read two ahead instead of all
+// at once (no spilled register) 31.9 -> 29.4 us.
 #include "kla_common.hpp"
 #include "kla_kernels.hpp"
 #include "kla_f32_ops.hpp"
@@ -52,7 +53,8 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int h = blockIdx.x % a.H;
-    const ChunkPos cp = chunk_pos(a.cu_seqlens, a.chunk_off, a.n_seq, a.T, a.NT, blockIdx.x / a.H);
+    const ChunkPos cp = a.pos_out ? chunk_pos_scan(a.cu_seqlens, a.n_seq, blockIdx.x / a.H, lane, tid < 64 && blockIdx.x == 0 ? a.pos_out : nullptr)
+                                  : chunk_pos(a.cu_seqlens, a.chunk_off, a.n_seq, a.T, a.NT, blockIdx.x / a.H);
     const int clen = cp.clen;
     const size_t ks = (size_t)a.H * DK;
     char* rec = reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC;
@@ -196,18 +198,31 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
     // ---- (I + L)^{-1}: the diagonal 16x16 blocks by forward substitution (wave w: block w, lane r: column r; the rows
     //      of L are read ahead, they do not depend on the result)
     {
+        constexpr int AHEAD = 2;
         const float* Lb = Lm + 16 * wave * kLdm + 16 * wave;
         float xs[16];
+        floatx4 rows[AHEAD + 1][4];
+        auto read_row = [&](auto ic) {
+            constexpr int i = ic;
+            if constexpr (i < 16) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+                for (int c4 = 0; c4 < (i + 3) / 4; ++c4) rows[i % (AHEAD + 1)][c4] = lda4(Lb + i * kLdm + 4 * c4);
+            }
+        };
+        static_for<AHEAD>([&](auto ic) { read_row(IntC<ic + 1>()); });
+        xs[0] = (r == 0) ? 1.f : 0.f;
+        static_for<15>([&](auto ic) {
+            constexpr int i = ic + 1;
+            read_row(IntC<i + AHEAD>());
             float s0 = (i == r) ? 1.f : 0.f, s1 = 0.f;
-            floatx4 row[4];
-#pragma unroll
-            for (int c4 = 0; c4 < (i + 3) / 4; ++c4) row[c4] = lda4(Lb + i * kLdm + 4 * c4);
-#pragma unroll
-            for (int j = 0; j < i; ++j) { if (j & 1) s1 -= row[j >> 2][j & 3] * xs[j]; else s0 -= row[j >> 2][j & 3] * xs[j]; }
+            static_for<i>([&](auto rc) {
+                constexpr int rr = rc;
+                if constexpr (rr & 1) s1 -= rows[i % (AHEAD + 1)][rr >> 2][rr & 3] * xs[rr];
+                else                  s0 -= rows[i % (AHEAD + 1)][rr >> 2][rr & 3] * xs[rr];
+            });
             xs[i] = s0 + s1;
-        }
+            asm volatile("" : "+v"(xs[i]) : : "memory");     // no row is read earlier than said: 15 rows at once spill
+        });
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             if ((i >> 2) == g) Tm[(16 * wave + i) * kLdm + 16 * wave + r] = xs[i];

@@ -35,6 +35,9 @@ template <typename E> struct IntraArgs {
     int T, NT, H;
     E* wsT; E* wsP; float* wsG;
     unsigned opts;                               // kOptNormalizeQ | kOptGdnBeta
+    // Packed batches of at most kPosScanMax sequences: where this stage leaves the chunk offsets and the scan order for the
+    // kernels behind it (NULL: launch_chunk_offsets has run).  Not for the element-type-generic kernels.
+    int* pos_out = nullptr;
 };
 hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);       // bf16, plain form
 // the records of the backward pass (see bwd_record_bytes in kla_mma.hpp) at a.wsT; a.wsP, a.wsG unused; a.opts: kOptNormalizeQ | kOptGdnBeta
@@ -54,6 +57,7 @@ template <typename E> struct IntraDiagArgs {
     E* wsT; float* wsG;
     E* kplus; E* qplus; E* ktilde; float* gc;
     unsigned opts;                               // kOptNormalizeQ (folded into qplus and P) | kOptGdnBeta
+    int* pos_out = nullptr;                      // as in IntraArgs
 };
 template <typename E> hipError_t launch_intra_diag(const IntraDiagArgs<E>& a, int dk, int n_chunks, hipStream_t st);
 
