@@ -418,8 +418,13 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     const int waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
     if constexpr (sizeof(E) == 2) {
         if (fast) {
-            if (kla::launch_bwd_states_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
-            if (kla::launch_bwd_scan_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
+            // four waves (64 columns) where that saves rounds of workgroups, one per CU: its visits are about 1.15 times as
+            // long (call of 8 x 4096 tokens, 8 heads, one round either way: 469 us with two, 511 us with four; 9 x 2000,
+            // two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347; 40 x 1000, five rounds against three: 584, 520)
+            const long wg2 = chains8 * (dv / 32), r2 = (wg2 + 255) / 256, r4 = (wg2 / 2 + 255) / 256;
+            const int bw = waves == 2 && r4 * 115 < r2 * 100 ? 4 : waves;
+            if (kla::launch_bwd_states_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
+            if (kla::launch_bwd_scan_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }

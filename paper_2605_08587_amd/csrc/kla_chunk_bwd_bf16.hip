@@ -47,10 +47,13 @@ struct SweepCfg16 {
     // the store wave.  Reverse: a stage also holds Q, M^T and P^T, and what decides its speed is a ring of three stages
     // (the copies of a chunk then have two visits to arrive): the staging tiles get one parity only (a counter in LDS
     // tells the compute waves that the store wave has read them) and the checkpoint is stored by the compute waves.
-    static constexpr int NPAR = REV ? 1 : 2;
+    // With four compute waves the reverse stage does not fit three times anyway, and there is room for both parities.
+    static constexpr int NPAR = REV && NW <= 2 ? 1 : 2, NTILE = REV ? 2 : 1;
     static constexpr int CKB = REV ? 0 : SLW * DK * 2;
-    static constexpr int NST = (3 * STAGE + 2 * NPAR * OSB + 2 * CKB <= 160 * 1024) ? 3 : 2;   // LDS ring depth
-    static constexpr int OFF_CK = NST * STAGE + 2 * NPAR * OSB;
+    static constexpr int NST = (3 * STAGE + NTILE * NPAR * OSB + 2 * CKB <= 160 * 1024) ? 3 : 2;   // LDS ring depth
+    static constexpr int OFF_CK = NST * STAGE + NTILE * NPAR * OSB;
+    // swizzle of the V / dO slice, as in the forward kernel (period 8 rows: the same for every copy block)
+    __host__ __device__ static constexpr int vswz(int row) { return NW == 4 ? 2 * ((row >> 1) & 3) : 0; }
     static constexpr int LDS = OFF_CK + 2 * CKB;
     static constexpr int NDMA = (REV ? 2 : 1) * NKB + NTB + NVB + 1;
     static_assert(LDS <= 160 * 1024 && NDMA < 64, "LDS budget of a gfx950 CU; 6-bit vmcnt");
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
 #pragma unroll
     for (int j = 0; j < NGK; ++j)
         gk[j] = lrow * (int)kq_row + ((pcol ^ swz_piece<DK>(RPB * j + lrow)) * 16);
-    const int gv = (lane / VPP) * (int)v_row + (lane % VPP) * 16;
+    const int gv = (lane / VPP) * (int)v_row + (((lane % VPP) ^ C::vswz(lane / VPP)) * 16);
     int oK[KP];
 #pragma unroll
     for (int kp = 0; kp < KP; ++kp) oK[kp] = r * RB + (((4 * kp + g) ^ swz_piece<DK>(r)) * 16);
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
     int oKT[KP];
 #pragma unroll
     for (int kp = 0; kp < KP; ++kp) oKT[kp] = (4 * g + a4) * RB + (((4 * kp + c4) ^ swz_piece<DK>(4 * g + a4)) * 16);
-    const int oV = (4 * g + a4) * VRW + (16 * wave + 4 * c4) * 2;
+    const int oV = (4 * g + a4) * VRW + (((2 * wave + (c4 >> 1)) ^ C::vswz(4 * g + a4)) * 16) + (c4 & 1) * 8;
     const int oO = (4 * g + (r & 3)) * ORB + (16 * wave + 4 * (r >> 2)) * 2;
     const bool q_lo = (r & 3) < 2;
     const uint32_t psel = (r & 1) ? 0x03020706u : 0x05040100u;
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
             static_for<C::NVB>([&](auto i) {
                 const int b = i;
                 const int row = b * RPV + lane / VPP;
-                dma16(vc, min(row, clen - 1) * (int)v_row + (lane % VPP) * 16, st + C::OFF_V + b * 1024);
+                dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + b * 1024);
             });
         }
         // forward: T' (first half of the record); backward: M^T | P^T (second and third)
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
             if constexpr (C::NPAR == 1) {
                 // one staging parity: the store wave must have read the tiles of the previous visit (it does so right
                 // after the barrier, a whole visit ago; the wait is a formality, and bounded)
-                for (int spin = 0; *reinterpret_cast<const volatile int*>(lds + NST * C::STAGE + 64) < vis - 1 && spin < (1 << 15); ++spin)
+                for (int spin = 0; *reinterpret_cast<const volatile int*>(lds + NST * C::STAGE + VRW) < vis - 1 && spin < (1 << 15); ++spin)
                     __builtin_amdgcn_s_sleep(1);
                 asm volatile("" ::: "memory");
             }
@@ -368,11 +371,11 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
     };
 
     char* ost0 = lds + NST * C::STAGE;
-    char* ost1 = C::NPAR == 2 ? ost0 + 2 * C::OSB : ost0;
+    char* ost1 = C::NPAR == 2 ? ost0 + C::NTILE * C::OSB : ost0;
     char* ckb0 = lds + C::OFF_CK;
     // last visit whose staged tiles the store wave has read (one staging parity only); in the padding of the first
-    // staging row (a row holds at most 64 of its ORB = 96 bytes)
-    int* oflag = reinterpret_cast<int*>(ost0 + 64);
+    // staging row (a row holds VRW of its ORB bytes)
+    int* oflag = reinterpret_cast<int*>(ost0 + VRW);
     if (C::NPAR == 1 && tid == 0) *oflag = -1;
     // chunks are visited in the order i = 0 .. nch-1; the backward sweep starts at the last chunk
     auto chunk_of = [&](int i) { return REV ? nch - 1 - i : i; };
@@ -841,18 +844,19 @@ static hipError_t launch_sweep_dk(const BwdArgs<bf16_t>& a, int waves, hipStream
     if (n_chains == 0) return hipSuccess;
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
     if (waves == 1) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 1, REV>), grid, dim3(192), 0, st, a);
-    else            hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 2, REV>), grid, dim3(256), 0, st, a);
+    else if (waves == 2) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 2, REV>), grid, dim3(256), 0, st, a);
+    else            hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 4, REV>), grid, dim3(384), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_states_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (waves != 1 && waves != 2) return hipErrorInvalidValue;
+    if (waves != 1 && waves != 2 && waves != 4) return hipErrorInvalidValue;
     return dk == 64 ? launch_sweep_dk<64, false>(a, waves, st) : launch_sweep_dk<128, false>(a, waves, st);
 }
 hipError_t launch_bwd_scan_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (waves != 1 && waves != 2) return hipErrorInvalidValue;
+    if (waves != 1 && waves != 2 && waves != 4) return hipErrorInvalidValue;
     return dk == 64 ? launch_sweep_dk<64, true>(a, waves, st) : launch_sweep_dk<128, true>(a, waves, st);
 }
 
