@@ -10,7 +10,8 @@
 //     state-shaped results (S, dS)                            : wave w owns d_k / 64 of the 16-row feature tiles
 // so each accumulator exists once, and what the next product contracts over (S, X, U; dS, dU, dX) is exchanged through
 // LDS as operand quads (kla_mma.hpp): one conflict-free 16-byte write and read per lane and tile.  A workgroup takes
-// NC = 1 or 2 column tiles; two halve the LDS reads per product and are used once there are more tiles than CUs.
+// NC = 1 or 2 column tiles; two halve the LDS reads per product and are used once there are more tiles than CUs.  The
+// forward has a form with four more waves (scan_f32_split_kernel) for batches that leave a workgroup a CU of its own.
 //
 // Operands.  K (and Q where it is contracted over the tokens) is needed row- and column-wise: it sits in LDS as plain
 // token rows whose 16-byte pieces are XORed with the row index mod 16, which makes the 128-bit row reads and the 32-bit
@@ -24,7 +25,7 @@
 // so they reach no result; in the reverse sweep dO is zeroed there - and behind the last chunk that chunk is read again.
 //
 // Measured, one wave per chain -> this file: forward of 4 sequences of 2000 tokens, 8 heads, d = 128 (256 column tiles):
-// 590 -> 118 us, 3.7 us per chunk against 1.7 us of MFMA per wave (143 us with conditional loads); 2 sequences of 500
+// 590 -> 118 us, 3.7 us per chunk against 1.7 us of MFMA per wave (143 us with conditional loads; 94 us with eight waves); 2 sequences of 500
 // tokens, 4 heads, d = 64 (32 tiles): forward 71 -> 20 us, forward sweep 53 -> 17 us, reverse sweep 124 -> 28 us.
 #include "kla_common.hpp"
 #include "kla_f32_ops.hpp"
@@ -281,6 +282,193 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
     if (a.hT) {
 #pragma unroll
         for (int n = 0; n < NC; ++n) store_state<DK>(S[n], a.hT + (size_t)p.chain * DK * a.dv + col0 + 16 * n, a.dv, wave, g);
+    }
+}
+
+// The same with eight waves, two per SIMD: waves 0 .. 3 carry the chain (K S, X, U, the state update), waves 4 .. 7, which
+// share their SIMDs, do everything off it (Q S, P U, the outputs, the copies of K).  With four waves a SIMD stands idle
+// whenever its only wave waits for LDS or a barrier: 3.7 us per chunk for 1.7 us of MFMA, here 2.9 us.  K and the exchanged
+// state have two images each, so a step needs three barriers instead of four.  (Loads requested two chunks ahead, two
+// accumulators per product and a raised priority of the chain change nothing: 123 us either way.)
+template <int DK, int NC, bool DIAG>
+__global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> a)
+{
+    typedef F32<DK> C;
+    constexpr int KB = C::KB, TS = C::TS;
+    constexpr int KIMG = (DIAG ? 2 : 1) * C::TILE, SIMG = NC * C::SXB;
+    constexpr int OFF_K2 = C::TILE, OFF_S = 2 * KIMG, OFF_X = OFF_S + 2 * SIMG, OFF_U = OFF_X + NC * C::RXB,
+                  OFF_UD = OFF_U + NC * C::RXB, LDS = OFF_UD + NC * C::RXB;
+    static_assert(LDS <= 160 * 1024, "LDS budget of a gfx950 CU");
+    __shared__ __attribute__((aligned(1024))) char lds[LDS];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;       // row tile, in either role
+    const bool chain = __builtin_amdgcn_readfirstlane(tid >> 8) == 0;
+    const int r = lane & 15, g = lane >> 4;
+    const Pos p = sweep_pos(a, a.dv, 16 * NC);
+    if (!p.valid) return;
+    const int col0 = p.slice * 16 * NC + r;
+    const size_t ks = (size_t)a.H * DK, vs = (size_t)a.H * a.dv;
+    constexpr int HALF = ws_half_bytes<float>(), REC = ws_record_bytes<float>();
+    const char* rec0 = reinterpret_cast<const char*>(a.wsT) + ((size_t)p.ch0 * a.H + p.h) * REC;
+    const size_t rec_step = (size_t)a.H * REC;
+    const int row0 = 16 * wave + 4 * g;
+
+    if (chain) {
+        const float* vb = a.v + (size_t)p.t0 * vs + (size_t)p.h * a.dv + col0;
+        TileOps<DK> ops;
+        ops.init(wave, r, g);
+        floatx4 S[NC][TS];
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            if (a.h0) load_state<DK>(S[n], a.h0 + (size_t)p.chain * DK * a.dv + col0 + 16 * n, a.dv, wave, g);
+            else
+#pragma unroll
+                for (int t = 0; t < TS; ++t) S[n][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto put_state = [&](char* img) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int t = 0; t < TS; ++t)
+                    *reinterpret_cast<float4*>(img + n * C::SXB + ((wave * TS + t) * 64 + lane) * 16) = quad(S[n][t]);
+        };
+        TriRegs tf;
+        floatx4 vf[NC], eg, ed, gcv[TS];
+        float gC = 1.f;
+        auto get_v = [&](int c) {
+            const int clen = min(64, p.len - 64 * c);
+#pragma unroll
+            for (int n = 0; n < NC; ++n) vf[n] = load_col(vb + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen);
+            const char* rec = rec0 + (size_t)c * rec_step + 2 * HALF;
+            eg = lda4(rec + 4 * row0);
+            ed = lda4(rec + 256 + 4 * row0);
+            gC = *reinterpret_cast<const float*>(rec + 252);
+            if constexpr (DIAG) {
+                const float* gc = a.gc_vec + ((size_t)(p.ch0 + c) * a.H + p.h) * DK + 4 * g;
+#pragma unroll
+                for (int t = 0; t < TS; ++t) gcv[t] = lda4(gc + 16 * (wave * TS + t));
+            }
+        };
+        if (p.nch > 0) {
+            get_v(0);
+            load_tri(tf, rec0, wave, lane);
+            put_state(lds + OFF_S);
+        }
+        __syncthreads();
+        for (int c = 0; c < p.nch; ++c) {
+            const int cn = min(c + 1, p.nch - 1);
+            const char* kt_img = lds + (c & 1) * KIMG;
+            const char* s_img = lds + OFF_S + (c & 1) * SIMG;
+            // ---- X = V - D_gamma K S
+            floatx4 x[NC];
+#pragma unroll
+            for (int n = 0; n < NC; ++n) x[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                const float4 ka = ops.row_quad(kt_img, b);
+#pragma unroll
+                for (int n = 0; n < NC; ++n) mma16(x[n], ka, ldf4(s_img + n * C::SXB + (b * 64 + lane) * 16));
+            }
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+                *reinterpret_cast<float4*>(lds + OFF_X + n * C::RXB + (wave * 64 + lane) * 16) = quad(vf[n] - eg * x[n]);
+            __syncthreads();
+            // ---- U = T' X
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                floatx4 u = {0.f, 0.f, 0.f, 0.f};
+                mma_tri(u, tf, lds + OFF_X + n * C::RXB, wave, lane);
+                *reinterpret_cast<float4*>(lds + OFF_UD + n * C::RXB + (wave * 64 + lane) * 16) = quad(u * ed);
+                *reinterpret_cast<float4*>(lds + OFF_U + n * C::RXB + (wave * 64 + lane) * 16) = quad(u);
+            }
+            __syncthreads();
+            load_tri(tf, rec0 + (size_t)cn * rec_step, wave, lane);
+            // ---- S = gamma_C S + K^T (diag(gamma_C/gamma_i) U)
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int t = 0; t < TS; ++t) { if constexpr (DIAG) S[n][t] = S[n][t] * gcv[t]; else S[n][t] = S[n][t] * gC; }
+            get_v(cn);
+#pragma unroll
+            for (int jb = 0; jb < 4; ++jb) {
+                float4 ud[NC];
+#pragma unroll
+                for (int n = 0; n < NC; ++n) ud[n] = ldf4(lds + OFF_UD + n * C::RXB + (jb * 64 + lane) * 16);
+#pragma unroll
+                for (int t = 0; t < TS; ++t) {
+                    const float4 kt = ops.col_quad(kt_img + (DIAG ? OFF_K2 : 0), t, jb);
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) mma16(S[n][t], kt, ud[n]);
+                }
+            }
+            put_state(lds + OFF_S + ((c + 1) & 1) * SIMG);       // the image chunk c - 1 was read from
+            __syncthreads();
+        }
+        if (a.hT) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n) store_state<DK>(S[n], a.hT + (size_t)p.chain * DK * a.dv + col0 + 16 * n, a.dv, wave, g);
+        }
+    } else {
+        const int t2 = tid - 256;
+        const float* kb = a.k + (size_t)p.t0 * ks + (size_t)p.h * DK;
+        const float* qb = a.q + (size_t)p.t0 * ks + (size_t)p.h * DK;
+        const float* k2b = DIAG ? a.kt_src + (size_t)p.t0 * ks + (size_t)p.h * DK : nullptr;
+        float* ob = a.o + (size_t)p.t0 * vs + (size_t)p.h * a.dv + col0;
+        float4 qf[KB];
+        TriRegs pf;
+        floatx4 eq;
+        auto get_q = [&](int c) {
+            const float* q = qb + (size_t)min(64 * c + 16 * wave + r, p.len - 1) * ks + 4 * g;
+#pragma unroll
+            for (int b = 0; b < KB; ++b) qf[b] = ldf4(q + 16 * b);
+            eq = lda4(rec0 + (size_t)c * rec_step + 2 * HALF + 512 + 4 * row0);
+        };
+        TileRegs<DK> kr, k2r;
+        auto fetch_k = [&](int c) {
+            const int clen = min(64, p.len - 64 * c);
+            kr.load(kb + (size_t)(64 * c) * ks, ks, clen, t2);
+            if constexpr (DIAG) k2r.load(k2b + (size_t)(64 * c) * ks, ks, clen, t2);
+        };
+        auto stash_k = [&](char* img) {
+            kr.stash(img, t2);
+            if constexpr (DIAG) k2r.stash(img + OFF_K2, t2);
+        };
+        if (p.nch > 0) {
+            fetch_k(0);
+            get_q(0);
+            load_tri(pf, rec0 + HALF, wave, lane);
+            stash_k(lds);
+        }
+        __syncthreads();
+        for (int c = 0; c < p.nch; ++c) {
+            const int cn = min(c + 1, p.nch - 1);
+            const char* s_img = lds + OFF_S + (c & 1) * SIMG;
+            fetch_k(cn);                                 // lands during this chunk's products
+            // ---- Q S, half of it on either side of the chain's first barrier
+            floatx4 o[NC];
+#pragma unroll
+            for (int n = 0; n < NC; ++n) o[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                if (b == KB / 2) __syncthreads();
+#pragma unroll
+                for (int n = 0; n < NC; ++n) mma16(o[n], qf[b], ldf4(s_img + n * C::SXB + (b * 64 + lane) * 16));
+            }
+#pragma unroll
+            for (int n = 0; n < NC; ++n) o[n] = o[n] * eq;
+            get_q(cn);
+            __syncthreads();
+            // ---- O = D_gamma (Q S) + P U
+            const int clen = min(64, p.len - 64 * c);
+#pragma unroll
+            for (int n = 0; n < NC; ++n) mma_tri(o[n], pf, lds + OFF_U + n * C::RXB, wave, lane);
+            load_tri(pf, rec0 + (size_t)cn * rec_step + HALF, wave, lane);
+            stash_k(lds + ((c + 1) & 1) * KIMG);         // the image chunk c - 1 was read from
+#pragma unroll
+            for (int n = 0; n < NC; ++n) store_col(ob + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen, o[n]);
+            __syncthreads();
+        }
     }
 }
 
@@ -582,8 +770,21 @@ static hipError_t launch_scan_dk(const ScanArgs<float>& a, int tiles, hipStream_
     const int n_chains = (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
     if (n_chains == 0) return hipSuccess;
     const dim3 grid = sweep_grid(n_chains, a.dv, tiles);
-    if (tiles == 1) hipLaunchKernelGGL((scan_f32_kernel<DK, 1, DIAG>), grid, dim3(256), 0, st, a);
-    else            hipLaunchKernelGGL((scan_f32_kernel<DK, 2, DIAG>), grid, dim3(256), 0, st, a);
+    // Eight waves per workgroup while every workgroup has a CU to itself: 256 tiles 139 -> 123 us per call (4 x 2000 tokens, 8
+    // heads, d = 128), 512 tiles, two per workgroup, 126 -> 111 us, 256 tiles with per-channel decay 97 -> 81 us.  With more
+    // tiles two workgroups of four waves share a CU and cover each other (1024 tiles 209 us against 217 us with eight
+    // waves); per-channel decay with two tiles per workgroup would not fit the second image of its two K tiles.
+    const long wgs = ((long)n_chains + 7) / 8 * 8 * (a.dv / (16 * tiles));
+    if (tiles == 1) hipLaunchKernelGGL((scan_f32_split_kernel<DK, 1, DIAG>), grid, dim3(512), 0, st, a);
+    else {
+        if constexpr (!DIAG) {
+            if (wgs <= 256) {
+                hipLaunchKernelGGL((scan_f32_split_kernel<DK, 2, DIAG>), grid, dim3(512), 0, st, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((scan_f32_kernel<DK, 2, DIAG>), grid, dim3(256), 0, st, a);
+    }
     return hipGetLastError();
 }
 hipError_t launch_scan_f32(const ScanArgs<float>& a, int dk, int tiles, hipStream_t st)
