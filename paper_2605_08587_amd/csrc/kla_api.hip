@@ -167,7 +167,8 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     if (p->tune.fused && !p->tune.scan_waves && p->waves > 2) p->waves = 2;
     // The fused kernel keeps the per-chunk objects on chip and needs nothing of the workspace (a token size is still
     // reported and asked for).  KLA_TUNE_FUSED forces it wherever it can run (one or two compute waves, no segments).
-    p->fused = dt == KLA_BF16 && p->seg_G <= 1 && !p->tune.unfused && !p->tune.generic_scan && !p->tune.generic_intra &&
+    // A batch without a token (whose inputs may be NULL) only hands its states on: the plain scan does that.
+    p->fused = dt == KLA_BF16 && n_chunks > 0 && p->seg_G <= 1 && !p->tune.unfused && !p->tune.generic_scan && !p->tune.generic_intra &&
                (p->tune.fused ? p->waves <= 2
                               : (p->tune.scan_waves ? p->waves == 2 && dv <= 128
                                                     : fused_pays((long)p->n_states * H, longest, n_chunks * H, dk, dv, n_seq > 0, cost)));

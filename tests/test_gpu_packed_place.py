@@ -43,3 +43,15 @@ def test_placement(kla, lens, dt, tol):
     rg = token_oracle.kla_recurrent_bwd(*f32, d["eps"], kla_inputs.to_numpy_f32(d_o), **ref)
     errs = {m: err(g[m], rg[m]) for m in rg}
     assert max(errs.values()) <= tol, errs
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+def test_no_tokens(kla, dt):
+    """No token anywhere: h_T is h_0, whichever form runs."""
+    h0 = torch.randn(2, 3, 128, 64, device="cuda")
+    cu = torch.zeros(3, dtype=torch.int32)
+    for shape, packed in (((2, 0, 3), {}), ((1, 0, 3), dict(cu_seqlens=cu.cuda(), cu_seqlens_host=cu))):
+        e = lambda *s, t=dt: torch.empty(*shape, *s, dtype=t, device="cuda")
+        for tune in (0, kla.tune(unfused=True), kla.tune(fused=True)):
+            o, hT = kla.kla_chunk_fwd(e(128), e(128), e(64), e(t=torch.float32), e(t=torch.float32), 1e-6, h0=h0, tune=tune, **packed)
+            assert o.numel() == 0 and torch.equal(hT, h0)
