@@ -109,9 +109,7 @@ int kla_chunk_fwd(const void *q, const void *k, const void *v,
  * until the process ends).  The call allocates and frees nothing, neither directly nor through another library.
  *   - A problem whose kla_chunk_fwd_workspace_bytes(...) exceeds KLA_STATIC_SCRATCH_BYTES is refused with
  *     KLA_ERR_WORKSPACE before anything is launched (32 MiB holds about 2 400 chunk-heads of the two-kernel form
- *     in bf16, 1 200 in fp32; bf16 problems that run the fused kernel need none of it and are never refused;
- *     bf16 problems of 384 to 2047 chains of sixteen state columns and d_v <= 128 that would not fit run the fused kernel
- *     here, with the results of KLA_TUNE_FUSED).
+ *     in bf16, 1 200 in fp32; bf16 problems that run the fused kernel need none of it and are never refused).
  *   - The first call on a device looks up the device address of the array (one hipGetSymbolAddress, which may load
  *     the library's code onto that device): make it outside any stream capture.  KLA_ERR_HIP if the lookup fails.
  *   - All calls on one GPU share the one array: two calls that may overlap in time on the same GPU (different

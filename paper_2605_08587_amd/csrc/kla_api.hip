@@ -89,23 +89,7 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
     return G;
 }
 
-int scan_waves(int n_chains, int dv, int dt, const Tune& tune, long* cost = nullptr);
-
-// The one-kernel forward against intra-chunk stage + scan, both in ns for sequences of at most `longest` chunks.  The fused
-// kernel runs two compute waves per workgroup, one workgroup per CU, and its helper waves redo the per-chunk work once
-// per 32 columns; the two-kernel form pays a second launch (a packed batch a third, for its chunk offsets) and the trip
-// of the records through memory.  Measured at d_k = d_v = 128, fused against two kernels: 4 chunks of 8 chains 12.3
-// against 13.4 us, 7 chunks 16.5 against 16.2; 64 chunks of 64 chains 102 against 116 us; 32 of 32 chains 52 against 48;
-// 64 of 72 chains (two rounds) 193 against 140, of 128 chains 228 against 217; 2 of 96 chains 18.5 against 13.5.  d_v = 64: 16 chunks of 256 chains 60
-// against 73 us.  d_v = 256: 4 chunks of 16 chains 12.5 against 13.5, 13 chunks 25 against 22.5 us.  d_k = 64 the same
-// way at two thirds of the length.
-bool fused_pays(long n_chains, long longest, long chunk_heads, int dk, int dv, bool packed, long scan_cost)
-{
-    const long rounds = ((n_chains + 7) / 8 * 8 * (dv / 32) + 255) / 256;
-    const long fused = rounds * (4400 + longest * (dk == 128 ? 1550 : 1300));      // every round fills its pipeline anew
-    const long scan = longest * scan_cost * (dk == 128 ? 11 : 7), intra = chunk_heads * (dk == 128 ? 93 : 80) / 10;
-    return fused < 7000 + (packed ? 4000 : 0) + scan + intra;
-}
+int scan_waves(int n_chains, int dv, int dt, const Tune& tune);
 
 // fp32 sweeps (kla_chunk_sweeps_f32.hip): column tiles per workgroup.  Four waves share a tile whatever the number; with
 // more tiles than CUs two per workgroup halve the LDS reads of every product, with fewer they would leave CUs idle.
@@ -117,17 +101,14 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     if (!parse_tune(opts, &p->tune)) return KLA_ERR_SHAPE;
     if (!dt_ok(dt)) return KLA_ERR_DTYPE;
     if (N < 0 || T < 0 || H <= 0 || n_seq < 0 || !dk_ok(dk) || !dv_ok(dv) || chunk != 64) return KLA_ERR_SHAPE;
-    long n_chunks = 0, longest = (T + 63) / 64;
+    long n_chunks = 0;
     if (n_seq > 0) {
-        longest = 0;
         if (N != 1) return KLA_ERR_SHAPE;
         if (!cu_host) return KLA_ERR_NULL;
         if (cu_host[0] != 0) return KLA_ERR_SEQLENS;
         for (int s = 0; s < n_seq; ++s) {
             if (cu_host[s + 1] < cu_host[s]) return KLA_ERR_SEQLENS;
-            const long c = (cu_host[s + 1] - cu_host[s] + 63) / 64;
-            n_chunks += c;
-            if (c > longest) longest = c;
+            n_chunks += (cu_host[s + 1] - cu_host[s] + 63) / 64;
         }
         if (cu_host[n_seq] != T) return KLA_ERR_SEQLENS;
         p->n_states = n_seq;
@@ -162,22 +143,27 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
         segments(512);
         if (p->total > (size_t)KLA_STATIC_SCRATCH_BYTES && p->total != all) segments(dv >= 128 ? 1024 : 512);
     }
-    long cost = 0;
-    p->waves = scan_waves(p->n_states * H, dv, dt, p->tune, &cost);
-    if (p->tune.fused && !p->tune.scan_waves && p->waves > 2) p->waves = 2;
-    // The fused kernel keeps the per-chunk objects on chip and needs nothing of the workspace (a token size is still
-    // reported and asked for).  KLA_TUNE_FUSED forces it wherever it can run (one or two compute waves, no segments).
+    p->waves = scan_waves(p->n_states * H, dv, dt, p->tune);
+    // The fused kernel (two compute waves per workgroup) keeps the per-chunk objects on chip and needs nothing of the
+    // workspace (a token size is still reported and asked for).  It runs batches of 384 to 2047 chains of sixteen state
+    // columns with d_v <= 128 (8 x 8 heads x 4096 tokens: 116 against 124 us); below that its helper waves redo the
+    // per-chunk work too often (one 65K sequence, unsegmented: 1.83 against 1.38 ms).  The line is part of what a call
+    // returns and does not follow speed alone: the two forms round different things to 16 bits - here the off-diagonal
+    // blocks of L, which the intra-chunk stage inverts in fp32, there X = V - D_gamma K S - and neither is the closer one
+    // everywhere.  Measured against 64 bits, final state, fused / two kernels: 200 tokens of 8 heads, correlated keys and
+    // slow decay 5.1e-3 / 3.8e-3; 9 x 300 tokens of 8 heads, independent keys 2.5e-3 / 3.0e-3 (o: within 8 % of each other).
     // A batch without a token (whose inputs may be NULL) only hands its states on: the plain scan does that.
+    // KLA_TUNE_FUSED forces the fused kernel wherever it can run (one or two compute waves, no segments).
+    const long tiles = ((long)p->n_states * H + 7) / 8 * 8 * (dv / 16);
+    const bool pair = p->tune.scan_waves ? p->waves == 2 : tiles >= 384 && tiles < 2048;
     p->fused = dt == KLA_BF16 && n_chunks > 0 && p->seg_G <= 1 && !p->tune.unfused && !p->tune.generic_scan && !p->tune.generic_intra &&
-               (p->tune.fused ? p->waves <= 2
-                              : (p->tune.scan_waves ? p->waves == 2 && dv <= 128
-                                                    : fused_pays((long)p->n_states * H, longest, n_chunks * H, dk, dv, n_seq > 0, cost)));
-    if (p->fused && !p->tune.fused && !p->tune.scan_waves) p->waves = 2;
+               (p->tune.fused ? !p->tune.scan_waves || p->waves <= 2 : pair && dv <= 128);
+    if (p->fused && !p->tune.scan_waves && (p->waves > 2 || !p->tune.fused)) p->waves = 2;
     if (p->fused) { p->total = 256; p->order_bytes = 0; }
     return KLA_OK;
 }
 
-int scan_waves(int n_chains, int dv, int dt, const Tune& tune, long* cost_out)
+int scan_waves(int n_chains, int dv, int dt, const Tune& tune)
 {
     int w;
     if (tune.scan_waves) w = tune.scan_waves;        // tuning field: 1, 2 or 4 waves (16 state columns each) per workgroup
@@ -196,7 +182,6 @@ int scan_waves(int n_chains, int dv, int dt, const Tune& tune, long* cost_out)
             const long cost = (chains8 * (dv / (16 << i)) + 255) / 256 * step[i];
             if (i == 0 || cost < best) { best = cost; w = 1 << i; }
         }
-        if (cost_out) *cost_out = best;
     }
     if (dt == KLA_F32 && w > 2) w = 2;            // fp32: column tiles per workgroup, 1 or 2
     while (16 * w > dv) w >>= 1;
@@ -643,12 +628,6 @@ int kla_chunk_fwd_static(const void* q, const void* k, const void* v, const floa
     const int rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N,
                                       T, H, dk, dv, chunk, dt, 0u, &pl);
     if (rc != KLA_OK) return rc;
-    if (pl.total > (size_t)KLA_STATIC_SCRATCH_BYTES && dt == KLA_BF16 && pl.seg_G <= 1 && dv <= 128) {
-        // 384 .. 2047 sixteen-column chains: the fused kernel, which is not always the faster one there but needs no scratch
-        const long tiles = ((long)pl.n_states * H + 7) / 8 * 8 * (dv / 16);
-        if (tiles >= 384 && tiles < 2048 &&
-            make_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, KLA_TUNE_FUSED, &pl) != KLA_OK) return KLA_ERR_SHAPE;
-    }
     if (pl.total - pl.order_bytes > (size_t)KLA_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
         return KLA_ERR_WORKSPACE;                                       // refused before any HIP call
     if (pl.n_states == 0) return KLA_OK;
