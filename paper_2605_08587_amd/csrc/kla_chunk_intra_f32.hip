@@ -9,7 +9,8 @@
 //     wave needs the Q rows of one row tile only, which go from memory straight into its registers.
 //   * The Gram tiles of P come out of the product in the orientation in which an accumulator tile is the operand quad
 //     that the record stores (K Q^T for P, Q K^T for the backward's P^T), so P never passes through LDS.
-//   * ||k_i||^2 is the diagonal of K K^T, ||q_i||^2 a sum over the registers of the lanes that hold row i.
+//   * ||k_i||^2 and ||q_i||^2 are sums over the operand registers of the lanes that hold row i, as a tree (the diagonal of
+//     K K^T is the same sum, but one chain of d_k roundings: beta 1.7e-7 off instead of 0.5e-7, d_k = 128).
 // Measured, K and Q staged as operand slots (101 KB, one workgroup per CU) -> this kernel: 1024 chunk-heads of d_k = 128
 // 79 -> 34 us, 64 chunk-heads of d_k = 64 13.3 -> 9.7 us; with the rows of the substitutions read two ahead instead of all
 // at once (no spilled register) 31.9 -> 29.4 us.
@@ -31,6 +32,16 @@ __device__ __forceinline__ float4 bquad(const float* m, int row0, int col0, int 
 __device__ __forceinline__ float4 aquad(const float* m, int row0, int col0, int r, int g)   // columns 4g..4g+3 of row r
 {
     return ldf4(m + (row0 + r) * kLdm + col0 + 4 * g);
+}
+// the squares of a row's values, summed as a tree over its quads (N: a power of two)
+__device__ __forceinline__ float sum_squares(float4 v) { return v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w; }
+template <int N> __device__ __forceinline__ float tree_sum(float (&x)[N])
+{
+#pragma unroll
+    for (int w = N / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int i = 0; i < w; ++i) x[i] += x[i + w];
+    return x[0];
 }
 
 }  // namespace
@@ -90,12 +101,13 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
     float rq = 1.f;
     {
         const bool live = 16 * wave + r < clen;
-        float ss = 0.f;
+        float sq[KB];
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
             if (!live) qf[b] = make_float4(0.f, 0.f, 0.f, 0.f);
-            ss += qf[b].x * qf[b].x; ss += qf[b].y * qf[b].y; ss += qf[b].z * qf[b].z; ss += qf[b].w * qf[b].w;
+            sq[b] = sum_squares(qf[b]);
         }
+        float ss = tree_sum(sq);
         ss += __shfl_xor(ss, 16, kWave);
         ss += __shfl_xor(ss, 32, kWave);
         if (a.opts & kOptNormalizeQ) rq = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
@@ -122,9 +134,11 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
         for (int t = 0; t <= A; ++t) kk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        float sq[KB];
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
             const float4 ka = ops.row_quad(area, b);
+            sq[b] = sum_squares(ka);
             static_for<NT>([&](auto tc) {
                 constexpr int t = tc;
                 const float4 kb = t == A ? ka : ldf4(area + boff[b & 3] + 16 * t * C::RB + 256 * (b >> 2));
@@ -164,11 +178,14 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
         // the tile of a stored pair that lies on the other side of the diagonal
         if constexpr (BWD) { if constexpr ((W & 1) == 1) put(rec + 2 * HALF, triu_pair(W, W >> 1), 0, z4); }
         else               { if constexpr ((W & 1) == 0) put(rec + HALF, tri_pair(W, W >> 1), 1, z4); }
-        // ---- beta of the rows of tile A: ||k_i||^2 sits on the diagonal, row 4 g + e in lane 20 g + e
+        // ---- beta of the rows of tile A (||k_i||^2 of row 16 A + r in the lanes of r)
+        float kn = tree_sum(sq);
+        kn += __shfl_xor(kn, 16, kWave);
+        kn += __shfl_xor(kn, 32, kWave);
         floatx4 be;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float ss = __shfl(kk[A][e], 20 * g + e, kWave), eta = __shfl(et, 16 * A + 4 * g + e, kWave);
+            const float ss = __shfl(kn, 4 * g + e, kWave), eta = __shfl(et, 16 * A + 4 * g + e, kWave);
             be[e] = gdn ? eta : kaczmarz_beta(eta, ss, a.eps);
             if (r == 4 * g + e) {
                 beta_s[16 * A + r] = be[e];
