@@ -6,7 +6,8 @@ missing, or a tensor is not on the GPU, the call raises.
 
 Calls with plain GPU tensors that fit each other are checked, given memory and launched by kla_binding.so
 (csrc/kla_binding.cpp), which hands back None for anything else; the code here then takes the same call step by step and
-raises what there is to raise.
+raises what there is to raise.  kla_binding.so is built against one PyTorch; without it, or with another one, every call goes
+step by step.
 """
 from __future__ import annotations
 
@@ -15,6 +16,7 @@ import importlib.machinery
 import importlib.util
 import os
 import threading
+import warnings
 
 import torch
 
@@ -28,7 +30,7 @@ KLA_F32, KLA_BF16 = 0, 1
 KLA_OPT_NORMALIZE_Q, KLA_OPT_GDN_BETA = 1, 2
 _lock = threading.Lock()
 _lib = None
-_native = None      # the module kla_binding, bound to _lib
+_native = None      # the module kla_binding, bound to _lib, or a _StepByStep
 
 _vp, _fp, _ip = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p
 _SIGNATURES = {
@@ -76,27 +78,48 @@ class KlaError(RuntimeError):
         super().__init__("%s failed: %s" % (where, lib().kla_status_string(code).decode()))
 
 
+class _StepByStep:
+    """In the place of kla_binding where it cannot be loaded: takes no call."""
+    @staticmethod
+    def decode(*args):
+        return None
+    chunk_fwd = chunk_bwd = decode
+
+
+def _load_native(l):
+    if not os.path.exists(BINDING_PATH):
+        return _StepByStep
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("kla_binding", BINDING_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("kla_binding", loader))
+        loader.exec_module(m)
+        built, here = getattr(m, "torch_version", "?"), torch.__version__.split("+")[0]
+        if built != here:
+            raise ImportError("built for PyTorch %s, this is %s" % (built, here))
+    except ImportError as e:
+        warnings.warn("kla_binding.so does not load, small calls will take longer (rebuild it with "
+                      "`python -m paper_2605_08587_amd.build`): %s" % e, RuntimeWarning, stacklevel=3)
+        return _StepByStep
+    m.bind(*(ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in (
+        "kla_decode_step_opts", "kla_decode_step_diag_opts", "kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_fwd_opts",
+        "kla_chunk_fwd_diag_workspace_bytes", "kla_chunk_fwd_diag_opts", "kla_chunk_bwd_workspace_bytes_opts",
+        "kla_chunk_bwd_opts")))
+    return m
+
+
 def lib():
     """The loaded C library; raises if it has not been built (python -m paper_2605_08587_amd.build)."""
     global _lib, _native
     with _lock:
         if _lib is None:
-            for path in (LIB_PATH, BINDING_PATH):
-                if not os.path.exists(path):
-                    raise RuntimeError("%s is not built: run `python -m paper_2605_08587_amd.build` "
-                                       "(there is no CPU fallback)" % os.path.basename(path))
+            if not os.path.exists(LIB_PATH):
+                raise RuntimeError("libkla.so is not built: run `python -m paper_2605_08587_amd.build` "
+                                   "(there is no CPU fallback)")
             l = ctypes.CDLL(LIB_PATH)
             for name, (res, args) in _SIGNATURES.items():
                 fn = getattr(l, name)
                 fn.restype, fn.argtypes = res, args
-            loader = importlib.machinery.ExtensionFileLoader("kla_binding", BINDING_PATH)
-            m = importlib.util.module_from_spec(importlib.util.spec_from_loader("kla_binding", loader))
-            loader.exec_module(m)
-            m.bind(*(ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in (
-                "kla_decode_step_opts", "kla_decode_step_diag_opts", "kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_fwd_opts",
-                "kla_chunk_fwd_diag_workspace_bytes", "kla_chunk_fwd_diag_opts", "kla_chunk_bwd_workspace_bytes_opts",
-                "kla_chunk_bwd_opts")))
-            _native, _lib = m, l
+            _native, _lib = _load_native(l), l
     return _lib
 
 

@@ -12,6 +12,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <climits>
 #include <initializer_list>
@@ -219,14 +220,14 @@ PyObject* chunk_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
             const size_t need = diag ? api.fwd_diag_bytes(N, T, H, dk, dv, (int)chunk, c.dt, c.cu_host, c.n_seq)
                                      : api.fwd_bytes(N, T, H, dk, dv, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
             ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
-    }
-    out = out_ ? *out_ : c.empty({c.N, c.T, c.H, c.dv}, c.type);
-    if (hT_) hT = *hT_;
-    else if (want_hT) hT = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
-    rc = (diag ? api.fwd_diag : api.fwd)(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0),
-                                         out->data_ptr(), hT ? static_cast<float*>(hT->data_ptr()) : nullptr,
-                                         static_cast<const int32_t*>(ptr(c.cu)), c.cu_host, c.n_seq, N, T, H, dk, dv, (int)chunk,
-                                         c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+        }
+        out = out_ ? *out_ : c.empty({c.N, c.T, c.H, c.dv}, c.type);
+        if (hT_) hT = *hT_;
+        else if (want_hT) hT = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
+        rc = (diag ? api.fwd_diag : api.fwd)(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0),
+                                             out->data_ptr(), hT ? static_cast<float*>(hT->data_ptr()) : nullptr,
+                                             static_cast<const int32_t*>(ptr(c.cu)), c.cu_host, c.n_seq, N, T, H, dk, dv, (int)chunk,
+                                             c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
     }
     if (rc != KLA_OK) return PyLong_FromLong(rc);
     PyObject* r = PyTuple_New(2);
@@ -282,4 +283,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "kla_binding", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_kla_binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_kla_binding()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) Py_CLEAR(m);   // whose tensors it can read
+    return m;
+}
