@@ -91,6 +91,11 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
 
 int scan_waves(int n_chains, int dv, int dt, const Tune& tune);
 
+// Packed batches: the order in which the scans take the sequences, behind the n_seq + 1 chunk offsets.  More than
+// kla::kOrderMax sequences have none: they are taken as they come.
+inline int order_ints(int n_seq) { return n_seq <= kla::kOrderMax ? n_seq : 0; }
+inline int* order_at(int* chunk_off, int n_seq) { return order_ints(n_seq) > 0 ? chunk_off + n_seq + 1 : nullptr; }
+
 // fp32 sweeps (kla_chunk_sweeps_f32.hip): column tiles per workgroup.  Four waves share a tile whatever the number; with
 // more tiles than CUs two per workgroup halve the LDS reads of every product, with fewer they would leave CUs idle.
 inline int f32_tiles(long n_tiles) { return n_tiles > 256 ? 2 : 1; }
@@ -125,7 +130,7 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     p->off_P = half;
     p->off_G = round256((size_t)n_chunks * H * (2 * half + 768));   // + three vectors of 64 fp32 (see kla_mma.hpp)
     p->off_C = round256(p->off_G + (size_t)n_chunks * H * 128 * sizeof(float));      // g and 1/||q||
-    p->off_M = round256(p->off_C + (size_t)(2 * n_seq + 1) * sizeof(int32_t));       // chunk offsets, scan order of the sequences
+    p->off_M = round256(p->off_C + (size_t)(n_seq + 1 + order_ints(n_seq)) * sizeof(int32_t));   // chunk offsets, scan order of the sequences
     p->order_bytes = p->off_M - round256(p->off_C + (size_t)(n_seq + 1) * sizeof(int32_t));
     auto segments = [&](int max_chains) {
         p->seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->tune, max_chains, &p->seg_Lc);
@@ -229,7 +234,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     }
     const bool generic_intra = sizeof(E) == 2 && pl.tune.generic_intra;
     if (intra && !intra_places(n_seq, pl.n_chunks, generic_intra)) {
-        if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+        if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
     } else if (intra) ia.pos_out = chunk_off;
     if (intra) {
         [[maybe_unused]] bool done = false;
@@ -252,7 +257,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     sa.q = static_cast<const E*>(q); sa.k = static_cast<const E*>(k); sa.v = static_cast<const E*>(v);
     sa.h0 = h0; sa.o = static_cast<E*>(o); sa.hT = hT;
     sa.cu_seqlens = ia.cu_seqlens; sa.chunk_off = chunk_off; sa.n_seq = n_seq;
-    sa.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
+    sa.seq_order = order_at(chunk_off, n_seq);
     sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
     sa.wsT = wsT; sa.wsP = wsP; sa.wsG = wsG; sa.opts = opts;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = nullptr; sa.gc_vec = nullptr;
@@ -301,7 +306,7 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     const size_t rows = (size_t)N * T * H * dv * elem_bytes(dt);
     p->off_rec = 0;                                              // [T' | M^T | P^T | five vectors] per chunk-head
     p->off_C = round256(ch * (3 * half + 1280));
-    p->off_S = round256(p->off_C + (size_t)(2 * n_seq + 1) * sizeof(int32_t));
+    p->off_S = round256(p->off_C + (size_t)(n_seq + 1 + order_ints(n_seq)) * sizeof(int32_t));
     p->off_dS = round256(p->off_S + states);
     // the bf16 kernels do not keep U (their assembly forms it again from T' and X); the generic ones do
     const size_t rows_u = (dt == KLA_BF16 && !p->base.tune.generic_bwd) ? 0 : rows;
@@ -328,7 +333,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     int* chunk_off = reinterpret_cast<int*>(ws + pl.off_C);
     const int NT = (T + 63) / 64;
     const bool placed = intra_places(n_seq, pl.base.n_chunks, sizeof(E) == 2 && pl.base.tune.generic_bwd);
-    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
 
     kla::IntraArgs<E> ia;
     if (placed) ia.pos_out = chunk_off;
@@ -355,7 +360,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     ba.dq = static_cast<E*>(dq); ba.dk = static_cast<E*>(dk_); ba.dv = static_cast<E*>(dv_);
     ba.dlog_alpha = dlog_alpha; ba.deta = deta; ba.dh0 = dh0;
     ba.cu_seqlens = ia.cu_seqlens; ba.chunk_off = chunk_off; ba.n_seq = n_seq;
-    ba.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
+    ba.seq_order = order_at(chunk_off, n_seq);
     ba.N = N; ba.T = T; ba.NT = NT; ba.H = H; ba.dv_dim = dv;
     ba.rec = ws + pl.off_rec;
     ba.s_chk = reinterpret_cast<E*>(ws + pl.off_S); ba.ds_chk = reinterpret_cast<E*>(ws + pl.off_dS);
@@ -458,7 +463,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     int* chunk_off = reinterpret_cast<int*>(ws + pl.base.off_C);
     const int NT = (T + 63) / 64;
     const bool placed = intra_places(n_seq, pl.base.n_chunks, false);
-    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, chunk_off + n_seq + 1, st) != hipSuccess) return KLA_ERR_HIP;
+    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
     kla::IntraDiagArgs<E> ia;
     if (placed) ia.pos_out = chunk_off;
     ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
@@ -475,7 +480,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     sa.q = ia.qplus; sa.k = ia.kplus; sa.v = static_cast<const E*>(v);
     sa.h0 = h0; sa.o = static_cast<E*>(o); sa.hT = hT;
     sa.cu_seqlens = ia.cu_seqlens; sa.chunk_off = chunk_off; sa.n_seq = n_seq;
-    sa.seq_order = n_seq > 0 ? chunk_off + n_seq + 1 : nullptr;
+    sa.seq_order = order_at(chunk_off, n_seq);
     sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
     sa.wsT = ia.wsT; sa.wsP = reinterpret_cast<E*>(ws + pl.base.off_P); sa.wsG = ia.wsG; sa.opts = 0u;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = ia.ktilde; sa.gc_vec = ia.gc;
@@ -496,8 +501,8 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the address that
 // kernels receive is looked up once per device, with that device current, and kept.
 // The bound that callers know, KLA_STATIC_SCRATCH_BYTES, does not count the scan order of a packed batch: it has room of
-// its own behind.
-constexpr size_t kStaticScratchBytes = (size_t)KLA_STATIC_SCRATCH_BYTES + (1u << 20);
+// its own behind (kOrderMax numbers, rounded up to 256 bytes).
+constexpr size_t kStaticScratchBytes = (size_t)KLA_STATIC_SCRATCH_BYTES + 4 * (size_t)kla::kOrderMax + 256;
 constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 std::mutex scratch_mutex;
@@ -628,8 +633,7 @@ int kla_chunk_fwd_static(const void* q, const void* k, const void* v, const floa
     const int rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N,
                                       T, H, dk, dv, chunk, dt, 0u, &pl);
     if (rc != KLA_OK) return rc;
-    if (pl.total - pl.order_bytes > (size_t)KLA_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
-        return KLA_ERR_WORKSPACE;                                       // refused before any HIP call
+    if (pl.total - pl.order_bytes > (size_t)KLA_STATIC_SCRATCH_BYTES) return KLA_ERR_WORKSPACE;   // refused before any HIP call
     if (pl.n_states == 0) return KLA_OK;
     void* ws = static_scratch();
     if (!ws) return KLA_ERR_HIP;

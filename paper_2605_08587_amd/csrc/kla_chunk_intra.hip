@@ -687,11 +687,11 @@ template hipError_t launch_intra_diag<bf16_t>(const IntraDiagArgs<bf16_t>&, int,
 
 // ---- chunk offsets of a packed batch: chunk_off[s] = sum_{s'<s} ceil(len_s'/64), and the order in which the sweeps take
 //      the sequences: most chunks first, so that the workgroups that run longest start first and the short ones fill
-//      the CUs that become free (up to kOrderMax sequences; more of them balance by number, and keep their order).
-constexpr int kOrderMax = 256;
+//      the CUs that become free (up to kOrderMax sequences; more of them balance by number, keep their order, and `order` is NULL).
 __global__ __launch_bounds__(256) void chunk_offsets_kernel(const int* __restrict__ cu_seqlens, int n_seq, int* __restrict__ chunk_off,
                                                             int* __restrict__ order)
 {
+    static_assert(kOrderMax <= 256, "a thread per sequence");
     __shared__ int nc_s[256];
     __shared__ int wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -709,8 +709,7 @@ __global__ __launch_bounds__(256) void chunk_offsets_kernel(const int* __restric
         for (int w = 0; w < wave; ++w) base += wsum[w];
         if (s < n_seq) chunk_off[s] = base + x - nc;
         carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        if (n_seq > kOrderMax) { if (s < n_seq) order[s] = s; }
-        else if (s < n_seq) {
+        if (order && s < n_seq) {                        // one pass: n_seq <= 256
             int rank = 0;
             for (int j = 0; j < n_seq; ++j) rank += (nc_s[j] > nc || (nc_s[j] == nc && j < s)) ? 1 : 0;
             order[rank] = s;

@@ -150,7 +150,9 @@ template <typename E> hipError_t launch_bwd_assemble(const BwdArgs<E>& a, int dk
 // measurement probes (kla_probe.hip)
 hipError_t launch_probe(int kind, void* buf, void* aux, size_t bytes, int iters, hipStream_t st);
 
-// chunk_off[n_seq + 1]: chunks before every sequence; order[n_seq]: the sequences, most chunks first (see ScanArgs::seq_order)
+// chunk_off[n_seq + 1]: chunks before every sequence; order[n_seq], for at most kOrderMax sequences, else NULL: the sequences,
+// most chunks first (see ScanArgs::seq_order)
+constexpr int kOrderMax = 256;
 hipError_t launch_chunk_offsets(const int* cu_seqlens, int n_seq, int* chunk_off, int* order, hipStream_t st);
 template <typename E>
 hipError_t launch_unpack(const E* wsT, const E* wsP, const float* wsG, float* Tb, float* P, float* gout, long n_ch,
