@@ -1,6 +1,7 @@
-"""The bf16 scan with eight compute waves per workgroup (what batches of more than 1024 sixteen-column chains run) and the
-scan order of packed batches, at the sizes where they can go wrong: one to three chunks, last chunks of 1, 63 and 64 rows,
-both head widths, both slices of d_v = 256, empty sequences, more sequences than the order is built for."""
+"""The bf16 scan with eight compute waves per workgroup (what batches of d_v >= 128 run where they save rounds of workgroups)
+and the scan order of packed batches, at the sizes where they can go wrong: one to three chunks, last chunks of 1, 63 and 64
+rows, both head widths, both slices of d_v = 256, empty sequences, more sequences than the order is built for.  The two-kernel
+form is asked for: some of these batches run the one-kernel form by themselves, which has neither."""
 import numpy as np
 import pytest
 import torch
@@ -23,7 +24,8 @@ def kla():
 
 def _check(kla, d, cu=None, **opts):
     c = lambda t: None if t is None else t.cuda()
-    o, hT = kla.kla_chunk_fwd(*(d[n].cuda() for n in ("q", "k", "v", "log_alpha", "eta")), d["eps"], h0=c(d["h0"]), cu_seqlens=c(cu), **opts)
+    o, hT = kla.kla_chunk_fwd(*(d[n].cuda() for n in ("q", "k", "v", "log_alpha", "eta")), d["eps"], h0=c(d["h0"]), cu_seqlens=c(cu),
+                              tune=kla.tune(unfused=True), **opts)
     ro, rh, _ = token_oracle.kla_recurrent(*(kla_inputs.to_numpy_f32(d[n]) for n in "qkv"), d["log_alpha"].numpy(), d["eta"].numpy(),
                                            d["eps"], h0=None if d["h0"] is None else d["h0"].numpy(),
                                            cu_seqlens=None if cu is None else cu.numpy(), **opts)
