@@ -399,7 +399,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             if (kla::launch_segment_combine_rev(maps, segB, segG, N, H, dk, dv, G, st) != hipSuccess) return KLA_ERR_HIP;
             ba.opts = opts;
             if (kla::launch_bwd_scan_bf16(ba, dk, wseg, st) != hipSuccess) return KLA_ERR_HIP;          // the real sweep
-            if (dh0 && kla::launch_segment_gather(segB, dh0, N, H, dk, dv, G, 0, st) != hipSuccess) return KLA_ERR_HIP;
+            if (dh0 && kla::launch_segment_gather(segB, dh0, N, H, dk, dv, G, st) != hipSuccess) return KLA_ERR_HIP;
             ba.seg_G = 0; ba.seg_Lc = 0; ba.h0 = h0; ba.d_hT = d_hT; ba.dh0 = dh0;
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }

@@ -37,15 +37,16 @@ __device__ __forceinline__ floatx4 ld_acc4(const float* p)
     floatx4 x; x[0] = f.x; x[1] = f.y; x[2] = f.z; x[3] = f.w; return x;
 }
 
-template <typename E, int DK, int NW>
+template <int DK, int NW>
 struct SweepCfg {
+    typedef bf16_t E;
     static constexpr int NTH = 64 * NW;
     static constexpr int KB = DK / 16, KP = DK / 32;
     static constexpr int SLW = 16 * NW;                         // state columns per workgroup
     static constexpr int PPR = DK * (int)sizeof(E) / 16;        // 16-byte pieces per K/Q row
     static constexpr int EPP = 16 / (int)sizeof(E);             // elements per piece
     static constexpr int VPP = SLW * (int)sizeof(E) / 16;       // pieces per row of a [tokens, d_v] slice
-    static constexpr int SB = 2 * (int)sizeof(typename QuadT<E>::type);
+    static constexpr int SB = 2 * (int)sizeof(QuadT<E>::type);
     static constexpr int OPB = 64 * DK * (int)sizeof(E);        // one K/Q operand area
     static constexpr int TPB = kTriPairs * 64 * SB;             // one triangular operand area
     static constexpr int VB = NW * 2 * 64 * SB;                 // one [tokens, slice] area
@@ -57,8 +58,7 @@ struct SweepCfg {
 
 // which (sequence, head, column slice) a workgroup of a sweep works on; the same XCD-aware numbering as the forward
 struct SweepPos { int chain, slice, h, nch, ch0; long t0; int len; bool valid; };
-template <typename E>
-__device__ __forceinline__ SweepPos sweep_pos(const BwdArgs<E>& a, int SLW)
+__device__ __forceinline__ SweepPos sweep_pos(const BwdArgs<bf16_t>& a, int SLW)
 {
     SweepPos p;
     const int nsl = a.dv_dim / SLW;
@@ -75,13 +75,12 @@ __device__ __forceinline__ SweepPos sweep_pos(const BwdArgs<E>& a, int SLW)
 }
 
 // accumulator tile (rows 16 it + 4 g + e, column col) -> a [tokens, H, d_v] tensor, rows below clen only
-template <typename E>
-__device__ __forceinline__ void store_rows(E* base, size_t v_stride, floatx4 x, int it, int g, int clen)
+__device__ __forceinline__ void store_rows(bf16_t* base, size_t v_stride, floatx4 x, int it, int g, int clen)
 {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int row = 16 * it + 4 * g + e;
-        if (row < clen) base[(size_t)row * v_stride] = from_float<E>(x[e]);
+        if (row < clen) base[(size_t)row * v_stride] = from_float<bf16_t>(x[e]);
     }
 }
 
@@ -90,12 +89,13 @@ __device__ __forceinline__ void store_rows(E* base, size_t v_stride, floatx4 x, 
 // =================================================================================================
 // forward sweep: incoming state of every chunk, X and U
 // =================================================================================================
-template <typename E, int DK, int NW>
-__global__ __launch_bounds__(64 * NW) void bwd_states_kernel(BwdArgs<E> a)
+template <int DK, int NW>
+__global__ __launch_bounds__(64 * NW) void bwd_states_kernel(BwdArgs<bf16_t> a)
 {
-    typedef SweepCfg<E, DK, NW> C;
+    typedef bf16_t E;
+    typedef SweepCfg<DK, NW> C;
     constexpr int NTH = C::NTH, KB = C::KB, KP = C::KP, SLW = C::SLW, PPR = C::PPR, EPP = C::EPP, VPP = C::VPP;
-    typedef typename QuadT<E>::type Quad;
+    typedef QuadT<E>::type Quad;
     // K rows | K transposed | T' | V slice | gamma_i | gamma_C/gamma_i | beta_i
     constexpr int OFF_KT = C::OPB, OFF_T = 2 * C::OPB, OFF_V = OFF_T + C::TPB, OFF_VEC = OFF_V + C::VB, LDS = OFF_VEC + 768;
     __shared__ __attribute__((aligned(16))) char lds[LDS];
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_states_kernel(BwdArgs<E> a)
             for (int kp = 0; kp < KP; ++kp) mma32<E>(ks, load_slot(Krq, it * KP + kp, lane), Sq[2 * kp], Sq[2 * kp + 1]);
             const Slot<E> sv = load_slot(Vtq, wave * 2 + (it >> 1), lane);
             const floatx4 x = quad_to_acc((it & 1) ? sv.q1 : sv.q0) - ld_acc4(eg + 16 * it + 4 * g) * ks;   // eq. (6), right side
-            store_rows<E>(xb, v_stride, x, it, g, clen);
+            store_rows(xb, v_stride, x, it, g, clen);
             Xq[it] = acc_to_quad<E>(x);
         }
         Quad Udq[4];
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_states_kernel(BwdArgs<E> a)
             floatx4 u = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int jp = 0; jp <= (it >> 1); ++jp) mma32<E>(u, load_slot(Trq, tri_pair(it, jp), lane), Xq[2 * jp], Xq[2 * jp + 1]);
-            store_rows<E>(ub, v_stride, u, it, g, clen);
+            store_rows(ub, v_stride, u, it, g, clen);
             Udq[it] = acc_to_quad<E>(u * ld_acc4(ed + 16 * it + 4 * g));
         }
         const float gC = eg[63];
@@ -242,12 +242,13 @@ __global__ __launch_bounds__(64 * NW) void bwd_states_kernel(BwdArgs<E> a)
 // =================================================================================================
 // backward sweep: gradient of the state, Y, dv, dh0
 // =================================================================================================
-template <typename E, int DK, int NW>
-__global__ __launch_bounds__(64 * NW) void bwd_scan_kernel(BwdArgs<E> a)
+template <int DK, int NW>
+__global__ __launch_bounds__(64 * NW) void bwd_scan_kernel(BwdArgs<bf16_t> a)
 {
-    typedef SweepCfg<E, DK, NW> C;
+    typedef bf16_t E;
+    typedef SweepCfg<DK, NW> C;
     constexpr int NTH = C::NTH, KB = C::KB, KP = C::KP, SLW = C::SLW, PPR = C::PPR, EPP = C::EPP, VPP = C::VPP;
-    typedef typename QuadT<E>::type Quad;
+    typedef QuadT<E>::type Quad;
     // K rows | K transposed | Q transposed | M^T | P^T | dO slice | gamma_i | gamma_C/gamma_i | beta_i
     constexpr int OFF_KT = C::OPB, OFF_QT = 2 * C::OPB, OFF_MT = 3 * C::OPB, OFF_PT = OFF_MT + C::TPB,
                   OFF_DO = OFF_PT + C::TPB, OFF_VEC = OFF_DO + C::VB, LDS = OFF_VEC + 1024;
@@ -406,9 +407,9 @@ __global__ __launch_bounds__(64 * NW) void bwd_scan_kernel(BwdArgs<E> a)
 #pragma unroll
             for (int jp = (it >> 1); jp < 2; ++jp)
                 mma32<E>(y, load_slot(MTr, triu_pair(it, jp), lane), dUq[2 * jp], dUq[2 * jp + 1]);
-            store_rows<E>(yb, v_stride, y, it, g, clen);
+            store_rows(yb, v_stride, y, it, g, clen);
             const floatx4 dx = y * ld_acc4(be + 16 * it + 4 * g);
-            store_rows<E>(vb, v_stride, dx, it, g, clen);
+            store_rows(vb, v_stride, dx, it, g, clen);
             const floatx4 egv = ld_acc4(eg + 16 * it + 4 * g);
             gdOq[it] = acc_to_quad<E>(egv * ld_acc4(rq + 16 * it + 4 * g) * dOa[it]);   // D_gamma dO / ||q||
             gdXq[it] = acc_to_quad<E>(-(egv * dx));
@@ -798,11 +799,11 @@ static hipError_t launch_sweep_dk(const BwdArgs<bf16_t>& a, int waves, bool reve
     if (n_chains == 0) return hipSuccess;
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
     if (reverse) {
-        if (waves == 1) hipLaunchKernelGGL((bwd_scan_kernel<bf16_t, DK, 1>), grid, dim3(64), 0, st, a);
-        else            hipLaunchKernelGGL((bwd_scan_kernel<bf16_t, DK, 2>), grid, dim3(128), 0, st, a);
+        if (waves == 1) hipLaunchKernelGGL((bwd_scan_kernel<DK, 1>), grid, dim3(64), 0, st, a);
+        else            hipLaunchKernelGGL((bwd_scan_kernel<DK, 2>), grid, dim3(128), 0, st, a);
     } else {
-        if (waves == 1) hipLaunchKernelGGL((bwd_states_kernel<bf16_t, DK, 1>), grid, dim3(64), 0, st, a);
-        else            hipLaunchKernelGGL((bwd_states_kernel<bf16_t, DK, 2>), grid, dim3(128), 0, st, a);
+        if (waves == 1) hipLaunchKernelGGL((bwd_states_kernel<DK, 1>), grid, dim3(64), 0, st, a);
+        else            hipLaunchKernelGGL((bwd_states_kernel<DK, 2>), grid, dim3(128), 0, st, a);
     }
     return hipGetLastError();
 }

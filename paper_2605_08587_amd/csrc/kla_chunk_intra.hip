@@ -158,9 +158,10 @@ __device__ __forceinline__ void invert_and_store(const float* Lm, float* Tm, con
 // BWD = false: the forward's records [T' | P | three vectors].  BWD = true: the records of the backward pass,
 // [T' | M^T | P^T | gamma_i | gamma_C/gamma_i | beta_i | 1/(||k_i||^2+eps)] with M = (I + L)^{-1}, T' = M B; the transposes are stored as the
 // 6 upper-triangular tile-pairs (see bwd_record_bytes in kla_mma.hpp).
-template <typename E, int DK, bool BWD>
-__global__ __launch_bounds__(256) void intra_kernel(IntraArgs<E> a)
+template <int DK, bool BWD>
+__global__ __launch_bounds__(256) void intra_kernel(IntraArgs<bf16_t> a)
 {
+    typedef bf16_t E;
     constexpr int REC = BWD ? bwd_record_bytes<E>() : ws_record_bytes<E>();
     constexpr int PPR = DK * (int)sizeof(E) / 16;    // 16-byte pieces per row
     constexpr int EPP = 16 / (int)sizeof(E);         // elements per piece
@@ -206,17 +207,11 @@ __global__ __launch_bounds__(256) void intra_kernel(IntraArgs<E> a)
             store_rq_piece(Qrq, KP, row, piece, qd);
             auto sum_squares = [](uint4 d) {
                 float ss = 0.f;
-                if constexpr (sizeof(E) == 2) {
-                    const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+                const uint32_t w[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const float x0 = bf16_bits_to_float(w[m] & 0xffffu), x1 = bf16_bits_to_float(w[m] >> 16);
-                        ss += x0 * x0; ss += x1 * x1;
-                    }
-                } else {
-                    const float x0 = __uint_as_float(d.x), x1 = __uint_as_float(d.y), x2 = __uint_as_float(d.z),
-                                x3 = __uint_as_float(d.w);
-                    ss = x0 * x0 + x1 * x1 + x2 * x2 + x3 * x3;
+                for (int m = 0; m < 4; ++m) {
+                    const float x0 = bf16_bits_to_float(w[m] & 0xffffu), x1 = bf16_bits_to_float(w[m] >> 16);
+                    ss += x0 * x0; ss += x1 * x1;
                 }
                 return ss;
             };
@@ -315,8 +310,8 @@ hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStr
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_kernel<bf16_t, 64, false>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_kernel<bf16_t, 128, false>), grid, block, 0, st, a);
+    if (dk == 64) hipLaunchKernelGGL((intra_kernel<64, false>), grid, block, 0, st, a);
+    else          hipLaunchKernelGGL((intra_kernel<128, false>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
@@ -326,8 +321,8 @@ hipError_t launch_intra_bwd(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hi
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_kernel<bf16_t, 64, true>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_kernel<bf16_t, 128, true>), grid, block, 0, st, a);
+    if (dk == 64) hipLaunchKernelGGL((intra_kernel<64, true>), grid, block, 0, st, a);
+    else          hipLaunchKernelGGL((intra_kernel<128, true>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 

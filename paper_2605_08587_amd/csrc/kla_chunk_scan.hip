@@ -36,15 +36,16 @@ __device__ __forceinline__ floatx4 ld_acc4(const float* p)
 }
 }  // namespace
 
-template <typename E, int DK, int NW>
+template <int DK, int NW>
 struct ScanCfg {
+    typedef bf16_t E;
     static constexpr int NTH = 64 * NW;
     static constexpr int KB = DK / 16, KP = DK / 32;
     static constexpr int SLW = 16 * NW;                         // state columns per workgroup
     static constexpr int PPR = DK * (int)sizeof(E) / 16;        // 16-byte pieces per K/Q row
     static constexpr int EPP = 16 / (int)sizeof(E);             // elements per piece
     static constexpr int VPP = SLW * (int)sizeof(E) / 16;       // pieces per V/O slice row
-    static constexpr int SB = 2 * (int)sizeof(typename QuadT<E>::type);
+    static constexpr int SB = 2 * (int)sizeof(QuadT<E>::type);
     static constexpr int OPB = 64 * DK * (int)sizeof(E);        // one K/Q operand area
     static constexpr int TPB = kTriPairs * 64 * SB;             // one T'/P operand area
     static constexpr int VB = NW * 2 * 64 * SB;                 // V slice area
@@ -63,9 +64,9 @@ struct ScanCfg {
 };
 
 // The next chunk's operands on their way from global memory to LDS.
-template <typename E, int DK, int NW, bool DIAG>
+template <int DK, int NW, bool DIAG>
 struct Prefetch {
-    typedef ScanCfg<E, DK, NW> C;
+    typedef ScanCfg<DK, NW> C;
     uint4 k[C::UK][4], q[C::UK][4], v[C::UV][4], t[C::UT], p[C::UT];
     uint4 kt[DIAG ? C::UK : 1][4];                   // diagonal gating: rows of the K operand of the state update
     float gc[(DK + C::NTH - 1) / C::NTH];           //                   gamma_C per channel
@@ -74,13 +75,14 @@ struct Prefetch {
 
 // DIAG: diagonal gating (App. B).  The decay then sits in the operands (a.k = K o Gamma, a.q = Q o Gamma, a.kt_src =
 // K o (gamma_C/Gamma), unit decay vectors in the records) and the state decays per row by a.gc_vec.
-template <typename E, int DK, int NW, bool DIAG>
-__global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
+template <int DK, int NW, bool DIAG>
+__global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<bf16_t> a)
 {
-    typedef ScanCfg<E, DK, NW> C;
+    typedef bf16_t E;
+    typedef ScanCfg<DK, NW> C;
     constexpr int NTH = C::NTH, KB = C::KB, KP = C::KP, SLW = C::SLW, PPR = C::PPR, EPP = C::EPP, VPP = C::VPP;
     constexpr int OLD = C::OLD;
-    typedef typename QuadT<E>::type Quad;
+    typedef QuadT<E>::type Quad;
 
     __shared__ __attribute__((aligned(16))) char lds[C::LDS];
 
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
     const size_t kq_stride = (size_t)a.H * DK, v_stride = (size_t)a.H * a.dv;
 
     // ---- global -> registers: everything chunk c needs -------------------------------------------
-    auto fetch = [&](int c, Prefetch<E, DK, NW, DIAG>& pf) {
+    auto fetch = [&](int c, Prefetch<DK, NW, DIAG>& pf) {
         const long tok0 = t0 + 64L * c;
         const int clen = min(64, len - 64 * c);
         const size_t ch = (size_t)(ch0 + c) * a.H + h;
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
     };
 
     // ---- registers -> LDS stage, in MFMA operand order ----------------------------------------
-    auto stash = [&](const Prefetch<E, DK, NW, DIAG>& pf, char* st) {
+    auto stash = [&](const Prefetch<DK, NW, DIAG>& pf, char* st) {
         E* Krq = reinterpret_cast<E*>(st);
         E* Qrq = reinterpret_cast<E*>(st + C::OFF_Q);
         E* Ktq = reinterpret_cast<E*>(st + C::OFF_KT);
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(64 * NW) void scan_kernel(ScanArgs<E> a)
         }
     };
 
-    Prefetch<E, DK, NW, DIAG> pf;
+    Prefetch<DK, NW, DIAG> pf;
     char* stage0 = lds;
     char* stage1 = lds + C::STAGE;
     E* ost0 = reinterpret_cast<E*>(lds + 2 * C::STAGE);
@@ -346,10 +348,10 @@ static hipError_t launch_scan_dk(const ScanArgs<bf16_t>& a, int waves, hipStream
     const int nsl = a.dv / (16 * waves);
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * nsl));
     switch (waves) {
-        case 1: hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 1, DIAG>), grid, dim3(64), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 2, DIAG>), grid, dim3(128), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((scan_kernel<DK, 1, DIAG>), grid, dim3(64), 0, st, a); break;
+        case 2: hipLaunchKernelGGL((scan_kernel<DK, 2, DIAG>), grid, dim3(128), 0, st, a); break;
         default:
-            if constexpr (!DIAG) { hipLaunchKernelGGL((scan_kernel<bf16_t, DK, 4, false>), grid, dim3(256), 0, st, a); break; }
+            if constexpr (!DIAG) { hipLaunchKernelGGL((scan_kernel<DK, 4, false>), grid, dim3(256), 0, st, a); break; }
             else return hipErrorInvalidValue;
     }
     return hipGetLastError();

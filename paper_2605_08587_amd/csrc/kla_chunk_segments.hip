@@ -357,14 +357,15 @@ __global__ void segment_scatter_kernel(const float* __restrict__ d_hT, float* __
     gseg[i] = (sg == G - 1 && d_hT) ? d_hT[(n * H + h) * per_head + e] : 0.f;
 }
 
-__global__ void segment_gather_kernel(const float* __restrict__ seg_state, float* __restrict__ hT, int H, long per_head,
-                                      int G, int g_last, long total)
+// d_h0 of a sequence: the gradient its first segment hands on
+__global__ void segment_gather_kernel(const float* __restrict__ seg_grad, float* __restrict__ dh0, int H, long per_head,
+                                      int G, long total)
 {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= total) return;
     const long nh = i / per_head, e = i % per_head;
     const long n = nh / H, h = nh % H;
-    hT[i] = seg_state[((n * G + g_last) * H + h) * per_head + e];
+    dh0[i] = seg_grad[(n * G * H + h) * per_head + e];
 }
 
 template <int DK, int NW, bool BREC>
@@ -424,12 +425,11 @@ hipError_t launch_segment_scatter(const float* d_hT, float* gseg, int N, int H, 
     return hipGetLastError();
 }
 
-hipError_t launch_segment_gather(const float* seg_state, float* hT, int N, int H, int dk, int dv, int G, int g_last,
-                                 hipStream_t st)
+hipError_t launch_segment_gather(const float* seg_grad, float* dh0, int N, int H, int dk, int dv, int G, hipStream_t st)
 {
     const long per_head = (long)dk * dv, total = (long)N * H * per_head;
-    hipLaunchKernelGGL(segment_gather_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seg_state, hT, H,
-                       per_head, G, g_last, total);
+    hipLaunchKernelGGL(segment_gather_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seg_grad, dh0, H,
+                       per_head, G, total);
     return hipGetLastError();
 }
 

@@ -109,8 +109,8 @@ hipError_t launch_segment_combine_rev(const float* maps, const float* bseg, floa
 hipError_t launch_segment_scatter(const float* d_hT, float* gseg, int N, int H, int dk, int dv, int G, hipStream_t st);
 hipError_t launch_segment_combine(const float* h0, const float* maps, float* seg_state, int N, int H, int dk, int dv,
                                   int G, hipStream_t st);
-hipError_t launch_segment_gather(const float* seg_state, float* hT, int N, int H, int dk, int dv, int G, int g_last,
-                                 hipStream_t st);
+// dh0 = what the first segment of every sequence has in seg_grad ([N * G][H][dk][dv])
+hipError_t launch_segment_gather(const float* seg_grad, float* dh0, int N, int H, int dk, int dv, int G, hipStream_t st);
 
 // ---- chunkwise backward (gradient of sum <d_o, o> + sum <d_hT, hT>) ----------------------------------
 // Stage 1 (launch_intra_bwd) leaves one record per chunk-head at `rec`.  Stage 2 walks every (sequence, head)

@@ -112,16 +112,11 @@ __device__ __forceinline__ void mma32(floatx4& acc, const Slot<E>& a, typename Q
 __host__ __device__ constexpr int pad_slots(int n) { return n + n / 8; }
 __device__ __forceinline__ size_t pad_pos(size_t slot) { return slot + (slot >> 3); }
 
-// Read the slot (tile-pair index tp, this lane) from an operand area in LDS.
+// Read the slot (tile-pair index tp, this lane) from an operand area in LDS (unpadded areas: bf16 only).
 __device__ __forceinline__ Slot<bf16_t> load_slot(const bf16_t* base, int tp, int lane)
 {
     const uint4 x = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + ((size_t)tp * 64 + lane) * 16);
     Slot<bf16_t> s; s.q0 = make_uint2(x.x, x.y); s.q1 = make_uint2(x.z, x.w); return s;
-}
-__device__ __forceinline__ Slot<float> load_slot(const float* base, int tp, int lane)
-{
-    const float4* p = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + ((size_t)tp * 64 + lane) * 32);
-    Slot<float> s; s.q0 = p[0]; s.q1 = p[1]; return s;
 }
 
 // Store one 16-byte piece of an operand ROW (row index `row` within the 64-row tile stack,
@@ -134,14 +129,6 @@ __device__ __forceinline__ void store_rq_piece(bf16_t* base, int n_pairs, int ro
     char* p = reinterpret_cast<char*>(base) + ((size_t)tp * 64 + r + 16 * g0) * 16 + blk * 8;
     *reinterpret_cast<uint2*>(p) = make_uint2(d.x, d.y);
     *reinterpret_cast<uint2*>(p + 16 * 16) = make_uint2(d.z, d.w);
-}
-__device__ __forceinline__ void store_rq_piece(float* base, int n_pairs, int row, int piece, uint4 d)
-{
-    // 4 elements k = 4*piece .. +3 : pair = piece/8, block = (piece%8)/4, quad g = piece%4
-    const int tp = (row >> 4) * n_pairs + (piece >> 3);
-    const int blk = (piece >> 2) & 1, g = piece & 3, r = row & 15;
-    char* p = reinterpret_cast<char*>(base) + ((size_t)tp * 64 + r + 16 * g) * 32 + blk * 16;
-    *reinterpret_cast<uint4*>(p) = d;
 }
 
 // Store four consecutive rows j = 4*tq .. 4*tq+3 of a row-major matrix, all at the same 16-byte
@@ -164,18 +151,6 @@ __device__ __forceinline__ void store_tq_rows(bf16_t* base, int n_pairs, int tq,
         *reinterpret_cast<uint2*>(p + (2 * m) * 16) = lo;
         *reinterpret_cast<uint2*>(p + (2 * m + 1) * 16) = hi;
     }
-}
-__device__ __forceinline__ void store_tq_rows(float* base, int n_pairs, int tq, int piece, const uint4 (&d)[4],
-                                              int ftile0)
-{
-    const int jp = tq >> 3, blk = (tq >> 2) & 1, g = tq & 3;
-    const int ft = (piece >> 2) - ftile0;
-    const int r0 = (piece & 3) * 4;
-    char* p = reinterpret_cast<char*>(base) + ((size_t)(ft * n_pairs + jp) * 64 + r0 + 16 * g) * 32 + blk * 16;
-    *reinterpret_cast<uint4*>(p + 0 * 32) = make_uint4(d[0].x, d[1].x, d[2].x, d[3].x);
-    *reinterpret_cast<uint4*>(p + 1 * 32) = make_uint4(d[0].y, d[1].y, d[2].y, d[3].y);
-    *reinterpret_cast<uint4*>(p + 2 * 32) = make_uint4(d[0].z, d[1].z, d[2].z, d[3].z);
-    *reinterpret_cast<uint4*>(p + 3 * 32) = make_uint4(d[0].w, d[1].w, d[2].w, d[3].w);
 }
 
 // ---- the same accessors for padded areas -----------------------------------------------------------
