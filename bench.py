@@ -218,7 +218,7 @@ def main():
             "whole_path_hbm_frac": round(alg_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
             "ms_per_chunk_step": round(ms_kernel / (T // C + 2), 6)}
 
-    # The same step as two kernels (intra-chunk stage, then scan), the form that runs for fp32, wide value heads and
+    # The same step as two kernels (intra-chunk stage, then scan), the form that runs for fp32, few or wide value heads and
     # segmented scans
     two = None
     rotating = None
@@ -275,11 +275,11 @@ def main():
         mfma["frac_of_measured_mfma"] = round(tflops / measured["mfma_bf16_TFLOPs"], 4)
         del big, aux
 
-    # ------------------------------------------------------------------ fp32 inputs: the element-type-generic kernels
+    # ------------------------------------------------------------------ fp32 inputs
     fp32_path = None
     if want("fp32"):
-        fp32_path = {"note": "fp32 q/k/v run the element-type-generic kernels (two-kernel form, fp32 MFMA and vector sums): "
-                             "the path that carries the 1e-4 parity bar, not tuned for speed"}
+        fp32_path = {"note": "fp32 q/k/v: intra-chunk stage and scan on fp32 MFMA (kla_chunk_intra_f32.hip, kla_chunk_sweeps_f32.hip), "
+                             "the path that carries the 1e-4 parity bar"}
         for name, cfg, shape in (("config1", kla_inputs.config(1), None), ("config2_shape", d, "fp32 copies of config 2's tensors")):
             f = {n: cfg[n].float().cuda() for n in ("q", "k", "v")}
             g = {n: cfg[n].cuda() for n in ("log_alpha", "eta")}
@@ -419,8 +419,8 @@ def main():
         run256(many)
         ms256_cold = _events(torch, lambda: run256(many), 3, groups=3)
         bytes256 = DECODE_BYTES_PER_TOKEN_HEAD * B * Hd * steps
-        # Back-to-back eager launches are bound by the host's launch path (about 13 us per call through the
-        # Python binding), so the kernel's own rate is taken from graph replays; the eager figures stay beside it.
+        # Back-to-back eager launches are bound by the host's launch path where a step is short (5 us per call through
+        # the Python binding), so the kernel's own rate is taken from graph replays; the eager figures stay beside it.
         try:
             gs = S0.clone()
             ms_graph = _events(torch, graph_of(lambda: run256([gs])).replay, 2, groups=20)

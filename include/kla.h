@@ -107,8 +107,8 @@ int kla_chunk_fwd(const void *q, const void *k, const void *v,
  * and states of the segment-parallel scan - goes to a fixed scratch array of KLA_STATIC_SCRATCH_BYTES that is part
  * of the library's device image (every GPU the library is used on holds its own copy from the first use there
  * until the process ends).  The call allocates and frees nothing, neither directly nor through another library.
- *   - A problem whose kla_chunk_fwd_workspace_bytes(...) exceeds KLA_STATIC_SCRATCH_BYTES is refused with
- *     KLA_ERR_WORKSPACE before anything is launched (32 MiB holds about 2 400 chunk-heads of the two-kernel form
+ *   - A problem whose kla_chunk_fwd_workspace_bytes(...) exceeds KLA_STATIC_SCRATCH_BYTES (the scan order of a packed
+ *     batch, at most 1 KiB, does not count) is refused with KLA_ERR_WORKSPACE before anything is launched (32 MiB holds about 2 400 chunk-heads of the two-kernel form
  *     in bf16, 1 200 in fp32; bf16 problems that run the fused kernel need none of it and are never refused).
  *   - The first call on a device looks up the device address of the array (one hipGetSymbolAddress, which may load
  *     the library's code onto that device): make it outside any stream capture.  KLA_ERR_HIP if the lookup fails.
@@ -157,10 +157,11 @@ enum { KLA_OPT_NORMALIZE_Q = 1, KLA_OPT_GDN_BETA = 2 };
  * unfused forms), so pass the same `opts` to the *_workspace_bytes_opts query and to the call.
  *   KLA_TUNE_SCAN_WAVES(n)     n = 1, 2, 4: compute waves (16 state columns each) per workgroup of the scan stage
  *   KLA_TUNE_SCAN_SEGMENTS(n)  n = 1: never cut sequences for the segment-parallel scan; n = 2..16: cut into n
- *   KLA_TUNE_GENERIC_SCAN / _INTRA / _BWD   bf16 inputs through the element-type-generic kernels of the fp32 path
+ *   KLA_TUNE_GENERIC_SCAN / _INTRA / _BWD   bf16 inputs through plain forms of the kernels, their reference
  *   KLA_TUNE_UNFUSED           bf16 forward as two kernels (intra-chunk stage, then scan) where one fused kernel would run
  *   KLA_TUNE_FUSED             bf16 forward as the one fused kernel wherever it can run (one or two compute waves per
- *                              workgroup, no segments), also where the two-kernel form is the library's choice
+ *                              workgroup, no segments), also where the two-kernel form is the library's choice.  The
+ *                              two round different operands to 16 bits (the off-diagonal blocks of I + L; V - D K S)
  *   KLA_TUNE_DECODE_SLICE(n)   n = 32, 64, 128, 256: state columns per workgroup of the decode step
  *   KLA_TUNE_DECODE_NT(n)      n = 0..3: bit 0 non-temporal state loads, bit 1 non-temporal state stores
  */

@@ -65,8 +65,8 @@ struct Plan {
 // sixteen-column chains, at least 64 chunks) is cut until max_chains sixteen-column chains run, into segments of at least
 // 16 chunks.  Forward: 1024 of them, 256 workgroups of four compute waves; 512, workgroups of two, where the value head
 // is narrow and the maps' d_k more columns weigh most (one 65K sequence of 8 heads 345 against 414 us, 8192 tokens of
-// d_v = 256 84 against 98 us; 2 x 16K tokens of d_v = 64 154 against 137 us).  Backward: 512, its sweeps have two compute
-// waves at most.  Beyond 16 segments their serial composition outweighs the shorter scans (32K tokens of 4 heads: 139 us
+// d_v = 256 84 against 98 us; 2 x 16K tokens of d_v = 64 154 against 137 us).  Backward: 512, its segmented sweeps
+// have two compute waves at most.  Beyond 16 segments their serial composition outweighs the shorter scans (32K tokens of 4 heads: 139 us
 // with 32, 128 us with 16).  The tuning field KLA_TUNE_SCAN_SEGMENTS(n) forces n (1 = never).  Returns the number of
 // non-empty segments and sets the chunks per segment.
 int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& tune, int max_chains, int* Lc)
@@ -239,7 +239,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     if (intra) {
         [[maybe_unused]] bool done = false;
         if constexpr (sizeof(E) == 2) {
-            if (!pl.tune.generic_intra) {                // else the element-type-generic kernel (A/B testing)
+            if (!pl.tune.generic_intra) {                // else the plain kernel (A/B testing)
                 if (kla::launch_intra_bf16(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
                 done = true;
             }
@@ -278,7 +278,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     }
     const int waves = pl.waves;
     if constexpr (sizeof(E) == 2) {
-        if (!pl.tune.generic_scan)                       // else the element-type-generic kernel (A/B testing)
+        if (!pl.tune.generic_scan)                       // else the plain kernel (A/B testing)
             return kla::launch_scan_bf16(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4) return kla::launch_scan_f32(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
@@ -487,7 +487,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     const long chains8 = ((long)pl.base.n_states * H + 7) / 8 * 8;
     const int waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
     if constexpr (sizeof(E) == 2) {
-        if (!pl.base.tune.generic_scan)                  // else the element-type-generic kernel (A/B testing)
+        if (!pl.base.tune.generic_scan)                  // else the plain kernel (A/B testing)
             return kla::launch_scan_bf16_diag(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4)

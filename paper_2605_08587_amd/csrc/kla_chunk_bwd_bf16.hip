@@ -43,11 +43,12 @@ struct SweepCfg16 {
                          OFF_EG = OFF_V + 64 * VRW, STAGE = OFF_EG + (REV ? 1024 : 768);
     static constexpr int ORB = NW <= 2 ? 96 : 160;       // row stride of a staging tile (see the forward kernel)
     static constexpr int OSB = 64 * ORB;
-    // Forward: two staged tiles and the workgroup's part of the checkpoint per chunk, in two parities, all written out by
-    // the store wave.  Reverse: a stage also holds Q, M^T and P^T, and what decides its speed is a ring of three stages
+    // Forward: one staged tile (X) and the workgroup's part of the checkpoint per chunk, in two parities, all written out by
+    // the store wave.  Reverse: two tiles (Y, dV); a stage also holds Q, M^T and P^T, and what decides its speed is a ring of three stages
     // (the copies of a chunk then have two visits to arrive): the staging tiles get one parity only (a counter in LDS
     // tells the compute waves that the store wave has read them) and the checkpoint is stored by the compute waves.
-    // With four compute waves the reverse stage does not fit three times anyway, and there is room for both parities.
+    // With four compute waves there is room for both parities: at d_k = 128 the reverse stage does not fit three times
+    // anyway, at d_k = 64 three stages fit beside them.
     static constexpr int NPAR = REV && NW <= 2 ? 1 : 2, NTILE = REV ? 2 : 1;
     static constexpr int CKB = REV ? 0 : SLW * DK * 2;
     static constexpr int NST = (3 * STAGE + NTILE * NPAR * OSB + 2 * CKB <= 160 * 1024) ? 3 : 2;   // LDS ring depth

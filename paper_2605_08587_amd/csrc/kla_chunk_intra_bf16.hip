@@ -16,8 +16,8 @@
 //   * Rows beyond a short last chunk re-read its last row; beta = 0 there zeroes their rows and columns
 //     of T', and their rows of P are masked.
 // 18 KB of LDS and at most 80 VGPRs: six workgroups per CU.  Measured, K, Q and P all staged in LDS (50 KB, three
-// workgroups per CU) -> this kernel: 7824 chunk-heads of d_k = 128 109 -> 76 us (4.6 TB/s of mixed traffic), 4096 with the
-// backward's records 58 -> 43 us.
+// workgroups per CU) -> this kernel: 7824 chunk-heads of d_k = 128 109 -> 76 us, 4096 with the backward's records 58 -> 43 us;
+// with the clocks up 69 and 40 us for 0.39 and 0.23 GB (5.7 TB/s by the counters, part of it out of the memory-side cache).
 #include "kla_bf16_ops.hpp"
 #include "kla_common.hpp"
 #include "kla_kernels.hpp"
@@ -387,7 +387,7 @@ hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, h
     return hipGetLastError();
 }
 
-// the records of the backward pass at a.wsT; a.wsP and a.wsG unused, a.opts = 0
+// the records of the backward pass at a.wsT (a.opts: the option bits of the call); a.wsP and a.wsG unused
 hipError_t launch_intra_bwd_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st)
 {
     if (n_chunks == 0) return hipSuccess;

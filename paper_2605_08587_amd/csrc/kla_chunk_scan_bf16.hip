@@ -29,12 +29,12 @@
 //     the chunks two and one steps ahead, straight into two LDS record buffers, so K and Q are read from memory
 //     once and the per-chunk objects never leave the CU (see the helper section below).  A seventh wave, otherwise
 //     idle, writes the staged outputs to memory.
-//   * Eight compute waves (SELF; batches of more than 1024 sixteen-column chains): a workgroup takes 128 columns, two
+//   * Eight compute waves (SELF; d_v >= 128, where they save rounds of workgroups: see scan_waves): a workgroup takes 128 columns, two
 //     waves per SIMD cover each other's latencies, and K, Q, T', P are copied once per 128 columns instead of once per
 //     64. There is no copy or write-out wave then (a ninth wave would cap the registers at 168 and the products spill):
 //     every wave issues an eighth of the copies a step ahead and writes an eighth of the previous outputs. What bounds
-//     it is memory: 16 packed sequences of 512..4096 tokens, 16 heads, d_v = 256 move about 1 GB through the scan:
-//     265 us with four waves, 220 us with eight (4.5 TB/s; a large copy reaches 4.9).
+//     it is memory: 16 packed sequences of 512..4096 tokens, 16 heads, d_v = 256 move 0.93 GB through the scan (counters):
+//     265 us with four waves, 225 us with eight (4.1 TB/s; reading and writing in place reaches 5.6).
 //   * A short last chunk is handled without zero filling: rows beyond it re-read the last valid row;
 //     their T' rows and columns are zero (beta = 0 there), so they contribute nothing to U, to the
 //     state or to any stored output.

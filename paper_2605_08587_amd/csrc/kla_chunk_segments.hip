@@ -12,8 +12,7 @@
 //      update), 32 or 64 columns per workgroup.
 //   2. segment_combine_kernel: S_in(0) = h0, S_in(g+1) = M_g S_in(g) + N_g, in fp32 (G - 1 small products).
 //   3. the ordinary scan kernel over all N x G segments at once, each starting from its S_in (the kernel's
-//      segmented mode), which also produces the outputs; segment_gather_kernel then copies the last segment's
-//      final state to h_T.
+//      segmented mode), which also produces the outputs and, from the last segment, h_T.
 //
 // Layouts, swizzles, the copy wave and the operand tricks are those of kla_chunk_scan_bf16.hip.
 #include "kla_bf16_ops.hpp"

@@ -25,7 +25,7 @@
 // so they reach no result; in the reverse sweep dO is zeroed there - and behind the last chunk that chunk is read again.
 //
 // Measured, one wave per chain -> this file: forward of 4 sequences of 2000 tokens, 8 heads, d = 128 (256 column tiles):
-// 590 -> 118 us, 3.7 us per chunk against 1.7 us of MFMA per wave (143 us with conditional loads; 94 us with eight waves); 2 sequences of 500
+// 590 -> 118 us, 3.7 us per chunk against 1.7 us of MFMA per wave (143 us with conditional loads; 100 us with eight waves); 2 sequences of 500
 // tokens, 4 heads, d = 64 (32 tiles): forward 71 -> 20 us, forward sweep 53 -> 17 us, reverse sweep 124 -> 28 us.
 #include "kla_common.hpp"
 #include "kla_f32_ops.hpp"
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
 
 // The same with eight waves, two per SIMD: waves 0 .. 3 carry the chain (K S, X, U, the state update), waves 4 .. 7, which
 // share their SIMDs, do everything off it (Q S, P U, the outputs, the copies of K).  With four waves a SIMD stands idle
-// whenever its only wave waits for LDS or a barrier: 3.7 us per chunk for 1.7 us of MFMA, here 2.9 us.  K and the exchanged
+// whenever its only wave waits for LDS or a barrier: 3.7 us per chunk for 1.7 us of MFMA, here 3.1 us.  K and the exchanged
 // state have two images each, so a step needs three barriers instead of four.  (Loads requested two chunks ahead, two
 // accumulators per product and a raised priority of the chain change nothing: 123 us either way.)
 template <int DK, int NC, bool DIAG>

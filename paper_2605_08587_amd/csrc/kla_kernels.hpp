@@ -36,7 +36,7 @@ template <typename E> struct IntraArgs {
     E* wsT; E* wsP; float* wsG;
     unsigned opts;                               // kOptNormalizeQ | kOptGdnBeta
     // Packed batches of at most kPosScanMax sequences: where this stage leaves the chunk offsets and the scan order for the
-    // kernels behind it (NULL: launch_chunk_offsets has run).  Not for the element-type-generic kernels.
+    // kernels behind it (NULL: launch_chunk_offsets has run).  Not for the plain kernels.
     int* pos_out = nullptr;
 };
 hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);       // bf16, plain form
