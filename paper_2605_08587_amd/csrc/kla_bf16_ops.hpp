@@ -97,6 +97,51 @@ __device__ __forceinline__ u32x2 quad_transpose4x4(u32x2 ob, bool q_lo, uint32_t
     ob.y = __builtin_amdgcn_perm(py, ob.y, psel);
     return ob;
 }
+
+// ---- what the sweeps leave in memory for the backward's assembly, written by the wave that holds it in registers ----
+// Both in the order in which the registers are: every store instruction fills whole 1 KiB blocks, and no wave transposes or
+// stages anything for them.  8 x 4096 tokens, 8 heads, d = 128, the whole backward: 476 us with rows transposed and staged in
+// LDS and checkpoints in rows of d_k (64 bytes per row and store instruction), 468 with X and Y in operand order, 457 with
+// the checkpoints too (the reverse sweep alone 157 -> 144 us).
+//
+// A state checkpoint (bf16, fragments q of the permuted feature index above), per chunk-head and 16 columns: 1 KiB per 32
+// features, in it column r's 64 bytes = features 32 kp + 8 g .. + 7 for g = 0 .. 3.  chk: the chunk-head's first byte.
+template <int DK> __device__ __forceinline__ void put_checkpoint(char* chk, int col_tile, const u32x2 (&q)[DK / 16], int r, int g)
+{
+    char* p = chk + col_tile * (16 * DK * 2) + r * 64 + g * 16;
+#pragma unroll
+    for (int kp = 0; kp < DK / 32; ++kp) {
+        const u32x4 w = {q[2 * kp].x, q[2 * kp].y, q[2 * kp + 1].x, q[2 * kp + 1].y};
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p + kp * 1024));
+    }
+}
+// The 64 rows of X or Y (quads q[it]: tokens 16 it + 4 g .. + 3 of column r), 16 columns at a time.  A whole chunk takes the
+// bytes of its 64 rows of a [tokens][H][d_v] tensor and keeps them head after head, per head and 16 columns as the two 1 KiB
+// tile-pairs of B-operand slots (kla_mma.hpp).  A short one has no room for its 64 rows: it is stored as rows.
+// chunk: the first byte of the chunk's rows; v_row: bytes between tokens; hd: head.
+__device__ __forceinline__ void put_rows(char* chunk, size_t v_row, int dv, int hd, int col_tile, const u32x2 (&q)[4], int clen, int r, int g)
+{
+    if (clen == 64) {
+        char* p = chunk + (size_t)hd * dv * 128 + col_tile * 2048 + (16 * g + r) * 16;
+#pragma unroll
+        for (int jp = 0; jp < 2; ++jp) {
+            const u32x4 w = {q[2 * jp].x, q[2 * jp].y, q[2 * jp + 1].x, q[2 * jp + 1].y};
+            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p + jp * 1024));
+        }
+    } else {
+        // (once per sequence: the lane goes through an empty asm so that none of these addresses is kept in registers)
+        asm volatile("" : "+v"(r), "+v"(g));
+        char* p = chunk + (size_t)hd * dv * 2 + (16 * col_tile + r) * 2;
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = 16 * it + 4 * g + e;
+                const uint32_t w = e < 2 ? q[it].x : q[it].y;
+                if (row < clen) *reinterpret_cast<uint16_t*>(p + (size_t)row * v_row) = (uint16_t)((e & 1) ? w >> 16 : w & 0xffffu);
+            }
+    }
+}
 __device__ __forceinline__ floatx4 ld_f4(const char* p) { return *reinterpret_cast<const floatx4*>(p); }
 
 }  // namespace kla

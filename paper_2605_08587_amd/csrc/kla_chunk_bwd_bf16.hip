@@ -6,9 +6,11 @@
 // index of that kernel: element e of lane (r, g) of tile kt = 2 kp + b is feature 32 kp + 8 g + 4 b + e.
 //
 //   REV = false   forward sweep:  X = V - D_gamma K S,  U = T' X,  S <- gamma_C S + K^T diag(gamma_C/gamma_i) U;
-//                 leaves S_c (before the chunk), X and U.
+//                 leaves S_c (before the chunk) and X.
 //   REV = true    backward sweep: dU = P^T dO + diag(gamma_C/gamma_i) K dS',  Y = M^T dU,  dV = B Y,
 //                 dS <- gamma_C dS' + Q^T D_gamma dO - K^T D_gamma dV;  leaves dS'_c, Y, dV and finally dh0.
+//
+// X, Y and the checkpoints go to memory as the registers hold them (put_rows, put_checkpoint in kla_bf16_ops.hpp).
 //
 // A short last chunk re-reads its last valid row for the rows beyond it (as in the forward).  Those rows have
 // beta = 0, zero rows and columns in T' and P^T and unit rows in M, so they reach neither U, Y (valid rows), dV nor
@@ -43,19 +45,11 @@ struct SweepCfg16 {
                          OFF_EG = OFF_V + 64 * VRW, STAGE = OFF_EG + (REV ? 1024 : 768);
     static constexpr int ORB = NW <= 2 ? 96 : 160;       // row stride of a staging tile (see the forward kernel)
     static constexpr int OSB = 64 * ORB;
-    // Forward: one staged tile (X) and the workgroup's part of the checkpoint per chunk, in two parities, all written out by
-    // the store wave.  Reverse: two tiles (Y, dV); a stage also holds Q, M^T and P^T, and what decides its speed is a ring of three stages
-    // (the copies of a chunk then have two visits to arrive): the staging tiles get one parity only (a counter in LDS
-    // tells the compute waves that the store wave has read them) and the checkpoint is stored by the compute waves.
-    // With four compute waves there is room for both parities: at d_k = 128 the reverse stage does not fit three times
-    // anyway, at d_k = 64 three stages fit beside them.
-    static constexpr int NPAR = REV && NW <= 2 ? 1 : 2, NTILE = REV ? 2 : 1;
-    static constexpr int CKB = REV ? 0 : SLW * DK * 2;
-    static constexpr int NST = (3 * STAGE + NTILE * NPAR * OSB + 2 * CKB <= 160 * 1024) ? 3 : 2;   // LDS ring depth
-    static constexpr int OFF_CK = NST * STAGE + NTILE * NPAR * OSB;
+    // Reverse sweep: the rows of dV are staged, in two parities, for the store wave.
+    static constexpr int NST = (3 * STAGE + (REV ? 2 * OSB : 0) <= 160 * 1024) ? 3 : 2;   // LDS ring depth
     // swizzle of the V / dO slice, as in the forward kernel (period 8 rows: the same for every copy block)
     __host__ __device__ static constexpr int vswz(int row) { return NW == 4 ? 2 * ((row >> 1) & 3) : 0; }
-    static constexpr int LDS = OFF_CK + 2 * CKB;
+    static constexpr int LDS = NST * STAGE + (REV ? 2 * OSB : 0);
     static constexpr int NDMA = (REV ? 2 : 1) * NKB + NTB + NVB + 1;
     static_assert(LDS <= 160 * 1024 && NDMA < 64, "LDS budget of a gfx950 CU; 6-bit vmcnt");
 };
@@ -63,7 +57,7 @@ struct SweepCfg16 {
 }  // namespace
 
 template <int DK, int NW, bool REV>
-__global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<bf16_t> a)
+__global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_kernel(BwdArgs<bf16_t> a)
 {
     typedef SweepCfg16<DK, NW, REV> C;
     constexpr int NTH = C::NTH, KB = C::KB, KP = C::KP, SLW = C::SLW, RB = C::RB, PPR = C::PPR, RPB = C::RPB,
@@ -183,7 +177,8 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
     auto stage_quad = [&](u32x2 ob, char* dst) { *reinterpret_cast<u32x2*>(dst) = quad_transpose4x4(ob, q_lo, psel); };
 
     // ---- one chunk for this wave's 16 columns -----------------------------------------------------------
-    auto compute = [&](const char* st, char* ost, char* ckb, int c, int vis) {
+    auto compute = [&](const char* st, char* ost, int c) {
+        const int clen = min(64, len - 64 * c);
         const char* pS = st + lane * 16;
         const char* pV = st + C::OFF_V + oV;
         const char* pG = st + C::OFF_EG + 16 * g;
@@ -201,28 +196,8 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
         u32x2 Sq[KB];
 #pragma unroll
         for (int kt = 0; kt < KB; ++kt) { Sq[kt] = to_quad(S[kt]); S[kt] = S[kt] * gC; }
-        if (store) {
-            // checkpoint, transposed ([column][feature]): features 32 kp + 8 g .. + 7 of this lane's column are 16
-            // contiguous bytes.
-            if constexpr (C::CKB > 0) {
-                // staged in LDS for the store wave; the 16-byte pieces of a column are XORed with the column so that the
-                // eight lanes a 128-bit write serves per cycle fall into different banks
-                const int cl = 16 * wave + r;
-                char* ck = ckb + cl * (DK * 2);
-#pragma unroll
-                for (int kp = 0; kp < KP; ++kp) {
-                    const u32x4 w = {Sq[2 * kp].x, Sq[2 * kp].y, Sq[2 * kp + 1].x, Sq[2 * kp + 1].y};
-                    st16(ck + (((4 * kp + g) ^ (cl & 7)) * 16), w);
-                }
-            } else {
-                bf16_t* ck = (REV ? a.ds_chk : a.s_chk) + (((size_t)(ch0 + c) * a.H + h) * a.dv_dim + col) * DK + 8 * g;
-#pragma unroll
-                for (int kp = 0; kp < KP; ++kp) {
-                    const u32x4 w = {Sq[2 * kp].x, Sq[2 * kp].y, Sq[2 * kp + 1].x, Sq[2 * kp + 1].y};
-                    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(ck + 32 * kp));
-                }
-            }
-        }
+        if (store) put_checkpoint<DK>(reinterpret_cast<char*>(REV ? a.ds_chk : a.s_chk) + ((size_t)(ch0 + c) * a.H + h) * a.dv_dim * RB,
+                                      slice * NW + wave, Sq, r, g);
 
         // ---- K S or K dS'
         floatx4 ks[4];
@@ -258,8 +233,8 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 Xq[it] = to_quad(quad_to_f(vq[it]) - egv[it] * ks[it]);       // eq. (6), right-hand side without B
-                stage_quad(Xq[it], ost + oO + 16 * it * ORB);
             }
+            put_rows(reinterpret_cast<char*>(a.X) + (size_t)(t0 + 64L * c) * v_row, v_row, a.dv_dim, h, slice * NW + wave, Xq, clen, r, g);
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 0, 0, kt[0][t][0], kt[0][t][1]);
             floatx4 U[4];
@@ -280,7 +255,6 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
 #pragma unroll
             for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[1][t][0], kt[1][t][1], Udq[2], Udq[3]);
         } else {
-            const int clen = min(64, len - 64 * c);
             u32x4 psl[kTriPairs];
 #pragma unroll
             for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pS + C::OFF_P + i * 1024);
@@ -308,24 +282,19 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 1, C::OFF_Q, kt[1][t][0], kt[1][t][1]);
             u32x2 gdOq[4], gdXq[4];
-            if constexpr (C::NPAR == 1) {
-                // one staging parity: the store wave must have read the tiles of the previous visit (it does so right
-                // after the barrier, a whole visit ago; the wait is a formality, and bounded)
-                for (int spin = 0; *reinterpret_cast<const volatile int*>(lds + NST * C::STAGE + VRW) < vis - 1 && spin < (1 << 15); ++spin)
-                    __builtin_amdgcn_s_sleep(1);
-                asm volatile("" ::: "memory");
-            }
+            u32x2 Yq[4];
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const floatx4 dx = Y[it] * ld_f4(pG + 512 + 64 * it);           // dV = B Y
-                stage_quad(to_quad(Y[it]), ost + oO + 16 * it * ORB);
-                stage_quad(to_quad(dx), ost + C::OSB + oO + 16 * it * ORB);
+                Yq[it] = to_quad(Y[it]);
+                stage_quad(to_quad(dx), ost + oO + 16 * it * ORB);
                 floatx4 eg = egv[it];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) eg[e] = (16 * it + 4 * g + e < clen) ? eg[e] : 0.f;   // rows past a ragged end
                 gdOq[it] = to_quad(eg * ld_f4(pG + 768 + 64 * it) * quad_to_f(vq[it]));   // D_gamma dO / ||q||
                 gdXq[it] = to_quad(-(eg * dx));
             }
+            if (store) put_rows(reinterpret_cast<char*>(a.Y) + (size_t)(t0 + 64L * c) * v_row, v_row, a.dv_dim, h, slice * NW + wave, Yq, clen, r, g);
             // ---- dS = gamma_C dS' + Q^T D_gamma dO - K^T D_gamma dV
 #pragma unroll
             for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[0][t][0], kt[0][t][1], gdOq[0], gdOq[1]);
@@ -342,59 +311,35 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
         }
     };
 
-    // Everything chunk c leaves in memory goes out through one wave that does nothing else, 16 bytes per lane: the two
-    // staged tiles (forward: X, U; backward: Y, dV) and the workgroup's columns of the checkpoint.  The compute waves
-    // never issue a global store, so they never stand in the store queue.
-    auto write_out = [&](int c, const char* ost, const char* ckb) {
+    // Reverse sweep: the staged rows of dV go out through a wave that does nothing else, 16 bytes per lane
+    auto write_out = [&](int c, const char* ost) {
         const int clen = min(64, len - 64 * c);
-        const size_t off = (size_t)(t0 + 64L * c) * v_row + ((size_t)h * a.dv_dim + slice * SLW) * 2;
-        char* o0 = reinterpret_cast<char*>(REV ? a.Y : a.X) + off;
-        char* o1 = reinterpret_cast<char*>(a.dv) + off;          // backward sweep only
+        char* o1 = reinterpret_cast<char*>(a.dv) + (size_t)(t0 + 64L * c) * v_row + ((size_t)h * a.dv_dim + slice * SLW) * 2;
 #pragma unroll
         for (int it = 0; it < VPP; ++it) {
             const int i = lane + 64 * it;
             const int row = i / VPP, pv = i % VPP;
-            if (row < clen) {
-                __builtin_nontemporal_store(ld16(ost + row * ORB + pv * 16), reinterpret_cast<u32x4*>(o0 + (size_t)row * v_row + pv * 16));
-                if constexpr (REV) __builtin_nontemporal_store(ld16(ost + C::OSB + row * ORB + pv * 16), reinterpret_cast<u32x4*>(o1 + (size_t)row * v_row + pv * 16));
-            }
-        }
-        if constexpr (C::CKB > 0) {
-            char* ck = reinterpret_cast<char*>(REV ? a.ds_chk : a.s_chk) +
-                       (((size_t)(ch0 + c) * a.H + h) * a.dv_dim + slice * SLW) * (DK * 2);
-#pragma unroll
-            for (int it = 0; it < C::CKB / 1024; ++it) {
-                const int i = lane + 64 * it;
-                const int cl = i / PPR, pp = i % PPR;        // column of the workgroup, physical piece
-                __builtin_nontemporal_store(ld16(ckb + i * 16), reinterpret_cast<u32x4*>(ck + cl * (DK * 2) + ((pp ^ (cl & 7)) * 16)));
-            }
+            if (row < clen) __builtin_nontemporal_store(ld16(ost + row * ORB + pv * 16), reinterpret_cast<u32x4*>(o1 + (size_t)row * v_row + pv * 16));
         }
     };
 
-    char* ost0 = lds + NST * C::STAGE;
-    char* ost1 = C::NPAR == 2 ? ost0 + C::NTILE * C::OSB : ost0;
-    char* ckb0 = lds + C::OFF_CK;
-    // last visit whose staged tiles the store wave has read (one staging parity only); in the padding of the first
-    // staging row (a row holds VRW of its ORB bytes)
-    int* oflag = reinterpret_cast<int*>(ost0 + VRW);
-    if (C::NPAR == 1 && tid == 0) *oflag = -1;
+    char* ost0 = lds + NST * C::STAGE;                   // reverse sweep only
+    char* ost1 = ost0 + C::OSB;
     // chunks are visited in the order i = 0 .. nch-1; the backward sweep starts at the last chunk
     auto chunk_of = [&](int i) { return REV ? nch - 1 - i : i; };
 
-    if (wave == NW + 1) {
-        // ---- the store wave: after the barrier that ends visit i, chunk_of(i) is complete in the staging areas of
-        //      parity i & 1, which the compute waves write again only in visit i + 2, behind the barrier this wave
-        //      reaches next
-        __syncthreads();
-        for (int i = 0; i < nch; ++i) {
+    if constexpr (REV) {
+        if (wave == NW + 1) {
+            // ---- the store wave: after the barrier that ends visit i, chunk_of(i) is complete in the staging area of
+            //      parity i & 1, which the compute waves write again only in visit i + 2, behind the barrier this wave
+            //      reaches next
             __syncthreads();
-            if (store) write_out(chunk_of(i), (i & 1) ? ost1 : ost0, ckb0 + (i & 1) * C::CKB);
-            if constexpr (C::NPAR == 1) {
-                asm volatile("" ::: "memory");
-                if (lane == 0) *reinterpret_cast<volatile int*>(oflag) = i;      // behind the reads above, in order
+            for (int i = 0; i < nch; ++i) {
+                __syncthreads();
+                if (store) write_out(chunk_of(i), (i & 1) ? ost1 : ost0);
             }
+            return;
         }
-        return;
     }
 
     if (wave == NW) {
@@ -420,8 +365,7 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
     int scur = 0;
     for (int i = 0; i < nch; ++i) {
         const int c = chunk_of(i);
-        char* ost = (i & 1) ? ost1 : ost0;
-        compute(lds + scur * C::STAGE, ost, ckb0 + (i & 1) * C::CKB, c, i);
+        compute(lds + scur * C::STAGE, (i & 1) ? ost1 : ost0, c);
         __syncthreads();
         scur = (scur + 1 == NST) ? 0 : scur + 1;
     }
@@ -440,11 +384,13 @@ __global__ __launch_bounds__(64 * NW + 128) void bwd_sweep_bf16_kernel(BwdArgs<b
 // =================================================================================================
 // per chunk-head contractions (bf16): the algebra of bwd_assemble_kernel in kla_chunk_bwd.hip on direct
 // global -> LDS copies.  Every operand sits in LDS as plain swizzled rows: the slab of S^T and dS'^T (64 rows of
-// d_k) and the K, Q tiles exactly like a K tile of the sweeps, the [64 tokens x 64 columns] slabs of dO, U, Y, X
-// like a K tile of d_k = 64.  Operands contracted along a row are two 64-bit reads, operands contracted down a
+// d_k) and the K, Q tiles exactly like a K tile of the sweeps, the [64 tokens x 32 columns] slabs of dO
+// in rows of 64 bytes.  Operands contracted along a row are two 64-bit reads, operands contracted down a
 // column (S^T, dS'^T, K, Q) come from the transposing read, which makes lane r of an output tile the feature
 // 32 kp + 8 (r / 4) + 4 b + r % 4 of tile 2 kp + b; the K and Q values that meet those outputs are read the same
-// way, and the 4x4 transposition before the staged write-out puts the features back in order.
+// way, and the 4x4 transposition before the staged write-out puts the features back in order.  X, Y and U are in the
+// operand order the sweeps leave them in: X is the B operand of T' X as it lies, and token rows of Y, U (and X) are the
+// columns of such a slot area, read with the transposing read.  (X and Y of a short chunk are rows in memory, and here.)
 // A short last chunk re-reads its last valid row for the rows beyond it; the rows of A o dP and D', of the
 // <.,k> sums and of dg that belong to those rows are masked to zero.
 // =================================================================================================
@@ -515,9 +461,9 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     // period 8 rows).  Rows past the end of a ragged chunk re-read its last one.
     const bool full = clen == 64;
     constexpr int NGK = 8 / RPB;
-    int gst[NGK];
+    int gst[NGK];                                    // piece 4 kp + g of column lrow (see put_checkpoint)
 #pragma unroll
-    for (int j = 0; j < NGK; ++j) gst[j] = lrow * RB + ((pcol ^ swz_piece<DK>(RPB * j + lrow)) * 16);
+    for (int j = 0; j < NGK; ++j) { const int pc = pcol ^ swz_piece<DK>(RPB * j + lrow); gst[j] = lrow * 64 + (pc >> 2) * 1024 + (pc & 3) * 16; }
     const int gsl = lrowA * (int)v_row + ((pcolA ^ ((lrowA >> 1) & 3)) * 16);
     auto copy_tile = [&](const char* src, size_t stride, char* dst, int b0, int b1) {       // blocks [b0, b1) of a [64 x d_k] tile
         for (int b = b0; b < b1; ++b) {
@@ -525,10 +471,10 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
             dma16(src, min(row, clen - 1) * (int)stride + ((pcol ^ swz_piece<DK>(row)) * 16), dst + b * 1024);
         }
     };
-    auto copy_state = [&](const char* src, char* dst) {                                      // 32 rows of a checkpoint: never ragged
+    auto copy_state = [&](const char* src, char* dst) {                                      // 32 columns of a checkpoint: never ragged
         static_for<NSB>([&](auto bb) {
             const int b = bb;
-            dma16(src + b * RPB * RB, gst[b % NGK], dst + b * 1024);
+            dma16(src + (b * RPB / 16) * (16 * RB) + (b * RPB % 16) * 64, gst[b % NGK], dst + b * 1024);
         });
     };
     auto copy_slab = [&](const char* src, char* dst) {                                       // 4 blocks of 16 token rows x 64 bytes
@@ -558,33 +504,54 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         q1 = lds_read_tr(p + 16 * RB);
     };
 
-    // U = T' X is not read back from the forward sweep but formed again, slab by slab: the T' tile pairs of this wave's 16
-    // rows (A operands, copied from the record into LDS once), the X slab through the transposing read (B operands), the
-    // result put into the slab's U area in the layout a copied slab has.  Per lane: where its 8 bytes of an X row sit.
-    for (int i = wave; i < kTriPairs; i += 4) dma16(rec + i * 1024, lane * 16, tp_s + i * 1024);   // lands with the first slab
-    // (column tile 0; tile 1 is two 16-byte pieces further, i.e. the same offsets with bit 5 flipped)
+    // Slot areas of a slab: [column tile ct][token pair jp][64 slots], 4 KiB.  Token row 16 t + r of one, contraction indices =
+    // columns {4 g .. +3 | 16 + 4 g .. +3}: source lane (a4, c4) of the transposing read points at the four tokens
+    // 16 t + 4 c4 .. of column 4 g + a4, i.e. at slot (r' = 4 g + a4, g' = c4).  In the areas of Y and U the slots of odd g'
+    // are exchanged by halves (slot index XOR 8), so that the 32 lanes served at once meet in pairs and not in fours.
+    const int oT = ((16 * c4 + 4 * g + a4) ^ (8 * (c4 & 1))) * 16, oTx = (16 * c4 + 4 * g + a4) * 16;
+    auto rowslot = [&](const char* tile, int t, int off, u32x2& q0, u32x2& q1) {
+        const char* p = tile + (t >> 1) * 1024 + 8 * (t & 1) + off;
+        q0 = lds_read_tr(p);
+        q1 = lds_read_tr(p + 2048);
+    };
+    const int swl = (lane ^ (8 * (g & 1))) * 16;         // this lane's slot of such an area
+    // rows of X (a short chunk), column-contracted: where this lane's 8 bytes sit (column tile 0; tile 1: bit 5 flipped)
     const int xo = (4 * g + a4) * RBA + ((((c4 >> 1)) ^ ((2 * g + (a4 >> 1)) & 3)) * 16) + (c4 & 1) * 8;
-    const int urow = 16 * wave + 4 * g + (r & 3);            // after the 4x4 transposition a lane holds 4 columns of one row
-    const int uo = urow * RBA + ((((r >> 3)) ^ ((urow >> 1) & 3)) * 16) + ((r >> 2) & 1) * 8;
+    // U = T' X is not read back from the forward sweep but formed again, slab by slab: the T' tile pairs of this wave's 16
+    // rows (A operands, copied from the record into LDS once) times the X slots, the result put into the slab's U area.
+    for (int i = wave; i < kTriPairs; i += 4) dma16(rec + i * 1024, lane * 16, tp_s + i * 1024);   // lands with the first slab
     floatx4 dQ[KB], dKr[KB], dKw[KB], dP[4], N1[4];
 #pragma unroll
     for (int ct = 0; ct < KB; ++ct) { dQ[ct] = floatx4{0.f, 0.f, 0.f, 0.f}; dKr[ct] = dQ[ct]; dKw[ct] = dQ[ct]; }
 #pragma unroll
     for (int jt = 0; jt < 4; ++jt) { dP[jt] = floatx4{0.f, 0.f, 0.f, 0.f}; N1[jt] = dP[jt]; }
-    float yx = 0.f, sdot = 0.f;
+    floatx4 YX = floatx4{0.f, 0.f, 0.f, 0.f};        // tile (wave, wave) of Y X^T: its diagonal is wanted
+    float sdot = 0.f;
 
     // ---- first phase: everything that contracts over d_v, 32 columns at a time; the next slab (after the last
     //      one: K and Q) is on its way while a slab is used ---------------------------------------------------
     const char* Sg = reinterpret_cast<const char*>(a.s_chk) + (size_t)blockIdx.x * DK * a.dv_dim * 2;
     const char* dSg = reinterpret_cast<const char*>(a.ds_chk) + (size_t)blockIdx.x * DK * a.dv_dim * 2;
+    // X and Y of a whole chunk: slots, 4 KiB per slab; of a short one: rows (put_rows)
+    const size_t xy0 = (size_t)tok0 * v_row + (size_t)h * a.dv_dim * (full ? 128 : 2);
+    const char* Xg = reinterpret_cast<const char*>(a.X) + xy0;
+    const char* Yg = reinterpret_cast<const char*>(a.Y) + xy0;
     const size_t vrow0 = (size_t)tok0 * v_row + (size_t)h * a.dv_dim * 2;
     auto issue_slab = [&](int sl, char* buf) {
         if (wave == 0)      copy_state(Sg + (size_t)(32 * sl) * RB, buf + OFF_S);
         else if (wave == 1) copy_state(dSg + (size_t)(32 * sl) * RB, buf + OFF_DS);
         else if (wave == 2) copy_slab(reinterpret_cast<const char*>(a.d_o) + vrow0 + 64 * sl, buf + OFF_DO);
         else {
-            copy_slab(reinterpret_cast<const char*>(a.Y) + vrow0 + 64 * sl, buf + OFF_Y);
-            copy_slab(reinterpret_cast<const char*>(a.X) + vrow0 + 64 * sl, buf + OFF_X);
+            if (full) {
+                static_for<4>([&](auto bb) {
+                    const int b = bb;
+                    dma16(Yg + (size_t)sl * 4096 + b * 1024, swl, buf + OFF_Y + b * 1024);
+                    dma16(Xg + (size_t)sl * 4096 + b * 1024, lane * 16, buf + OFF_X + b * 1024);
+                });
+            } else {
+                copy_slab(Yg + 64 * sl, buf + OFF_Y);
+                copy_slab(Xg + 64 * sl, buf + OFF_X);
+            }
         }
     };
     const int ns = a.dv_dim / 32;
@@ -600,30 +567,34 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
             if (wave < 2) copy_tile(kb, kq_row, lds + OFF_K, wave * (NKB / 2), (wave + 1) * (NKB / 2));
             else          copy_tile(qb, kq_row, lds + OFF_Q, (wave - 2) * (NKB / 2), (wave - 1) * (NKB / 2));
         }
-        // U = T' X: this wave's 16 rows of the slab.  (The lane index is passed through an empty asm so that the two
-        // transposition constants are formed here and not kept in registers until the staging of dq and dk, where the
-        // kernel has none to spare.)
-        int r1 = r;
-        asm volatile("" : "+v"(r1));
-        const bool q_lo = (r1 & 3) < 2;
-        const uint32_t psel = (r1 & 1) ? 0x03020706u : 0x05040100u;
+        // U = T' X: this wave's 16 rows of the slab
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
             floatx4 u = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int jp = 0; jp < 2; ++jp) {
                 if (2 * jp <= wave) {                      // T' is lower triangular (wave-uniform)
-                    const char* xp = buf + OFF_X + 32 * jp * RBA + (xo ^ (32 * ct));
-                    mma_bf16(u, ld16(tp_s + tri_pair(wave, jp) * 1024 + lane * 16), lds_read_tr(xp), lds_read_tr(xp + 16 * RBA));
+                    u32x2 x0, x1;
+                    if (full) {
+                        const u32x4 xs = ld16(buf + OFF_X + (2 * ct + jp) * 1024 + lane * 16);
+                        x0 = u32x2{xs[0], xs[1]}; x1 = u32x2{xs[2], xs[3]};
+                    } else {
+                        const char* xp = buf + OFF_X + 32 * jp * RBA + (xo ^ (32 * ct));
+                        x0 = lds_read_tr(xp); x1 = lds_read_tr(xp + 16 * RBA);
+                    }
+                    mma_bf16(u, ld16(tp_s + tri_pair(wave, jp) * 1024 + lane * 16), x0, x1);
                 }
             }
-            *reinterpret_cast<u32x2*>(lds + (sl & 1) * SLAB + OFF_U + (uo ^ (32 * ct))) = quad_transpose4x4(to_quad(u), q_lo, psel);
+            *reinterpret_cast<u32x2*>(lds + (sl & 1) * SLAB + OFF_U + ct * 2048 + (wave >> 1) * 1024 + 8 * (wave & 1) + swl) = to_quad(u);
         }
-        // Y_i . X_i and <dS', S>: plain 16-byte pieces, the swizzle is the same for both tiles of a pair
-        {
-            const u32x4 y = ld16(buf + OFF_Y + tid * 16), x = ld16(buf + OFF_X + tid * 16);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) yx = dot2_bf16(y[m], x[m], yx);
+        u32x2 y0, y1;
+        {   // Y_i . X_i
+            u32x2 x0, x1;
+            if (full) { rowslot(buf + OFF_Y, wave, oT, y0, y1); rowslot(buf + OFF_X, wave, oTx, x0, x1); }
+            else      { aslot(buf + OFF_Y, wave, y0, y1); aslot(buf + OFF_X, wave, x0, x1); }
+            mma_bf16(YX, y0, y1, x0, x1);
+        }
+        {   // <dS', S>: plain 16-byte pieces, the swizzle is the same for both tiles
 #pragma unroll
             for (int pc = 0; pc < TS / 16 / 256; ++pc) {
                 const int o = (tid + 256 * pc) * 16;
@@ -633,10 +604,9 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
             }
         }
         __syncthreads();                             // every wave's rows of U are in the slab
-        u32x2 do0, do1, u0, u1, y0, y1;
+        u32x2 do0, do1, u0, u1;
         aslot(buf + OFF_DO, wave, do0, do1);
-        aslot(buf + OFF_U, wave, u0, u1);
-        aslot(buf + OFF_Y, wave, y0, y1);
+        rowslot(buf + OFF_U, wave, oT, u0, u1);
 #pragma unroll
         for (int ct = 0; ct < KB; ++ct) {
             u32x2 s0, s1, d0, d1;
@@ -649,7 +619,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         static_for<4>([&](auto jt) {
             if (jt <= wave) {                              // lower-triangular tiles only
                 u32x2 b0, b1;
-                aslot(buf + OFF_U, jt, b0, b1);
+                rowslot(buf + OFF_U, jt, oT, b0, b1);
                 mma_bf16(dP[jt], do0, do1, b0, b1);        // dO U^T
                 mma_bf16(N1[jt], y0, y1, b0, b1);          // Y U^T
             }
@@ -669,8 +639,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
 #pragma unroll
         for (int ct = 0; ct < KB; ++ct) { dQ[ct] = dQ[ct] * egq; dKr[ct] = dKr[ct] * ngb; dKw[ct] = dKw[ct] * edv; }
     }
-    yx += __shfl_xor(yx, 1, kWave); yx += __shfl_xor(yx, 2, kWave);      // the 4 threads of a row are neighbours
-    if ((tid & 3) == 0) yx_s[tid >> 2] = yx;
+    if ((r >> 2) == g) yx_s[16 * wave + r] = (r & 2) ? ((r & 1) ? YX[3] : YX[2]) : ((r & 1) ? YX[1] : YX[0]);
     sdot = wave_sum(sdot);
     if (lane == 0) red_s[wave] = sdot;
     wait_vmcnt<0>();                                 // this wave's part of K and Q
@@ -844,9 +813,9 @@ static hipError_t launch_sweep_dk(const BwdArgs<bf16_t>& a, int waves, hipStream
     const int n_chains = (a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N)) * a.H;
     if (n_chains == 0) return hipSuccess;
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
-    if (waves == 1) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 1, REV>), grid, dim3(192), 0, st, a);
-    else if (waves == 2) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 2, REV>), grid, dim3(256), 0, st, a);
-    else            hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 4, REV>), grid, dim3(384), 0, st, a);
+    if (waves == 1) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 1, REV>), grid, dim3(128 + (REV ? 64 : 0)), 0, st, a);
+    else if (waves == 2) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 2, REV>), grid, dim3(192 + (REV ? 64 : 0)), 0, st, a);
+    else            hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 4, REV>), grid, dim3(320 + (REV ? 64 : 0)), 0, st, a);
     return hipGetLastError();
 }
 

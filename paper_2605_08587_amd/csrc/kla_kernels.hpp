@@ -117,8 +117,9 @@ hipError_t launch_segment_gather(const float* seg_grad, float* dh0, int N, int H
 // forward and leaves, per chunk, the incoming state S_c and the rows X = V - D_gamma K S_c and U = T' X of eq. (6).
 // Stage 3 walks backward and leaves the gradient dS'_c of the state each chunk hands on and Y = M^T dU, and writes
 // dv = B Y and dh0.  Stage 4 contracts those over d_v per chunk-head and writes dq, dk, dlog_alpha, deta.
-// X, U, Y are laid out like v.  The state checkpoints are stored transposed and in the element type:
-// [chunk-head][d_v][d_k], because stage 4 uses them only as MFMA operands contracted over d_v.
+// fp32 and the plain bf16 kernels: X, U, Y are laid out like v, the checkpoints are transposed, [chunk-head][d_v][d_k], in the
+// element type, because stage 4 uses them only as MFMA operands contracted over d_v.  The bf16 kernels keep no U, and X, Y and the
+// checkpoints in the same bytes but in operand order (put_rows, put_checkpoint in kla_bf16_ops.hpp).
 template <typename E> struct BwdArgs {
     const E* q; const E* k; const E* v;
     const float* log_alpha; const float* eta; float eps;
