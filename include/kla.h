@@ -249,6 +249,40 @@ int kla_chunk_bwd_opts(const void *q, const void *k, const void *v,
                        void *workspace, size_t workspace_bytes, void *hip_stream, unsigned opts);
 
 /*
+ * A training step calls both directions on the same inputs, and the backward begins by recomputing what the forward had in
+ * its hands: the per-chunk operands, the incoming state of every chunk, the right-hand sides X of eq. (6).  This pair passes them
+ * on instead.  kla_chunk_fwd_save is kla_chunk_fwd_opts (same outputs, bit for bit, same workspace) and also fills `saved`;
+ * kla_chunk_bwd_saved is kla_chunk_bwd_opts (same gradients, bit for bit) from the unchanged inputs of that forward and `saved`,
+ * which it only reads.
+ *   saved            device memory, 256-byte aligned, of at least kla_chunk_saved_bytes(...) bytes: about
+ *                    (dk * dv / 64 + dv + 154) * sizeof(dt) bytes per token and head (fp32: one dv more).  0: this call
+ *                    cannot leave its intermediates (shapes whose forward runs as one kernel or in segments, batches without a
+ *                    token, more than KLA_SAVED_MAX_BYTES, the plain kernels); the pair then returns KLA_ERR_SHAPE.
+ *   workspace        of kla_chunk_bwd_saved: kla_chunk_bwd_saved_workspace_bytes(...)
+ * The size arguments and opts have to be those of the forward.
+ */
+#define KLA_SAVED_MAX_BYTES (1024u << 20)
+size_t kla_chunk_saved_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,
+                             const int32_t *cu_seqlens_host, int n_seq, unsigned opts);
+size_t kla_chunk_bwd_saved_workspace_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,
+                                           const int32_t *cu_seqlens_host, int n_seq, unsigned opts);
+int kla_chunk_fwd_save(const void *q, const void *k, const void *v,
+                       const float *log_alpha, const float *eta, float eps,
+                       const float *h0, void *o, float *hT,
+                       const int32_t *cu_seqlens_dev, const int32_t *cu_seqlens_host, int n_seq,
+                       int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,
+                       void *workspace, size_t workspace_bytes, void *saved, size_t saved_bytes,
+                       void *hip_stream, unsigned opts);
+int kla_chunk_bwd_saved(const void *q, const void *k, const void *v,
+                        const float *log_alpha, const float *eta, float eps,
+                        const float *h0, const void *d_o, const float *d_hT,
+                        void *dq, void *dk_, void *dv_, float *dlog_alpha, float *deta, float *dh0,
+                        const int32_t *cu_seqlens_dev, const int32_t *cu_seqlens_host, int n_seq,
+                        int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,
+                        void *workspace, size_t workspace_bytes, const void *saved, size_t saved_bytes,
+                        void *hip_stream, unsigned opts);
+
+/*
  * Diagonal gating (App. B, "Extension to diagonal gating"; App. A, decay-agnostic remark): the decay operator is
  * D_t = diag(alpha_t) with one decay per key channel, S~ = diag(alpha_t) S_{t-1} (row i of the d_k x d_v state is
  * scaled by alpha_t[i]); the residual, the Kaczmarz coefficient of eq. (3), the write and the read-out are unchanged.

@@ -59,6 +59,13 @@ _SIGNATURES = {
     "kla_chunk_bwd_opts": (ctypes.c_int, [_vp, _vp, _vp, _fp, _fp, ctypes.c_float, _fp, _vp, _fp, _vp, _vp, _vp, _fp, _fp, _fp,
                                           _ip, _ip, ctypes.c_int] + [ctypes.c_int] * 6
                            + [ctypes.c_int, _vp, ctypes.c_size_t, _vp, ctypes.c_uint]),
+    "kla_chunk_saved_bytes": (ctypes.c_size_t, [ctypes.c_int] * 6 + [ctypes.c_int, _ip, ctypes.c_int, ctypes.c_uint]),
+    "kla_chunk_bwd_saved_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int] * 6 + [ctypes.c_int, _ip, ctypes.c_int, ctypes.c_uint]),
+    "kla_chunk_fwd_save": (ctypes.c_int, [_vp, _vp, _vp, _fp, _fp, ctypes.c_float, _fp, _vp, _fp, _ip, _ip, ctypes.c_int]
+                           + [ctypes.c_int] * 6 + [ctypes.c_int, _vp, ctypes.c_size_t, _vp, ctypes.c_size_t, _vp, ctypes.c_uint]),
+    "kla_chunk_bwd_saved": (ctypes.c_int, [_vp, _vp, _vp, _fp, _fp, ctypes.c_float, _fp, _vp, _fp, _vp, _vp, _vp, _fp, _fp, _fp,
+                                           _ip, _ip, ctypes.c_int] + [ctypes.c_int] * 6
+                            + [ctypes.c_int, _vp, ctypes.c_size_t, _vp, ctypes.c_size_t, _vp, ctypes.c_uint]),
     "kla_debug_chunk_stage": (ctypes.c_int, [_vp, _vp, _vp, _fp, _fp, ctypes.c_float, _fp, _vp, _fp, _ip, _ip, ctypes.c_int]
                               + [ctypes.c_int] * 6 + [ctypes.c_int, _vp, ctypes.c_size_t, _vp, ctypes.c_int]),
     "kla_decode_step": (ctypes.c_int, [_vp, _vp, _vp, _fp, _fp, ctypes.c_float, _fp, _vp]
@@ -83,7 +90,7 @@ class _StepByStep:
     @staticmethod
     def decode(*args):
         return None
-    chunk_fwd = chunk_bwd = decode
+    chunk_fwd = chunk_fwd_save = chunk_bwd = decode
 
 
 def _load_native(l):
@@ -103,7 +110,8 @@ def _load_native(l):
     m.bind(*(ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in (
         "kla_decode_step_opts", "kla_decode_step_diag_opts", "kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_fwd_opts",
         "kla_chunk_fwd_diag_workspace_bytes", "kla_chunk_fwd_diag_opts", "kla_chunk_bwd_workspace_bytes_opts",
-        "kla_chunk_bwd_opts")))
+        "kla_chunk_bwd_opts", "kla_chunk_saved_bytes", "kla_chunk_fwd_save", "kla_chunk_bwd_saved_workspace_bytes",
+        "kla_chunk_bwd_saved")))
     return m
 
 
@@ -261,7 +269,7 @@ def _fast_fwd(diag, q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_hos
 
 def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_hT=True, workspace=None,
                   out=None, hT=None, chunk=64, _stage=None, normalize_q=False, gdn_beta=False, cu_seqlens_host=None,
-                  tune=None):
+                  tune=None, _saved=None):
     """Chunkwise forward.  q,k [N,T,H,dk], v [N,T,H,dv], gates [N,T,H] fp32; returns (o, hT).
 
     cu_seqlens: int32 device tensor [n_seq+1] for a packed batch (then N == 1); cu_seqlens_host: the same offsets
@@ -270,7 +278,7 @@ def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_h
     normalize_q: o_t = S_t^T q_t / ||q_t||;  gdn_beta: beta_t = eta_t (kla_chunk_fwd_opts of the C ABI).
     tune: tuning fields (see tune()); None = DEFAULT_TUNE.
     """
-    if _stage is None:
+    if _stage is None and _saved is None:
         r = _fast_fwd(False, q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, want_hT, workspace, out, hT, chunk,
                       _opts(normalize_q, gdn_beta) | _tune(tune))
         if r is not None:
@@ -299,6 +307,8 @@ def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_h
             _ptr(workspace), _ws_bytes(workspace), _stream())
     if _stage is not None:
         rc = lib().kla_debug_chunk_stage(*args, int(_stage))
+    elif _saved is not None:                             # of kla_chunk (_fwd_save): filled for kla_chunk_bwd
+        rc = lib().kla_chunk_fwd_save(*args[:-1], _ptr(_saved), _ws_bytes(_saved), args[-1], bits)
     elif bits:
         rc = lib().kla_chunk_fwd_opts(*args, bits)
     else:
@@ -391,18 +401,20 @@ def kla_chunk_bwd_workspace_bytes(N, T, H, dk, dv, dtype, cu_seqlens=None, chunk
 
 
 def kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=None, d_hT=None, cu_seqlens=None, want_dh0=True,
-                  workspace=None, out=None, chunk=64, gdn_beta=False, normalize_q=False, cu_seqlens_host=None, tune=None):
+                  workspace=None, out=None, chunk=64, gdn_beta=False, normalize_q=False, cu_seqlens_host=None, tune=None,
+                  _saved=None):
     """Backward of kla_chunk_fwd: gradients of sum <d_o, o> + sum <d_hT, hT>.  gdn_beta, normalize_q: of the forward
     with the same options (kla_chunk_bwd_opts of the C ABI).
 
     d_o [N,T,H,dv] in the dtype of q; d_hT [n_states,H,dk,dv] fp32 or None (zeros).
     Returns a dict: dq, dk, dv (dtype of q), dlog_alpha, deta (fp32 [N,T,H]), dh0 (fp32, or None).
     `out` may hold preallocated tensors under the same names; `workspace` a uint8 buffer.
+    _saved: what kla_chunk's forward left behind for these inputs (kla_chunk_bwd_saved of the C ABI).
     """
     if not out and workspace is None:
         host = _host_cu(cu_seqlens)[0] if cu_seqlens is not None and cu_seqlens_host is None else cu_seqlens_host
         r = _binding().chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else host, d_o, d_hT,
-                                 bool(want_dh0), chunk, _opts(normalize_q, gdn_beta) | _tune(tune))
+                                 bool(want_dh0), chunk, _opts(normalize_q, gdn_beta) | _tune(tune), _saved)
         if r is not None:
             if type(r) is int:
                 raise KlaError(r, "kla_chunk_bwd")
@@ -421,7 +433,8 @@ def kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=None, d_hT=None, cu_seql
     dt = _dt(q)
     bits = _opts(normalize_q, gdn_beta) | _tune(tune)
     if workspace is None:
-        need = int(lib().kla_chunk_bwd_workspace_bytes_opts(N, T, H, dk, dv, chunk, dt, cu_hp, n_seq, bits & ~3))
+        bytes_of = lib().kla_chunk_bwd_workspace_bytes_opts if _saved is None else lib().kla_chunk_bwd_saved_workspace_bytes
+        need = int(bytes_of(N, T, H, dk, dv, chunk, dt, cu_hp, n_seq, bits & ~3))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     for name, like in (("dq", q), ("dk", k), ("dv", v)):
         if name not in out:
@@ -434,8 +447,11 @@ def kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=None, d_hT=None, cu_seql
     args = (_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(eta), float(eps), _ptr(h0), _ptr(d_o),
             _ptr(d_hT), _ptr(out["dq"]), _ptr(out["dk"]), _ptr(out["dv"]), _ptr(out["dlog_alpha"]),
             _ptr(out["deta"]), _ptr(out["dh0"]), _ptr(cu_seqlens), cu_hp, n_seq, N, T, H, dk, dv, chunk,
-            dt, _ptr(workspace), _ws_bytes(workspace), _stream())
-    rc = lib().kla_chunk_bwd_opts(*args, bits) if bits else lib().kla_chunk_bwd(*args)
+            dt, _ptr(workspace), _ws_bytes(workspace))
+    if _saved is not None:
+        rc = lib().kla_chunk_bwd_saved(*args, _ptr(_saved), _ws_bytes(_saved), _stream(), bits)
+    else:
+        rc = lib().kla_chunk_bwd_opts(*args, _stream(), bits) if bits else lib().kla_chunk_bwd(*args, _stream())
     if rc != 0:
         raise KlaError(rc, "kla_chunk_bwd")
     return out
@@ -528,31 +544,65 @@ def kla_debug_peak_probe(kind, buf=None, aux=None, n=0, iters=0):
         raise KlaError(rc, "kla_debug_peak_probe")
 
 
+def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta):
+    """kla_chunk_fwd that also leaves behind what kla_chunk_bwd would recompute: (o, hT, saved), saved None where the library
+    leaves nothing behind or the memory for it is not there."""
+    if cu_seqlens is not None and cu_seqlens_host is None:
+        cu_seqlens_host = _host_cu(cu_seqlens)[0]
+    bits = _opts(normalize_q, gdn_beta) | DEFAULT_TUNE
+    r = _binding().chunk_fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else cu_seqlens_host, bits)
+    if type(r) is int:
+        raise KlaError(r, "kla_chunk_fwd")
+    if r is not None:
+        return r
+    saved = None
+    if q.is_cuda and q.dim() == 4 and v.dim() == 4 and q.dtype in (torch.bfloat16, torch.float32):
+        cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
+        sizes = (*q.shape, v.shape[-1], 64, _dt(q), cu_hp, n_seq)
+        keep = int(lib().kla_chunk_saved_bytes(*sizes, bits)) if max(sizes[:5]) < 2 ** 31 else 0
+        if keep:
+            try:
+                saved = torch.empty(keep, dtype=torch.uint8, device=q.device)
+            except torch.OutOfMemoryError:
+                pass
+    o, hT = kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
+                          normalize_q=normalize_q, gdn_beta=gdn_beta, _saved=saved)
+    return o, hT, saved
+
+
 class _KlaChunk(torch.autograd.Function):
     """kla_chunk_fwd / kla_chunk_bwd as one differentiable call (marshalling only: every step runs in the library)."""
 
     @staticmethod
-    def forward(ctx, q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta):
-        o, hT = kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
-                              normalize_q=normalize_q, gdn_beta=gdn_beta)
-        ctx.save_for_backward(q, k, v, log_alpha, eta, h0)
+    def forward(ctx, q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, save):
+        if save and any(ctx.needs_input_grad[:6]):
+            o, hT, saved = _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta)
+        else:
+            o, hT = kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
+                                  normalize_q=normalize_q, gdn_beta=gdn_beta)
+            saved = None
+        ctx.save_for_backward(q, k, v, log_alpha, eta, h0, saved)
         ctx.set_materialize_grads(False)     # the library takes a missing d_hT for zeros: no buffer of them is filled and read
-        ctx.misc = (eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta)
+        ctx.misc = (eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, DEFAULT_TUNE)     # saved follows from the tuning fields too
         return o, hT
 
     @staticmethod
     def backward(ctx, d_o, d_hT):
-        q, k, v, log_alpha, eta, h0 = ctx.saved_tensors
-        eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta = ctx.misc
+        q, k, v, log_alpha, eta, h0, saved = ctx.saved_tensors
+        eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, tune_bits = ctx.misc
         d_o = q.new_zeros(v.shape) if d_o is None else d_o.contiguous()
         g = kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=h0, d_hT=None if d_hT is None else d_hT.contiguous(),
                           cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
-                          want_dh0=h0 is not None and ctx.needs_input_grad[5], normalize_q=normalize_q, gdn_beta=gdn_beta)
-        return (g["dq"], g["dk"], g["dv"], g["dlog_alpha"], g["deta"], g["dh0"], None, None, None, None, None)
+                          want_dh0=h0 is not None and ctx.needs_input_grad[5], normalize_q=normalize_q, gdn_beta=gdn_beta,
+                          tune=None if saved is None else tune_bits, _saved=saved)
+        return (g["dq"], g["dk"], g["dv"], g["dlog_alpha"], g["deta"], g["dh0"], None, None, None, None, None, None)
 
 
 def kla_chunk(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, cu_seqlens_host=None, normalize_q=False,
               gdn_beta=False):
     """Differentiable chunkwise forward for training loops: returns (o, hT) like kla_chunk_fwd; gradients with respect to
-    q, k, v, log_alpha, eta and h0 come from kla_chunk_bwd (the forward is recomputed there, nothing else is saved)."""
-    return _KlaChunk.apply(q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta)
+    q, k, v, log_alpha, eta and h0 come from kla_chunk_bwd.  Where a gradient is wanted, the forward leaves the per-chunk
+    operands and states behind for it (kla_chunk_fwd_save of the C ABI: at d_k = d_v = 128 about 1.1 KB per token and head in
+    bf16, at most KLA_SAVED_MAX_BYTES per call), elsewhere, and where that memory is not there, the backward recomputes
+    them: same bits either way."""
+    return _KlaChunk.apply(q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, torch.is_grad_enabled())

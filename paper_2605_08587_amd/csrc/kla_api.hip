@@ -58,6 +58,7 @@ struct Plan {
     int seg_G, seg_Lc;   // segment-parallel scan: segments per sequence (1 = off) and chunks per segment
     int waves;           // compute waves per scan workgroup (of the unsegmented scan)
     bool fused;          // bf16 only: one kernel, no intra-chunk stage, nothing in the workspace
+    int fwd_seg_G;       // make_bwd_plan only: the forward's segments (seg_G are the backward's there)
     Tune tune;
 };
 
@@ -240,12 +241,12 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
         [[maybe_unused]] bool done = false;
         if constexpr (sizeof(E) == 2) {
             if (!pl.tune.generic_intra) {                // else the plain kernel (A/B testing)
-                if (kla::launch_intra_bf16(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+                if (kla::launch_intra_bf16(ia, dk, kla::kIntraFwd, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
                 done = true;
             }
         }
         if constexpr (sizeof(E) == 4) {
-            if (kla::launch_intra_f32(ia, dk, false, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+            if (kla::launch_intra_f32(ia, dk, kla::kIntraFwd, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
         } else {
             if (!done && kla::launch_intra(ia, dk, (int)pl.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
         }
@@ -288,7 +289,11 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
 // ---- backward pass ---------------------------------------------------------------------------------
 struct BwdPlan {
     Plan base;
-    size_t off_rec, off_C, off_S, off_dS, off_X, off_U, off_Y, total;
+    // The first `saved` bytes of the workspace hold what follows from the inputs of the forward alone; a forward that leaves
+    // them behind (kla_chunk_fwd_save) spares the backward its first two kernels.  Offsets from off_dS on count from there.
+    size_t off_rec, off_C, off_S, off_X, off_U, saved;
+    size_t off_dS, off_Y, total;             // total: of both parts
+    bool can_save;
     // segment-parallel sweeps (base.seg_G > 1): maps of the segments, states entering them, and for the reverse
     // direction the state gradients leaving them and what each segment's pre-pass returns; all fp32
     size_t off_maps, off_segS, off_segG, off_segB;
@@ -299,6 +304,7 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
 {
     const int rc = make_plan(N, T, H, dk, dv, chunk, dt, cu_host, n_seq, opts, &p->base);
     if (rc != KLA_OK) return rc;
+    p->base.fwd_seg_G = p->base.seg_G;
     p->base.seg_G = plan_segments(N, (T + 63) / 64, H, dv, dt, n_seq, p->base.tune, 512, &p->base.seg_Lc);
     const size_t half = (size_t)384 * 8 * elem_bytes(dt);
     const size_t ch = (size_t)p->base.n_chunks * H;
@@ -307,12 +313,13 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     p->off_rec = 0;                                              // [T' | M^T | P^T | five vectors] per chunk-head
     p->off_C = round256(ch * (3 * half + 1280));
     p->off_S = round256(p->off_C + (size_t)(n_seq + 1 + order_ints(n_seq)) * sizeof(int32_t));
-    p->off_dS = round256(p->off_S + states);
+    p->off_X = round256(p->off_S + states);
     // the bf16 kernels do not keep U (their assembly forms it again from T' and X); the generic ones do
     const size_t rows_u = (dt == KLA_BF16 && !p->base.tune.generic_bwd) ? 0 : rows;
-    p->off_X = round256(p->off_dS + states);
     p->off_U = round256(p->off_X + rows);
-    p->off_Y = round256(p->off_U + rows_u);
+    p->saved = round256(p->off_U + rows_u);
+    p->off_dS = 0;
+    p->off_Y = round256(p->off_dS + states);
     const int G = p->base.seg_G;
     const size_t maps = G > 1 ? (size_t)N * (G - 1) * H * dk * (dv + dk) * sizeof(float) : 0;
     const size_t segst = G > 1 ? (size_t)N * G * H * dk * dv * sizeof(float) : 0;
@@ -320,7 +327,13 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     p->off_segS = round256(p->off_maps + maps);
     p->off_segG = round256(p->off_segS + segst);
     p->off_segB = round256(p->off_segG + segst);
-    p->total = round256(p->off_segB + segst);
+    p->total = p->saved + round256(p->off_segB + segst);
+    // A forward leaves its intermediates where it forms the very ones the backward would: not in one kernel (which rounds other
+    // things), not in segments (whose number differs), not through the plain kernels.  And within a bound: what is kept lives
+    // until the backward, in every layer of a model.
+    const Tune& t = p->base.tune;
+    p->can_save = p->base.n_chunks > 0 && !p->base.fused && p->base.fwd_seg_G <= 1 && G <= 1 && !t.generic_scan && !t.generic_intra &&
+                  !t.generic_bwd && p->saved <= (size_t)KLA_SAVED_MAX_BYTES;
     return KLA_OK;
 }
 
@@ -328,12 +341,13 @@ template <typename E>
 int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
                    const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
                    float* dlog_alpha, float* deta, float* dh0, const int32_t* cu_dev, int n_seq, int N, int T, int H,
-                   int dk, int dv, const BwdPlan& pl, char* ws, hipStream_t st, unsigned opts)
+                   int dk, int dv, const BwdPlan& pl, char* sv, char* ws, bool have, hipStream_t st, unsigned opts)
 {
-    int* chunk_off = reinterpret_cast<int*>(ws + pl.off_C);
+    // sv: what the forward leaves behind (have: it has; else it is made here); ws: the rest of the workspace
+    int* chunk_off = reinterpret_cast<int*>(sv + pl.off_C);
     const int NT = (T + 63) / 64;
     const bool placed = intra_places(n_seq, pl.base.n_chunks, sizeof(E) == 2 && pl.base.tune.generic_bwd);
-    if (n_seq > 0 && !placed && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
+    if (n_seq > 0 && !placed && !have && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
 
     kla::IntraArgs<E> ia;
     if (placed) ia.pos_out = chunk_off;
@@ -341,14 +355,14 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     ia.log_alpha = log_alpha; ia.eta = eta; ia.eps = eps;
     ia.cu_seqlens = n_seq > 0 ? cu_dev : nullptr; ia.chunk_off = chunk_off; ia.n_seq = n_seq;
     ia.T = T; ia.NT = NT; ia.H = H;
-    ia.wsT = reinterpret_cast<E*>(ws + pl.off_rec); ia.wsP = nullptr; ia.wsG = nullptr; ia.opts = opts;
+    ia.wsT = reinterpret_cast<E*>(sv + pl.off_rec); ia.wsP = nullptr; ia.wsG = nullptr; ia.opts = opts;
     bool fast = false;                                // bf16: the specialised kernels, unless the generic ones are asked for (A/B testing)
     if constexpr (sizeof(E) == 2) fast = !pl.base.tune.generic_bwd;
     if constexpr (sizeof(E) == 2) {
-        if (fast && kla::launch_intra_bwd_bf16(ia, dk, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+        if (fast && !have && kla::launch_intra_bf16(ia, dk, kla::kIntraBwd, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4) {
-        if (kla::launch_intra_f32(ia, dk, true, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
+        if (!have && kla::launch_intra_f32(ia, dk, kla::kIntraBwd, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     } else {
         if (!fast && kla::launch_intra_bwd(ia, dk, (int)pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     }
@@ -362,9 +376,9 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     ba.cu_seqlens = ia.cu_seqlens; ba.chunk_off = chunk_off; ba.n_seq = n_seq;
     ba.seq_order = order_at(chunk_off, n_seq);
     ba.N = N; ba.T = T; ba.NT = NT; ba.H = H; ba.dv_dim = dv;
-    ba.rec = ws + pl.off_rec;
-    ba.s_chk = reinterpret_cast<E*>(ws + pl.off_S); ba.ds_chk = reinterpret_cast<E*>(ws + pl.off_dS);
-    ba.X = reinterpret_cast<E*>(ws + pl.off_X); ba.U = reinterpret_cast<E*>(ws + pl.off_U);
+    ba.rec = sv + pl.off_rec;
+    ba.s_chk = reinterpret_cast<E*>(sv + pl.off_S); ba.ds_chk = reinterpret_cast<E*>(ws + pl.off_dS);
+    ba.X = reinterpret_cast<E*>(sv + pl.off_X); ba.U = reinterpret_cast<E*>(sv + pl.off_U);
     ba.Y = reinterpret_cast<E*>(ws + pl.off_Y);
     ba.opts = opts;
     ba.seg_G = 0; ba.seg_Lc = 0;
@@ -384,7 +398,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             sa.q = ba.q; sa.k = ba.k; sa.v = ba.v; sa.h0 = nullptr; sa.o = nullptr; sa.hT = nullptr;
             sa.cu_seqlens = nullptr; sa.chunk_off = chunk_off; sa.n_seq = 0;
             sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
-            sa.wsT = reinterpret_cast<const E*>(ws + pl.off_rec); sa.wsP = nullptr; sa.wsG = nullptr; sa.opts = 0u;
+            sa.wsT = reinterpret_cast<const E*>(sv + pl.off_rec); sa.wsP = nullptr; sa.wsG = nullptr; sa.opts = 0u;
             sa.seg_G = G; sa.seg_Lc = pl.base.seg_Lc; sa.kt_src = nullptr; sa.gc_vec = nullptr;
             if (kla::launch_segment_maps_bwdrec_bf16(sa, dk, maps, st) != hipSuccess) return KLA_ERR_HIP;
             if (kla::launch_segment_combine(h0, maps, segS, N, H, dk, dv, G, st) != hipSuccess) return KLA_ERR_HIP;
@@ -414,14 +428,14 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             // two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347; 40 x 1000, five rounds against three: 584, 520)
             const long wg2 = chains8 * (dv / 32), r2 = (wg2 + 255) / 256, r4 = (wg2 / 2 + 255) / 256;
             const int bw = waves == 2 && r4 * 115 < r2 * 100 ? 4 : waves;
-            if (kla::launch_bwd_states_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
+            if (!have && kla::launch_bwd_states_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
             if (kla::launch_bwd_scan_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
     if constexpr (sizeof(E) == 4) {
         const int tiles = f32_tiles((long)pl.base.n_states * H * (dv / 16));
-        if (kla::launch_bwd_states_f32(ba, dk, tiles, st) != hipSuccess) return KLA_ERR_HIP;
+        if (!have && kla::launch_bwd_states_f32(ba, dk, tiles, st) != hipSuccess) return KLA_ERR_HIP;
         if (kla::launch_bwd_scan_f32(ba, dk, tiles, st) != hipSuccess) return KLA_ERR_HIP;
     } else {
         if (kla::launch_bwd_states(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
@@ -429,6 +443,44 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     }
     if (kla::launch_bwd_assemble<E>(ba, dk, pl.base.n_chunks, st) != hipSuccess) return KLA_ERR_HIP;
     return KLA_OK;
+}
+
+// The forward that leaves its intermediates (pl: its own plan, bp: the backward's, bp.can_save): stage 1 writes both kinds of
+// record at once, the scan stores every chunk's incoming state and X (and, fp32, U) on its way.
+template <typename E>
+int chunk_fwd_save_impl(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
+                        const float* h0, void* o, float* hT, const int32_t* cu_dev, int n_seq, int N, int T, int H, int dk, int dv,
+                        const Plan& pl, const BwdPlan& bp, char* ws, char* sv, hipStream_t st, unsigned opts)
+{
+    // (the records of P take half of the room the plain forward's records have in the workspace)
+    int* chunk_off = reinterpret_cast<int*>(sv + bp.off_C);
+    kla::IntraArgs<E> ia;
+    ia.q = static_cast<const E*>(q); ia.k = static_cast<const E*>(k);
+    ia.log_alpha = log_alpha; ia.eta = eta; ia.eps = eps;
+    ia.cu_seqlens = n_seq > 0 ? cu_dev : nullptr; ia.chunk_off = chunk_off; ia.n_seq = n_seq;
+    ia.T = T; ia.NT = (T + 63) / 64; ia.H = H;
+    ia.wsT = reinterpret_cast<E*>(sv + bp.off_rec); ia.wsP = reinterpret_cast<E*>(ws + pl.off_T); ia.wsG = nullptr; ia.opts = opts;
+    if (intra_places(n_seq, pl.n_chunks, false)) ia.pos_out = chunk_off;
+    else if (n_seq > 0 && kla::launch_chunk_offsets(cu_dev, n_seq, chunk_off, order_at(chunk_off, n_seq), st) != hipSuccess) return KLA_ERR_HIP;
+
+    kla::ScanArgs<E> sa;
+    sa.q = ia.q; sa.k = ia.k; sa.v = static_cast<const E*>(v);
+    sa.h0 = h0; sa.o = static_cast<E*>(o); sa.hT = hT;
+    sa.cu_seqlens = ia.cu_seqlens; sa.chunk_off = chunk_off; sa.n_seq = n_seq;
+    sa.seq_order = order_at(chunk_off, n_seq);
+    sa.N = N; sa.T = T; sa.NT = ia.NT; sa.H = H; sa.dv = dv;
+    sa.wsT = ia.wsT; sa.wsP = ia.wsP; sa.wsG = nullptr; sa.opts = opts;
+    sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = nullptr; sa.gc_vec = nullptr;
+    sa.s_chk = reinterpret_cast<E*>(sv + bp.off_S); sa.X = reinterpret_cast<E*>(sv + bp.off_X); sa.U = reinterpret_cast<E*>(sv + bp.off_U);
+    hipError_t e;
+    if constexpr (sizeof(E) == 2) {
+        e = kla::launch_intra_bf16(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
+        if (e == hipSuccess) e = kla::launch_scan_bf16(sa, dk, pl.waves, st);
+    } else {
+        e = kla::launch_intra_f32(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
+        if (e == hipSuccess) e = kla::launch_scan_f32(sa, dk, pl.waves, st);
+    }
+    return e == hipSuccess ? KLA_OK : KLA_ERR_HIP;
 }
 
 // ---- diagonal gating ----------------------------------------------------------------------------------
@@ -666,6 +718,52 @@ int kla_chunk_bwd(const void* q, const void* k, const void* v, const float* log_
                               workspace_bytes, hip_stream, 0u);
 }
 
+// Everything kla_chunk_bwd checks except its workspace; fills the plan.
+static int chunk_bwd_validate(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
+                              const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
+                              float* dlog_alpha, float* deta, float* dh0, const int32_t* cu_seqlens_dev,
+                              const int32_t* cu_seqlens_host, int n_seq, int N, int T, int H, int dk, int dv, int chunk,
+                              kla_dtype dt, unsigned opts, BwdPlan* pl)
+{
+    const int rc = make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, pl);
+    if (rc != KLA_OK) return rc;
+    if (!(eps >= 0.0f) || isinf(eps)) return KLA_ERR_SHAPE;
+    if (n_seq > 0 && !cu_seqlens_dev) return KLA_ERR_NULL;
+    if (n_seq == 0 && cu_seqlens_dev) return KLA_ERR_SHAPE;
+    const bool any_tokens = (long)N * T > 0;
+    if (any_tokens && (!q || !k || !v || !log_alpha || !eta || !d_o || !dq || !dk_ || !dv_ || !dlog_alpha || !deta))
+        return KLA_ERR_NULL;
+    return KLA_OK;
+}
+static int chunk_bwd_align(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, const float* h0,
+                           const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_, float* dlog_alpha, float* deta, float* dh0)
+{
+    if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(d_o) || !aligned16(dq) || !aligned16(dk_) ||
+        !aligned16(dv_) || !aligned16(h0) || !aligned16(d_hT) || !aligned16(dh0) ||
+        (reinterpret_cast<uintptr_t>(log_alpha) & 3u) || (reinterpret_cast<uintptr_t>(eta) & 3u) ||
+        (reinterpret_cast<uintptr_t>(dlog_alpha) & 3u) || (reinterpret_cast<uintptr_t>(deta) & 3u))
+        return KLA_ERR_ALIGN;
+    return KLA_OK;
+}
+// a buffer of the caller's: present, 256-byte aligned, large enough
+static bool buffer_ok(const void* p, size_t bytes, size_t need) { return p && (reinterpret_cast<uintptr_t>(p) & 255u) == 0 && bytes >= need; }
+
+static int chunk_bwd_launch(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
+                            const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
+                            float* dlog_alpha, float* deta, float* dh0, const int32_t* cu_seqlens_dev, int n_seq, int N, int T,
+                            int H, int dk, int dv, kla_dtype dt, const BwdPlan& pl, char* sv, char* ws, bool have, void* hip_stream,
+                            unsigned opts)
+{
+    if (pl.base.n_states == 0) return KLA_OK;
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    opts &= kOptMask;
+    if (dt == KLA_BF16)
+        return chunk_bwd_impl<bf16_t>(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0,
+                                      cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, sv, ws, have, st, opts);
+    return chunk_bwd_impl<float>(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0,
+                                 cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, sv, ws, have, st, opts);
+}
+
 int kla_chunk_bwd_opts(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
                        const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
                        float* dlog_alpha, float* deta, float* dh0, const int32_t* cu_seqlens_dev,
@@ -673,30 +771,74 @@ int kla_chunk_bwd_opts(const void* q, const void* k, const void* v, const float*
                        kla_dtype dt, void* workspace, size_t workspace_bytes, void* hip_stream, unsigned opts)
 {
     BwdPlan pl;
-    const int rc = make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &pl);
+    int rc = chunk_bwd_validate(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0, cu_seqlens_dev,
+                                cu_seqlens_host, n_seq, N, T, H, dk, dv, chunk, dt, opts, &pl);
     if (rc != KLA_OK) return rc;
-    opts &= kOptMask;
-    if (!(eps >= 0.0f) || isinf(eps)) return KLA_ERR_SHAPE;
-    if (n_seq > 0 && !cu_seqlens_dev) return KLA_ERR_NULL;
-    if (n_seq == 0 && cu_seqlens_dev) return KLA_ERR_SHAPE;
-    const bool any_tokens = (long)N * T > 0;
-    if (any_tokens && (!q || !k || !v || !log_alpha || !eta || !d_o || !dq || !dk_ || !dv_ || !dlog_alpha || !deta))
-        return KLA_ERR_NULL;
-    if (!workspace) return KLA_ERR_WORKSPACE;
-    if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < pl.total) return KLA_ERR_WORKSPACE;
-    if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(d_o) || !aligned16(dq) || !aligned16(dk_) ||
-        !aligned16(dv_) || !aligned16(h0) || !aligned16(d_hT) || !aligned16(dh0) ||
-        (reinterpret_cast<uintptr_t>(log_alpha) & 3u) || (reinterpret_cast<uintptr_t>(eta) & 3u) ||
-        (reinterpret_cast<uintptr_t>(dlog_alpha) & 3u) || (reinterpret_cast<uintptr_t>(deta) & 3u))
-        return KLA_ERR_ALIGN;
-    if (pl.base.n_states == 0) return KLA_OK;
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (!buffer_ok(workspace, workspace_bytes, pl.total)) return KLA_ERR_WORKSPACE;
+    rc = chunk_bwd_align(q, k, v, log_alpha, eta, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0);
+    if (rc != KLA_OK) return rc;
     char* ws = static_cast<char*>(workspace);
+    return chunk_bwd_launch(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0, cu_seqlens_dev, n_seq, N,
+                            T, H, dk, dv, dt, pl, ws, ws + pl.saved, false, hip_stream, opts);
+}
+
+// ---- a forward that leaves its intermediates, and the backward that takes them ---------------------------------------
+size_t kla_chunk_saved_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt, const int32_t* cu_seqlens_host, int n_seq,
+                             unsigned opts)
+{
+    BwdPlan pl;
+    if (make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &pl) != KLA_OK) return 0;
+    return pl.can_save ? pl.saved : 0;
+}
+
+size_t kla_chunk_bwd_saved_workspace_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt, const int32_t* cu_seqlens_host,
+                                           int n_seq, unsigned opts)
+{
+    BwdPlan pl;
+    if (make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &pl) != KLA_OK) return 0;
+    return pl.can_save ? pl.total - pl.saved : 0;
+}
+
+int kla_chunk_fwd_save(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
+                       const float* h0, void* o, float* hT, const int32_t* cu_seqlens_dev, const int32_t* cu_seqlens_host,
+                       int n_seq, int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt, void* workspace,
+                       size_t workspace_bytes, void* saved, size_t saved_bytes, void* hip_stream, unsigned opts)
+{
+    Plan pl;
+    int rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N, T, H, dk, dv, chunk,
+                                dt, opts, &pl);
+    if (rc != KLA_OK) return rc;
+    BwdPlan bp;
+    rc = make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &bp);
+    if (rc != KLA_OK) return rc;
+    if (!bp.can_save) return KLA_ERR_SHAPE;
+    if (!buffer_ok(workspace, workspace_bytes, pl.total) || !buffer_ok(saved, saved_bytes, bp.saved)) return KLA_ERR_WORKSPACE;
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    char *ws = static_cast<char*>(workspace), *sv = static_cast<char*>(saved);
+    opts &= kOptMask;
     if (dt == KLA_BF16)
-        return chunk_bwd_impl<bf16_t>(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0,
-                                      cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, ws, st, opts);
-    return chunk_bwd_impl<float>(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0,
-                                 cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, ws, st, opts);
+        return chunk_fwd_save_impl<bf16_t>(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, bp, ws, sv, st, opts);
+    return chunk_fwd_save_impl<float>(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, n_seq, N, T, H, dk, dv, pl, bp, ws, sv, st, opts);
+}
+
+int kla_chunk_bwd_saved(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
+                        const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
+                        float* dlog_alpha, float* deta, float* dh0, const int32_t* cu_seqlens_dev,
+                        const int32_t* cu_seqlens_host, int n_seq, int N, int T, int H, int dk, int dv, int chunk,
+                        kla_dtype dt, void* workspace, size_t workspace_bytes, const void* saved, size_t saved_bytes,
+                        void* hip_stream, unsigned opts)
+{
+    BwdPlan pl;
+    int rc = chunk_bwd_validate(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0, cu_seqlens_dev,
+                                cu_seqlens_host, n_seq, N, T, H, dk, dv, chunk, dt, opts, &pl);
+    if (rc != KLA_OK) return rc;
+    if (!pl.can_save) return KLA_ERR_SHAPE;
+    if (!buffer_ok(workspace, workspace_bytes, pl.total - pl.saved) || !buffer_ok(saved, saved_bytes, pl.saved)) return KLA_ERR_WORKSPACE;
+    rc = chunk_bwd_align(q, k, v, log_alpha, eta, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0);
+    if (rc != KLA_OK) return rc;
+    return chunk_bwd_launch(q, k, v, log_alpha, eta, eps, h0, d_o, d_hT, dq, dk_, dv_, dlog_alpha, deta, dh0, cu_seqlens_dev, n_seq, N,
+                            T, H, dk, dv, dt, pl, const_cast<char*>(static_cast<const char*>(saved)), static_cast<char*>(workspace), true,
+                            hip_stream, opts);
 }
 
 size_t kla_chunk_fwd_diag_workspace_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,

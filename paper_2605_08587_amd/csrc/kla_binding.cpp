@@ -31,6 +31,10 @@ struct Api {
     decltype(&kla_chunk_fwd_diag_opts) fwd_diag;
     decltype(&kla_chunk_bwd_workspace_bytes_opts) bwd_bytes;
     decltype(&kla_chunk_bwd_opts) bwd;
+    decltype(&kla_chunk_saved_bytes) saved_bytes;
+    decltype(&kla_chunk_fwd_save) fwd_save;
+    decltype(&kla_chunk_bwd_saved_workspace_bytes) bwd_saved_bytes;
+    decltype(&kla_chunk_bwd_saved) bwd_saved;
 } api = {};
 
 // A plain, dense tensor: torch.Tensor or Parameter itself, strided and contiguous, with memory of its own.  (What
@@ -145,9 +149,9 @@ struct Chunk {
 
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
-    if (n != 8) { PyErr_SetString(PyExc_TypeError, "bind takes eight addresses"); return nullptr; }
-    void* p[8];
-    for (int i = 0; i < 8; ++i) {
+    if (n != 12) { PyErr_SetString(PyExc_TypeError, "bind takes twelve addresses"); return nullptr; }
+    void* p[12];
+    for (int i = 0; i < 12; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (!p[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address"); return nullptr; }
     }
@@ -159,6 +163,10 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
     api.fwd_diag = reinterpret_cast<decltype(api.fwd_diag)>(p[5]);
     api.bwd_bytes = reinterpret_cast<decltype(api.bwd_bytes)>(p[6]);
     api.bwd = reinterpret_cast<decltype(api.bwd)>(p[7]);
+    api.saved_bytes = reinterpret_cast<decltype(api.saved_bytes)>(p[8]);
+    api.fwd_save = reinterpret_cast<decltype(api.fwd_save)>(p[9]);
+    api.bwd_saved_bytes = reinterpret_cast<decltype(api.bwd_saved_bytes)>(p[10]);
+    api.bwd_saved = reinterpret_cast<decltype(api.bwd_saved)>(p[11]);
     Py_RETURN_NONE;
 }
 
@@ -238,24 +246,69 @@ PyObject* chunk_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, d_o, d_hT, want_dh0, chunk, opts)
-// -> (dq, dk, dv, dlog_alpha, deta, dh0), all of them new
+// The forward of a training step: chunk_fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, opts)
+// -> (out, hT, saved); saved is None where the library leaves nothing behind for the backward, or where there is no memory for it
+// (the backward then recomputes it)
+PyObject* chunk_fwd_save(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 10 || !api.fwd_save) Py_RETURN_NONE;
+    Chunk c;
+    long opts;
+    if (!c.take(a, false) || !integer(a[9], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
+    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk = (int)c.dk, dv = (int)c.dv, chunk = 64;
+    std::optional<at::Tensor> out, hT, saved;
+    int rc;
+    {
+        const NoGil no_gil;
+        const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
+        const size_t keep = api.saved_bytes(N, T, H, dk, dv, chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts);
+        const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
+        out = c.empty({c.N, c.T, c.H, c.dv}, c.type);
+        hT = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
+        if (keep) {
+            try { saved = c.empty({(int64_t)keep}, at::kByte); } catch (const c10::OutOfMemoryError&) {}
+        }
+        const int32_t* cu = static_cast<const int32_t*>(ptr(c.cu));
+        float* h = static_cast<float*>(hT->data_ptr());
+        if (saved)
+            rc = api.fwd_save(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), out->data_ptr(), h, cu,
+                              c.cu_host, c.n_seq, N, T, H, dk, dv, chunk, c.dt, ws.data_ptr(), ws.nbytes(), saved->data_ptr(), keep, stream(),
+                              (unsigned)opts);
+        else
+            rc = api.fwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), out->data_ptr(), h, cu, c.cu_host,
+                         c.n_seq, N, T, H, dk, dv, chunk, c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+    }
+    if (rc != KLA_OK) return PyLong_FromLong(rc);
+    PyObject* r = PyTuple_New(3);
+    if (!r) return nullptr;
+    PyTuple_SET_ITEM(r, 0, wrap(out));
+    PyTuple_SET_ITEM(r, 1, wrap(hT));
+    PyTuple_SET_ITEM(r, 2, wrap(saved));
+    return r;
+    END_HANDLE_TH_ERRORS
+}
+
+// chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, d_o, d_hT, want_dh0, chunk, opts, saved)
+// -> (dq, dk, dv, dlog_alpha, deta, dh0), all of them new; saved: of chunk_fwd_save with the same arguments, or None
 PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 14 || !api.bwd) Py_RETURN_NONE;
+    if (n != 15 || !api.bwd) Py_RETURN_NONE;
     const bool want_dh0 = a[11] == Py_True;
     Chunk c;
     long chunk, opts;
     if (!c.take(a, false) || !integer(a[12], INT_MIN, INT_MAX, &chunk) || !integer(a[13], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
     const at::Tensor *d_o = gpu(a[9], c.type, {c.N, c.T, c.H, c.dv}), *d_hT = nullptr;
     if (!d_o || !gpu_or_none(a[10], at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &d_hT)) Py_RETURN_NONE;
+    const at::Tensor* saved = nullptr;
+    if (a[14] != Py_None && !(saved = on_gpu(a[14]))) Py_RETURN_NONE;
     const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk_ = (int)c.dk, dv_ = (int)c.dv;
     std::optional<at::Tensor> dq, dk, dv, dla, deta, dh0;
     int rc;
     {
         const NoGil no_gil;
-        const size_t need = api.bwd_bytes(N, T, H, dk_, dv_, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
+        const size_t need = (saved ? api.bwd_saved_bytes : api.bwd_bytes)(N, T, H, dk_, dv_, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
         const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
         dq = c.empty(c.q->sizes(), c.type);
         dk = c.empty(c.q->sizes(), c.type);
@@ -263,10 +316,17 @@ PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
         dla = c.empty({c.N, c.T, c.H}, at::kFloat);
         deta = c.empty({c.N, c.T, c.H}, at::kFloat);
         if (want_dh0) dh0 = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
-        rc = api.bwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT), dq->data_ptr(),
-                     dk->data_ptr(), dv->data_ptr(), static_cast<float*>(dla->data_ptr()), static_cast<float*>(deta->data_ptr()),
-                     dh0 ? static_cast<float*>(dh0->data_ptr()) : nullptr, static_cast<const int32_t*>(ptr(c.cu)), c.cu_host, c.n_seq, N, T,
-                     H, dk_, dv_, (int)chunk, c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+        float *g_la = static_cast<float*>(dla->data_ptr()), *g_eta = static_cast<float*>(deta->data_ptr());
+        float* g_h0 = dh0 ? static_cast<float*>(dh0->data_ptr()) : nullptr;
+        const int32_t* cu = static_cast<const int32_t*>(ptr(c.cu));
+        if (saved)
+            rc = api.bwd_saved(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT),
+                               dq->data_ptr(), dk->data_ptr(), dv->data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk_, dv_,
+                               (int)chunk, c.dt, ws.data_ptr(), ws.nbytes(), ptr(saved), saved->nbytes(), stream(), (unsigned)opts);
+        else
+            rc = api.bwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT), dq->data_ptr(),
+                         dk->data_ptr(), dv->data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk_, dv_, (int)chunk, c.dt,
+                         ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
     }
     if (rc != KLA_OK) return PyLong_FromLong(rc);
     PyObject* r = PyTuple_New(6);
@@ -278,7 +338,8 @@ PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 }
 
 #define KLA_FASTCALL(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {KLA_FASTCALL(bind), KLA_FASTCALL(decode), KLA_FASTCALL(chunk_fwd), KLA_FASTCALL(chunk_bwd), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {KLA_FASTCALL(bind), KLA_FASTCALL(decode), KLA_FASTCALL(chunk_fwd), KLA_FASTCALL(chunk_fwd_save),
+                         KLA_FASTCALL(chunk_bwd), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "kla_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

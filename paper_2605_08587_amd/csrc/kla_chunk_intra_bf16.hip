@@ -82,14 +82,17 @@ __device__ __forceinline__ void write_transposed(char* out, const float* m, int 
 // (M = (I + L)^{-1}; the transposes as the 6 upper-triangular tile-pairs, see kla_mma.hpp).  kOptGdnBeta: beta = eta
 // and the fourth vector, d beta / d eta, is 1; kOptNormalizeQ: P^T carries 1/||q_i|| and the fifth vector holds it
 // (1 otherwise).
-template <int DK, bool BWD>
-__global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
+// MODE (IntraMode): the forward's record, the backward's, or both but for the forward's copy of T'.  For both, Q K^T is formed twice, in
+// the orientation of P and in that of P^T: 46 us for 4096 chunk-heads of d_k = 128 where the two separate launches take 35 + 40.
+template <int DK, int MODE>
+__global__ __launch_bounds__(256, MODE == kIntraPair ? 5 : 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
 {
     constexpr int RB = DK * 2, PPR = DK / 8, KP = DK / 32;
     constexpr int RPB = 1024 / RB, NKB = 64 / RPB;           // rows per 1 KiB copy block, blocks per tile
     constexpr int TILE = 64 * RB, MB = 64 * kLd * 4;
+    constexpr bool FWD = MODE != kIntraBwd, BWD = MODE != kIntraFwd;
     constexpr int REC = BWD ? bwd_record_bytes<bf16_t>() : ws_record_bytes<bf16_t>(), HALF = ws_half_bytes<bf16_t>();
-    constexpr int VEC = (BWD ? 3 : 2) * HALF;                // offset of the fp32 vectors in the record
+    constexpr int PREC = pair_record_bytes<bf16_t>();
 
     __shared__ __attribute__((aligned(1024))) char area[TILE > MB ? TILE : MB];   // the K tile, then M
     __shared__ __attribute__((aligned(16))) float beta_s[64];
@@ -110,7 +113,10 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
     const long tok0 = cp.tok0;
     const int clen = cp.clen;
     char* rec = reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC;
-    float* vec = reinterpret_cast<float*>(rec + VEC);
+    // P and the forward's vectors: behind T', or records of their own
+    char* recp = MODE == kIntraPair ? reinterpret_cast<char*>(a.wsP) + (size_t)blockIdx.x * PREC : rec + HALF;
+    float* vec = reinterpret_cast<float*>(rec + 3 * HALF);   // the backward's five
+    float* vecf = reinterpret_cast<float*>(recp + HALF);     // the forward's three
 
     // ---- everything the workgroup reads, requested at once: K -> LDS by the copy engine, this wave's Q rows -> registers
     //      (lane (r, g): features 32 kp + 8 g .. + 7 of row 16 w + r), the gates (wave 0) ---------------------------
@@ -152,8 +158,9 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
         eta_s[lane] = et;
         if constexpr (!BWD) a.wsG[(size_t)blockIdx.x * 128 + lane] = x;
         const float gl2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x2), 63));
-        vec[lane] = __builtin_amdgcn_exp2f(x2);            // gamma_i
-        vec[64 + lane] = __builtin_amdgcn_exp2f(gl2 - x2); // gamma_C / gamma_i
+        const float gam = __builtin_amdgcn_exp2f(x2), dec = __builtin_amdgcn_exp2f(gl2 - x2);   // gamma_i, gamma_C / gamma_i
+        if constexpr (BWD) { vec[lane] = gam; vec[64 + lane] = dec; }
+        if constexpr (FWD) { vecf[lane] = gam; vecf[64 + lane] = dec; }
     }
     wait_vmcnt<0>();
     __syncthreads();
@@ -175,10 +182,8 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
     }
     if (g == 0) {
         if constexpr (BWD) vec[256 + 16 * wave + r] = rq;
-        else {
-            vec[128 + 16 * wave + r] = __builtin_amdgcn_exp2f(g_s[16 * wave + r]) * rq;
-            a.wsG[(size_t)blockIdx.x * 128 + 64 + 16 * wave + r] = rq;
-        }
+        if constexpr (FWD) vecf[128 + 16 * wave + r] = __builtin_amdgcn_exp2f(g_s[16 * wave + r]) * rq;
+        if constexpr (!BWD) a.wsG[(size_t)blockIdx.x * 128 + 64 + 16 * wave + r] = rq;
     }
 
     // ---- Gram tiles, P to the record, L to LDS, the diagonal block of the inverse.  One instance per wave: every tile
@@ -190,30 +195,36 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
         floatx4 kk[A + 1], qk[W + 1];
 #pragma unroll
         for (int t = 0; t <= A; ++t) kk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         u32x4 sl[2][NT];
         auto load = [&](int kp, u32x4 (&dst)[NT]) {
             const int c16 = ((4 * kp + g) ^ sw) * 16;
 #pragma unroll
             for (int t = 0; t < NT; ++t) dst[t] = ld16(rowp + t * 16 * RB + c16);
         };
-        load(0, sl[0]);
-        static_for<KP>([&](auto kc) {
-            constexpr int kp = kc;
-            if constexpr (kp + 1 < KP) load(kp + 1, sl[(kp + 1) & 1]);
-            static_for<NT>([&](auto tc) {
-                constexpr int t = tc;
-                const u32x4 b = sl[kp & 1][t];
-                const u32x2 b0 = {b[0], b[1]}, b1 = {b[2], b[3]};
-                if constexpr (t <= A) mma_bf16(kk[t], sl[kp & 1][A], b0, b1);         // rows: token of tile A, column: token of tile t
-                if constexpr (t <= W) {
-                    const u32x2 q0 = {qf[kp][0], qf[kp][1]}, q1 = {qf[kp][2], qf[kp][3]};
-                    if constexpr (BWD) mma_bf16(qk[t], qf[kp], b0, b1);              // rows: query of tile W, column: key of tile t
-                    else               mma_bf16(qk[t], b, q0, q1);                   // rows: key of tile t, column: query of tile W
-                }
+        // KK: the tiles of K K^T too.  TR = false: tiles of P, TR = true: of P^T
+        auto products = [&](auto kkc, auto trc) {
+            constexpr bool KK = decltype(kkc)::value != 0, TR = decltype(trc)::value != 0;
+            constexpr int N = KK ? NT : W + 1;
+#pragma unroll
+            for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            load(0, sl[0]);
+            static_for<KP>([&](auto kc) {
+                constexpr int kp = kc;
+                if constexpr (kp + 1 < KP) load(kp + 1, sl[(kp + 1) & 1]);
+                static_for<N>([&](auto tc) {
+                    constexpr int t = tc;
+                    const u32x4 b = sl[kp & 1][t];
+                    const u32x2 b0 = {b[0], b[1]}, b1 = {b[2], b[3]};
+                    if constexpr (KK && t <= A) mma_bf16(kk[t], sl[kp & 1][A], b0, b1);   // rows: token of tile A, column: token of tile t
+                    if constexpr (t <= W) {
+                        const u32x2 q0 = {qf[kp][0], qf[kp][1]}, q1 = {qf[kp][2], qf[kp][3]};
+                        if constexpr (TR) mma_bf16(qk[t], qf[kp], b0, b1);               // rows: query of tile W, column: key of tile t
+                        else              mma_bf16(qk[t], b, q0, q1);                    // rows: key of tile t, column: query of tile W
+                    }
+                });
             });
-        });
+        };
+        products(IntC<1>(), IntC<FWD ? 0 : 1>());
         // ||k_i||^2 is the diagonal of K K^T (exact bf16 products, fp32 sums): beta of eq. (3) by the lane that holds
         // element (i, i)
         if ((r >> 2) == g) {
@@ -229,10 +240,37 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
         // ---- P (or P^T): decay, mask, 1/||q||; straight into the record
         const u32x2 zq = {0u, 0u};
         u32x2 pt[W + 1];
-        static_for<W + 1>([&](auto tc) {
-            constexpr int t = tc;
-            floatx4 v;
-            if constexpr (BWD) {                         // lane: P[16 W + 4 g + e][16 t + r], the quad of row 16 t + r of P^T
+        if constexpr (FWD) {
+            static_for<W + 1>([&](auto tc) {             // lane: P[16 W + r][16 t + 4 g + e]
+                constexpr int t = tc;
+                floatx4 v;
+                const float gi = g_s[16 * W + r];
+                const floatx4 gj = ldf4(g_s + 16 * t + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float y = __builtin_amdgcn_exp2f(t == W ? fminf(gi - gj[e], 0.f) : gi - gj[e]) * qk[t][e] * rq;
+                    if (t == W) y = (4 * g + e <= r) ? y : 0.f;
+                    if (clen < 64) y = (16 * W + r < clen) ? y : 0.f;                  // rows beyond a short chunk
+                    v[e] = y;
+                }
+                pt[t] = to_quad(v);
+            });
+            char* out = recp + lane * 16;
+            static_for<W / 2 + 1>([&](auto pc) {
+                constexpr int jp = pc;
+                const u32x2 q0 = pt[2 * jp], q1 = 2 * jp + 1 <= W ? pt[2 * jp + 1 <= W ? 2 * jp + 1 : 0] : zq;
+                const u32x4 v = {q0.x, q0.y, q1.x, q1.y};
+                st16(out + tri_pair(W, jp) * 1024, v);
+            });
+        }
+        if constexpr (BWD) {
+            if constexpr (FWD) {
+                asm volatile("" ::: "memory");           // K is read again: kept from the first time, it would spill
+                products(IntC<0>(), IntC<1>());
+            }
+            static_for<W + 1>([&](auto tc) {             // lane: P[16 W + 4 g + e][16 t + r], the quad of row 16 t + r of P^T
+                constexpr int t = tc;
+                floatx4 v;
                 const float gj = g_s[16 * t + r];
                 const floatx4 gi = ldf4(g_s + 16 * W + 4 * g);
 #pragma unroll
@@ -240,23 +278,11 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
                     float y = __builtin_amdgcn_exp2f(t == W ? fminf(gi[e] - gj, 0.f) : gi[e] - gj) * qk[t][e];
                     if (norm_q) y *= __shfl(rq, 4 * g + e, kWave);
                     if (t == W) y = (r <= 4 * g + e) ? y : 0.f;
-                    if (clen < 64) y = (16 * W + 4 * g + e < clen) ? y : 0.f;          // rows beyond a short chunk
+                    if (clen < 64) y = (16 * W + 4 * g + e < clen) ? y : 0.f;
                     v[e] = y;
                 }
-            } else {                                     // lane: P[16 W + r][16 t + 4 g + e]
-                const float gi = g_s[16 * W + r];
-                const floatx4 gj = ldf4(g_s + 16 * t + 4 * g);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float y = __builtin_amdgcn_exp2f(t == W ? fminf(gi - gj[e], 0.f) : gi - gj[e]) * qk[t][e] * rq;
-                    if (t == W) y = (4 * g + e <= r) ? y : 0.f;
-                    if (clen < 64) y = (16 * W + r < clen) ? y : 0.f;
-                    v[e] = y;
-                }
-            }
-            pt[t] = to_quad(v);
-        });
-        if constexpr (BWD) {
+                pt[t] = to_quad(v);
+            });
             // pair (t, W / 2) of P^T holds the quads of waves W & ~1 and W | 1 side by side; below the diagonal it is zero
             char* out = rec + 2 * HALF + lane * 16;
             static_for<W + 1>([&](auto tc) {
@@ -264,14 +290,6 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
                 char* p = out + triu_pair(t, W >> 1) * 1024;
                 if constexpr (t == W && (W & 1)) { const u32x4 v = {0u, 0u, pt[t].x, pt[t].y}; st16(p, v); }
                 else *reinterpret_cast<u32x2*>(p + 8 * (W & 1)) = pt[t];
-            });
-        } else {
-            char* out = rec + HALF + lane * 16;
-            static_for<W / 2 + 1>([&](auto pc) {
-                constexpr int jp = pc;
-                const u32x2 q0 = pt[2 * jp], q1 = 2 * jp + 1 <= W ? pt[2 * jp + 1 <= W ? 2 * jp + 1 : 0] : zq;
-                const u32x4 v = {q0.x, q0.y, q1.x, q1.y};
-                st16(out + tri_pair(W, jp) * 1024, v);
             });
         }
         __syncthreads();                                 // the K tile is dead from here on: M overlays it
@@ -378,23 +396,19 @@ __global__ __launch_bounds__(256, 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
     }
 }
 
-hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st)
+template <int DK>
+static hipError_t launch_dk(const IntraArgs<bf16_t>& a, IntraMode mode, int n_chunks, hipStream_t st)
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_bf16_kernel<64, false>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_bf16_kernel<128, false>), grid, block, 0, st, a);
+    if (mode == kIntraFwd)      hipLaunchKernelGGL((intra_bf16_kernel<DK, kIntraFwd>), grid, block, 0, st, a);
+    else if (mode == kIntraBwd) hipLaunchKernelGGL((intra_bf16_kernel<DK, kIntraBwd>), grid, block, 0, st, a);
+    else                        hipLaunchKernelGGL((intra_bf16_kernel<DK, kIntraPair>), grid, block, 0, st, a);
     return hipGetLastError();
 }
-
-// the records of the backward pass at a.wsT (a.opts: the option bits of the call); a.wsP and a.wsG unused
-hipError_t launch_intra_bwd_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st)
+hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, IntraMode mode, int n_chunks, hipStream_t st)
 {
-    if (n_chunks == 0) return hipSuccess;
-    const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (dk == 64) hipLaunchKernelGGL((intra_bf16_kernel<64, true>), grid, block, 0, st, a);
-    else          hipLaunchKernelGGL((intra_bf16_kernel<128, true>), grid, block, 0, st, a);
-    return hipGetLastError();
+    return dk == 64 ? launch_dk<64>(a, mode, n_chunks, st) : launch_dk<128>(a, mode, n_chunks, st);
 }
 
 }  // namespace kla

@@ -46,12 +46,13 @@ template <int N> __device__ __forceinline__ float tree_sum(float (&x)[N])
 
 }  // namespace
 
-// BWD = false: the forward's records [T' | P | three vectors].  BWD = true: those of the backward pass,
-// [T' | M^T | P^T | five vectors] (see bwd_record_bytes in kla_mma.hpp).
-template <int DK, bool BWD>
+// MODE (IntraMode): the forward's records [T' | P | three vectors], those of the backward pass, [T' | M^T | P^T | five vectors]
+// (see bwd_record_bytes in kla_mma.hpp), or the backward's and [P | three vectors].
+template <int DK, int MODE>
 __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
 {
     typedef F32<DK> C;
+    constexpr bool FWD = MODE != kIntraBwd, BWD = MODE != kIntraFwd;
     constexpr int KB = C::KB, REC = BWD ? bwd_record_bytes<float>() : ws_record_bytes<float>(), HALF = ws_half_bytes<float>();
     constexpr int MB = 64 * kLdm * 4;
     __shared__ __attribute__((aligned(1024))) char area[C::TILE > 2 * MB ? C::TILE : 2 * MB];
@@ -69,7 +70,9 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
     const int clen = cp.clen;
     const size_t ks = (size_t)a.H * DK;
     char* rec = reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC;
-    float* vec = reinterpret_cast<float*>(rec + (BWD ? 3 : 2) * HALF);
+    char* recp = MODE == kIntraPair ? reinterpret_cast<char*>(a.wsP) + (size_t)blockIdx.x * pair_record_bytes<float>() : rec + HALF;
+    float* vec = reinterpret_cast<float*>(rec + 3 * HALF);   // the backward's five vectors
+    float* vecf = reinterpret_cast<float*>(recp + HALF);     // the forward's three
     const bool gdn = (a.opts & kOptGdnBeta) != 0;
 
     // ---- everything the workgroup reads, requested at once (rows beyond a short chunk: its last row, zeroed below)
@@ -92,8 +95,9 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
     for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_up(x, off, kWave); if (lane >= off) x += y; }
     g_s[wave][lane] = x;
     if (wave == 0) {
-        vec[lane] = expf(x);
-        vec[64 + lane] = expf(__shfl(x, 63, kWave) - x);
+        const float gam = expf(x), dec = expf(__shfl(x, 63, kWave) - x);
+        if constexpr (BWD) { vec[lane] = gam; vec[64 + lane] = dec; }
+        if constexpr (FWD) { vecf[lane] = gam; vecf[64 + lane] = dec; }
         if constexpr (!BWD) a.wsG[(size_t)blockIdx.x * 128 + lane] = x;
     }
     kr.template stash<true>(area, tid, clen);
@@ -113,10 +117,8 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
         if (a.opts & kOptNormalizeQ) rq = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
         if (g == 0) {
             if constexpr (BWD) vec[256 + 16 * wave + r] = rq;
-            else {
-                vec[128 + 16 * wave + r] = expf(g_s[wave][16 * wave + r]) * rq;
-                a.wsG[(size_t)blockIdx.x * 128 + 64 + 16 * wave + r] = rq;
-            }
+            if constexpr (FWD) vecf[128 + 16 * wave + r] = expf(g_s[wave][16 * wave + r]) * rq;
+            if constexpr (!BWD) a.wsG[(size_t)blockIdx.x * 128 + 64 + 16 * wave + r] = rq;
         }
     }
     __syncthreads();
@@ -132,33 +134,56 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
         floatx4 kk[A + 1], qk[W + 1];
 #pragma unroll
         for (int t = 0; t <= A; ++t) kk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
         float sq[KB];
+        // KK: the tiles of K K^T and the key norms too.  TR = false: tiles of P, TR = true: of P^T
+        auto products = [&](auto kkc, auto trc) {
+            constexpr bool KK = decltype(kkc)::value != 0, TR = decltype(trc)::value != 0;
+            constexpr int N = KK ? NT : W + 1;
 #pragma unroll
-        for (int b = 0; b < KB; ++b) {
-            const float4 ka = ops.row_quad(area, b);
-            sq[b] = sum_squares(ka);
-            static_for<NT>([&](auto tc) {
-                constexpr int t = tc;
-                const float4 kb = t == A ? ka : ldf4(area + boff[b & 3] + 16 * t * C::RB + 256 * (b >> 2));
-                if constexpr (t <= A) mma16(kk[t], ka, kb);                  // rows: token of tile A, column: token of tile t
-                if constexpr (t <= W) {
-                    if constexpr (BWD) mma16(qk[t], qf[b], kb);              // rows: query of tile W, column: key of tile t
-                    else               mma16(qk[t], kb, qf[b]);              // rows: key of tile t, column: query of tile W
-                }
-            });
-        }
+            for (int t = 0; t <= W; ++t) qk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                float4 ka;
+                if constexpr (KK) { ka = ops.row_quad(area, b); sq[b] = sum_squares(ka); }
+                static_for<N>([&](auto tc) {
+                    constexpr int t = tc;
+                    const float4 kb = KK && t == A ? ka : ldf4(area + boff[b & 3] + 16 * t * C::RB + 256 * (b >> 2));
+                    if constexpr (KK && t <= A) mma16(kk[t], ka, kb);        // rows: token of tile A, column: token of tile t
+                    if constexpr (t <= W) {
+                        if constexpr (TR) mma16(qk[t], qf[b], kb);           // rows: query of tile W, column: key of tile t
+                        else              mma16(qk[t], kb, qf[b]);           // rows: key of tile t, column: query of tile W
+                    }
+                });
+            }
+        };
+        products(IntC<1>(), IntC<FWD ? 0 : 1>());
         const float* gw = g_s[W];
         // ---- P (or P^T): decay, mask, 1/||q||; straight into the record
         const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
         auto put = [&](char* half, int pair, int blk, floatx4 v) {
             *reinterpret_cast<float4*>(half + ((size_t)pair * 64 + lane) * 32 + 16 * blk) = quad(v);
         };
-        static_for<W + 1>([&](auto tc) {
-            constexpr int t = tc;
-            floatx4 v;
-            if constexpr (BWD) {                         // lane: P[16 W + 4 g + e][16 t + r], the quad of row 16 t + r of P^T
+        // (and, zero, the tile of a stored pair that lies on the other side of the diagonal)
+        if constexpr (FWD) {
+            static_for<W + 1>([&](auto tc) {             // lane: P[16 W + r][16 t + 4 g + e]
+                constexpr int t = tc;
+                floatx4 v;
+                const float gi = gw[16 * W + r];
+                const floatx4 gj = lda4(gw + 16 * t + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (t < W || 4 * g + e <= r) ? expf(gi - gj[e]) * qk[t][e] * rq : 0.f;
+                put(recp, tri_pair(W, t >> 1), t & 1, v);
+            });
+            if constexpr ((W & 1) == 0) put(recp, tri_pair(W, W >> 1), 1, z4);
+        }
+        if constexpr (BWD) {
+            if constexpr (FWD) {
+                asm volatile("" ::: "memory");           // K is read again: kept from the first time, it would spill
+                products(IntC<0>(), IntC<1>());
+            }
+            static_for<W + 1>([&](auto tc) {             // lane: P[16 W + 4 g + e][16 t + r], the quad of row 16 t + r of P^T
+                constexpr int t = tc;
+                floatx4 v;
                 const float gj = gw[16 * t + r];
                 const floatx4 gi = lda4(gw + 16 * W + 4 * g);
 #pragma unroll
@@ -167,17 +192,9 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
                     v[e] = (t < W || r <= 4 * g + e) ? expf(gi[e] - gj) * qk[t][e] * rqi : 0.f;
                 }
                 put(rec + 2 * HALF, triu_pair(t, W >> 1), W & 1, v);
-            } else {                                     // lane: P[16 W + r][16 t + 4 g + e]
-                const float gi = gw[16 * W + r];
-                const floatx4 gj = lda4(gw + 16 * t + 4 * g);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (t < W || 4 * g + e <= r) ? expf(gi - gj[e]) * qk[t][e] * rq : 0.f;
-                put(rec + HALF, tri_pair(W, t >> 1), t & 1, v);
-            }
-        });
-        // the tile of a stored pair that lies on the other side of the diagonal
-        if constexpr (BWD) { if constexpr ((W & 1) == 1) put(rec + 2 * HALF, triu_pair(W, W >> 1), 0, z4); }
-        else               { if constexpr ((W & 1) == 0) put(rec + HALF, tri_pair(W, W >> 1), 1, z4); }
+            });
+            if constexpr ((W & 1) == 1) put(rec + 2 * HALF, triu_pair(W, W >> 1), 0, z4);
+        }
         // ---- beta of the rows of tile A (||k_i||^2 of row 16 A + r in the lanes of r)
         float kn = tree_sum(sq);
         kn += __shfl_xor(kn, 16, kWave);
@@ -278,17 +295,18 @@ __global__ __launch_bounds__(256, 4) void intra_f32_kernel(IntraArgs<float> a)
 }
 
 template <int DK>
-static hipError_t launch_dk(const IntraArgs<float>& a, bool bwd, int n_chunks, hipStream_t st)
+static hipError_t launch_dk(const IntraArgs<float>& a, IntraMode mode, int n_chunks, hipStream_t st)
 {
     if (n_chunks == 0) return hipSuccess;
     const dim3 grid((unsigned)n_chunks * a.H), block(256);
-    if (bwd) hipLaunchKernelGGL((intra_f32_kernel<DK, true>), grid, block, 0, st, a);
-    else     hipLaunchKernelGGL((intra_f32_kernel<DK, false>), grid, block, 0, st, a);
+    if (mode == kIntraFwd)      hipLaunchKernelGGL((intra_f32_kernel<DK, kIntraFwd>), grid, block, 0, st, a);
+    else if (mode == kIntraBwd) hipLaunchKernelGGL((intra_f32_kernel<DK, kIntraBwd>), grid, block, 0, st, a);
+    else                        hipLaunchKernelGGL((intra_f32_kernel<DK, kIntraPair>), grid, block, 0, st, a);
     return hipGetLastError();
 }
-hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, bool bwd, int n_chunks, hipStream_t st)
+hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, IntraMode mode, int n_chunks, hipStream_t st)
 {
-    return dk == 64 ? launch_dk<64>(a, bwd, n_chunks, st) : launch_dk<128>(a, bwd, n_chunks, st);
+    return dk == 64 ? launch_dk<64>(a, mode, n_chunks, st) : launch_dk<128>(a, mode, n_chunks, st);
 }
 
 }  // namespace kla

@@ -605,7 +605,9 @@ struct PHelper : HelperBase<DK> {
 // DG: diagonal gating (App. B): a.k = K o Gamma and a.q = Q o Gamma feed K S and Q S, a.kt_src = K o (gamma_C/Gamma)
 // the state update, the records carry unit decay vectors and the state rows decay by a.gc_vec (see intra_diag_kernel).
 // FU: fused mode, see the top of the file; a.wsT / a.wsP / a.wsG are not used, a.log_alpha / a.eta / a.eps are.
-template <int DK, int NW, bool NQ, bool DG = false, bool FU = false>
+// SV: the incoming state of every chunk and the rows of X stay behind for the backward pass (a.s_chk, a.X: put_checkpoint, put_rows),
+// stored by the compute waves as they hold them; T' comes from the backward's records and P from records of its own.
+template <int DK, int NW, bool NQ, bool DG = false, bool FU = false, bool SV = false>
 __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_kernel(ScanArgs<bf16_t> a)
 {
     typedef Cfg<DK, NW, DG, FU> C;
@@ -657,8 +659,11 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     const char* vbase = reinterpret_cast<const char*>(a.v) + (size_t)t0 * v_row + ((size_t)h * a.dv + slice * SLW) * 2;
     const char* k2base = DG ? reinterpret_cast<const char*>(a.kt_src) + (size_t)t0 * kq_row + (size_t)h * DK * 2 : nullptr;
     const char* gcbase = DG ? reinterpret_cast<const char*>(a.gc_vec) + ((size_t)ch0 * a.H + h) * DK * 4 : nullptr;
-    constexpr int REC = ws_record_bytes<bf16_t>();
+    static_assert(!SV || (!DG && !FU), "plain scan only");
+    // records: T', and P with the vectors behind it
+    constexpr int REC = SV ? bwd_record_bytes<bf16_t>() : ws_record_bytes<bf16_t>(), RECP = SV ? pair_record_bytes<bf16_t>() : REC;
     const char* tpbase = FU ? nullptr : reinterpret_cast<const char*>(a.wsT) + ((size_t)ch0 * a.H + h) * REC;
+    const char* ppbase = SV ? reinterpret_cast<const char*>(a.wsP) + ((size_t)ch0 * a.H + h) * RECP : FU ? nullptr : tpbase + C::TPB;
 
     // ---- loop-invariant per-lane offsets ------------------------------------------------------------
     // copy engine, global side: lane l of copy block b fills LDS bytes [1024 b + 16 l, +16) of a tile, i.e.
@@ -715,6 +720,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             }
         };
         const char* tc = FU ? nullptr : tpbase + (size_t)c * a.H * REC;
+        const char* pc = FU ? nullptr : ppbase + (size_t)c * a.H * RECP;
         if constexpr (!FU && first) tile(kbase + (size_t)(64 * c) * kq_row, st);   // fused mode: the helper waves bring K and Q
         if constexpr (first) {
             const char* vc = vbase + (size_t)(64 * c) * v_row;
@@ -731,11 +737,11 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
                 });
             }
             if constexpr (!FU) {
-                static_for<C::NTB / 2>([&](auto i) {     // T': the first half of the record's tile area
+                static_for<C::NTB / 2>([&](auto i) {     // T'
                     const int b = i;
                     dma16(tc + b * 1024, lane * 16, st + C::OFF_T + b * 1024);
                 });
-                if (lane < 48) dma16(tc + 2 * C::TPB, lane * 16, st + C::OFF_EG);   // gamma_i | gamma_C/gamma_i | gamma_i/||q_i||: 768 bytes
+                if (lane < 48) dma16(pc + C::TPB, lane * 16, st + C::OFF_EG);   // gamma_i | gamma_C/gamma_i | gamma_i/||q_i||: 768 bytes
             }
             if constexpr (DG) {
                 if (lane < DK / 4) dma16(gcbase + (size_t)c * a.H * DK * 4, lane * 16, st + C::OFF_GC);   // gamma_C per channel
@@ -745,9 +751,9 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             if constexpr (!FU) {
                 tile(qbase + (size_t)(64 * c) * kq_row, st + C::OFF_Q);
                 if constexpr (DG) tile(k2base + (size_t)(64 * c) * kq_row, st + C::OFF_K2);
-                static_for<C::NTB / 2>([&](auto i) {     // P: the second half
-                    const int b = C::NTB / 2 + i;
-                    dma16(tc + b * 1024, lane * 16, st + C::OFF_T + b * 1024);
+                static_for<C::NTB / 2>([&](auto i) {
+                    const int b = i;
+                    dma16(pc + b * 1024, lane * 16, st + C::OFF_P + b * 1024);
                 });
             }
         }
@@ -755,7 +761,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 
     // ---- one chunk of the recurrence for this wave's 16 columns ------------------------------------
     // rc: where T', P and the vectors of this chunk are (the ring stage itself, or a record buffer when fused)
-    auto compute = [&](const char* st, const char* rc, char* ost) {
+    auto compute = [&](const char* st, const char* rc, char* ost, [[maybe_unused]] int c) {
         const char* pS = rc + lane * 16;                 // T' / P slots
         const char* pV = st + C::OFF_V + oV;
         const char* pG = rc + C::R_EG + 16 * g;          // 4 consecutive floats: rows 4 g .. 4 g + 3
@@ -780,6 +786,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             if constexpr (DG) S[kt] = S[kt] * ld_f4(st + C::OFF_GC + (32 * (kt >> 1) + 8 * g + 4 * (kt & 1)) * 4);
             else              S[kt] = S[kt] * gC;
         }
+        if constexpr (SV) put_checkpoint<DK>(reinterpret_cast<char*>(a.s_chk) + ((size_t)(ch0 + c) * a.H + h) * a.dv * RB, slice * NW + wave, Sq, r, g);
 
         // Products are issued "independent first": consecutive MFMAs write different accumulators, so that a
         // dependent one (same accumulator) follows only several instructions later.
@@ -835,6 +842,8 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             Xf[it - 1] = quad_to_f(vq[it]) - egv[it] * ks[it];
             if constexpr (!FU) Xq[it] = to_quad(Xf[it - 1]);
         }
+        if constexpr (SV)
+            put_rows(reinterpret_cast<char*>(a.X) + (size_t)(t0 + 64L * c) * v_row, v_row, a.dv, h, slice * NW + wave, Xq, min(64, len - 64 * c), r, g);
 
         // K^T slots of the first state tiles and the P slots: on their way during the solve
         u32x2 kt[2][KB][2];                              // [token pair jp][state tile][token block]
@@ -1099,6 +1108,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             const char* qc = qbase + (size_t)(64 * c) * kq_row;
             const char* vc = vbase + (size_t)(64 * c) * v_row;
             const char* tc = tpbase + (size_t)c * a.H * REC;
+            const char* pc = ppbase + (size_t)c * a.H * RECP;
             constexpr int NK = C::NKB / 8, NV = C::NVB / 8;          // blocks of K (and Q), V per wave
             static_assert(C::NKB % 8 == 0 && C::NVB == 16 && C::NTB == 12, "shares of the copy blocks");
             const int bk = wave * NK, bv = wave * NV;
@@ -1114,10 +1124,11 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
                 dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + (bv + i) * 1024);
             });
             if (wave < 6) {
-                dma16(tc + wave * 2048, lane * 16, st + C::OFF_T + wave * 2048);
-                dma16(tc + wave * 2048 + 1024, lane * 16, st + C::OFF_T + wave * 2048 + 1024);
+                const char* src = wave < 3 ? tc + wave * 2048 : pc + (wave - 3) * 2048;
+                dma16(src, lane * 16, st + C::OFF_T + wave * 2048);
+                dma16(src + 1024, lane * 16, st + C::OFF_T + wave * 2048 + 1024);
             } else if (wave == 6 && lane < 48) {
-                dma16(tc + 2 * C::TPB, lane * 16, st + C::OFF_EG);
+                dma16(pc + C::TPB, lane * 16, st + C::OFF_EG);
             }
         };
         if (nch > 0) issue_part(0, lds);
@@ -1127,7 +1138,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             char* st = lds + (c & 1) * C::STAGE;
             if (c + 1 < nch) issue_part(c + 1, lds + ((c + 1) & 1) * C::STAGE);
             if (c > 0) write_out(c - 1, (c & 1) ? ost0 : ost1, tid, IntC<512>());
-            compute(st, st, (c & 1) ? ost1 : ost0);
+            compute(st, st, (c & 1) ? ost1 : ost0, c);
             wait_vmcnt<0>();                             // this wave's copies (and stores); the barrier covers the others'
             __syncthreads();
         }
@@ -1141,7 +1152,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     int scur = 0;                                        // ring position of chunk c
     for (int c = 0; c < nch; ++c) {
         char* ost = (c & 1) ? ost1 : ost0;
-        compute(lds + scur * C::STAGE, FU ? lds + C::OFF_REC + (c & 1) * C::RECB : lds + scur * C::STAGE, ost);
+        compute(lds + scur * C::STAGE, FU ? lds + C::OFF_REC + (c & 1) * C::RECB : lds + scur * C::STAGE, ost, c);
         // The barrier that ends a chunk step: staged outputs before their write-out; chunk c+1's operands before
         // their use; all reads of this stage before it is refilled; and the write-out of chunk c-1 (finished by
         // its wave before it arrives here) before the staging tile of that parity is written again in chunk c+1.
@@ -1152,7 +1163,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     store_final();
 }
 
-template <int DK>
+template <int DK, bool SV>
 static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st)
 {
     const int n_states = a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N);
@@ -1161,31 +1172,25 @@ static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st
     const int nsl = a.dv / (16 * waves);
     const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * nsl));
     const bool nq = (a.opts & kOptNormalizeQ) != 0;
+    auto go = [&](auto nw_c) {
+        constexpr int NW = decltype(nw_c)::value;
+        const dim3 block(64 * Cfg<DK, NW>::NWAVES);
+        if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, true, false, false, SV>), grid, block, 0, st, a);
+        else    hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, false, false, false, SV>), grid, block, 0, st, a);
+    };
     switch (waves) {
-        case 1:
-            if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 1, true>), grid, dim3(64 * 3), 0, st, a);
-            else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 1, false>), grid, dim3(64 * 3), 0, st, a);
-            break;
-        case 2:
-            if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 2, true>), grid, dim3(64 * 4), 0, st, a);
-            else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 2, false>), grid, dim3(64 * 4), 0, st, a);
-            break;
-        case 4:
-            if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 4, true>), grid, dim3(64 * 6), 0, st, a);
-            else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 4, false>), grid, dim3(64 * 6), 0, st, a);
-            break;
-        default:
-            if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, 8, true>), grid, dim3(64 * 8), 0, st, a);
-            else    hipLaunchKernelGGL((scan_bf16_kernel<DK, 8, false>), grid, dim3(64 * 8), 0, st, a);
-            break;
+        case 1: go(IntC<1>()); break;
+        case 2: go(IntC<2>()); break;
+        case 4: go(IntC<4>()); break;
+        default: go(IntC<8>()); break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_scan_bf16(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (dk == 64) return launch_dk<64>(a, waves, st);
-    return launch_dk<128>(a, waves, st);
+    if (a.s_chk) return dk == 64 ? launch_dk<64, true>(a, waves, st) : launch_dk<128, true>(a, waves, st);
+    return dk == 64 ? launch_dk<64, false>(a, waves, st) : launch_dk<128, false>(a, waves, st);
 }
 
 template <int DK>

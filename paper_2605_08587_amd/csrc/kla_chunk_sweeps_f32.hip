@@ -121,8 +121,9 @@ template <int DK> __device__ __forceinline__ void store_state(const floatx4 (&S)
 //     X = V - D_gamma (K S)    U = T' X    O = D_gamma (Q S) + P U    S = gamma_C S + K^T diag(gamma_C/gamma_i) U
 // DIAG: diagonal gating (App. B): a.k = K o Gamma, a.q = Q o Gamma, a.kt_src = K o (gamma_C/Gamma), unit decay vectors in
 // the records, and the state decays per row by a.gc_vec.
+// SV: S of every chunk, X and U stay behind for the backward pass (see ScanArgs), as bwd_states_f32_kernel leaves them.
 // =================================================================================================
-template <int DK, int NC, bool DIAG>
+template <int DK, int NC, bool DIAG, bool SV>
 __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
 {
     typedef F32<DK> C;
@@ -144,9 +145,12 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
     const float* k2b = DIAG ? a.kt_src + (size_t)p.t0 * ks + (size_t)p.h * DK : nullptr;
     const float* vb = a.v + (size_t)p.t0 * vs + (size_t)p.h * a.dv + col0;
     float* ob = a.o + (size_t)p.t0 * vs + (size_t)p.h * a.dv + col0;
-    constexpr int HALF = ws_half_bytes<float>(), REC = ws_record_bytes<float>();
+    // records: T', and P with the vectors behind it
+    constexpr int HALF = ws_half_bytes<float>(), REC = SV ? bwd_record_bytes<float>() : ws_record_bytes<float>(),
+                  RECP = SV ? pair_record_bytes<float>() : REC;
     const char* rec0 = reinterpret_cast<const char*>(a.wsT) + ((size_t)p.ch0 * a.H + p.h) * REC;
-    const size_t rec_step = (size_t)a.H * REC;
+    const char* recp0 = SV ? reinterpret_cast<const char*>(a.wsP) + ((size_t)p.ch0 * a.H + p.h) * RECP : rec0 + HALF;
+    const size_t rec_step = (size_t)a.H * REC, recp_step = (size_t)a.H * RECP;
     const int row0 = 16 * wave + 4 * g;
 
     TileOps<DK> ops;
@@ -160,12 +164,17 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
 #pragma unroll
             for (int t = 0; t < TS; ++t) S[n][t] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    auto put_state = [&]() {
+    // to the exchange area (and to the checkpoint of chunk c)
+    auto put_state = [&]([[maybe_unused]] int c) {
 #pragma unroll
         for (int n = 0; n < NC; ++n)
 #pragma unroll
-            for (int t = 0; t < TS; ++t)
+            for (int t = 0; t < TS; ++t) {
                 *reinterpret_cast<float4*>(lds + OFF_S + n * C::SXB + ((wave * TS + t) * 64 + lane) * 16) = quad(S[n][t]);
+                if constexpr (SV) {
+                    if (c < p.nch) *reinterpret_cast<float4*>(a.s_chk + (((size_t)(p.ch0 + c) * a.H + p.h) * a.dv + col0 + 16 * n) * DK + 16 * (wave * TS + t) + 4 * g) = quad(S[n][t]);
+                }
+            }
     };
 
     // operands of one wave alone, each requested as soon as its previous value has been used
@@ -182,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
         const int clen = min(64, p.len - 64 * c);
 #pragma unroll
         for (int n = 0; n < NC; ++n) vf[n] = load_col(vb + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen);
-        const char* rec = rec0 + (size_t)c * rec_step + 2 * HALF;
+        const char* rec = recp0 + (size_t)c * recp_step + HALF;
         eg = lda4(rec + 4 * row0);
         ed = lda4(rec + 256 + 4 * row0);
         eq = lda4(rec + 512 + 4 * row0);
@@ -210,9 +219,9 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
         get_v(0);
         load_tri(tf, rec0, wave, lane);
         get_q(0);
-        load_tri(pf, rec0 + HALF, wave, lane);
+        load_tri(pf, recp0, wave, lane);
         stash_k();
-        put_state();
+        put_state(0);
     }
     __syncthreads();
     for (int c = 0; c < p.nch; ++c) {
@@ -230,8 +239,10 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
             for (int n = 0; n < NC; ++n) mma16(x[n], ka, ldf4(lds + OFF_S + n * C::SXB + (b * 64 + lane) * 16));
         }
 #pragma unroll
-        for (int n = 0; n < NC; ++n)
-            *reinterpret_cast<float4*>(lds + OFF_X + n * C::RXB + (wave * 64 + lane) * 16) = quad(vf[n] - eg * x[n]);
+        for (int n = 0; n < NC; ++n) {
+            x[n] = vf[n] - eg * x[n];
+            *reinterpret_cast<float4*>(lds + OFF_X + n * C::RXB + (wave * 64 + lane) * 16) = quad(x[n]);
+        }
 #pragma unroll
         for (int b = 0; b < KB; ++b)
 #pragma unroll
@@ -246,6 +257,11 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
             *reinterpret_cast<float4*>(lds + OFF_UD + n * C::RXB + (wave * 64 + lane) * 16) = quad(u * ed);
             *reinterpret_cast<float4*>(lds + OFF_U + n * C::RXB + (wave * 64 + lane) * 16) = quad(u);
             o[n] = o[n] * eq;
+            if constexpr (SV) {
+                const size_t at = (size_t)(p.t0 + 64L * c) * vs + (size_t)p.h * a.dv + col0 + 16 * n;
+                store_col(a.X + at, vs, row0, min(64, p.len - 64 * c), x[n]);
+                store_col(a.U + at, vs, row0, min(64, p.len - 64 * c), u);
+            }
         }
         __syncthreads();
         load_tri(tf, rec_n, wave, lane);
@@ -269,12 +285,12 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
         }
         __syncthreads();                                 // K and the exchanged state are no longer read
         stash_k();
-        put_state();
+        put_state(c + 1);
         // ---- O = D_gamma (Q S) + P U, off the chain
         const int clen = min(64, p.len - 64 * c);
 #pragma unroll
         for (int n = 0; n < NC; ++n) mma_tri(o[n], pf, lds + OFF_U + n * C::RXB, wave, lane);
-        load_tri(pf, rec_n + HALF, wave, lane);
+        load_tri(pf, recp0 + (size_t)cn * recp_step, wave, lane);
 #pragma unroll
         for (int n = 0; n < NC; ++n) store_col(ob + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen, o[n]);
         __syncthreads();
@@ -290,7 +306,8 @@ __global__ __launch_bounds__(256, 2) void scan_f32_kernel(ScanArgs<float> a)
 // whenever its only wave waits for LDS or a barrier: 3.7 us per chunk for 1.7 us of MFMA, here 3.1 us.  K and the exchanged
 // state have two images each, so a step needs three barriers instead of four.  (Loads requested two chunks ahead, two
 // accumulators per product and a raised priority of the chain change nothing: 123 us either way.)
-template <int DK, int NC, bool DIAG>
+// SV: the waves off the chain store what the backward needs, which they find in the exchange areas.
+template <int DK, int NC, bool DIAG, bool SV>
 __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> a)
 {
     typedef F32<DK> C;
@@ -309,9 +326,12 @@ __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> 
     if (!p.valid) return;
     const int col0 = p.slice * 16 * NC + r;
     const size_t ks = (size_t)a.H * DK, vs = (size_t)a.H * a.dv;
-    constexpr int HALF = ws_half_bytes<float>(), REC = ws_record_bytes<float>();
+    // records: T', and P with the vectors behind it
+    constexpr int HALF = ws_half_bytes<float>(), REC = SV ? bwd_record_bytes<float>() : ws_record_bytes<float>(),
+                  RECP = SV ? pair_record_bytes<float>() : REC;
     const char* rec0 = reinterpret_cast<const char*>(a.wsT) + ((size_t)p.ch0 * a.H + p.h) * REC;
-    const size_t rec_step = (size_t)a.H * REC;
+    const char* recp0 = SV ? reinterpret_cast<const char*>(a.wsP) + ((size_t)p.ch0 * a.H + p.h) * RECP : rec0 + HALF;
+    const size_t rec_step = (size_t)a.H * REC, recp_step = (size_t)a.H * RECP;
     const int row0 = 16 * wave + 4 * g;
 
     if (chain) {
@@ -340,7 +360,7 @@ __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> 
             const int clen = min(64, p.len - 64 * c);
 #pragma unroll
             for (int n = 0; n < NC; ++n) vf[n] = load_col(vb + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen);
-            const char* rec = rec0 + (size_t)c * rec_step + 2 * HALF;
+            const char* rec = recp0 + (size_t)c * recp_step + HALF;
             eg = lda4(rec + 4 * row0);
             ed = lda4(rec + 256 + 4 * row0);
             gC = *reinterpret_cast<const float*>(rec + 252);
@@ -422,7 +442,7 @@ __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> 
             const float* q = qb + (size_t)min(64 * c + 16 * wave + r, p.len - 1) * ks + 4 * g;
 #pragma unroll
             for (int b = 0; b < KB; ++b) qf[b] = ldf4(q + 16 * b);
-            eq = lda4(rec0 + (size_t)c * rec_step + 2 * HALF + 512 + 4 * row0);
+            eq = lda4(recp0 + (size_t)c * recp_step + HALF + 512 + 4 * row0);
         };
         TileRegs<DK> kr, k2r;
         auto fetch_k = [&](int c) {
@@ -437,7 +457,7 @@ __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> 
         if (p.nch > 0) {
             fetch_k(0);
             get_q(0);
-            load_tri(pf, rec0 + HALF, wave, lane);
+            load_tri(pf, recp0, wave, lane);
             stash_k(lds);
         }
         __syncthreads();
@@ -455,18 +475,35 @@ __global__ __launch_bounds__(512, 2) void scan_f32_split_kernel(ScanArgs<float> 
 #pragma unroll
                 for (int n = 0; n < NC; ++n) mma16(o[n], qf[b], ldf4(s_img + n * C::SXB + (b * 64 + lane) * 16));
             }
+            const int clen = min(64, p.len - 64 * c);
+            if constexpr (SV) {
+                float* chk = a.s_chk + (((size_t)(p.ch0 + c) * a.H + p.h) * a.dv + col0) * DK + 4 * g;
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+#pragma unroll
+                    for (int t = 0; t < TS; ++t)
+                        *reinterpret_cast<float4*>(chk + (size_t)(16 * n) * DK + 16 * (wave * TS + t)) =
+                            ldf4(s_img + n * C::SXB + ((wave * TS + t) * 64 + lane) * 16);
+                    store_col(a.X + (size_t)(p.t0 + 64L * c) * vs + (size_t)p.h * a.dv + col0 + 16 * n, vs, row0, clen,
+                              lda4(lds + OFF_X + n * C::RXB + (wave * 64 + lane) * 16));
+                }
+            }
 #pragma unroll
             for (int n = 0; n < NC; ++n) o[n] = o[n] * eq;
             get_q(cn);
             __syncthreads();
             // ---- O = D_gamma (Q S) + P U
-            const int clen = min(64, p.len - 64 * c);
 #pragma unroll
             for (int n = 0; n < NC; ++n) mma_tri(o[n], pf, lds + OFF_U + n * C::RXB, wave, lane);
-            load_tri(pf, rec0 + (size_t)cn * rec_step + HALF, wave, lane);
+            load_tri(pf, recp0 + (size_t)cn * recp_step, wave, lane);
             stash_k(lds + ((c + 1) & 1) * KIMG);         // the image chunk c - 1 was read from
 #pragma unroll
             for (int n = 0; n < NC; ++n) store_col(ob + (size_t)(64 * c) * vs + 16 * n, vs, row0, clen, o[n]);
+            if constexpr (SV)
+#pragma unroll
+                for (int n = 0; n < NC; ++n)
+                    store_col(a.U + (size_t)(p.t0 + 64L * c) * vs + (size_t)p.h * a.dv + col0 + 16 * n, vs, row0, clen,
+                              lda4(lds + OFF_U + n * C::RXB + (wave * 64 + lane) * 16));
             __syncthreads();
         }
     }
@@ -776,7 +813,7 @@ __global__ __launch_bounds__(256, DK == 128 ? 1 : 2) void bwd_scan_f32_kernel(Bw
 // =================================================================================================
 static dim3 sweep_grid(int n_chains, int dv, int tiles) { return dim3((unsigned)(((n_chains + 7) / 8) * 8 * (dv / (16 * tiles)))); }
 
-template <int DK, bool DIAG>
+template <int DK, bool DIAG, bool SV>
 static hipError_t launch_scan_dk(const ScanArgs<float>& a, int tiles, hipStream_t st)
 {
     const int n_chains = (a.n_seq > 0 ? a.n_seq : a.N) * a.H;
@@ -787,23 +824,24 @@ static hipError_t launch_scan_dk(const ScanArgs<float>& a, int tiles, hipStream_
     // tiles two workgroups of four waves share a CU and cover each other (1024 tiles 209 us against 217 us with eight
     // waves); per-channel decay with two tiles per workgroup would not fit the second image of its two K tiles.
     const long wgs = ((long)n_chains + 7) / 8 * 8 * (a.dv / (16 * tiles));
-    if (tiles == 1) hipLaunchKernelGGL((scan_f32_split_kernel<DK, 1, DIAG>), grid, dim3(512), 0, st, a);
+    if (tiles == 1) hipLaunchKernelGGL((scan_f32_split_kernel<DK, 1, DIAG, SV>), grid, dim3(512), 0, st, a);
     else {
         if constexpr (!DIAG) {
             if (wgs <= 256) {
-                hipLaunchKernelGGL((scan_f32_split_kernel<DK, 2, DIAG>), grid, dim3(512), 0, st, a);
+                hipLaunchKernelGGL((scan_f32_split_kernel<DK, 2, DIAG, SV>), grid, dim3(512), 0, st, a);
                 return hipGetLastError();
             }
         }
-        hipLaunchKernelGGL((scan_f32_kernel<DK, 2, DIAG>), grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((scan_f32_kernel<DK, 2, DIAG, SV>), grid, dim3(256), 0, st, a);
     }
     return hipGetLastError();
 }
 hipError_t launch_scan_f32(const ScanArgs<float>& a, int dk, int tiles, hipStream_t st)
 {
     if (tiles != 1 && tiles != 2) return hipErrorInvalidValue;
-    if (a.kt_src) return dk == 64 ? launch_scan_dk<64, true>(a, tiles, st) : launch_scan_dk<128, true>(a, tiles, st);
-    return dk == 64 ? launch_scan_dk<64, false>(a, tiles, st) : launch_scan_dk<128, false>(a, tiles, st);
+    if (a.kt_src) return dk == 64 ? launch_scan_dk<64, true, false>(a, tiles, st) : launch_scan_dk<128, true, false>(a, tiles, st);
+    if (a.s_chk) return dk == 64 ? launch_scan_dk<64, false, true>(a, tiles, st) : launch_scan_dk<128, false, true>(a, tiles, st);
+    return dk == 64 ? launch_scan_dk<64, false, false>(a, tiles, st) : launch_scan_dk<128, false, false>(a, tiles, st);
 }
 
 template <int DK>

@@ -39,11 +39,14 @@ template <typename E> struct IntraArgs {
     // kernels behind it (NULL: launch_chunk_offsets has run).  Not for the plain kernels.
     int* pos_out = nullptr;
 };
+// Which records stage 1 writes: those of the forward, those of the backward (at wsT; wsP, wsG unused), or what a forward needs that
+// leaves its intermediates for the backward: the backward's records at wsT (T' is in them) and the rest of the
+// forward's, [P | three vectors], at wsP (pair_record_bytes in kla_mma.hpp; wsG unused).
+enum IntraMode { kIntraFwd = 0, kIntraBwd = 1, kIntraPair = 2 };
 hipError_t launch_intra(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);       // bf16, plain form
 // the records of the backward pass (see bwd_record_bytes in kla_mma.hpp) at a.wsT; a.wsP, a.wsG unused; a.opts: kOptNormalizeQ | kOptGdnBeta
 hipError_t launch_intra_bwd(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);   // bf16, plain form
-// fp32: the forward's records, or (bwd) those of the backward pass
-hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, bool bwd, int n_chunks, hipStream_t st);
+hipError_t launch_intra_f32(const IntraArgs<float>& a, int dk, IntraMode mode, int n_chunks, hipStream_t st);
 
 // Diagonal gating (App. B): log_alpha is [tokens, H, dk].  Besides the records (with unit decay vectors) the stage
 // writes the operands the scan is then given in place of k and q - kplus = K o Gamma, qplus = Q o Gamma (rows of the
@@ -79,6 +82,10 @@ template <typename E> struct ScanArgs {
     const int* seq_order = nullptr;
     // Fused bf16 scan only (the stage forms T', P and the decay vectors itself; wsT, wsP, wsG unused): the gates.
     const float* log_alpha = nullptr; const float* eta = nullptr; float eps = 0.f;
+    // A forward that leaves its intermediates for the backward (s_chk set; plain scans of either type, no segments): the
+    // incoming state of every chunk, X and (fp32) U, laid out as the backward's forward sweep leaves them.  wsT: the
+    // backward's records, wsP: [P | three vectors] (kIntraPair).
+    E* s_chk = nullptr; E* X = nullptr; E* U = nullptr;
 };
 // bf16, plain form (A/B reference of the specialised kernel below): waves = 1, 2 or 4, each wave of a workgroup carries 16
 // state columns through the whole sequence
@@ -88,7 +95,7 @@ hipError_t launch_scan_diag(const ScanArgs<bf16_t>& a, int dk, int waves, hipStr
 hipError_t launch_scan_f32(const ScanArgs<float>& a, int dk, int tiles, hipStream_t st);
 
 // bf16 specialisations (direct global->LDS copies, swizzled token-major staging, transposing LDS reads)
-hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);
+hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, IntraMode mode, int n_chunks, hipStream_t st);
 hipError_t launch_scan_bf16(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
 hipError_t launch_scan_bf16_diag(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);   // diagonal gating
 // Fused forward (no intra-chunk stage, no workspace): waves = 1 or 2; fixed-length, packed or segmented batches.
@@ -142,7 +149,6 @@ hipError_t launch_bwd_scan(const BwdArgs<bf16_t>& a, int dk, int waves, hipStrea
 hipError_t launch_bwd_states_f32(const BwdArgs<float>& a, int dk, int tiles, hipStream_t st);
 hipError_t launch_bwd_scan_f32(const BwdArgs<float>& a, int dk, int tiles, hipStream_t st);
 // bf16 specialisations of the two sweeps (copy wave, LDS ring, transposing reads: see kla_chunk_bwd_bf16.hip)
-hipError_t launch_intra_bwd_bf16(const IntraArgs<bf16_t>& a, int dk, int n_chunks, hipStream_t st);
 hipError_t launch_bwd_states_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
 hipError_t launch_bwd_scan_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
 hipError_t launch_bwd_assemble_bf16(const BwdArgs<bf16_t>& a, int dk, long n_chunks, hipStream_t st);

@@ -54,6 +54,8 @@ __host__ __device__ constexpr int triu_pair(int it, int jp) { return it < 2 ? 2 
 // M = (I + L)^{-1}, T' = M B; three operand halves and five vectors of 64 fp32.  The last vector is 1 unless the
 // read-out is normalised (then P^T carries it too).
 template <typename E> constexpr int bwd_record_bytes() { return 3 * ws_half_bytes<E>() + 1280; }
+// What the forward needs beside the backward's record where both are made at once: [P | gamma_i | gamma_C/gamma_i | gamma_i/||q_i||]
+template <typename E> constexpr int pair_record_bytes() { return ws_half_bytes<E>() + 768; }
 
 // ---- conversions between accumulator tiles and quads -------------------------------------
 __device__ __forceinline__ uint2 make_quad(floatx4 x, bf16_t)

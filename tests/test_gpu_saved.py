@@ -1,0 +1,84 @@
+"""kla_chunk's forward leaves the per-chunk operands and states behind for its backward (kla_chunk_fwd_save, kla_chunk_bwd_saved):
+the same bits as the two calls by hand, whose backward recomputes them; one shape per number of compute waves of the bf16 scan
+and per form of the fp32 one; last chunks of 1, 63 and 64 rows, packed batches with empty sequences, both options."""
+import pytest
+import torch
+
+import kla_inputs
+
+pytestmark = pytest.mark.gpu
+B, F = torch.bfloat16, torch.float32
+
+
+@pytest.fixture(scope="module")
+def kla():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_08587_amd as m
+    m.lib()
+    return m
+
+
+def _case(dt, N, T, H, dk, dv, lens, seed):
+    cu = None
+    if lens:
+        cu = torch.tensor([0] + [sum(lens[:i + 1]) for i in range(len(lens))], dtype=torch.int32)
+        N, T = 1, int(cu[-1])
+    d = kla_inputs.chunk_inputs(N, T, H, dk, dv, dtype=dt, seed=seed, h0_std=0.3, n_h0=len(lens) if lens else None, log_alpha_scale=0.1)
+    gen = torch.Generator().manual_seed(seed)
+    d_o, d_hT = (torch.randn(d[n].shape, generator=gen).to(d[n].dtype).cuda() for n in ("v", "h0"))
+    return [d[n].cuda() for n in ("q", "k", "v", "log_alpha", "eta", "h0")], d_o, d_hT, cu
+
+
+@pytest.mark.parametrize("dt,N,T,H,dk,dv,lens,opts", [
+    (B, 1, 1, 3, 128, 128, None, {}), (B, 2, 64, 2, 64, 64, None, {}), (B, 2, 200, 4, 128, 128, None, dict(normalize_q=True)),
+    (B, 3, 70, 8, 128, 256, None, {}), (B, 6, 127, 8, 64, 256, None, dict(gdn_beta=True)), (B, 10, 65, 10, 128, 256, None, {}),
+    (B, 0, 0, 5, 128, 128, [130, 0, 64, 1, 63], {}), (B, 0, 0, 9, 64, 256, [65] * 11, dict(normalize_q=True)),
+    (B, 0, 0, 1, 64, 64, [3] * 70, {}),
+    (F, 1, 1, 3, 128, 128, None, {}), (F, 2, 200, 4, 64, 64, None, dict(normalize_q=True)), (F, 5, 130, 8, 128, 128, None, {}),
+    (F, 10, 65, 8, 64, 128, None, dict(gdn_beta=True)), (F, 0, 0, 3, 128, 128, [64, 0, 127, 2], {}),
+])
+def test_saved_equals_recomputed(kla, dt, N, T, H, dk, dv, lens, opts):
+    x, d_o, d_hT, cu = _case(dt, N, T, H, dk, dv, lens, 11 + T)
+    if opts.get("gdn_beta"):                         # the gated delta rule needs keys of length one
+        x[1] = (x[1].float() / x[1].float().norm(dim=-1, keepdim=True)).to(dt)
+    packed = dict(cu_seqlens=None if cu is None else cu.cuda(), cu_seqlens_host=cu)
+    o, hT = kla.kla_chunk_fwd(*x[:5], 1e-6, h0=x[5], **packed, **opts)
+    ref = kla.kla_chunk_bwd(*x[:5], 1e-6, d_o, h0=x[5], d_hT=d_hT, **packed, **opts)
+    o_opts = (opts.get("normalize_q", False), opts.get("gdn_beta", False))
+    assert kla._fwd_save(*x[:5], 1e-6, x[5], packed["cu_seqlens"], cu, *o_opts)[2] is not None
+    for native in (True, False):                     # the native half of the binding and the calls step by step
+        with pytest.MonkeyPatch.context() as m:
+            if not native:
+                m.setattr(kla, "_native", kla._StepByStep)
+            y = [t.detach().requires_grad_(True) for t in x]
+            o2, h2 = kla.kla_chunk(*y[:5], 1e-6, h0=y[5], **packed, **opts)
+            assert torch.equal(o, o2) and torch.equal(hT, h2)
+            for a, b in zip(torch.autograd.grad([o2, h2], y, [d_o, d_hT]), ref.values()):
+                assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,T,H,dv", [(8, 70, 8, 128), (1, 4160, 2, 128), (2, 0, 2, 64)])
+def test_nothing_saved(kla, N, T, H, dv):
+    """One kernel, segments, no tokens: kla_chunk goes on as the two calls by hand do."""
+    x, d_o, d_hT, _ = _case(B, N, T, H, 128, dv, None, 5)
+    assert kla._fwd_save(*x[:5], 1e-6, x[5], None, None, False, False)[2] is None
+    y = [t.detach().requires_grad_(True) for t in x]
+    o, hT = kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
+    o2, h2 = kla.kla_chunk_fwd(*x[:5], 1e-6, h0=x[5])
+    assert torch.equal(o, o2) and torch.equal(hT, h2)
+    ref = kla.kla_chunk_bwd(*x[:5], 1e-6, d_o, h0=x[5], d_hT=d_hT)
+    for a, b in zip(torch.autograd.grad([o, hT], y, [d_o, d_hT]), ref.values()):
+        assert torch.equal(a, b)
+
+
+def test_no_grad_saves_nothing(kla):
+    x, _, _, _ = _case(B, 2, 200, 2, 128, 128, None, 3)
+    y = [t.detach().requires_grad_(True) for t in x]
+    torch.cuda.synchronize()
+    with torch.no_grad():
+        kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
+        before = torch.cuda.memory_allocated()
+        keep = kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
+        assert torch.cuda.memory_allocated() - before < 2 * sum(t.numel() * t.element_size() for t in keep)
+        assert not keep[0].requires_grad
