@@ -3,6 +3,8 @@
 // from the environment; everything is enqueued on the caller's stream.
 #include <math.h>
 
+#include <algorithm>
+#include <functional>
 #include <mutex>
 
 #include "../../include/kla.h"
@@ -90,7 +92,10 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
     return G;
 }
 
-int scan_waves(int n_chains, int dv, int dt, const Tune& tune);
+// The sequences of a call, as far as the lengths of its sweeps go: n of them of NT chunks each, or (cu != NULL) packed.
+struct Lengths { int n, NT; const int32_t* cu; };
+long busiest_cu(const Lengths& seqs, int H, int slices);
+int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tune& tune);
 
 // Packed batches: the order in which the scans take the sequences, behind the n_seq + 1 chunk offsets.  More than
 // kla::kOrderMax sequences have none: they are taken as they come.
@@ -149,7 +154,8 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
         segments(512);
         if (p->total > (size_t)KLA_STATIC_SCRATCH_BYTES && p->total != all) segments(dv >= 128 ? 1024 : 512);
     }
-    p->waves = scan_waves(p->n_states * H, dv, dt, p->tune);
+    const Lengths seqs = {p->n_states, (T + 63) / 64, cu_host};
+    p->waves = scan_waves(seqs, H, dv, dt, false, p->tune);
     // The fused kernel (two compute waves per workgroup) keeps the per-chunk objects on chip and needs nothing of the
     // workspace (a token size is still reported and asked for).  It runs batches of 384 to 2047 chains of sixteen state
     // columns with d_v <= 128 (8 x 8 heads x 4096 tokens: 116 against 124 us); below that its helper waves redo the
@@ -169,23 +175,62 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     return KLA_OK;
 }
 
-int scan_waves(int n_chains, int dv, int dt, const Tune& tune)
+// Chunk steps the busiest CU takes in a sweep of `slices` workgroups per (sequence, head), one at a time on a CU (a bf16
+// workgroup fills one with its LDS).  Equal lengths: rounds of workgroups times chunks.  A packed batch starts its workgroups
+// longest sequence first, each on the first CU to become free, so a second round of shorter ones costs less than a
+// round: that schedule is played through, for batches small enough that it matters.
+long busiest_cu(const Lengths& s, int H, int slices)
+{
+    constexpr int kCUs = 256;
+    if (!s.cu) return (((long)s.n * H + 7) / 8 * 8 * slices + kCUs - 1) / kCUs * (s.NT > 1 ? s.NT : 1);
+    const long per_seq = (long)H * slices;
+    long longest = 0, total = 0;
+    for (int i = 0; i < s.n; ++i) {
+        const long c = ((long)s.cu[i + 1] - s.cu[i] + 63) / 64;
+        longest = std::max(longest, c);
+        total += c;
+    }
+    if (s.n > 64 || s.n * per_seq > 4096) return std::max(longest, (total * per_seq + kCUs - 1) / kCUs);
+    int len[64];
+    for (int i = 0; i < s.n; ++i) len[i] = (s.cu[i + 1] - s.cu[i] + 63) / 64;
+    std::sort(len, len + s.n, std::greater<int>());
+    struct { long load; int n; } level[kCUs + 1] = {{0, kCUs}};   // CUs by load, least first
+    int k = 1;
+    for (int i = 0; i < s.n && len[i] > 0; ++i) {
+        for (long left = per_seq; left > 0;) {
+            const int m = (int)std::min<long>(left, level[0].n);
+            const long to = level[0].load + len[i];
+            left -= m;
+            if ((level[0].n -= m) == 0) std::copy(level + 1, level + k--, level);
+            int at = 0;
+            while (at < k && level[at].load < to) ++at;
+            if (at < k && level[at].load == to) level[at].n += m;
+            else { std::copy_backward(level + at, level + k, level + k + 1); ++k; level[at] = {to, m}; }
+        }
+    }
+    return level[k - 1].load;
+}
+
+int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tune& tune)
 {
     int w;
     if (tune.scan_waves) w = tune.scan_waves;        // tuning field: 1, 2 or 4 waves (16 state columns each) per workgroup
-    else if (dt == KLA_F32) w = f32_tiles((long)n_chains * (dv / 16));
+    else if (dt == KLA_F32) w = f32_tiles((long)seqs.n * H * (dv / 16));
     else {
-        // bf16: a workgroup fills a CU (LDS), so the scan runs in ceil(workgroups / 256) rounds of a length that depends on
-        // the waves of a workgroup.  Relative lengths of a chunk step with 1, 2, 4 and 8 waves, measured with the chip
-        // full (8 x 2048 tokens, 8 heads, d_v = 256: 174, 107, 85 us per call for 4, 2, 1 rounds of 1, 2, 4 waves; 16 x
-        // 2048, 16 heads, d_v = 256: 361 us for 4 rounds of 4 waves, 305 us for 2 of 8; 20 x 1024, 8 heads, d_v = 256: 117
-        // us for 3 of 4, 125 us for 2 of 8).  The cheapest wins; between equals the narrower, which uses more CUs.
-        const long chains8 = ((long)n_chains + 7) / 8 * 8;
-        const int step[4] = {100, 100, 136, 215};
+        // bf16: relative lengths of a chunk step with 1, 2, 4 and 8 waves, times the steps of the busiest CU; the cheapest wins,
+        // between equals the narrower, which uses more CUs.  Steps measured with the chip full (8 x 2048 tokens, 8 heads, d_v = 256:
+        // 174, 107, 85 us per call for 4, 2, 1 rounds of 1, 2, 4 waves; 16 x 2048, 16 heads, d_v = 256: 361 us for 4 rounds of 4
+        // waves, 305 us for 2 of 8; 20 x 1024, 8 heads, d_v = 256: 117 us for 3 of 4, 125 us for 2 of 8).  A forward that
+        // leaves its intermediates also stores 512 bytes per token, head and 16 columns, which more waves share a CU for: 8 x 700
+        // tokens, 8 heads, d_v = 256 48 us for 2 rounds of 2 waves, 40 for one of 4; 16 x 700 88 us for 2 of 4, 81 for one of 8.
+        // Packed, 12 sequences of 653 .. 2056 tokens, 8 heads, d_v = 256: 113 us with 8 waves, 93 with 4, whose second round is of
+        // short sequences (leaving intermediates: 174 and 143); 5 of 422 .. 1597, 16 heads, d_v = 128: 51 with 4, 45 with 2.
+        const int plain[4] = {100, 100, 136, 215}, saving[4] = {100, 100, 150, 290};
+        const int* step = saves ? saving : plain;
         long best = 0;
         w = 1;
         for (int i = 0; i < 4 && 16 << i <= dv; ++i) {
-            const long cost = (chains8 * (dv / (16 << i)) + 255) / 256 * step[i];
+            const long cost = busiest_cu(seqs, H, dv / (16 << i)) * step[i];
             if (i == 0 || cost < best) { best = cost; w = 1 << i; }
         }
     }
@@ -273,7 +318,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             if (kla::launch_segment_maps_bf16(sa, dk, maps, st) != hipSuccess) return KLA_ERR_HIP;
             if (kla::launch_segment_combine(h0, maps, seg_state, N, H, dk, dv, pl.seg_G, st) != hipSuccess) return KLA_ERR_HIP;
             sa.h0 = seg_state;
-            const int wseg = scan_waves(pl.n_states * pl.seg_G * H, dv, KLA_BF16, pl.tune);
+            const int wseg = scan_waves({pl.n_states * pl.seg_G, pl.seg_Lc, nullptr}, H, dv, KLA_BF16, false, pl.tune);
             return kla::launch_scan_bf16(sa, dk, wseg, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
@@ -294,6 +339,7 @@ struct BwdPlan {
     size_t off_rec, off_C, off_S, off_X, off_U, saved;
     size_t off_dS, off_Y, total;             // total: of both parts
     bool can_save;
+    int sweep_waves, save_waves;             // bf16: compute waves of the sweeps, and of a forward that leaves its intermediates
     // segment-parallel sweeps (base.seg_G > 1): maps of the segments, states entering them, and for the reverse
     // direction the state gradients leaving them and what each segment's pre-pass returns; all fp32
     size_t off_maps, off_segS, off_segG, off_segB;
@@ -328,6 +374,16 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     p->off_segG = round256(p->off_segS + segst);
     p->off_segB = round256(p->off_segG + segst);
     p->total = p->saved + round256(p->off_segB + segst);
+    // Sweeps: two waves (32 state columns) per workgroup once that still gives a workgroup per CU, four (64 columns) where that
+    // shortens the work of the busiest CU: their visits are about 1.15 times as long (call of 8 x 4096 tokens, 8 heads, one round
+    // either way: 469 us with two, 511 us with four; 9 x 2000, two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347;
+    // 40 x 1000, five rounds against three: 584, 520)
+    const Lengths seqs = {p->base.n_states, (T + 63) / 64, cu_host};
+    const long chains8 = ((long)p->base.n_states * H + 7) / 8 * 8;
+    p->sweep_waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
+    if (dt == KLA_BF16 && !p->base.tune.generic_bwd && p->sweep_waves == 2 && dv >= 64 &&
+        busiest_cu(seqs, H, dv / 64) * 115 < busiest_cu(seqs, H, dv / 32) * 100) p->sweep_waves = 4;
+    p->save_waves = scan_waves(seqs, H, dv, dt, true, p->base.tune);
     // A forward leaves its intermediates where it forms the very ones the backward would: not in one kernel (which rounds other
     // things), not in segments (whose number differs), not through the plain kernels.  And within a bound: what is kept lives
     // until the backward, in every layer of a model.
@@ -418,18 +474,11 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    // two waves (32 state columns) per workgroup once that still gives a workgroup per CU
-    const long chains8 = ((long)pl.base.n_states * H + 7) / 8 * 8;
-    const int waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
+    [[maybe_unused]] const int waves = pl.sweep_waves;
     if constexpr (sizeof(E) == 2) {
         if (fast) {
-            // four waves (64 columns) where that saves rounds of workgroups, one per CU: its visits are about 1.15 times as
-            // long (call of 8 x 4096 tokens, 8 heads, one round either way: 469 us with two, 511 us with four; 9 x 2000,
-            // two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347; 40 x 1000, five rounds against three: 584, 520)
-            const long wg2 = chains8 * (dv / 32), r2 = (wg2 + 255) / 256, r4 = (wg2 / 2 + 255) / 256;
-            const int bw = waves == 2 && r4 * 115 < r2 * 100 ? 4 : waves;
-            if (!have && kla::launch_bwd_states_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
-            if (kla::launch_bwd_scan_bf16(ba, dk, bw, st) != hipSuccess) return KLA_ERR_HIP;
+            if (!have && kla::launch_bwd_states_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
+            if (kla::launch_bwd_scan_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
@@ -475,7 +524,7 @@ int chunk_fwd_save_impl(const void* q, const void* k, const void* v, const float
     hipError_t e;
     if constexpr (sizeof(E) == 2) {
         e = kla::launch_intra_bf16(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
-        if (e == hipSuccess) e = kla::launch_scan_bf16(sa, dk, pl.waves, st);
+        if (e == hipSuccess) e = kla::launch_scan_bf16(sa, dk, bp.save_waves, st);
     } else {
         e = kla::launch_intra_f32(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
         if (e == hipSuccess) e = kla::launch_scan_f32(sa, dk, pl.waves, st);
