@@ -90,7 +90,7 @@ class _StepByStep:
     @staticmethod
     def decode(*args):
         return None
-    chunk_fwd = chunk_fwd_save = chunk_bwd = decode
+    chunk_fwd = chunk_bwd = train = decode
 
 
 def _load_native(l):
@@ -547,19 +547,13 @@ def kla_debug_peak_probe(kind, buf=None, aux=None, n=0, iters=0):
 def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta):
     """kla_chunk_fwd that also leaves behind what kla_chunk_bwd would recompute: (o, hT, saved), saved None where the library
     leaves nothing behind or the memory for it is not there."""
-    if cu_seqlens is not None and cu_seqlens_host is None:
-        cu_seqlens_host = _host_cu(cu_seqlens)[0]
-    bits = _opts(normalize_q, gdn_beta) | DEFAULT_TUNE
-    r = _binding().chunk_fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else cu_seqlens_host, bits)
-    if type(r) is int:
-        raise KlaError(r, "kla_chunk_fwd")
-    if r is not None:
-        return r
     saved = None
     if q.is_cuda and q.dim() == 4 and v.dim() == 4 and q.dtype in (torch.bfloat16, torch.float32):
         cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
         sizes = (*q.shape, v.shape[-1], 64, _dt(q), cu_hp, n_seq)
-        keep = int(lib().kla_chunk_saved_bytes(*sizes, bits)) if max(sizes[:5]) < 2 ** 31 else 0
+        keep = 0
+        if max(sizes[:5]) < 2 ** 31:
+            keep = int(lib().kla_chunk_saved_bytes(*sizes, _opts(normalize_q, gdn_beta) | DEFAULT_TUNE))
         if keep:
             try:
                 saved = torch.empty(keep, dtype=torch.uint8, device=q.device)
@@ -571,7 +565,8 @@ def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, nor
 
 
 class _KlaChunk(torch.autograd.Function):
-    """kla_chunk_fwd / kla_chunk_bwd as one differentiable call (marshalling only: every step runs in the library)."""
+    """kla_chunk_fwd / kla_chunk_bwd as one differentiable call (marshalling only: every step runs in the library).  The native
+    half of the binding holds the same in C++ (KlaChunk) and takes ordinary calls."""
 
     @staticmethod
     def forward(ctx, q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, save):
@@ -605,4 +600,14 @@ def kla_chunk(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, cu_seqlens
     operands and states behind for it (kla_chunk_fwd_save of the C ABI: at d_k = d_v = 128 about 1.1 KB per token and head in
     bf16, at most KLA_SAVED_MAX_BYTES per call), elsewhere, and where that memory is not there, the backward recomputes
     them: same bits either way."""
+    # tracing, function transforms and forward-mode differentiation are for the Python function to take or to refuse
+    if (torch.is_grad_enabled() and torch._C._get_tracing_state() is None and not torch._C._are_functorch_transforms_active()
+            and torch.autograd.forward_ad._current_level < 0):
+        host = _host_cu(cu_seqlens)[0] if cu_seqlens is not None and cu_seqlens_host is None else cu_seqlens_host
+        r = _binding().train(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else host,
+                             _opts(normalize_q, gdn_beta) | DEFAULT_TUNE)
+        if type(r) is int:
+            raise KlaError(r, "kla_chunk_fwd")
+        if r is not None:
+            return r
     return _KlaChunk.apply(q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, torch.is_grad_enabled())

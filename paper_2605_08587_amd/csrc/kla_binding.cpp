@@ -11,6 +11,7 @@
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/version.h>
 
@@ -39,10 +40,8 @@ struct Api {
 
 // A plain, dense tensor: torch.Tensor or Parameter itself, strided and contiguous, with memory of its own.  (What
 // function transforms and fake modes pass around is not.)
-const at::Tensor* dense(PyObject* o)
+const at::Tensor* dense(const at::Tensor& t)
 {
-    if (!THPVariable_CheckExact(o)) return nullptr;
-    const at::Tensor& t = THPVariable_Unpack(o);
     if (!t.defined() || t.layout() != at::kStrided) return nullptr;
     const c10::TensorImpl* impl = t.unsafeGetTensorImpl();
     const c10::DispatchKeySet ks = impl->key_set();
@@ -51,22 +50,25 @@ const at::Tensor* dense(PyObject* o)
         return nullptr;
     return t.is_contiguous() ? &t : nullptr;
 }
-const at::Tensor* on_gpu(PyObject* o)
+const at::Tensor* dense(PyObject* o) { return THPVariable_CheckExact(o) ? dense(THPVariable_Unpack(o)) : nullptr; }
+template <typename O> const at::Tensor* on_gpu(const O& o)
 {
     const at::Tensor* t = dense(o);
     return t && t->is_cuda() ? t : nullptr;
 }
 // GPU tensor of this element type and these extents
-const at::Tensor* gpu(PyObject* o, at::ScalarType type, at::IntArrayRef shape)
+template <typename O> const at::Tensor* gpu(const O& o, at::ScalarType type, at::IntArrayRef shape)
 {
     const at::Tensor* t = on_gpu(o);
     return t && t->scalar_type() == type && t->sizes() == shape ? t : nullptr;
 }
+bool is_none(PyObject* o) { return o == Py_None; }
+bool is_none(const at::Tensor& t) { return !t.defined(); }
 // the same, or None (then *t stays null); false: neither
-bool gpu_or_none(PyObject* o, at::ScalarType type, at::IntArrayRef shape, const at::Tensor** t)
+template <typename O> bool gpu_or_none(const O& o, at::ScalarType type, at::IntArrayRef shape, const at::Tensor** t)
 {
     *t = nullptr;
-    if (o == Py_None) return true;
+    if (is_none(o)) return true;
     *t = gpu(o, type, shape);
     return *t != nullptr;
 }
@@ -122,27 +124,36 @@ struct Chunk {
     // args: q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host
     bool take(PyObject* const* a, bool diag)
     {
-        q = on_gpu(a[0]); v = on_gpu(a[2]);
+        double e;
+        return number(a[5], &e) && take(a[0], a[1], a[2], a[3], a[4], a[6], a[7], a[8], e, diag);
+    }
+    // the same of Python objects (None: not given) or of tensors (undefined: not given)
+    template <typename O>
+    bool take(const O& q_, const O& k_, const O& v_, const O& la_, const O& eta_, const O& h0_, const O& cu_, const O& host_, double eps_,
+              bool diag = false)
+    {
+        eps = eps_;
+        q = on_gpu(q_); v = on_gpu(v_);
         if (!q || !v || q->dim() != 4 || v->dim() != 4 || !type_of(*q, &dt)) return false;
         type = q->scalar_type();
         N = q->size(0); T = q->size(1); H = q->size(2); dk = q->size(3); dv = v->size(3);
         if (!ints({N, T, H, dk, dv}) || v->scalar_type() != type || v->sizes() != at::IntArrayRef({N, T, H, dv})) return false;
-        k = gpu(a[1], type, q->sizes());
-        la = diag ? gpu(a[3], at::kFloat, q->sizes()) : gpu(a[3], at::kFloat, {N, T, H});
-        eta = gpu(a[4], at::kFloat, {N, T, H});
-        if (!k || !la || !eta || !number(a[5], &eps)) return false;
+        k = gpu(k_, type, q->sizes());
+        la = diag ? gpu(la_, at::kFloat, q->sizes()) : gpu(la_, at::kFloat, {N, T, H});
+        eta = gpu(eta_, at::kFloat, {N, T, H});
+        if (!k || !la || !eta) return false;
         cu = nullptr; cu_host = nullptr; n_seq = 0; n_states = N;
-        if (a[7] != Py_None) {
-            cu = on_gpu(a[7]);
-            const at::Tensor* c = dense(a[8]);
+        if (!is_none(cu_)) {
+            cu = on_gpu(cu_);
+            const at::Tensor* c = dense(host_);
             if (!cu || !c || !c->is_cpu() || cu->scalar_type() != at::kInt || c->scalar_type() != at::kInt || cu->dim() != 1 ||
                 c->dim() != 1 || cu->numel() != c->numel() || cu->numel() < 2 || cu->numel() > INT_MAX)
                 return false;
             cu_host = static_cast<const int32_t*>(c->data_ptr());
             n_seq = (int)cu->numel() - 1;
             n_states = n_seq;
-        } else if (a[8] != Py_None) return false;
-        return gpu_or_none(a[6], at::kFloat, {n_states, H, dk, dv}, &h0);
+        } else if (!is_none(host_)) return false;
+        return gpu_or_none(h0_, at::kFloat, {n_states, H, dk, dv}, &h0);
     }
     at::Tensor empty(at::IntArrayRef shape, at::ScalarType t) const { return at::empty(shape, q->options().dtype(t).requires_grad(false)); }
 };
@@ -246,51 +257,34 @@ PyObject* chunk_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// The forward of a training step: chunk_fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, opts)
-// -> (out, hT, saved); saved is None where the library leaves nothing behind for the backward, or where there is no memory for it
-// (the backward then recomputes it)
-PyObject* chunk_fwd_save(PyObject*, PyObject* const* a, Py_ssize_t n)
+// The gradients dq, dk, dv, dlog_alpha, deta, dh0 (if wanted), all of them new, and the status of the call.  saved: what a forward with
+// the same arguments left behind, or null.
+int run_bwd(const Chunk& c, const at::Tensor& d_o, const at::Tensor* d_hT, const at::Tensor* saved, bool want_dh0, int chunk, unsigned opts,
+            at::Tensor (&g)[6])
 {
-    HANDLE_TH_ERRORS
-    if (n != 10 || !api.fwd_save) Py_RETURN_NONE;
-    Chunk c;
-    long opts;
-    if (!c.take(a, false) || !integer(a[9], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
-    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk = (int)c.dk, dv = (int)c.dv, chunk = 64;
-    std::optional<at::Tensor> out, hT, saved;
-    int rc;
-    {
-        const NoGil no_gil;
-        const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
-        const size_t keep = api.saved_bytes(N, T, H, dk, dv, chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts);
-        const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
-        out = c.empty({c.N, c.T, c.H, c.dv}, c.type);
-        hT = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
-        if (keep) {
-            try { saved = c.empty({(int64_t)keep}, at::kByte); } catch (const c10::OutOfMemoryError&) {}
-        }
-        const int32_t* cu = static_cast<const int32_t*>(ptr(c.cu));
-        float* h = static_cast<float*>(hT->data_ptr());
-        if (saved)
-            rc = api.fwd_save(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), out->data_ptr(), h, cu,
-                              c.cu_host, c.n_seq, N, T, H, dk, dv, chunk, c.dt, ws.data_ptr(), ws.nbytes(), saved->data_ptr(), keep, stream(),
-                              (unsigned)opts);
-        else
-            rc = api.fwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), out->data_ptr(), h, cu, c.cu_host,
-                         c.n_seq, N, T, H, dk, dv, chunk, c.dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
-    }
-    if (rc != KLA_OK) return PyLong_FromLong(rc);
-    PyObject* r = PyTuple_New(3);
-    if (!r) return nullptr;
-    PyTuple_SET_ITEM(r, 0, wrap(out));
-    PyTuple_SET_ITEM(r, 1, wrap(hT));
-    PyTuple_SET_ITEM(r, 2, wrap(saved));
-    return r;
-    END_HANDLE_TH_ERRORS
+    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk = (int)c.dk, dv = (int)c.dv;
+    const size_t need = (saved ? api.bwd_saved_bytes : api.bwd_bytes)(N, T, H, dk, dv, chunk, c.dt, c.cu_host, c.n_seq, opts & ~3u);
+    const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
+    g[0] = c.empty(c.q->sizes(), c.type);
+    g[1] = c.empty(c.q->sizes(), c.type);
+    g[2] = c.empty(c.v->sizes(), c.type);
+    g[3] = c.empty({c.N, c.T, c.H}, at::kFloat);
+    g[4] = c.empty({c.N, c.T, c.H}, at::kFloat);
+    if (want_dh0) g[5] = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
+    float *g_la = static_cast<float*>(g[3].data_ptr()), *g_eta = static_cast<float*>(g[4].data_ptr());
+    float* g_h0 = want_dh0 ? static_cast<float*>(g[5].data_ptr()) : nullptr;
+    const int32_t* cu = static_cast<const int32_t*>(ptr(c.cu));
+    if (saved)
+        return api.bwd_saved(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), d_o.data_ptr(), fptr(d_hT),
+                             g[0].data_ptr(), g[1].data_ptr(), g[2].data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk, dv,
+                             chunk, c.dt, ws.data_ptr(), ws.nbytes(), ptr(saved), saved->nbytes(), stream(), opts);
+    return api.bwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), d_o.data_ptr(), fptr(d_hT),
+                   g[0].data_ptr(), g[1].data_ptr(), g[2].data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk, dv, chunk, c.dt,
+                   ws.data_ptr(), ws.nbytes(), stream(), opts);
 }
 
 // chunk_bwd(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, d_o, d_hT, want_dh0, chunk, opts, saved)
-// -> (dq, dk, dv, dlog_alpha, deta, dh0), all of them new; saved: of chunk_fwd_save with the same arguments, or None
+// -> (dq, dk, dv, dlog_alpha, deta, dh0)
 PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
@@ -299,47 +293,115 @@ PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     Chunk c;
     long chunk, opts;
     if (!c.take(a, false) || !integer(a[12], INT_MIN, INT_MAX, &chunk) || !integer(a[13], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
-    const at::Tensor *d_o = gpu(a[9], c.type, {c.N, c.T, c.H, c.dv}), *d_hT = nullptr;
+    const at::Tensor *d_o = gpu(a[9], c.type, {c.N, c.T, c.H, c.dv}), *d_hT = nullptr, *saved = nullptr;
     if (!d_o || !gpu_or_none(a[10], at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &d_hT)) Py_RETURN_NONE;
-    const at::Tensor* saved = nullptr;
     if (a[14] != Py_None && !(saved = on_gpu(a[14]))) Py_RETURN_NONE;
-    const int N = (int)c.N, T = (int)c.T, H = (int)c.H, dk_ = (int)c.dk, dv_ = (int)c.dv;
-    std::optional<at::Tensor> dq, dk, dv, dla, deta, dh0;
+    at::Tensor g[6];
     int rc;
     {
         const NoGil no_gil;
-        const size_t need = (saved ? api.bwd_saved_bytes : api.bwd_bytes)(N, T, H, dk_, dv_, (int)chunk, c.dt, c.cu_host, c.n_seq, (unsigned)opts & ~3u);
-        const at::Tensor ws = c.empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
-        dq = c.empty(c.q->sizes(), c.type);
-        dk = c.empty(c.q->sizes(), c.type);
-        dv = c.empty(c.v->sizes(), c.type);
-        dla = c.empty({c.N, c.T, c.H}, at::kFloat);
-        deta = c.empty({c.N, c.T, c.H}, at::kFloat);
-        if (want_dh0) dh0 = c.empty({c.n_states, c.H, c.dk, c.dv}, at::kFloat);
-        float *g_la = static_cast<float*>(dla->data_ptr()), *g_eta = static_cast<float*>(deta->data_ptr());
-        float* g_h0 = dh0 ? static_cast<float*>(dh0->data_ptr()) : nullptr;
-        const int32_t* cu = static_cast<const int32_t*>(ptr(c.cu));
-        if (saved)
-            rc = api.bwd_saved(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT),
-                               dq->data_ptr(), dk->data_ptr(), dv->data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk_, dv_,
-                               (int)chunk, c.dt, ws.data_ptr(), ws.nbytes(), ptr(saved), saved->nbytes(), stream(), (unsigned)opts);
-        else
-            rc = api.bwd(ptr(c.q), ptr(c.k), ptr(c.v), fptr(c.la), fptr(c.eta), (float)c.eps, fptr(c.h0), ptr(d_o), fptr(d_hT), dq->data_ptr(),
-                         dk->data_ptr(), dv->data_ptr(), g_la, g_eta, g_h0, cu, c.cu_host, c.n_seq, N, T, H, dk_, dv_, (int)chunk, c.dt,
-                         ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+        rc = run_bwd(c, *d_o, d_hT, saved, want_dh0, (int)chunk, (unsigned)opts, g);
     }
     if (rc != KLA_OK) return PyLong_FromLong(rc);
     PyObject* r = PyTuple_New(6);
     if (!r) return nullptr;
-    const std::optional<at::Tensor>* g[6] = {&dq, &dk, &dv, &dla, &deta, &dh0};
-    for (int i = 0; i < 6; ++i) PyTuple_SET_ITEM(r, i, wrap(*g[i]));
+    for (int i = 0; i < 6; ++i) PyTuple_SET_ITEM(r, i, g[i].defined() ? THPVariable_Wrap(g[i]) : Py_NewRef(Py_None));
     return r;
     END_HANDLE_TH_ERRORS
 }
 
+// ---- kla_chunk: the two directions as one node of the autograd graph -------------------------------------------------------
+// What _KlaChunk of the Python module does, without Python in it: the engine runs a backward on a thread of its own, which would
+// have to wait for the interpreter twice.  A step of 2 x 35 tokens, 8 heads (30 us of kernels) 119 -> 57 us.
+struct Refused { int code; };                            // by the library, in the forward: handed back as its status code
+
+struct KlaChunk : public torch::autograd::Function<KlaChunk> {
+    // c: of these very tensors
+    static torch::autograd::variable_list forward(torch::autograd::AutogradContext* ctx, const at::Tensor& q, const at::Tensor& k,
+                                                  const at::Tensor& v, const at::Tensor& la, const at::Tensor& eta,
+                                                  const std::optional<at::Tensor>& h0,
+                                                  const Chunk* c, const at::Tensor* cu_host, int64_t opts, bool wanted)
+    {
+        const int N = (int)c->N, T = (int)c->T, H = (int)c->H, dk = (int)c->dk, dv = (int)c->dv, chunk = 64;
+        const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts & ~3u);
+        const size_t keep = wanted ? api.saved_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts) : 0;
+        const at::Tensor ws = c->empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
+        const at::Tensor out = c->empty({c->N, c->T, c->H, c->dv}, c->type), hT = c->empty({c->n_states, c->H, c->dk, c->dv}, at::kFloat);
+        at::Tensor saved;
+        if (keep) {
+            // no memory for it: the backward recomputes
+            try { saved = c->empty({(int64_t)keep}, at::kByte); } catch (const c10::OutOfMemoryError&) {}
+        }
+        const int32_t* cu = static_cast<const int32_t*>(ptr(c->cu));
+        float* h = static_cast<float*>(hT.data_ptr());
+        const int rc = saved.defined()
+            ? api.fwd_save(ptr(&q), ptr(&k), ptr(&v), fptr(&la), fptr(&eta), (float)c->eps, fptr(c->h0), out.data_ptr(), h, cu, c->cu_host,
+                           c->n_seq, N, T, H, dk, dv, chunk, c->dt, ws.data_ptr(), ws.nbytes(), saved.data_ptr(), keep, stream(), (unsigned)opts)
+            : api.fwd(ptr(&q), ptr(&k), ptr(&v), fptr(&la), fptr(&eta), (float)c->eps, fptr(c->h0), out.data_ptr(), h, cu, c->cu_host,
+                      c->n_seq, N, T, H, dk, dv, chunk, c->dt, ws.data_ptr(), ws.nbytes(), stream(), (unsigned)opts);
+        if (rc != KLA_OK) throw Refused{rc};
+        if (wanted) {
+            ctx->save_for_backward({q, k, v, la, eta, h0 ? *h0 : at::Tensor(), saved});
+            ctx->set_materialize_grads(false);           // the library takes a missing d_hT for zeros
+            ctx->saved_data["eps"] = c->eps;
+            ctx->saved_data["opts"] = opts;
+            if (c->cu) { ctx->saved_data["cu"] = *c->cu; ctx->saved_data["cu_host"] = *cu_host; }
+        }
+        return {out, hT};
+    }
+
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads)
+    {
+        const torch::autograd::variable_list s = ctx->get_saved_variables();
+        const auto cu = ctx->saved_data.find("cu");
+        at::Tensor cu_dev, cu_host;
+        if (cu != ctx->saved_data.end()) { cu_dev = cu->second.toTensor(); cu_host = ctx->saved_data["cu_host"].toTensor(); }
+        Chunk c;
+        // (a hook on saved tensors may hand back others than it was given)
+        TORCH_CHECK(c.take(s[0], s[1], s[2], s[3], s[4], s[5], cu_dev, cu_host, ctx->saved_data["eps"].toDouble()),
+                    "kla_chunk: the saved tensors are not those of the forward");
+        const bool want_dh0 = s[5].defined() && ctx->needs_input_grad(5);
+        const at::Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros_like(s[2]);
+        const at::Tensor d_hT = grads[1].defined() ? grads[1].contiguous() : at::Tensor();
+        TORCH_CHECK(d_o.is_cuda() && d_o.scalar_type() == c.type && d_o.sizes() == s[2].sizes() &&
+                    (!d_hT.defined() || (d_hT.is_cuda() && d_hT.scalar_type() == at::kFloat && d_hT.sizes() == at::IntArrayRef({c.n_states, c.H, c.dk, c.dv}))),
+                    "kla_chunk: gradients that do not fit the outputs");
+        at::Tensor g[6];
+        const int rc = run_bwd(c, d_o, d_hT.defined() ? &d_hT : nullptr, s[6].defined() ? &s[6] : nullptr, want_dh0, 64,
+                               (unsigned)ctx->saved_data["opts"].toInt(), g);
+        TORCH_CHECK(rc == KLA_OK, "kla_chunk_bwd failed: ", rc);
+        return {g[0], g[1], g[2], g[3], g[4], g[5], at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
+    }
+};
+
+// train(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, opts) -> (out, hT), differentiable
+PyObject* train(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 10 || !api.fwd_save) Py_RETURN_NONE;
+    Chunk c;
+    long opts;
+    if (!c.take(a, false) || !integer(a[9], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
+    torch::autograd::variable_list r;
+    try {
+        const NoGil no_gil;
+        bool wanted = c.h0 && c.h0->requires_grad();
+        for (const at::Tensor* t : {c.q, c.k, c.v, c.la, c.eta}) wanted = wanted || t->requires_grad();
+        r = KlaChunk::apply(*c.q, *c.k, *c.v, *c.la, *c.eta, c.h0 ? std::optional<at::Tensor>(*c.h0) : std::nullopt, &c, c.cu ? &THPVariable_Unpack(a[8]) : nullptr,
+                            (int64_t)opts, wanted);
+    } catch (const Refused& e) {
+        return PyLong_FromLong(e.code);
+    }
+    PyObject* t = PyTuple_New(2);
+    if (!t) return nullptr;
+    for (int i = 0; i < 2; ++i) PyTuple_SET_ITEM(t, i, THPVariable_Wrap(r[i]));
+    return t;
+    END_HANDLE_TH_ERRORS
+}
+
 #define KLA_FASTCALL(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {KLA_FASTCALL(bind), KLA_FASTCALL(decode), KLA_FASTCALL(chunk_fwd), KLA_FASTCALL(chunk_fwd_save),
-                         KLA_FASTCALL(chunk_bwd), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {KLA_FASTCALL(bind), KLA_FASTCALL(decode), KLA_FASTCALL(chunk_fwd), KLA_FASTCALL(chunk_bwd),
+                         KLA_FASTCALL(train), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "kla_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
