@@ -59,6 +59,7 @@ struct Plan {
     size_t order_bytes;  // of these, what the scan order of a packed batch adds
     int seg_G, seg_Lc;   // segment-parallel scan: segments per sequence (1 = off) and chunks per segment
     int waves;           // compute waves per scan workgroup (of the unsegmented scan)
+    bool rows;           // bf16 only: the scan that splits a chunk by rows
     bool fused;          // bf16 only: one kernel, no intra-chunk stage, nothing in the workspace
     int fwd_seg_G;       // make_bwd_plan only: the forward's segments (seg_G are the backward's there)
     Tune tune;
@@ -156,6 +157,10 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     }
     const Lengths seqs = {p->n_states, (T + 63) / 64, cu_host};
     p->waves = scan_waves(seqs, H, dv, dt, false, p->tune);
+    // Up to 256 chains of sixteen columns each have a CU to themselves: the scan that shares a chain among the waves of one (8
+    // heads of 128 columns, 700 tokens: 18.7 against 20.9 us; 256 chains, 4 x 1000 tokens of 8 heads: 27.5 against 29.3; 384: 35.7
+    // against 26.0).  Same bits.
+    p->rows = dt == KLA_BF16 && !p->tune.scan_waves && !p->tune.generic_scan && ((long)p->n_states * H + 7) / 8 * 8 * (dv / 16) <= 256;
     // The fused kernel (two compute waves per workgroup) keeps the per-chunk objects on chip and needs nothing of the
     // workspace (a token size is still reported and asked for).  It runs batches of 384 to 2047 chains of sixteen state
     // columns with d_v <= 128 (8 x 8 heads x 4096 tokens: 116 against 124 us); below that its helper waves redo the
@@ -325,7 +330,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
     const int waves = pl.waves;
     if constexpr (sizeof(E) == 2) {
         if (!pl.tune.generic_scan)                       // else the plain kernel (A/B testing)
-            return kla::launch_scan_bf16(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+            return (pl.rows ? kla::launch_scan_rows_bf16(sa, dk, st) : kla::launch_scan_bf16(sa, dk, waves, st)) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4) return kla::launch_scan_f32(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     else                          return kla::launch_scan(sa, dk, waves > 4 ? 4 : waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
@@ -524,7 +529,7 @@ int chunk_fwd_save_impl(const void* q, const void* k, const void* v, const float
     hipError_t e;
     if constexpr (sizeof(E) == 2) {
         e = kla::launch_intra_bf16(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
-        if (e == hipSuccess) e = kla::launch_scan_bf16(sa, dk, bp.save_waves, st);
+        if (e == hipSuccess) e = pl.rows ? kla::launch_scan_rows_bf16(sa, dk, st) : kla::launch_scan_bf16(sa, dk, bp.save_waves, st);
     } else {
         e = kla::launch_intra_f32(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
         if (e == hipSuccess) e = kla::launch_scan_f32(sa, dk, pl.waves, st);

@@ -97,6 +97,8 @@ hipError_t launch_scan_f32(const ScanArgs<float>& a, int dk, int tiles, hipStrea
 // bf16 specialisations (direct global->LDS copies, swizzled token-major staging, transposing LDS reads)
 hipError_t launch_intra_bf16(const IntraArgs<bf16_t>& a, int dk, IntraMode mode, int n_chunks, hipStream_t st);
 hipError_t launch_scan_bf16(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
+// the same scan with a workgroup of nine waves per 16 state columns (kla_chunk_rows_bf16.hip); no segments
+hipError_t launch_scan_rows_bf16(const ScanArgs<bf16_t>& a, int dk, hipStream_t st);
 hipError_t launch_scan_bf16_diag(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);   // diagonal gating
 // Fused forward (no intra-chunk stage, no workspace): waves = 1 or 2; fixed-length, packed or segmented batches.
 hipError_t launch_scan_fused_bf16(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
