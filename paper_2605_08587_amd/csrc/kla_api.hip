@@ -225,12 +225,13 @@ int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tun
         // bf16: relative lengths of a chunk step with 1, 2, 4 and 8 waves, times the steps of the busiest CU; the cheapest wins,
         // between equals the narrower, which uses more CUs.  Steps measured with the chip full (8 x 2048 tokens, 8 heads, d_v = 256:
         // 174, 107, 85 us per call for 4, 2, 1 rounds of 1, 2, 4 waves; 16 x 2048, 16 heads, d_v = 256: 361 us for 4 rounds of 4
-        // waves, 305 us for 2 of 8; 20 x 1024, 8 heads, d_v = 256: 117 us for 3 of 4, 125 us for 2 of 8).  A forward that
+        // waves, 305 us for 2 of 8; 20 x 1024, 8 heads, d_v = 256: 117 us for 3 of 4, 125 us for 2 of 8; with the two rings of the four
+        // waves 300, 299, 101 us and, 40 x 1024, 16 heads, d_v = 128, 265 us for 5 of 4, 282 us for 3 of 8).  A forward that
         // leaves its intermediates also stores 512 bytes per token, head and 16 columns, which more waves share a CU for: 8 x 700
         // tokens, 8 heads, d_v = 256 48 us for 2 rounds of 2 waves, 40 for one of 4; 16 x 700 88 us for 2 of 4, 81 for one of 8.
         // Packed, 12 sequences of 653 .. 2056 tokens, 8 heads, d_v = 256: 113 us with 8 waves, 93 with 4, whose second round is of
         // short sequences (leaving intermediates: 174 and 143); 5 of 422 .. 1597, 16 heads, d_v = 128: 51 with 4, 45 with 2.
-        const int plain[4] = {100, 100, 136, 215}, saving[4] = {100, 100, 150, 290};
+        const int plain[4] = {100, 100, 128, 215}, saving[4] = {100, 100, 150, 290};
         const int* step = saves ? saving : plain;
         long best = 0;
         w = 1;

@@ -39,17 +39,24 @@ struct SweepCfg16 {
     static constexpr int NVB = 64 / RPV;
     static constexpr int TPB = kTriPairs * 64 * 16;      // bytes of one triangular operand area
     static constexpr int NTB = (REV ? 2 : 1) * TPB / 1024;   // forward: T'; backward: M^T | P^T
+    // TWO (reverse, four compute waves at d_k = 128): two rings, as in the forward kernel (both sweeps of 8 x 4096 tokens, 8 heads,
+    // d_v = 256, and the assembly: 632 -> 594 us).  Q and P^T have one of two stages, from which OFF_Q and OFF_P count.
+    static constexpr bool TWO = REV && NW == 4 && DK == 128;
     // stage: K rows | (Q rows) | T'  or  M^T | P^T | V or dO slice | gamma_i | gamma_C/gamma_i | beta_i | (1/||q_i||)
-    static constexpr int OFF_Q = 64 * RB;
-    static constexpr int OFF_T = (REV ? 2 : 1) * 64 * RB, OFF_P = OFF_T + TPB, OFF_V = OFF_T + (REV ? 2 : 1) * TPB,
+    static constexpr int OFF_Q = TWO ? 0 : 64 * RB;
+    static constexpr int OFF_T = (REV && !TWO ? 2 : 1) * 64 * RB, OFF_P = TWO ? 64 * RB : OFF_T + TPB, OFF_V = OFF_T + (REV && !TWO ? 2 : 1) * TPB,
                          OFF_EG = OFF_V + 64 * VRW, STAGE = OFF_EG + (REV ? 1024 : 768);
     static constexpr int ORB = NW <= 2 ? 96 : 160;       // row stride of a staging tile (see the forward kernel)
     static constexpr int OSB = 64 * ORB;
     // Reverse sweep: the rows of dV are staged, in two parities, for the store wave.
-    static constexpr int NST = (3 * STAGE + (REV ? 2 * OSB : 0) <= 160 * 1024) ? 3 : 2;   // LDS ring depth
+    static constexpr int QST = TWO ? 64 * RB + TPB : 0;  // a stage of the second ring
+    static constexpr int NST = (3 * STAGE + 2 * QST + (REV ? 2 * OSB : 0) <= 160 * 1024) ? 3 : 2;   // LDS ring depth
+    static constexpr int OFF_OST = NST * STAGE + 2 * QST;
+    static constexpr int N_FIRST = NKB + TPB / 1024 + NVB + 1;   // TWO: copies of the first part
+    static_assert(!TWO || (NST == 3 && N_FIRST < 64), "two rings; 6-bit vmcnt");
     // swizzle of the V / dO slice, as in the forward kernel (period 8 rows: the same for every copy block)
     __host__ __device__ static constexpr int vswz(int row) { return NW == 4 ? 2 * ((row >> 1) & 3) : 0; }
-    static constexpr int LDS = NST * STAGE + (REV ? 2 * OSB : 0);
+    static constexpr int LDS = OFF_OST + (REV ? 2 * OSB : 0);
     static constexpr int NDMA = (REV ? 2 : 1) * NKB + NTB + NVB + 1;
     static_assert(LDS <= 160 * 1024 && NDMA < 64, "LDS budget of a gfx950 CU; 6-bit vmcnt");
 };
@@ -130,7 +137,10 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
     const uint32_t psel = (r & 1) ? 0x03020706u : 0x05040100u;
 
     // ---- global -> LDS copy of everything chunk c needs ---------------------------------------------------
-    auto issue = [&](int c, char* st) {
+    // part 0: all of it; TWO: part 1 = K, M^T, the dO slice, the vectors, part 2 = Q and P^T (at sq)
+    auto issue = [&](int c, char* st, char* sq, auto part_c) {
+        constexpr int part = decltype(part_c)::value;
+        constexpr bool first = part != 2, rest = REV && part != 1;
         const int clen = min(64, len - 64 * c);
         const char* kc = kbase + (size_t)(64 * c) * kq_row;
         const char* qc = qbase + (size_t)(64 * c) * kq_row;
@@ -141,35 +151,40 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
                 const int b = i;
                 const size_t o = (size_t)(b * RPB) * kq_row;
                 const int lo = gk[b % NGK];
-                dma16(kc + o, lo, st + b * 1024);
-                if constexpr (REV) dma16(qc + o, lo, st + C::OFF_Q + b * 1024);
+                if constexpr (first) dma16(kc + o, lo, st + b * 1024);
+                if constexpr (rest) dma16(qc + o, lo, sq + C::OFF_Q + b * 1024);
             });
-            static_for<C::NVB>([&](auto i) {
-                const int b = i;
-                dma16(vc + (size_t)(b * RPV) * v_row, gv, st + C::OFF_V + b * 1024);
-            });
+            if constexpr (first)
+                static_for<C::NVB>([&](auto i) {
+                    const int b = i;
+                    dma16(vc + (size_t)(b * RPV) * v_row, gv, st + C::OFF_V + b * 1024);
+                });
         } else {                                         // ragged last chunk: clamp the row
             static_for<C::NKB>([&](auto i) {
                 const int b = i;
                 const int row = b * RPB + lrow;
                 const int lo = min(row, clen - 1) * (int)kq_row + ((pcol ^ swz_piece<DK>(row)) * 16);
-                dma16(kc, lo, st + b * 1024);
-                if constexpr (REV) dma16(qc, lo, st + C::OFF_Q + b * 1024);
+                if constexpr (first) dma16(kc, lo, st + b * 1024);
+                if constexpr (rest) dma16(qc, lo, sq + C::OFF_Q + b * 1024);
             });
-            static_for<C::NVB>([&](auto i) {
-                const int b = i;
-                const int row = b * RPV + lane / VPP;
-                dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + b * 1024);
-            });
+            if constexpr (first)
+                static_for<C::NVB>([&](auto i) {
+                    const int b = i;
+                    const int row = b * RPV + lane / VPP;
+                    dma16(vc, min(row, clen - 1) * (int)v_row + (((lane % VPP) ^ C::vswz(row)) * 16), st + C::OFF_V + b * 1024);
+                });
         }
-        // forward: T' (first half of the record); backward: M^T | P^T (second and third)
-        static_for<C::NTB>([&](auto i) {
+        // forward: T' (first part of the record); backward: M^T, P^T (second and third)
+        static_for<C::TPB / 1024>([&](auto i) {
             const int b = i;
-            dma16(tc + (REV ? C::TPB : 0) + b * 1024, lane * 16, st + C::OFF_T + b * 1024);
+            if constexpr (first) dma16(tc + (REV ? C::TPB : 0) + b * 1024, lane * 16, st + C::OFF_T + b * 1024);
+            if constexpr (rest) dma16(tc + 2 * C::TPB + b * 1024, lane * 16, sq + C::OFF_P + b * 1024);
         });
         // gamma_i | gamma_C/gamma_i | beta_i, and for the reverse sweep 1/||q_i|| (the fifth vector of the record)
-        if constexpr (REV) dma16(tc + 3 * C::TPB, lane < 48 ? lane * 16 : 1024 + (lane - 48) * 16, st + C::OFF_EG);
-        else if (lane < 48) dma16(tc + 3 * C::TPB, lane * 16, st + C::OFF_EG);
+        if constexpr (first) {
+            if constexpr (REV) dma16(tc + 3 * C::TPB, lane < 48 ? lane * 16 : 1024 + (lane - 48) * 16, st + C::OFF_EG);
+            else if (lane < 48) dma16(tc + 3 * C::TPB, lane * 16, st + C::OFF_EG);
+        }
     };
 
     // 4x4 transposition inside each quad of lanes, then one 64-bit write: lane (r, g) ends up with row 4 g + (r & 3),
@@ -177,7 +192,8 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
     auto stage_quad = [&](u32x2 ob, char* dst) { *reinterpret_cast<u32x2*>(dst) = quad_transpose4x4(ob, q_lo, psel); };
 
     // ---- one chunk for this wave's 16 columns -----------------------------------------------------------
-    auto compute = [&](const char* st, char* ost, int c) {
+    // sq: where Q and P^T are (TWO: a stage of the second ring; else st)
+    auto compute = [&](const char* st, [[maybe_unused]] const char* sq, char* ost, int c) {
         const int clen = min(64, len - 64 * c);
         const char* pS = st + lane * 16;
         const char* pV = st + C::OFF_V + oV;
@@ -185,9 +201,9 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
         auto kslot = [&](int it, int kp) {
             return ld16(st + oK[kp] + 16 * it * RB);
         };
-        auto ktslot = [&](int kt, int jp, int base, u32x2& q0, u32x2& q1) {      // base 0: K^T, OFF_Q: Q^T
+        auto ktslot = [&](int kt, int jp, const char* tile, u32x2& q0, u32x2& q1) {      // tile: K or Q
             const int kp = kt >> 1, b = kt & 1;
-            const char* p = st + oKT[kp] + base + 32 * jp * RB + 8 * b;
+            const char* p = tile + oKT[kp] + 32 * jp * RB + 8 * b;
             q0 = lds_read_tr(p);
             q1 = lds_read_tr(p + 16 * RB);
         };
@@ -236,7 +252,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             }
             put_rows(reinterpret_cast<char*>(a.X) + (size_t)(t0 + 64L * c) * v_row, v_row, a.dv_dim, h, slice * NW + wave, Xq, clen, r, g);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 0, 0, kt[0][t][0], kt[0][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 0, st, kt[0][t][0], kt[0][t][1]);
             floatx4 U[4];
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
@@ -246,7 +262,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             mma_bf16(U[2], tsl[tri_pair(2, 1)], Xq[2], Xq[3]);
             mma_bf16(U[3], tsl[tri_pair(3, 1)], Xq[2], Xq[3]);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 1, 0, kt[1][t][0], kt[1][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 1, st, kt[1][t][0], kt[1][t][1]);
             u32x2 Udq[4];
 #pragma unroll
             for (int it = 0; it < 4; ++it) Udq[it] = to_quad(U[it] * edv[it]);   // U itself is not kept: the assembly forms it again from T' and X
@@ -257,7 +273,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
         } else {
             u32x4 psl[kTriPairs];
 #pragma unroll
-            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pS + C::OFF_P + i * 1024);
+            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(sq + lane * 16 + C::OFF_P + i * 1024);
             // ---- dU = diag(gamma_C/gamma_i) K dS' + P^T dO   (P^T upper triangular)
             floatx4 dU[4];
 #pragma unroll
@@ -270,7 +286,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
 #pragma unroll
             for (int it = 0; it < 4; ++it) dUq[it] = to_quad(dU[it]);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 0, C::OFF_Q, kt[0][t][0], kt[0][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 0, sq + C::OFF_Q, kt[0][t][0], kt[0][t][1]);
             // ---- Y = M^T dU
             floatx4 Y[4];
 #pragma unroll
@@ -280,7 +296,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
 #pragma unroll
             for (int it = 0; it < 4; ++it) mma_bf16(Y[it], tsl[triu_pair(it, 1)], dUq[2], dUq[3]);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 1, C::OFF_Q, kt[1][t][0], kt[1][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 1, sq + C::OFF_Q, kt[1][t][0], kt[1][t][1]);
             u32x2 gdOq[4], gdXq[4];
             u32x2 Yq[4];
 #pragma unroll
@@ -301,9 +317,9 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
 #pragma unroll
             for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[1][t][0], kt[1][t][1], gdOq[2], gdOq[3]);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 0, 0, kt[0][t][0], kt[0][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 0, st, kt[0][t][0], kt[0][t][1]);
 #pragma unroll
-            for (int t = 0; t < KB; ++t) ktslot(t, 1, 0, kt[1][t][0], kt[1][t][1]);
+            for (int t = 0; t < KB; ++t) ktslot(t, 1, st, kt[1][t][0], kt[1][t][1]);
 #pragma unroll
             for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[0][t][0], kt[0][t][1], gdXq[0], gdXq[1]);
 #pragma unroll
@@ -323,7 +339,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
         }
     };
 
-    char* ost0 = lds + NST * C::STAGE;                   // reverse sweep only
+    char* ost0 = lds + C::OFF_OST;                       // reverse sweep only
     char* ost1 = ost0 + C::OSB;
     // chunks are visited in the order i = 0 .. nch-1; the backward sweep starts at the last chunk
     auto chunk_of = [&](int i) { return REV ? nch - 1 - i : i; };
@@ -342,17 +358,33 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
         }
     }
 
+    if constexpr (C::TWO) {
+        if (wave == NW) {
+            // ---- the copy wave of two rings, as in the forward kernel (i: visits)
+            auto first = [&](int i) { issue(chunk_of(i), lds + (i % 3) * C::STAGE, nullptr, IntC<1>()); };
+            auto rest = [&](int i) { issue(chunk_of(i), nullptr, lds + 3 * C::STAGE + (i & 1) * C::QST, IntC<2>()); };
+            if (nch > 0) { first(0); rest(0); }
+            if (nch > 1) { first(1); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();
+            __syncthreads();
+            for (int i = 0; i < nch; ++i) {
+                if (i + 1 < nch) rest(i + 1);
+                if (i + 2 < nch) { first(i + 2); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();
+                __syncthreads();
+            }
+            return;
+        }
+    }
     if (wave == NW) {
         // ---- the copy wave: keeps the next NST-1 chunks on their way while one is computed -----------------
 #pragma unroll
         for (int p = 0; p < NST - 1; ++p)
-            if (p < nch) issue(chunk_of(p), lds + p * C::STAGE);
+            if (p < nch) issue(chunk_of(p), lds + p * C::STAGE, lds + p * C::STAGE, IntC<0>());
         if (NST == 3 && nch > 1) wait_vmcnt<C::NDMA>(); else wait_vmcnt<0>();
         __syncthreads();
         int spre = NST - 1;
         for (int i = 0; i < nch; ++i) {
             const bool ahead = i + NST - 1 < nch;
-            if (ahead) issue(chunk_of(i + NST - 1), lds + spre * C::STAGE);
+            if (ahead) issue(chunk_of(i + NST - 1), lds + spre * C::STAGE, lds + spre * C::STAGE, IntC<0>());
             if (NST == 3 && ahead) wait_vmcnt<C::NDMA>(); else wait_vmcnt<0>();
             __syncthreads();
             spre = (spre + 1 == NST) ? 0 : spre + 1;
@@ -365,7 +397,8 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
     int scur = 0;
     for (int i = 0; i < nch; ++i) {
         const int c = chunk_of(i);
-        compute(lds + scur * C::STAGE, (i & 1) ? ost1 : ost0, c);
+        char* st = lds + scur * C::STAGE;
+        compute(st, C::TWO ? lds + 3 * C::STAGE + (i & 1) * C::QST : st, (i & 1) ? ost1 : ost0, c);
         __syncthreads();
         scur = (scur + 1 == NST) ? 0 : scur + 1;
     }

@@ -63,11 +63,19 @@ struct Cfg {
     static constexpr int NVB = 64 / RPV;                 // copy blocks of the V slice (= 2 NW)
     static constexpr int TPB = kTriPairs * 64 * 16;      // bytes of one T' or P area; [T' | P] is one 12 KiB record
     static constexpr int NTB = 2 * TPB / 1024;           // = 12
+    // TWO (four compute waves at d_k = 128, of whose whole stage LDS holds two): K, T', the V slice and the vectors have a ring
+    // of three stages, Q and P one of two of their own, so that 31 of a chunk's 53 copies have two steps to arrive and only
+    // 22, issued first thing in the step, have one.  With two whole stages all 53 had to go out and land within a step
+    // (8 x 4096 tokens, 8 heads, d_v = 256: 153 -> 145 us, leaving its intermediates 264 -> 234; one 65K sequence of 8 heads,
+    // whose segments run here, 349 -> 336; 24 x 1500, 16 heads, d_v = 128: 252 -> 235).  A second barrier in the step, before the
+    // first read of Q, gives those 22 two steps as well and is dearer than that is worth (149, 240, 339, 236 us).
+    static constexpr bool TWO = NW == 4 && DK == 128 && !DG && !FU;
     // DG (diagonal gating): a third [64 x d_k] tile, the K operand of the state update, and gamma_C per channel.
     // FU: a ring stage holds K, Q and the V slice only; the record [T' | P | three vectors] of a chunk lives in one of
     // two record buffers behind the ring, written by a helper wave.
-    static constexpr int OFF_Q = 64 * RB, OFF_K2 = 2 * 64 * RB, OFF_T = (DG ? 3 : 2) * 64 * RB, OFF_P = OFF_T + TPB,
-                         OFF_V = FU ? OFF_T : OFF_T + 2 * TPB, OFF_EG = OFF_V + 64 * VRW, OFF_ED = OFF_EG + 256,
+    // (TWO: OFF_Q and R_P count from the stage of the second ring)
+    static constexpr int OFF_Q = TWO ? 0 : 64 * RB, OFF_K2 = 2 * 64 * RB, OFF_T = (DG ? 3 : TWO ? 1 : 2) * 64 * RB, OFF_P = TWO ? 64 * RB : OFF_T + TPB,
+                         OFF_V = FU ? OFF_T : OFF_T + (TWO ? 1 : 2) * TPB, OFF_EG = OFF_V + 64 * VRW, OFF_ED = OFF_EG + 256,
                          OFF_EQ = OFF_ED + 256, OFF_GC = OFF_EQ + 256, STAGE = FU ? OFF_EG : OFF_GC + (DG ? 512 : 0);
     // where a compute wave finds T', P and the vectors, relative to the ring stage (not fused) or the record buffer
     static constexpr int R_T = FU ? 0 : OFF_T, R_P = FU ? TPB : OFF_P, R_EG = FU ? 2 * TPB : OFF_EG;
@@ -83,17 +91,21 @@ struct Cfg {
     static constexpr int NGV = RPV >= 8 ? 1 : 8 / RPV;   // copy blocks after which the swizzle repeats
     static constexpr int OSB = 64 * ORB;
     static constexpr int EXTRA = FU ? 2 * RECB + 2 * HSCR_T + 2 * HSCR_P : 0;
-    static constexpr int NST = (3 * STAGE + 2 * OSB + EXTRA <= 160 * 1024) ? 3 : 2;   // LDS ring depth
-    static constexpr int LDS = NST * STAGE + 2 * OSB + EXTRA;
-    static constexpr int OFF_REC = NST * STAGE + 2 * OSB, OFF_HST = OFF_REC + 2 * RECB, OFF_HSP = OFF_HST + 2 * HSCR_T;   // FU only
+    static constexpr int QST = TWO ? 64 * RB + TPB : 0;  // a stage of the second ring
+    static constexpr int NST = (3 * STAGE + 2 * QST + 2 * OSB + EXTRA <= 160 * 1024) ? 3 : 2;   // LDS ring depth
+    static_assert(!TWO || NST == 3, "the first ring of the two");
+    static constexpr int OFF_OST = NST * STAGE + 2 * QST;
+    static constexpr int LDS = OFF_OST + 2 * OSB + EXTRA;
+    static constexpr int OFF_REC = OFF_OST + 2 * OSB, OFF_HST = OFF_REC + 2 * RECB, OFF_HSP = OFF_HST + 2 * HSCR_T;   // FU only
     // copy instructions per chunk (+1: decay factors)
     static constexpr int NDMA = FU ? NVB : (DG ? 3 : 2) * NKB + NTB + NVB + 1 + (DG ? 1 : 0);
     // Split schedule of a two-stage ring (diagonal gating at d_k = 128, whose stage holds three K-sized tiles): a chunk's
     // copies go out in two parts, each a full step before its first use, with a second barrier in the step between
     // them.  N_FIRST, N_REST: copy instructions of the two parts.
     static constexpr bool SPLIT = DG && NST == 2;
-    static constexpr int N_FIRST = NKB + NVB + NTB / 2 + 2, N_REST = 2 * NKB + NTB / 2;
+    static constexpr int N_FIRST = NKB + NVB + NTB / 2 + (DG ? 2 : 1), N_REST = 2 * NKB + NTB / 2;
     static_assert(!SPLIT || (N_FIRST + N_REST == NDMA && N_FIRST < 64 && N_REST < 64), "parts of the split schedule; 6-bit vmcnt");
+    static_assert(!TWO || N_FIRST < 64, "6-bit vmcnt");
     // waves of a workgroup: compute waves, then the copy wave and the wave that writes the outputs; fused: compute
     // waves, two T-side helpers, the copy wave, the write-out wave - placed so that the two P-side helpers after it land
     // on the SIMDs of the T-side ones - and those two
@@ -705,7 +717,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     // step reads first (the K tile, the V slice, T', the vectors), 2 = the rest (Q, the second K tile, P).  One tile
     // after the other: the K, Q and second-K rows of one token sit at the same offset of three arrays, and requests for
     // them issued back to back meet in the same memory channel.
-    auto issue = [&](int c, char* st, auto part_c) {
+    auto issue = [&](int c, char* st, char* sq, auto part_c) {
         constexpr int part = decltype(part_c)::value;
         constexpr bool first = part != 2, rest = part != 1;
         const int clen = min(64, len - 64 * c);
@@ -753,11 +765,11 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         }
         if constexpr (rest) {
             if constexpr (!FU) {
-                tile(qbase + (size_t)(64 * c) * kq_row, st + C::OFF_Q);
+                tile(qbase + (size_t)(64 * c) * kq_row, sq + C::OFF_Q);
                 if constexpr (DG) tile(k2base + (size_t)(64 * c) * kq_row, st + C::OFF_K2);
                 static_for<C::NTB / 2>([&](auto i) {
                     const int b = i;
-                    dma16(pc + b * 1024, lane * 16, st + C::OFF_P + b * 1024);
+                    dma16(pc + b * 1024, lane * 16, sq + C::OFF_P + b * 1024);
                 });
             }
         }
@@ -765,13 +777,14 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 
     // ---- one chunk of the recurrence for this wave's 16 columns ------------------------------------
     // rc: where T', P and the vectors of this chunk are (the ring stage itself, or a record buffer when fused)
-    auto compute = [&](const char* st, const char* rc, char* ost, [[maybe_unused]] int c) {
-        const char* pS = rc + lane * 16;                 // T' / P slots
+    // sq: where Q is, rp: where P is (TWO: the stage of the second ring; else the ring stage, and rc)
+    auto compute = [&](const char* st, const char* rc, const char* sq, const char* rp, char* ost, [[maybe_unused]] int c) {
+        const char* pS = rc + lane * 16;                 // T' slots
+        const char* pP = rp + lane * 16;                 // P slots
         const char* pV = st + C::OFF_V + oV;
         const char* pG = rc + C::R_EG + 16 * g;          // 4 consecutive floats: rows 4 g .. 4 g + 3
-        auto kslot = [&](int it, int kp, int base) {     // base 0: K, OFF_Q: Q
-            return ld16(st + oK[kp] + base + 16 * it * RB);
-        };
+        auto kslot = [&](int it, int kp) { return ld16(st + oK[kp] + 16 * it * RB); };
+        auto qslot = [&](int it, int kp) { return ld16(sq + oK[kp] + C::OFF_Q + 16 * it * RB); };
         auto ktslot = [&](int kt, int jp, u32x2& q0, u32x2& q1) {
             const int kp = kt >> 1, b = kt & 1;
             const char* p = st + oKT[kp] + (DG ? C::OFF_K2 : 0) + 32 * jp * RB + 8 * b;
@@ -800,12 +813,12 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         for (int it = 0; it < 4; ++it) { ks[it] = floatx4{0.f, 0.f, 0.f, 0.f}; qs[it] = floatx4{0.f, 0.f, 0.f, 0.f}; }
         u32x4 ka[2][4];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) ka[0][it] = kslot(it, 0, 0);
+        for (int it = 0; it < 4; ++it) ka[0][it] = kslot(it, 0);
 #pragma unroll
         for (int kp = 0; kp < KP; ++kp) {
             if (kp + 1 < KP) {
 #pragma unroll
-                for (int it = 0; it < 4; ++it) ka[(kp + 1) & 1][it] = kslot(it, kp + 1, 0);
+                for (int it = 0; it < 4; ++it) ka[(kp + 1) & 1][it] = kslot(it, kp + 1);
             }
 #pragma unroll
             for (int it = 0; it < 4; ++it) mma_bf16(ks[it], ka[kp & 1][it], Sq[2 * kp], Sq[2 * kp + 1]);
@@ -826,14 +839,14 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         if constexpr (C::SPLIT) __syncthreads();
         u32x4 qa[2][4];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) qa[0][it] = kslot(it, 0, C::OFF_Q);
+        for (int it = 0; it < 4; ++it) qa[0][it] = qslot(it, 0);
 
         // ---- Q S (off the chain) fills the matrix pipe while X = V - D_gamma K S is formed on the VALU
 #pragma unroll
         for (int kp = 0; kp < KP; ++kp) {
             if (kp + 1 < KP) {
 #pragma unroll
-                for (int it = 0; it < 4; ++it) qa[(kp + 1) & 1][it] = kslot(it, kp + 1, C::OFF_Q);
+                for (int it = 0; it < 4; ++it) qa[(kp + 1) & 1][it] = qslot(it, kp + 1);
             }
 #pragma unroll
             for (int it = 0; it < 4; ++it) mma_bf16(qs[it], qa[kp & 1][it], Sq[2 * kp], Sq[2 * kp + 1]);
@@ -882,7 +895,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 1, kt[1][t][0], kt[1][t][1]);
 #pragma unroll
-            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pS + C::R_P + i * 1024);
+            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pP + C::R_P + i * 1024);
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 Udq[it] = to_quad(U[it] * edv[it]);
@@ -924,7 +937,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 1, kt[1][t][0], kt[1][t][1]);
 #pragma unroll
-            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pS + C::R_P + i * 1024);
+            for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(pP + C::R_P + i * 1024);
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 if constexpr (NQ) o[it] = ld_f4(pG + 512 + 64 * it) * qs[it]; else o[it] = egv[it] * qs[it];
@@ -987,7 +1000,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             }
     };
 
-    char* ost0 = lds + NST * C::STAGE;
+    char* ost0 = lds + C::OFF_OST;
     char* ost1 = ost0 + C::OSB;
 
     // Fused mode: every wave passes nch + 2 barriers.  Step s = -2 .. nch - 1 ends with one; in step s the compute waves
@@ -1068,18 +1081,35 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             // before that barrier of step c + 1.  The stage they fill was left by chunk c - 1 at the end of its step.
             // Copies retire in order, so "all but the last n" is a wait on the counter.
             if (nch > 0) {
-                issue(0, lds, IntC<1>());
-                issue(0, lds, IntC<2>());
+                issue(0, lds, lds, IntC<1>());
+                issue(0, lds, lds, IntC<2>());
                 wait_vmcnt<C::N_REST>();                 // first part of chunk 0
             }
             __syncthreads();
             for (int c = 0; c < nch; ++c) {
                 const bool ahead = c + 1 < nch;
                 char* nx = lds + ((c + 1) & 1) * C::STAGE;
-                if (ahead) { issue(c + 1, nx, IntC<1>()); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();   // second part of chunk c
+                if (ahead) { issue(c + 1, nx, nx, IntC<1>()); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();   // second part of chunk c
                 __syncthreads();                         // in step c, before the first read of Q
-                if (ahead) { issue(c + 1, nx, IntC<2>()); wait_vmcnt<C::N_REST>(); } else wait_vmcnt<0>();    // first part of chunk c + 1
+                if (ahead) { issue(c + 1, nx, nx, IntC<2>()); wait_vmcnt<C::N_REST>(); } else wait_vmcnt<0>();    // first part of chunk c + 1
                 __syncthreads();                         // end of step c
+            }
+            return;
+        }
+    }
+    if constexpr (C::TWO) {
+        if (wave == C::W_COPY) {
+            // ---- the copy wave of two rings: step c brings Q and P of chunk c + 1, then the first part of chunk c + 2, into the
+            // stages that chunk c - 1 left.  Copies retire in order: all but the last N_FIRST are there when chunk c + 1 is.
+            auto first = [&](int c) { issue(c, lds + (c % 3) * C::STAGE, nullptr, IntC<1>()); };
+            auto rest = [&](int c) { issue(c, nullptr, lds + 3 * C::STAGE + (c & 1) * C::QST, IntC<2>()); };
+            if (nch > 0) { first(0); rest(0); }
+            if (nch > 1) { first(1); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();
+            __syncthreads();
+            for (int c = 0; c < nch; ++c) {
+                if (c + 1 < nch) rest(c + 1);
+                if (c + 2 < nch) { first(c + 2); wait_vmcnt<C::N_FIRST>(); } else wait_vmcnt<0>();
+                __syncthreads();
             }
             return;
         }
@@ -1088,7 +1118,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         // ---- the copy wave: keeps chunks c+1 .. c+NST-1 on their way while chunk c is computed ---------
 #pragma unroll
         for (int p = 0; p < NST - 1; ++p)
-            if (p < nch) issue(p, lds + p * C::STAGE, IntC<0>());
+            if (p < nch) issue(p, lds + p * C::STAGE, lds + p * C::STAGE, IntC<0>());
         if constexpr (FU) __syncthreads();               // step -2
         if (NST == 3 && nch > 1) wait_vmcnt<(NST == 3 ? C::NDMA : 0)>(); else wait_vmcnt<0>();      // chunk 0 has landed
         __syncthreads();
@@ -1096,7 +1126,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         for (int c = 0; c < nch; ++c) {
             const bool ahead = c + NST - 1 < nch;
             // the stage being refilled was read by chunk c-1, which every wave finished before the last barrier
-            if (ahead) issue(c + NST - 1, lds + spre * C::STAGE, IntC<0>());
+            if (ahead) issue(c + NST - 1, lds + spre * C::STAGE, lds + spre * C::STAGE, IntC<0>());
             // Copies retire in order and this wave issues nothing else: all but the NDMA just issued (when
             // NST = 3) have landed once the counter is down to NDMA, i.e. chunk c+1 is complete.
             if (NST == 3 && ahead) wait_vmcnt<(NST == 3 ? C::NDMA : 0)>(); else wait_vmcnt<0>();
@@ -1161,7 +1191,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             char* st = lds + (c & 1) * C::STAGE;
             if (c + 1 < nch) issue_part(c + 1, lds + ((c + 1) & 1) * C::STAGE);
             if (c > 0) write_out(c - 1, (c & 1) ? ost0 : ost1, tid, IntC<512>());
-            compute(st, st, (c & 1) ? ost1 : ost0, c);
+            compute(st, st, st, st, (c & 1) ? ost1 : ost0, c);
             wait_vmcnt<0>();                             // this wave's copies (and stores); the barrier covers the others'
             __syncthreads();
         }
@@ -1175,7 +1205,10 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     int scur = 0;                                        // ring position of chunk c
     for (int c = 0; c < nch; ++c) {
         char* ost = (c & 1) ? ost1 : ost0;
-        compute(lds + scur * C::STAGE, FU ? lds + C::OFF_REC + (c & 1) * C::RECB : lds + scur * C::STAGE, ost, c);
+        char* st = lds + scur * C::STAGE;
+        char* rc = FU ? lds + C::OFF_REC + (c & 1) * C::RECB : st;
+        char* sq = C::TWO ? lds + 3 * C::STAGE + (c & 1) * C::QST : st;
+        compute(st, rc, sq, C::TWO ? sq : rc, ost, c);
         // The barrier that ends a chunk step: staged outputs before their write-out; chunk c+1's operands before
         // their use; all reads of this stage before it is refilled; and the write-out of chunk c-1 (finished by
         // its wave before it arrives here) before the staging tile of that parity is written again in chunk c+1.
