@@ -83,7 +83,7 @@ __device__ __forceinline__ void write_transposed(char* out, const float* m, int 
 // and the fourth vector, d beta / d eta, is 1; kOptNormalizeQ: P^T carries 1/||q_i|| and the fifth vector holds it
 // (1 otherwise).
 // MODE (IntraMode): the forward's record, the backward's, or both but for the forward's copy of T'.  For both, Q K^T is formed twice, in
-// the orientation of P and in that of P^T: 46 us for 4096 chunk-heads of d_k = 128 where the two separate launches take 35 + 40.
+// the orientation of P and in that of P^T: 48 us for 4096 chunk-heads of d_k = 128 where the two separate launches take 35 + 40.
 template <int DK, int MODE>
 __global__ __launch_bounds__(256, MODE == kIntraPair ? 5 : 6) void intra_bf16_kernel(IntraArgs<bf16_t> a)
 {
