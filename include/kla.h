@@ -251,16 +251,14 @@ int kla_chunk_bwd_opts(const void *q, const void *k, const void *v,
 /*
  * A training step calls both directions on the same inputs, and the backward begins by recomputing what the forward had in
  * its hands: the per-chunk operands, the incoming state of every chunk, the right-hand sides X of eq. (6).  This pair passes them
- * on instead.  kla_chunk_fwd_save is kla_chunk_fwd_opts and also fills `saved`; kla_chunk_bwd_saved is kla_chunk_bwd_opts from
- * the unchanged inputs of that forward and `saved`, which it only reads.  Outputs and gradients are those of the two other
- * calls to the last bit, except for bf16 batches whose kla_chunk_fwd runs as one kernel (its workspace is a token 256 bytes): there
- * the pair rounds less, and its results differ from theirs within the rounding of bf16.
+ * on instead.  kla_chunk_fwd_save is kla_chunk_fwd_opts (same outputs, bit for bit, same workspace) and also fills `saved`;
+ * kla_chunk_bwd_saved is kla_chunk_bwd_opts (same gradients, bit for bit) from the unchanged inputs of that forward and `saved`,
+ * which it only reads.
  *   saved            device memory, 256-byte aligned, of at least kla_chunk_saved_bytes(...) bytes: about
  *                    (dk * dv / 64 + dv + 154) * sizeof(dt) bytes per token and head (fp32: one dv more).  0: this call
- *                    cannot leave its intermediates (shapes whose forward runs in segments, batches without a token, more than
- *                    KLA_SAVED_MAX_BYTES, the plain kernels, a forced one-kernel forward); the pair then returns KLA_ERR_SHAPE.
- *   workspace        of kla_chunk_fwd_save: kla_chunk_fwd_workspace_bytes_opts(..., opts | KLA_TUNE_UNFUSED);
- *                    of kla_chunk_bwd_saved: kla_chunk_bwd_saved_workspace_bytes(...)
+ *                    cannot leave its intermediates (shapes whose forward runs as one kernel or in segments, batches without a
+ *                    token, more than KLA_SAVED_MAX_BYTES, the plain kernels); the pair then returns KLA_ERR_SHAPE.
+ *   workspace        of kla_chunk_bwd_saved: kla_chunk_bwd_saved_workspace_bytes(...)
  * The size arguments and opts have to be those of the forward.
  */
 #define KLA_SAVED_MAX_BYTES (1024u << 20)

@@ -296,8 +296,7 @@ def kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, want_h
             raise ValueError("the single-stage hook takes no options")
         bits = KLA_TUNE_UNFUSED
     if workspace is None:
-        form = bits & ~3 if _saved is None else bits & ~3 | KLA_TUNE_UNFUSED
-        need = int(lib().kla_chunk_fwd_workspace_bytes_opts(N, T, H, dk, dv, chunk, dt, cu_hp, n_seq, form))
+        need = int(lib().kla_chunk_fwd_workspace_bytes_opts(N, T, H, dk, dv, chunk, dt, cu_hp, n_seq, bits & ~3))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty((N, T, H, dv), dtype=q.dtype, device=q.device)
@@ -599,9 +598,8 @@ def kla_chunk(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, cu_seqlens
     """Differentiable chunkwise forward for training loops: returns (o, hT) like kla_chunk_fwd; gradients with respect to
     q, k, v, log_alpha, eta and h0 come from kla_chunk_bwd.  Where a gradient is wanted, the forward leaves the per-chunk
     operands and states behind for it (kla_chunk_fwd_save of the C ABI: at d_k = d_v = 128 about 1.1 KB per token and head in
-    bf16, at most KLA_SAVED_MAX_BYTES per call); elsewhere, and where that memory is not there, the backward recomputes
-    them.  The results are those of kla_chunk_fwd and kla_chunk_bwd to the last bit, except for bf16 batches whose
-    kla_chunk_fwd is one kernel: there they are rounded less."""
+    bf16, at most KLA_SAVED_MAX_BYTES per call), elsewhere, and where that memory is not there, the backward recomputes
+    them: same bits either way."""
     # tracing, function transforms and forward-mode differentiation are for the Python function to take or to refuse
     if (torch.is_grad_enabled() and torch._C._get_tracing_state() is None and not torch._C._are_functorch_transforms_active()
             and torch.autograd.forward_ad._current_level < 0):

@@ -390,13 +390,11 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     if (dt == KLA_BF16 && !p->base.tune.generic_bwd && p->sweep_waves == 2 && dv >= 64 &&
         busiest_cu(seqs, H, dv / 64) * 115 < busiest_cu(seqs, H, dv / 32) * 100) p->sweep_waves = 4;
     p->save_waves = scan_waves(seqs, H, dv, dt, true, p->base.tune);
-    // A forward leaves its intermediates where it forms the very ones the backward would: not in segments (whose number
-    // differs), not through the plain kernels.  And within a bound: what is kept lives until the backward, in every layer of a
-    // model.  A batch whose plain forward is the fused kernel takes the two-kernel form here with X and U split, so that what it
-    // returns is no further from 64 bits (8 x 4096 tokens, 8 heads: 115 us for the fused kernel
-    // and 136 in the backward for what this form leaves behind in 196).
+    // A forward leaves its intermediates where it forms the very ones the backward would: not in one kernel (which rounds other
+    // things), not in segments (whose number differs), not through the plain kernels.  And within a bound: what is kept lives
+    // until the backward, in every layer of a model.
     const Tune& t = p->base.tune;
-    p->can_save = p->base.n_chunks > 0 && !t.fused && p->base.fwd_seg_G <= 1 && G <= 1 && !t.generic_scan && !t.generic_intra &&
+    p->can_save = p->base.n_chunks > 0 && !p->base.fused && p->base.fwd_seg_G <= 1 && G <= 1 && !t.generic_scan && !t.generic_intra &&
                   !t.generic_bwd && p->saved <= (size_t)KLA_SAVED_MAX_BYTES;
     return KLA_OK;
 }
@@ -528,7 +526,6 @@ int chunk_fwd_save_impl(const void* q, const void* k, const void* v, const float
     sa.N = N; sa.T = T; sa.NT = ia.NT; sa.H = H; sa.dv = dv;
     sa.wsT = ia.wsT; sa.wsP = ia.wsP; sa.wsG = nullptr; sa.opts = opts;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = nullptr; sa.gc_vec = nullptr;
-    sa.split = bp.base.fused;
     sa.s_chk = reinterpret_cast<E*>(sv + bp.off_S); sa.X = reinterpret_cast<E*>(sv + bp.off_X); sa.U = reinterpret_cast<E*>(sv + bp.off_U);
     hipError_t e;
     if constexpr (sizeof(E) == 2) {
@@ -862,14 +859,14 @@ int kla_chunk_fwd_save(const void* q, const void* k, const void* v, const float*
                        int n_seq, int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt, void* workspace,
                        size_t workspace_bytes, void* saved, size_t saved_bytes, void* hip_stream, unsigned opts)
 {
+    Plan pl;
+    int rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N, T, H, dk, dv, chunk,
+                                dt, opts, &pl);
+    if (rc != KLA_OK) return rc;
     BwdPlan bp;
-    int rc = make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &bp);
+    rc = make_bwd_plan(N, T, H, dk, dv, chunk, (int)dt, cu_seqlens_host, n_seq, opts, &bp);
     if (rc != KLA_OK) return rc;
     if (!bp.can_save) return KLA_ERR_SHAPE;
-    Plan pl;                                             // always the two-kernel form
-    rc = chunk_fwd_validate(q, k, v, log_alpha, eta, eps, h0, o, hT, cu_seqlens_dev, cu_seqlens_host, n_seq, N, T, H, dk, dv, chunk, dt,
-                            opts | KLA_TUNE_UNFUSED, &pl);
-    if (rc != KLA_OK) return rc;
     if (!buffer_ok(workspace, workspace_bytes, pl.total) || !buffer_ok(saved, saved_bytes, bp.saved)) return KLA_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     char *ws = static_cast<char*>(workspace), *sv = static_cast<char*>(saved);

@@ -323,16 +323,15 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
                                                   const Chunk* c, const at::Tensor* cu_host, int64_t opts, bool wanted)
     {
         const int N = (int)c->N, T = (int)c->T, H = (int)c->H, dk = (int)c->dk, dv = (int)c->dv, chunk = 64;
+        const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts & ~3u);
         const size_t keep = wanted ? api.saved_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts) : 0;
+        const at::Tensor ws = c->empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
         const at::Tensor out = c->empty({c->N, c->T, c->H, c->dv}, c->type), hT = c->empty({c->n_states, c->H, c->dk, c->dv}, at::kFloat);
         at::Tensor saved;
         if (keep) {
             // no memory for it: the backward recomputes
             try { saved = c->empty({(int64_t)keep}, at::kByte); } catch (const c10::OutOfMemoryError&) {}
         }
-        const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq,
-                                          ((unsigned)opts & ~3u) | (saved.defined() ? KLA_TUNE_UNFUSED : 0u));
-        const at::Tensor ws = c->empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
         const int32_t* cu = static_cast<const int32_t*>(ptr(c->cu));
         float* h = static_cast<float*>(hT.data_ptr());
         const int rc = saved.defined()

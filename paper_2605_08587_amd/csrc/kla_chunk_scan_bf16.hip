@@ -619,11 +619,7 @@ struct PHelper : HelperBase<DK> {
 // FU: fused mode, see the top of the file; a.wsT / a.wsP / a.wsG are not used, a.log_alpha / a.eta / a.eps are.
 // SV: the incoming state of every chunk and the rows of X stay behind for the backward pass (a.s_chk, a.X: put_checkpoint, put_rows),
 // stored by the compute waves as they hold them; T' comes from the backward's records and P from records of its own.
-// HL (SV only): X enters U = T' X and U enters P U as two 16-bit numbers each, high and low, twelve products more per chunk and wave.
-// For batches whose plain forward is the fused kernel: with them this form is nowhere further from 64 bits than that one. Relative
-// 2-norms of o and h_T (200 tokens, d = 128, an emulation of the roundings): independent keys fused 3.48e-3 / 2.77e-3, this form plain
-// 3.68e-3 / 3.06e-3, with HL 3.14e-3 / 2.55e-3; keys close to one another 6.82e-3 / 5.37e-3, 7.19e-3 / 4.09e-3, 6.00e-3 / 3.66e-3.
-template <int DK, int NW, bool NQ, bool DG = false, bool FU = false, bool SV = false, bool HL = false>
+template <int DK, int NW, bool NQ, bool DG = false, bool FU = false, bool SV = false>
 __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_kernel(ScanArgs<bf16_t> a)
 {
     typedef Cfg<DK, NW, DG, FU> C;
@@ -675,7 +671,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     const char* vbase = reinterpret_cast<const char*>(a.v) + (size_t)t0 * v_row + ((size_t)h * a.dv + slice * SLW) * 2;
     const char* k2base = DG ? reinterpret_cast<const char*>(a.kt_src) + (size_t)t0 * kq_row + (size_t)h * DK * 2 : nullptr;
     const char* gcbase = DG ? reinterpret_cast<const char*>(a.gc_vec) + ((size_t)ch0 * a.H + h) * DK * 4 : nullptr;
-    static_assert((!SV || (!DG && !FU)) && (!HL || SV), "plain scan only");
+    static_assert(!SV || (!DG && !FU), "plain scan only");
     // records: T', and P with the vectors behind it
     constexpr int REC = SV ? bwd_record_bytes<bf16_t>() : ws_record_bytes<bf16_t>(), RECP = SV ? pair_record_bytes<bf16_t>() : REC;
     const char* tpbase = FU ? nullptr : reinterpret_cast<const char*>(a.wsT) + ((size_t)ch0 * a.H + h) * REC;
@@ -853,8 +849,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         }
         u32x2 Xq[4];
         floatx4 Xf[3];                                   // fused mode: rows 16.. of X stay in fp32 until beta and the L U terms are in
-        const floatx4 X0 = quad_to_f(vq[0]) - egv[0] * ks[0];
-        Xq[0] = to_quad(X0);
+        Xq[0] = to_quad(quad_to_f(vq[0]) - egv[0] * ks[0]);
 #pragma unroll
         for (int it = 1; it < 4; ++it) {
             Xf[it - 1] = quad_to_f(vq[it]) - egv[it] * ks[it];
@@ -872,7 +867,6 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
         //      U_top = T'11 X_top, U_bot = T22 (B_bot X_bot - L21 U_top)
         floatx4 U[4];
         u32x2 Uq[4], Udq[4];
-        [[maybe_unused]] u32x2 Ul[4];                    // HL: what rounding to 16 bits leaves of U
         u32x4 psl[kTriPairs];
         if constexpr (!FU) {
 #pragma unroll
@@ -882,16 +876,6 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             }
             mma_bf16(U[2], tsl[tri_pair(2, 1)], Xq[2], Xq[3]);
             mma_bf16(U[3], tsl[tri_pair(3, 1)], Xq[2], Xq[3]);
-            if constexpr (HL) {
-                u32x2 Xl[4];
-                Xl[0] = to_quad(X0 - quad_to_f(Xq[0]));
-#pragma unroll
-                for (int it = 1; it < 4; ++it) Xl[it] = to_quad(Xf[it - 1] - quad_to_f(Xq[it]));
-#pragma unroll
-                for (int it = 0; it < 4; ++it) mma_bf16(U[it], tsl[tri_pair(it, 0)], Xl[0], Xl[1]);
-                mma_bf16(U[2], tsl[tri_pair(2, 1)], Xl[2], Xl[3]);
-                mma_bf16(U[3], tsl[tri_pair(3, 1)], Xl[2], Xl[3]);
-            }
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 1, kt[1][t][0], kt[1][t][1]);
 #pragma unroll
@@ -900,7 +884,6 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             for (int it = 0; it < 4; ++it) {
                 Udq[it] = to_quad(U[it] * edv[it]);
                 Uq[it] = to_quad(U[it]);
-                if constexpr (HL) Ul[it] = to_quad(U[it] - quad_to_f(Uq[it]));
             }
         }
         floatx4 o[4];
@@ -919,12 +902,6 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             }
             mma_bf16(o[2], psl[tri_pair(2, 1)], Uq[2], Uq[3]);
             mma_bf16(o[3], psl[tri_pair(3, 1)], Uq[2], Uq[3]);
-            if constexpr (HL) {
-#pragma unroll
-                for (int it = 0; it < 4; ++it) mma_bf16(o[it], psl[tri_pair(it, 0)], Ul[0], Ul[1]);
-                mma_bf16(o[2], psl[tri_pair(2, 1)], Ul[2], Ul[3]);
-                mma_bf16(o[3], psl[tri_pair(3, 1)], Ul[2], Ul[3]);
-            }
         } else {
             // Fused mode: block forward substitution over the four 16-row blocks (see the helper section for the record's
             // tiles), U_0 = (D0 B0) X_0, U_t = D_t (B_t X_t - sum_{j<t} L_tj U_j).  Its chain of eight dependent
@@ -1219,7 +1196,7 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
     store_final();
 }
 
-template <int DK, bool SV, bool HL>
+template <int DK, bool SV>
 static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st)
 {
     const int n_states = a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N);
@@ -1231,8 +1208,8 @@ static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st
     auto go = [&](auto nw_c) {
         constexpr int NW = decltype(nw_c)::value;
         const dim3 block(64 * Cfg<DK, NW>::NWAVES);
-        if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, true, false, false, SV, HL>), grid, block, 0, st, a);
-        else    hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, false, false, false, SV, HL>), grid, block, 0, st, a);
+        if (nq) hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, true, false, false, SV>), grid, block, 0, st, a);
+        else    hipLaunchKernelGGL((scan_bf16_kernel<DK, NW, false, false, false, SV>), grid, block, 0, st, a);
     };
     switch (waves) {
         case 1: go(IntC<1>()); break;
@@ -1245,9 +1222,8 @@ static hipError_t launch_dk(const ScanArgs<bf16_t>& a, int waves, hipStream_t st
 
 hipError_t launch_scan_bf16(const ScanArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (a.s_chk && a.split) return dk == 64 ? launch_dk<64, true, true>(a, waves, st) : launch_dk<128, true, true>(a, waves, st);
-    if (a.s_chk) return dk == 64 ? launch_dk<64, true, false>(a, waves, st) : launch_dk<128, true, false>(a, waves, st);
-    return dk == 64 ? launch_dk<64, false, false>(a, waves, st) : launch_dk<128, false, false>(a, waves, st);
+    if (a.s_chk) return dk == 64 ? launch_dk<64, true>(a, waves, st) : launch_dk<128, true>(a, waves, st);
+    return dk == 64 ? launch_dk<64, false>(a, waves, st) : launch_dk<128, false>(a, waves, st);
 }
 
 template <int DK>

@@ -86,7 +86,6 @@ template <typename E> struct ScanArgs {
     // incoming state of every chunk, X and (fp32) U, laid out as the backward's forward sweep leaves them.  wsT: the
     // backward's records, wsP: [P | three vectors] (kIntraPair).
     E* s_chk = nullptr; E* X = nullptr; E* U = nullptr;
-    bool split = false;                          // bf16, with s_chk: X and U as two 16-bit numbers each (see scan_bf16_kernel, HL)
 };
 // bf16, plain form (A/B reference of the specialised kernel below): waves = 1, 2 or 4, each wave of a workgroup carries 16
 // state columns through the whole sequence

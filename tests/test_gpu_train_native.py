@@ -88,6 +88,26 @@ def test_checkpointing(kla):
     _same(torch.autograd.grad(torch.utils.checkpoint.checkpoint(f, *x, use_reentrant=False).float().sum(), x), ref)
 
 
+@pytest.mark.parametrize("N,T,H,dk,dv", [(8, 130, 8, 128, 128), (12, 65, 9, 64, 64), (30, 64, 8, 128, 128)])
+def test_same_outputs_without_gradients(kla, N, T, H, dk, dv):
+    """bf16 batches whose plain forward is one kernel: kla_chunk gives kla_chunk_fwd's bits whether a gradient is wanted or not, so that
+    checkpointing whose first pass runs without gradients (re-entrant) differentiates the outputs it handed on."""
+    d = kla_inputs.chunk_inputs(N, T, H, dk, dv, seed=T + dv, h0_std=0.1)
+    x = [d[n].cuda().requires_grad_(True) for n in NAMES]
+    plain = kla.kla_chunk_fwd(*(t.detach() for t in x[:5]), 1e-6, h0=x[5].detach())
+    with torch.no_grad():
+        _same(plain, _call(kla, x))
+    got = _call(kla, x)
+    _same(plain, got)
+    w = torch.linspace(-1, 1, got[0].numel(), device="cuda").view(got[0].shape)
+    ref = torch.autograd.grad((got[0].float() * w).sum() + got[1].sum(), x)
+    again = torch.utils.checkpoint.checkpoint(lambda *y: _call(kla, y), *x, use_reentrant=True)
+    _same(plain, again)
+    # (the re-entrant form takes backward() only)
+    ((again[0].float() * w).sum() + again[1].sum()).backward()
+    _same(ref, [t.grad for t in x])
+
+
 def test_refusals(kla):
     x = _leaves()
     o, _ = _call(kla, x)

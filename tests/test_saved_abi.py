@@ -22,7 +22,7 @@ def test_sizes(lib):
         assert lib.kla_chunk_saved_bytes(*a) == saved
         # the two parts are the workspace of the backward that recomputes
         assert saved + lib.kla_chunk_bwd_saved_workspace_bytes(*a) == lib.kla_chunk_bwd_workspace_bytes(*a[:-1])
-    for none in ((1, 8192, 2, 128, 128), (2, 0, 2, 64, 64), (64, 1 << 15, 8, 64, 64)):   # segments, empty, too large
+    for none in ((8, 4096, 8, 128, 128), (1, 8192, 2, 128, 128), (2, 0, 2, 64, 64), (1, 1 << 20, 8, 64, 64)):   # one kernel, segments, empty, too large
         assert lib.kla_chunk_saved_bytes(*none, 64, kla.KLA_BF16, None, 0, 0) == 0
         assert lib.kla_chunk_bwd_saved_workspace_bytes(*none, 64, kla.KLA_BF16, None, 0, 0) == 0
     for bits in (kla.tune(generic_bwd=True), kla.tune(generic_scan=True), kla.tune(generic_intra=True), kla.tune(fused=True)):
@@ -45,21 +45,10 @@ def test_refusals(lib):
 
     for f, n in ((fwd, n_fwd), (bwd, n_bwd)):
         assert f(None) == E_NULL
-        assert f(sizes=[1, 8192, 2, 128, 128, 64, kla.KLA_BF16]) == E_SHAPE          # runs in segments: leaves nothing
+        assert f(sizes=[8, 4096, 8, 128, 128, 64, kla.KLA_BF16]) == E_SHAPE          # runs as one kernel: leaves nothing
         assert f(sizes=sizes[:-1] + [7]) == E_DTYPE
         assert f(ws=None) == E_WS and f(sv=None) == E_WS
         assert f(nws=n - 1) == E_WS and f(nsv=n_sv - 1) == E_WS
         assert f(ws=0x100010) == E_WS and f(sv=0x200010) == E_WS
     assert fwd(ctypes.c_void_p(0x10008)) == E_ALIGN and bwd(ctypes.c_void_p(0x10008)) == E_ALIGN
     assert lib.kla_chunk_saved_bytes(2, 200, 2, 96, 64, 64, kla.KLA_BF16, None, 0, 0) == 0
-
-
-def test_batches_of_the_one_kernel_forward(lib):
-    """They take the two-kernel form when they leave their intermediates: its workspace, not the token one."""
-    sizes = (8, 4096, 8, 128, 128, 64, kla.KLA_BF16)
-    assert lib.kla_chunk_fwd_workspace_bytes(*sizes, None, 0) == 256
-    assert lib.kla_chunk_saved_bytes(*sizes, None, 0, 0) > 0
-    p, need = ctypes.c_void_p(0x10000), lib.kla_chunk_fwd_workspace_bytes_opts(*sizes, None, 0, kla.tune(unfused=True))
-    for ws in (256, need - 1):
-        assert lib.kla_chunk_fwd_save(p, p, p, p, p, 1e-6, None, p, None, None, None, 0, *sizes, 0x100000, ws, 0x200000,
-                                      lib.kla_chunk_saved_bytes(*sizes, None, 0, 0), None, 0) == E_WS
