@@ -429,7 +429,9 @@ def kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=None, d_hT=None, cu_seql
                                    deta=(out.get("deta"), sg, torch.float32), dh0=(out.get("dh0"), ss, torch.float32))
     if d_o is None:
         raise ValueError("d_o is required")
-    _dev(q, k, v, log_alpha, eta, d_o, h0, d_hT, cu_seqlens, workspace, *out.values())
+    _dev(q, k, v, log_alpha, eta, d_o, h0, d_hT, cu_seqlens, workspace, _saved, *out.values())
+    if _saved is not None and (_saved.dtype != torch.uint8 or _saved.device != q.device):
+        raise TypeError("what the forward left behind must come back as bytes on the device of q")
     dt = _dt(q)
     bits = _opts(normalize_q, gdn_beta) | _tune(tune)
     if workspace is None:

@@ -72,6 +72,15 @@ template <typename O> bool gpu_or_none(const O& o, at::ScalarType type, at::IntA
     *t = gpu(o, type, shape);
     return *t != nullptr;
 }
+// What a forward left behind for the backward of q: bytes on q's device, or none (then *t stays null); false: something else.
+// (It comes back through the caller's hands, a hook on saved tensors, and goes to the kernels as a bare pointer.)
+template <typename O> bool saved_or_none(const O& o, const at::Tensor& q, const at::Tensor** t)
+{
+    *t = nullptr;
+    if (is_none(o)) return true;
+    *t = on_gpu(o);
+    return *t && (*t)->scalar_type() == at::kByte && (*t)->device() == q.device();
+}
 void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
 float* fptr(const at::Tensor* t) { return static_cast<float*>(ptr(t)); }
 
@@ -295,7 +304,7 @@ PyObject* chunk_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!c.take(a, false) || !integer(a[12], INT_MIN, INT_MAX, &chunk) || !integer(a[13], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
     const at::Tensor *d_o = gpu(a[9], c.type, {c.N, c.T, c.H, c.dv}), *d_hT = nullptr, *saved = nullptr;
     if (!d_o || !gpu_or_none(a[10], at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &d_hT)) Py_RETURN_NONE;
-    if (a[14] != Py_None && !(saved = on_gpu(a[14]))) Py_RETURN_NONE;
+    if (!saved_or_none(a[14], *c.q, &saved)) Py_RETURN_NONE;
     at::Tensor g[6];
     int rc;
     {
@@ -357,8 +366,10 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
         at::Tensor cu_dev, cu_host;
         if (cu != ctx->saved_data.end()) { cu_dev = cu->second.toTensor(); cu_host = ctx->saved_data["cu_host"].toTensor(); }
         Chunk c;
+        const at::Tensor* saved;
         // (a hook on saved tensors may hand back others than it was given)
-        TORCH_CHECK(c.take(s[0], s[1], s[2], s[3], s[4], s[5], cu_dev, cu_host, ctx->saved_data["eps"].toDouble()),
+        TORCH_CHECK(c.take(s[0], s[1], s[2], s[3], s[4], s[5], cu_dev, cu_host, ctx->saved_data["eps"].toDouble()) &&
+                        saved_or_none(s[6], *c.q, &saved),
                     "kla_chunk: the saved tensors are not those of the forward");
         const bool want_dh0 = s[5].defined() && ctx->needs_input_grad(5);
         const at::Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros_like(s[2]);
@@ -367,7 +378,7 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
                     (!d_hT.defined() || (d_hT.is_cuda() && d_hT.scalar_type() == at::kFloat && d_hT.sizes() == at::IntArrayRef({c.n_states, c.H, c.dk, c.dv}))),
                     "kla_chunk: gradients that do not fit the outputs");
         at::Tensor g[6];
-        const int rc = run_bwd(c, d_o, d_hT.defined() ? &d_hT : nullptr, s[6].defined() ? &s[6] : nullptr, want_dh0, 64,
+        const int rc = run_bwd(c, d_o, d_hT.defined() ? &d_hT : nullptr, saved, want_dh0, 64,
                                (unsigned)ctx->saved_data["opts"].toInt(), g);
         TORCH_CHECK(rc == KLA_OK, "kla_chunk_bwd failed: ", rc);
         return {g[0], g[1], g[2], g[3], g[4], g[5], at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};

@@ -81,6 +81,19 @@ def test_gradient_layouts_and_hooks(kla):
     assert len(seen) >= 7                                # the six inputs and what the forward leaves behind
 
 
+@pytest.mark.parametrize("swap", [lambda t: t.cpu(), lambda t: t.repeat_interleave(2)[::2], lambda t: t.view(torch.float32), lambda t: t[:-1]])
+def test_hook_swaps_what_the_forward_left(kla, swap):
+    """The bytes that the forward leaves behind go to the kernels as a pointer: others than it left are refused, natively and step by step."""
+    def run():
+        x = _leaves()
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: swap(t) if t.dtype == torch.uint8 else t):
+            o, _ = _call(kla, x)
+        with pytest.raises((RuntimeError, ValueError, TypeError)):
+            torch.autograd.grad(o.float().sum(), x)
+    run()
+    _python(kla, run)
+
+
 def test_checkpointing(kla):
     x = _leaves()
     f = lambda *y: _call(kla, y)[0]
