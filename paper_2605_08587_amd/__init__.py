@@ -572,6 +572,12 @@ class _KlaChunk(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, save):
+        if cu_seqlens is not None:
+            # the plan of the backward and what is left behind for it are for these offsets: a host copy of our own (the caller may
+            # fill its own anew), and the device's unchanged (an inference tensor does not count its changes)
+            cu_seqlens_host = _host_cu(cu_seqlens, cu_seqlens_host)[0].clone()
+            if cu_seqlens.is_inference():
+                cu_seqlens = cu_seqlens.clone()
         if save and any(ctx.needs_input_grad[:6]):
             o, hT, saved = _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta)
         else:
@@ -581,12 +587,15 @@ class _KlaChunk(torch.autograd.Function):
         ctx.save_for_backward(q, k, v, log_alpha, eta, h0, saved)
         ctx.set_materialize_grads(False)     # the library takes a missing d_hT for zeros: no buffer of them is filled and read
         ctx.misc = (eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, DEFAULT_TUNE)     # saved follows from the tuning fields too
+        ctx.cu_version = None if cu_seqlens is None else cu_seqlens._version
         return o, hT
 
     @staticmethod
     def backward(ctx, d_o, d_hT):
         q, k, v, log_alpha, eta, h0, saved = ctx.saved_tensors
         eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, tune_bits = ctx.misc
+        if cu_seqlens is not None and cu_seqlens._version != ctx.cu_version:
+            raise RuntimeError("one of the variables needed for gradient computation has been modified by an inplace operation: cu_seqlens")
         d_o = q.new_zeros(v.shape) if d_o is None else d_o.contiguous()
         g = kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=h0, d_hT=None if d_hT is None else d_hT.contiguous(),
                           cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,

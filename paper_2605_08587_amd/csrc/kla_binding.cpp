@@ -354,7 +354,14 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
             ctx->set_materialize_grads(false);           // the library takes a missing d_hT for zeros
             ctx->saved_data["eps"] = c->eps;
             ctx->saved_data["opts"] = opts;
-            if (c->cu) { ctx->saved_data["cu"] = *c->cu; ctx->saved_data["cu_host"] = *cu_host; }
+            if (c->cu) {
+                // The plan of the backward and what the forward leaves behind are for these offsets: a host copy of our own (the
+                // caller may fill its own anew), and the device's unchanged (an inference tensor does not count its changes)
+                const at::Tensor cu = c->cu->is_inference() ? c->cu->clone() : *c->cu;
+                ctx->saved_data["cu"] = cu;
+                ctx->saved_data["cu_version"] = (int64_t)cu._version();
+                ctx->saved_data["cu_host"] = cu_host->clone();
+            }
         }
         return {out, hT};
     }
@@ -364,7 +371,12 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
         const torch::autograd::variable_list s = ctx->get_saved_variables();
         const auto cu = ctx->saved_data.find("cu");
         at::Tensor cu_dev, cu_host;
-        if (cu != ctx->saved_data.end()) { cu_dev = cu->second.toTensor(); cu_host = ctx->saved_data["cu_host"].toTensor(); }
+        if (cu != ctx->saved_data.end()) {
+            cu_dev = cu->second.toTensor();
+            cu_host = ctx->saved_data["cu_host"].toTensor();
+            TORCH_CHECK((int64_t)cu_dev._version() == ctx->saved_data["cu_version"].toInt(),
+                        "one of the variables needed for gradient computation has been modified by an inplace operation: cu_seqlens");
+        }
         Chunk c;
         const at::Tensor* saved;
         // (a hook on saved tensors may hand back others than it was given)

@@ -81,6 +81,29 @@ def test_gradient_layouts_and_hooks(kla):
     assert len(seen) >= 7                                # the six inputs and what the forward leaves behind
 
 
+def test_offsets_between_the_directions(kla):
+    """A packed batch whose offsets change after its forward: the caller's host copy does not matter any more, the device's are
+    refused (an inference tensor's, which count no changes, were copied); natively and step by step."""
+    offs = torch.tensor([0, 100, 100, 150], dtype=torch.int32)
+
+    def run(touch, host, inference=False):
+        with torch.inference_mode(inference):
+            cu = offs.cuda()
+        mine = offs.clone() if host else None
+        x = [t.detach()[:1].requires_grad_(True) for t in _leaves()[:5]]
+        o, hT = kla.kla_chunk(*x, 1e-6, cu_seqlens=cu, cu_seqlens_host=mine)
+        with torch.inference_mode(inference):
+            touch(cu, mine)
+        return torch.autograd.grad([o.float().sum(), hT.sum()], x)
+    for call in (lambda f: f(), lambda f: _python(kla, f)):
+        ref = call(lambda: run(lambda cu, mine: None, True))
+        _same(ref, call(lambda: run(lambda cu, mine: mine.copy_(torch.tensor([0, 1, 2, 150])), True)))
+        _same(ref, call(lambda: run(lambda cu, mine: cu.copy_(torch.tensor([0, 1, 2, 150])), False, True)))
+        for host in (True, False):
+            with pytest.raises(RuntimeError, match="modified by an inplace"):
+                call(lambda: run(lambda cu, mine: cu.add_(0), host))
+
+
 @pytest.mark.parametrize("swap", [lambda t: t.cpu(), lambda t: t.repeat_interleave(2)[::2], lambda t: t.view(torch.float32), lambda t: t[:-1]])
 def test_hook_swaps_what_the_forward_left(kla, swap):
     """The bytes that the forward leaves behind go to the kernels as a pointer: others than it left are refused, natively and step by step."""
