@@ -550,6 +550,8 @@ def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, nor
     """kla_chunk_fwd that also leaves behind what kla_chunk_bwd would recompute: (o, hT, saved), saved None where the library
     leaves nothing behind or the memory for it is not there."""
     saved = None
+    args = (q, k, v, log_alpha, eta, eps)
+    kw = dict(h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host, normalize_q=normalize_q, gdn_beta=gdn_beta)
     if q.is_cuda and q.dim() == 4 and v.dim() == 4 and q.dtype in (torch.bfloat16, torch.float32):
         cu_host, cu_hp, n_seq = _host_cu(cu_seqlens, cu_seqlens_host)
         sizes = (*q.shape, v.shape[-1], 64, _dt(q), cu_hp, n_seq)
@@ -559,11 +561,10 @@ def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, nor
         if keep:
             try:
                 saved = torch.empty(keep, dtype=torch.uint8, device=q.device)
-            except torch.OutOfMemoryError:
-                pass
-    o, hT = kla_chunk_fwd(q, k, v, log_alpha, eta, eps, h0=h0, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
-                          normalize_q=normalize_q, gdn_beta=gdn_beta, _saved=saved)
-    return o, hT, saved
+                return (*kla_chunk_fwd(*args, **kw, _saved=saved), saved)
+            except torch.OutOfMemoryError:               # of any buffer of the call: without saved the others may fit
+                saved = None
+    return (*kla_chunk_fwd(*args, **kw), saved)
 
 
 class _KlaChunk(torch.autograd.Function):

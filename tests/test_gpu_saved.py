@@ -82,3 +82,33 @@ def test_no_grad_saves_nothing(kla):
         keep = kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
         assert torch.cuda.memory_allocated() - before < 2 * sum(t.numel() * t.element_size() for t in keep)
         assert not keep[0].requires_grad
+
+
+@pytest.mark.parametrize("room", ["plain", "saved"])
+@pytest.mark.parametrize("native", [True, False])
+def test_no_memory_to_save(kla, native, room):
+    """Memory for the plain forward but not for what it would leave behind, or for that and nothing else: the backward recomputes."""
+    x, d_o, d_hT, _ = _case(B, 4, 1000, 16, 128, 256, None, 9)
+    y = [t.detach().requires_grad_(True) for t in x]
+    ref = torch.autograd.grad(kla.kla_chunk(*y[:5], 1e-6, h0=y[5]), y, [d_o, d_hT])
+    sizes = (4, 1000, 16, 128, 256, 64, kla.KLA_BF16, None, 0)
+    keep = kla.lib().kla_chunk_saved_bytes(*sizes, 0)
+    plain = kla.lib().kla_chunk_fwd_workspace_bytes(*sizes) + x[2].nbytes + x[5].nbytes + (20 << 20)     # (20 MiB: the allocator's rounding)
+    assert plain < 0.8 * keep
+    total = torch.cuda.get_device_properties(0).total_memory
+    kinds = []
+    with pytest.MonkeyPatch.context() as m:
+        if not native:
+            m.setattr(kla, "_native", kla._StepByStep)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        limit = torch.cuda.memory_reserved() + int(0.8 * keep if room == "plain" else keep + (2 << 20))
+        torch.cuda.set_per_process_memory_fraction(limit / total)
+        try:
+            with torch.autograd.graph.saved_tensors_hooks(lambda t: kinds.append(t.dtype) or t, lambda t: t):
+                out = kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+        assert torch.uint8 not in kinds and len(kinds) >= 6
+        for a, b in zip(torch.autograd.grad(out, y, [d_o, d_hT]), ref):
+            assert torch.equal(a, b)
