@@ -111,7 +111,7 @@ def _load_native(l):
         "kla_decode_step_opts", "kla_decode_step_diag_opts", "kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_fwd_opts",
         "kla_chunk_fwd_diag_workspace_bytes", "kla_chunk_fwd_diag_opts", "kla_chunk_bwd_workspace_bytes_opts",
         "kla_chunk_bwd_opts", "kla_chunk_saved_bytes", "kla_chunk_fwd_save", "kla_chunk_bwd_saved_workspace_bytes",
-        "kla_chunk_bwd_saved")))
+        "kla_chunk_bwd_saved")), _bwd_by_steps)
     return m
 
 
@@ -565,6 +565,15 @@ def _fwd_save(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, nor
             except torch.OutOfMemoryError:               # of any buffer of the call: without saved the others may fit
                 saved = None
     return (*kla_chunk_fwd(*args, **kw), saved)
+
+
+def _bwd_by_steps(tensors, eps, opts, want_dh0):
+    """The backward of the native node where it does not take the call or the library refuses it: raises what there is to raise."""
+    q, k, v, log_alpha, eta, d_o, h0, d_hT, cu_seqlens, cu_seqlens_host, saved = tensors
+    g = kla_chunk_bwd(q, k, v, log_alpha, eta, eps, d_o, h0=h0, d_hT=d_hT, cu_seqlens=cu_seqlens, cu_seqlens_host=cu_seqlens_host,
+                      want_dh0=want_dh0, normalize_q=bool(opts & KLA_OPT_NORMALIZE_Q), gdn_beta=bool(opts & KLA_OPT_GDN_BETA),
+                      tune=opts & ~3, _saved=saved)
+    return tuple(g[n] for n in ("dq", "dk", "dv", "dlog_alpha", "deta", "dh0"))
 
 
 class _KlaChunk(torch.autograd.Function):

@@ -8,6 +8,8 @@
 // that bind() was given, so that they are those of the library the package has loaded.
 #include <Python.h>
 
+#include <pybind11/pybind11.h>
+
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -36,6 +38,7 @@ struct Api {
     decltype(&kla_chunk_fwd_save) fwd_save;
     decltype(&kla_chunk_bwd_saved_workspace_bytes) bwd_saved_bytes;
     decltype(&kla_chunk_bwd_saved) bwd_saved;
+    PyObject* bwd_by_steps;                              // the Python module's function for a backward that is not taken here
 } api = {};
 
 // A plain, dense tensor: torch.Tensor or Parameter itself, strided and contiguous, with memory of its own.  (What
@@ -169,7 +172,7 @@ struct Chunk {
 
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
-    if (n != 12) { PyErr_SetString(PyExc_TypeError, "bind takes twelve addresses"); return nullptr; }
+    if (n != 13 || !PyCallable_Check(a[12])) { PyErr_SetString(PyExc_TypeError, "bind takes twelve addresses and a function"); return nullptr; }
     void* p[12];
     for (int i = 0; i < 12; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
@@ -187,6 +190,9 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
     api.fwd_save = reinterpret_cast<decltype(api.fwd_save)>(p[9]);
     api.bwd_saved_bytes = reinterpret_cast<decltype(api.bwd_saved_bytes)>(p[10]);
     api.bwd_saved = reinterpret_cast<decltype(api.bwd_saved)>(p[11]);
+    Py_INCREF(a[12]);
+    Py_XDECREF(api.bwd_by_steps);
+    api.bwd_by_steps = a[12];
     Py_RETURN_NONE;
 }
 
@@ -377,23 +383,48 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
             TORCH_CHECK((int64_t)cu_dev._version() == ctx->saved_data["cu_version"].toInt(),
                         "one of the variables needed for gradient computation has been modified by an inplace operation: cu_seqlens");
         }
-        Chunk c;
-        const at::Tensor* saved;
-        // (a hook on saved tensors may hand back others than it was given)
-        TORCH_CHECK(c.take(s[0], s[1], s[2], s[3], s[4], s[5], cu_dev, cu_host, ctx->saved_data["eps"].toDouble()) &&
-                        saved_or_none(s[6], *c.q, &saved),
-                    "kla_chunk: the saved tensors are not those of the forward");
+        const double eps = ctx->saved_data["eps"].toDouble();
+        const int64_t opts = ctx->saved_data["opts"].toInt();
         const bool want_dh0 = s[5].defined() && ctx->needs_input_grad(5);
         const at::Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros_like(s[2]);
         const at::Tensor d_hT = grads[1].defined() ? grads[1].contiguous() : at::Tensor();
-        TORCH_CHECK(d_o.is_cuda() && d_o.scalar_type() == c.type && d_o.sizes() == s[2].sizes() &&
-                    (!d_hT.defined() || (d_hT.is_cuda() && d_hT.scalar_type() == at::kFloat && d_hT.sizes() == at::IntArrayRef({c.n_states, c.H, c.dk, c.dv}))),
-                    "kla_chunk: gradients that do not fit the outputs");
+        Chunk c;
+        const at::Tensor *saved, *state_grad;
         at::Tensor g[6];
-        const int rc = run_bwd(c, d_o, d_hT.defined() ? &d_hT : nullptr, saved, want_dh0, 64,
-                               (unsigned)ctx->saved_data["opts"].toInt(), g);
-        TORCH_CHECK(rc == KLA_OK, "kla_chunk_bwd failed: ", rc);
+        // (a hook on saved tensors may hand back others than it was given)
+        if (!c.take(s[0], s[1], s[2], s[3], s[4], s[5], cu_dev, cu_host, eps) || !saved_or_none(s[6], *c.q, &saved) ||
+            !gpu(d_o, c.type, c.v->sizes()) || !gpu_or_none(d_hT, at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &state_grad) ||
+            run_bwd(c, d_o, state_grad, saved, want_dh0, 64, (unsigned)opts, g) != KLA_OK)
+            by_steps({s[0], s[1], s[2], s[3], s[4], d_o, s[5], d_hT, cu_dev, cu_host, s[6]}, eps, opts, want_dh0, g);
         return {g[0], g[1], g[2], g[3], g[4], g[5], at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
+    }
+
+    // A backward that is not taken here, or that the library refuses: the Python function goes through it step by step and raises
+    // what there is to raise.  t (undefined: None): q, k, v, log_alpha, eta, d_o, h0, d_hT, the offsets, their host copy, saved
+    static void by_steps(std::initializer_list<at::Tensor> t, double eps, int64_t opts, bool want_dh0, at::Tensor (&g)[6])
+    {
+        const pybind11::gil_scoped_acquire gil;
+        pybind11::list args;
+        for (const at::Tensor& x : t) {
+            PyObject* o = THPVariable_Wrap(x);
+            if (!o) raise();
+            args.append(pybind11::reinterpret_steal<pybind11::object>(o));
+        }
+        const auto r = pybind11::reinterpret_steal<pybind11::object>(
+            PyObject_CallFunction(api.bwd_by_steps, "OdLO", args.ptr(), eps, (long long)opts, want_dh0 ? Py_True : Py_False));
+        if (!r) raise();
+        if (!PyTuple_Check(r.ptr()) || PyTuple_GET_SIZE(r.ptr()) != 6) { PyErr_SetString(PyExc_TypeError, "kla_chunk_bwd: six gradients"); raise(); }
+        for (int i = 0; i < 6; ++i) {
+            PyObject* o = PyTuple_GET_ITEM(r.ptr(), i);
+            g[i] = THPVariable_Check(o) ? at::Tensor(THPVariable_Unpack(o)) : at::Tensor();
+        }
+    }
+    // the Python error there is, for the thread that called the engine
+    [[noreturn]] static void raise()
+    {
+        python_error e;
+        e.persist();
+        throw e;
     }
 };
 

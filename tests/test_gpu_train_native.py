@@ -170,6 +170,31 @@ def test_refusals(kla):
             _call(kla, z)
 
 
+def test_errors_of_the_backward(kla):
+    """What the native node refuses in the backward raises what the Python function raises: type, code and text."""
+    def unaligned():                                     # an output gradient that does not start at 16 bytes
+        o, _ = _call(kla, _leaves())
+        d = torch.zeros(o.numel() + 1, dtype=o.dtype, device="cuda")[1:].view(o.shape)
+        torch.autograd.grad(o, o.grad_fn.next_functions[0][0].variable, d)
+
+    def strided():                                       # a hook that hands back an input of other strides
+        x = _leaves()
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, lambda t: t.transpose(0, 1) if t.dim() == 4 else t):
+            o, _ = _call(kla, x)
+        torch.autograd.grad(o.float().sum(), x[0])
+    for f in (unaligned, strided):
+        with pytest.raises(Exception) as fast:
+            f()
+        with pytest.raises(Exception) as slow:
+            _python(kla, f)
+        assert type(fast.value) is type(slow.value) and str(fast.value) == str(slow.value)
+        assert getattr(fast.value, "code", None) == getattr(slow.value, "code", None)
+    assert type(slow.value) is ValueError
+    with pytest.raises(kla.KlaError) as e:
+        unaligned()
+    assert e.value.code == -4
+
+
 def test_streams(kla):
     """Forward on a side stream: the backward runs there too, whatever stream is current when it is called."""
     x = _leaves()
