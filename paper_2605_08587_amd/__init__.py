@@ -615,20 +615,23 @@ class _KlaChunk(torch.autograd.Function):
 
 
 def kla_chunk(q, k, v, log_alpha, eta, eps, h0=None, cu_seqlens=None, cu_seqlens_host=None, normalize_q=False,
-              gdn_beta=False):
+              gdn_beta=False, save=True):
     """Differentiable chunkwise forward for training loops: returns (o, hT) like kla_chunk_fwd; gradients with respect to
     q, k, v, log_alpha, eta and h0 come from kla_chunk_bwd.  Where a gradient is wanted, the forward leaves the per-chunk
     operands and states behind for it (kla_chunk_fwd_save of the C ABI: at d_k = d_v = 128 about 1.1 KB per token and head in
-    bf16, at most KLA_SAVED_MAX_BYTES per call), elsewhere, and where that memory is not there, the backward recomputes
-    them: same bits either way."""
+    bf16, about as much as q, k, v and o together, held until the backward; at most KLA_SAVED_MAX_BYTES per call).  save=False: it
+    does not, and the backward recomputes them, as it does where the library leaves nothing behind (one-kernel and segmented
+    forwards) or the memory is not there.  Same bits either way.
+    The offsets of a packed batch must not change before the backward, which refuses them then."""
     # tracing, function transforms and forward-mode differentiation are for the Python function to take or to refuse
     if (torch.is_grad_enabled() and torch._C._get_tracing_state() is None and not torch._C._are_functorch_transforms_active()
             and torch.autograd.forward_ad._current_level < 0):
         host = _host_cu(cu_seqlens)[0] if cu_seqlens is not None and cu_seqlens_host is None else cu_seqlens_host
         r = _binding().train(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, None if cu_seqlens is None else host,
-                             _opts(normalize_q, gdn_beta) | DEFAULT_TUNE)
+                             _opts(normalize_q, gdn_beta) | DEFAULT_TUNE, bool(save))
         if type(r) is int:
             raise KlaError(r, "kla_chunk_fwd")
         if r is not None:
             return r
-    return _KlaChunk.apply(q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta, torch.is_grad_enabled())
+    return _KlaChunk.apply(q, k, v, log_alpha, eta, h0, eps, cu_seqlens, cu_seqlens_host, normalize_q, gdn_beta,
+                           bool(save) and torch.is_grad_enabled())

@@ -335,11 +335,11 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
     static torch::autograd::variable_list forward(torch::autograd::AutogradContext* ctx, const at::Tensor& q, const at::Tensor& k,
                                                   const at::Tensor& v, const at::Tensor& la, const at::Tensor& eta,
                                                   const std::optional<at::Tensor>& h0,
-                                                  const Chunk* c, const at::Tensor* cu_host, int64_t opts, bool wanted)
+                                                  const Chunk* c, const at::Tensor* cu_host, int64_t opts, bool wanted, bool save)
     {
         const int N = (int)c->N, T = (int)c->T, H = (int)c->H, dk = (int)c->dk, dv = (int)c->dv, chunk = 64;
         const size_t need = api.fwd_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts & ~3u);
-        const size_t keep = wanted ? api.saved_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts) : 0;
+        const size_t keep = wanted && save ? api.saved_bytes(N, T, H, dk, dv, chunk, c->dt, c->cu_host, c->n_seq, (unsigned)opts) : 0;
         const at::Tensor ws = c->empty({(int64_t)(need < 256 ? 256 : need)}, at::kByte);
         const at::Tensor out = c->empty({c->N, c->T, c->H, c->dv}, c->type), hT = c->empty({c->n_states, c->H, c->dk, c->dv}, at::kFloat);
         at::Tensor saved;
@@ -396,7 +396,7 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
             !gpu(d_o, c.type, c.v->sizes()) || !gpu_or_none(d_hT, at::kFloat, {c.n_states, c.H, c.dk, c.dv}, &state_grad) ||
             run_bwd(c, d_o, state_grad, saved, want_dh0, 64, (unsigned)opts, g) != KLA_OK)
             by_steps({s[0], s[1], s[2], s[3], s[4], d_o, s[5], d_hT, cu_dev, cu_host, s[6]}, eps, opts, want_dh0, g);
-        return {g[0], g[1], g[2], g[3], g[4], g[5], at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
+        return {g[0], g[1], g[2], g[3], g[4], g[5], at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
     }
 
     // A backward that is not taken here, or that the library refuses: the Python function goes through it step by step and raises
@@ -428,11 +428,12 @@ struct KlaChunk : public torch::autograd::Function<KlaChunk> {
     }
 };
 
-// train(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, opts) -> (out, hT), differentiable
+// train(q, k, v, log_alpha, eta, eps, h0, cu_seqlens, cu_seqlens_host, opts, save) -> (out, hT), differentiable
 PyObject* train(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 10 || !api.fwd_save) Py_RETURN_NONE;
+    if (n != 11 || !api.fwd_save) Py_RETURN_NONE;
+    const bool save = a[10] == Py_True;
     Chunk c;
     long opts;
     if (!c.take(a, false) || !integer(a[9], 0, UINT_MAX, &opts)) Py_RETURN_NONE;
@@ -442,7 +443,7 @@ PyObject* train(PyObject*, PyObject* const* a, Py_ssize_t n)
         bool wanted = c.h0 && c.h0->requires_grad();
         for (const at::Tensor* t : {c.q, c.k, c.v, c.la, c.eta}) wanted = wanted || t->requires_grad();
         r = KlaChunk::apply(*c.q, *c.k, *c.v, *c.la, *c.eta, c.h0 ? std::optional<at::Tensor>(*c.h0) : std::nullopt, &c, c.cu ? &THPVariable_Unpack(a[8]) : nullptr,
-                            (int64_t)opts, wanted);
+                            (int64_t)opts, wanted, save);
     } catch (const Refused& e) {
         return PyLong_FromLong(e.code);
     }

@@ -84,6 +84,25 @@ def test_no_grad_saves_nothing(kla):
         assert not keep[0].requires_grad
 
 
+@pytest.mark.parametrize("native", [True, False])
+def test_save_switched_off(kla, native):
+    """save=False: nothing but the outputs is held between the directions; same bits."""
+    x, d_o, d_hT, _ = _case(B, 4, 1000, 16, 128, 256, None, 9)
+    y = [t.detach().requires_grad_(True) for t in x]
+    got, held = [], []
+    with pytest.MonkeyPatch.context() as m:
+        if not native:
+            m.setattr(kla, "_native", kla._StepByStep)
+        for save in (True, False):
+            before = torch.cuda.memory_allocated()
+            out = kla.kla_chunk(*y[:5], 1e-6, h0=y[5], save=save)
+            held.append(torch.cuda.memory_allocated() - before - sum(t.nbytes for t in out))
+            got.append([*out, *torch.autograd.grad(out, y, [d_o, d_hT])])
+            del out
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    assert held[0] >= kla.lib().kla_chunk_saved_bytes(4, 1000, 16, 128, 256, 64, kla.KLA_BF16, None, 0, 0) and held[1] <= 1 << 20
+
+
 @pytest.mark.parametrize("room", ["plain", "saved"])
 @pytest.mark.parametrize("native", [True, False])
 def test_no_memory_to_save(kla, native, room):
