@@ -52,13 +52,16 @@ bool parse_tune(unsigned opts, Tune* t)
     return true;
 }
 
+// The sequences of a call, as far as the lengths of its sweeps go: n of them of NT chunks each, or (cu != NULL) packed.
+struct Lengths { int n, NT; const int32_t* cu; };
+
 struct Plan {
     long n_chunks;       // over all sequences
     int n_states;        // sequences
     size_t off_T, off_P, off_G, off_C, off_M, off_S, total;
     size_t order_bytes;  // of these, what the scan order of a packed batch adds
     int seg_G, seg_Lc;   // segment-parallel scan: segments per sequence (1 = off) and chunks per segment
-    int waves;           // compute waves per scan workgroup (of the unsegmented scan)
+    Lengths seqs;        // (cu: the caller's, for the length of the call)
     bool rows;           // bf16 only: the scan that splits a chunk by rows
     bool fused;          // bf16 only: one kernel, no intra-chunk stage, nothing in the workspace
     int fwd_seg_G;       // make_bwd_plan only: the forward's segments (seg_G are the backward's there)
@@ -93,8 +96,6 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
     return G;
 }
 
-// The sequences of a call, as far as the lengths of its sweeps go: n of them of NT chunks each, or (cu != NULL) packed.
-struct Lengths { int n, NT; const int32_t* cu; };
 long busiest_cu(const Lengths& seqs, int H, int slices);
 int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tune& tune);
 
@@ -155,8 +156,7 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
         segments(512);
         if (p->total > (size_t)KLA_STATIC_SCRATCH_BYTES && p->total != all) segments(dv >= 128 ? 1024 : 512);
     }
-    const Lengths seqs = {p->n_states, (T + 63) / 64, cu_host};
-    p->waves = scan_waves(seqs, H, dv, dt, false, p->tune);
+    p->seqs = {p->n_states, (T + 63) / 64, cu_host};
     // Up to 256 chains of sixteen columns each have a CU to themselves: the scan that shares a chain among the waves of one (8
     // heads of 128 columns, 700 tokens: 18.7 against 20.9 us; 256 chains, 4 x 1000 tokens of 8 heads: 27.5 against 29.3; 384: 35.7
     // against 26.0).  Same bits.
@@ -172,10 +172,10 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     // A batch without a token (whose inputs may be NULL) only hands its states on: the plain scan does that.
     // KLA_TUNE_FUSED forces the fused kernel wherever it can run (one or two compute waves, no segments).
     const long tiles = ((long)p->n_states * H + 7) / 8 * 8 * (dv / 16);
-    const bool pair = p->tune.scan_waves ? p->waves == 2 : tiles >= 384 && tiles < 2048;
+    const int forced = p->tune.scan_waves ? scan_waves(p->seqs, H, dv, dt, false, p->tune) : 0;
+    const bool pair = forced ? forced == 2 : tiles >= 384 && tiles < 2048;
     p->fused = dt == KLA_BF16 && n_chunks > 0 && p->seg_G <= 1 && !p->tune.unfused && !p->tune.generic_scan && !p->tune.generic_intra &&
-               (p->tune.fused ? !p->tune.scan_waves || p->waves <= 2 : pair && dv <= 128);
-    if (p->fused && !p->tune.scan_waves && (p->waves > 2 || !p->tune.fused)) p->waves = 2;
+               (p->tune.fused ? forced <= 2 : pair && dv <= 128);
     if (p->fused) { p->total = 256; p->order_bytes = 0; }
     return KLA_OK;
 }
@@ -245,6 +245,16 @@ int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tun
     return w;
 }
 
+// Compute waves per workgroup of the forward's scan.  The widths of a packed batch cost the host some microseconds (busiest_cu), so
+// they are chosen where a kernel is launched and not with the plan, which is made several times per call, also for its sizes alone
+// (kla_chunk_saved_bytes through ctypes, 64 sequences: 1.3 us; with the widths in the plan 7.1).
+int fwd_waves(const Plan& p, int H, int dv, int dt)
+{
+    if (p.fused && !p.tune.scan_waves && !p.tune.fused) return 2;
+    const int w = scan_waves(p.seqs, H, dv, dt, false, p.tune);
+    return p.fused && !p.tune.scan_waves && w > 2 ? 2 : w;
+}
+
 // Whether the intra-chunk stage finds its chunks by itself and leaves the offsets and the scan order of a packed batch to the
 // kernels behind it; a batch without a single chunk has no such stage.
 bool intra_places(int n_seq, long n_chunks, bool generic)
@@ -281,7 +291,7 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             fa.wsT = nullptr; fa.wsP = nullptr; fa.wsG = nullptr; fa.opts = opts;
             fa.seg_G = 0; fa.seg_Lc = 0; fa.kt_src = nullptr; fa.gc_vec = nullptr;
             fa.log_alpha = log_alpha; fa.eta = eta; fa.eps = eps;
-            return kla::launch_scan_fused_bf16(fa, dk, pl.waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+            return kla::launch_scan_fused_bf16(fa, dk, fwd_waves(pl, H, dv, KLA_BF16), st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
     const bool generic_intra = sizeof(E) == 2 && pl.tune.generic_intra;
@@ -328,10 +338,13 @@ int chunk_fwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_scan_bf16(sa, dk, wseg, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    const int waves = pl.waves;
+    if constexpr (sizeof(E) == 2) {
+        if (pl.rows) return kla::launch_scan_rows_bf16(sa, dk, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+    }
+    const int waves = fwd_waves(pl, H, dv, sizeof(E) == 2 ? KLA_BF16 : KLA_F32);
     if constexpr (sizeof(E) == 2) {
         if (!pl.tune.generic_scan)                       // else the plain kernel (A/B testing)
-            return (pl.rows ? kla::launch_scan_rows_bf16(sa, dk, st) : kla::launch_scan_bf16(sa, dk, waves, st)) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
+            return kla::launch_scan_bf16(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     }
     if constexpr (sizeof(E) == 4) return kla::launch_scan_f32(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
     else                          return kla::launch_scan(sa, dk, waves > 4 ? 4 : waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
@@ -345,7 +358,6 @@ struct BwdPlan {
     size_t off_rec, off_C, off_S, off_X, off_U, saved;
     size_t off_dS, off_Y, total;             // total: of both parts
     bool can_save;
-    int sweep_waves, save_waves;             // bf16: compute waves of the sweeps, and of a forward that leaves its intermediates
     // segment-parallel sweeps (base.seg_G > 1): maps of the segments, states entering them, and for the reverse
     // direction the state gradients leaving them and what each segment's pre-pass returns; all fp32
     size_t off_maps, off_segS, off_segG, off_segB;
@@ -380,16 +392,6 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     p->off_segG = round256(p->off_segS + segst);
     p->off_segB = round256(p->off_segG + segst);
     p->total = p->saved + round256(p->off_segB + segst);
-    // Sweeps: two waves (32 state columns) per workgroup once that still gives a workgroup per CU, four (64 columns) where that
-    // shortens the work of the busiest CU: their visits are about 1.15 times as long (call of 8 x 4096 tokens, 8 heads, one round
-    // either way: 469 us with two, 511 us with four; 9 x 2000, two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347;
-    // 40 x 1000, five rounds against three: 584, 520)
-    const Lengths seqs = {p->base.n_states, (T + 63) / 64, cu_host};
-    const long chains8 = ((long)p->base.n_states * H + 7) / 8 * 8;
-    p->sweep_waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
-    if (dt == KLA_BF16 && !p->base.tune.generic_bwd && p->sweep_waves == 2 && dv >= 64 &&
-        busiest_cu(seqs, H, dv / 64) * 115 < busiest_cu(seqs, H, dv / 32) * 100) p->sweep_waves = 4;
-    p->save_waves = scan_waves(seqs, H, dv, dt, true, p->base.tune);
     // A forward leaves its intermediates where it forms the very ones the backward would: not in one kernel (which rounds other
     // things), not in segments (whose number differs), not through the plain kernels.  And within a bound: what is kept lives
     // until the backward, in every layer of a model.
@@ -397,6 +399,17 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     p->can_save = p->base.n_chunks > 0 && !p->base.fused && p->base.fwd_seg_G <= 1 && G <= 1 && !t.generic_scan && !t.generic_intra &&
                   !t.generic_bwd && p->saved <= (size_t)KLA_SAVED_MAX_BYTES;
     return KLA_OK;
+}
+
+// Compute waves of the bf16 sweeps: two (32 state columns) per workgroup once that still gives a workgroup per CU, four (64 columns)
+// where that shortens the work of the busiest CU: their visits are about 1.15 times as long (call of 8 x 4096 tokens, 8 heads, one
+// round either way: 469 us with two, 511 us with four; 9 x 2000, two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347;
+// 40 x 1000, five rounds against three: 584, 520)
+int sweep_waves(const Plan& p, int H, int dv)
+{
+    const long chains8 = ((long)p.n_states * H + 7) / 8 * 8;
+    if (chains8 * (dv / 32) < 192) return 1;
+    return !p.tune.generic_bwd && dv >= 64 && busiest_cu(p.seqs, H, dv / 64) * 115 < busiest_cu(p.seqs, H, dv / 32) * 100 ? 4 : 2;
 }
 
 template <typename E>
@@ -480,7 +493,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    [[maybe_unused]] const int waves = pl.sweep_waves;
+    [[maybe_unused]] const int waves = sizeof(E) == 2 ? sweep_waves(pl.base, H, dv) : 0;
     if constexpr (sizeof(E) == 2) {
         if (fast) {
             if (!have && kla::launch_bwd_states_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
@@ -530,10 +543,10 @@ int chunk_fwd_save_impl(const void* q, const void* k, const void* v, const float
     hipError_t e;
     if constexpr (sizeof(E) == 2) {
         e = kla::launch_intra_bf16(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
-        if (e == hipSuccess) e = pl.rows ? kla::launch_scan_rows_bf16(sa, dk, st) : kla::launch_scan_bf16(sa, dk, bp.save_waves, st);
+        if (e == hipSuccess) e = pl.rows ? kla::launch_scan_rows_bf16(sa, dk, st) : kla::launch_scan_bf16(sa, dk, scan_waves(pl.seqs, H, dv, KLA_BF16, true, pl.tune), st);
     } else {
         e = kla::launch_intra_f32(ia, dk, kla::kIntraPair, (int)pl.n_chunks, st);
-        if (e == hipSuccess) e = kla::launch_scan_f32(sa, dk, pl.waves, st);
+        if (e == hipSuccess) e = kla::launch_scan_f32(sa, dk, fwd_waves(pl, H, dv, KLA_F32), st);
     }
     return e == hipSuccess ? KLA_OK : KLA_ERR_HIP;
 }

@@ -1,5 +1,6 @@
 """C ABI of the forward that leaves its intermediates and the backward that takes them: sizes and refusals, without a GPU."""
 import ctypes
+import timeit
 
 import pytest
 
@@ -52,3 +53,17 @@ def test_refusals(lib):
         assert f(ws=0x100010) == E_WS and f(sv=0x200010) == E_WS
     assert fwd(ctypes.c_void_p(0x10008)) == E_ALIGN and bwd(ctypes.c_void_p(0x10008)) == E_ALIGN
     assert lib.kla_chunk_saved_bytes(2, 200, 2, 96, 64, 64, kla.KLA_BF16, None, 0, 0) == 0
+
+
+@pytest.mark.parametrize("entry", ["kla_chunk_fwd_workspace_bytes_opts", "kla_chunk_saved_bytes", "kla_chunk_bwd_workspace_bytes_opts"])
+def test_sizes_of_a_packed_batch_are_cheap(lib, entry):
+    """The sizes of a packed batch do not pay for the widths of its kernels' workgroups: 64 sequences hardly
+    dearer than one (quickest of many calls; 2 to 5 times that if the schedule of the workgroups is played through)."""
+    n = 64
+    offs = [0]
+    for i in range(n):
+        offs.append(offs[-1] + 100 + 37 * i % 900)
+    cu = (ctypes.c_int32 * (n + 1))(*offs)
+    f = getattr(lib, entry)
+    quickest = lambda n_seq, bits: min(timeit.repeat(lambda: f(1, offs[n_seq], 8, 128, 256, 64, kla.KLA_BF16, cu, n_seq, bits), number=50, repeat=200))
+    assert quickest(n, 0) < 1.6 * quickest(1, 0)
