@@ -1,5 +1,5 @@
 """Packed batches whose workgroups' width follows from their lengths (one, two, four or eight waves by the work of the busiest
-CU): every column is a recurrence of its own, so any width gives the bits of one wave per workgroup."""
+CU; here 2, 2, 1, 4, 8 and 8): every column is a recurrence of its own, so any width gives the bits of one wave per workgroup."""
 import pytest
 import torch
 
@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("lens,H,dv", [([130, 1, 64, 640, 65, 0, 400], 16, 128), ([650, 60, 600, 63, 580, 127, 64], 8, 256),
+                                       ([640, 64, 60, 1, 64], 8, 128), ([575, 65, 449, 300, 1, 64, 130, 385, 0, 511], 8, 256),
                                        ([(29 * i) % 140 for i in range(64)], 4, 256), ([(29 * i) % 140 for i in range(65)], 4, 256)])
 def test_any_width(lens, H, dv):
     if not torch.cuda.is_available():

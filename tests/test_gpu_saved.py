@@ -1,6 +1,6 @@
 """kla_chunk's forward leaves the per-chunk operands and states behind for its backward (kla_chunk_fwd_save, kla_chunk_bwd_saved):
-the same bits as the two calls by hand, whose backward recomputes them; one shape per number of compute waves of the bf16 scan
-and per form of the fp32 one; last chunks of 1, 63 and 64 rows, packed batches with empty sequences, both options."""
+the same bits as the two calls by hand, whose backward recomputes them, for the row-split bf16 scan, for its workgroups of 2, 4 and 8
+waves and for each form of the fp32 one; last chunks of 1, 63 and 64 rows, packed batches with empty sequences, both options."""
 import pytest
 import torch
 
@@ -56,6 +56,26 @@ def test_saved_equals_recomputed(kla, dt, N, T, H, dk, dv, lens, opts):
             assert torch.equal(o, o2) and torch.equal(hT, h2)
             for a, b in zip(torch.autograd.grad([o2, h2], y, [d_o, d_hT]), ref.values()):
                 assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T,lens", [(1, None), (65, None), (300, None), (449, None), (0, [449, 320, 0, 449, 385, 449, 1, 400, 449])])
+def test_four_waves(kla, T, lens):
+    """d_k = 128, where four compute waves read from two LDS rings: these batches (512 workgroups of two waves, 256 of four) leave behind
+    with four; the outputs, and the gradients from what was left, are those of one and two waves and of the two calls by hand."""
+    x, d_o, d_hT, cu = _case(B, 8, T, 8, 128, 256, lens, 3 + T)
+    packed = dict(cu_seqlens=None if cu is None else cu.cuda(), cu_seqlens_host=cu)
+
+    def run(waves):
+        with pytest.MonkeyPatch.context() as m:
+            m.setattr(kla, "DEFAULT_TUNE", kla.tune(scan_waves=waves))
+            y = [t.detach().requires_grad_(True) for t in x]
+            assert kla._fwd_save(*x[:5], 1e-6, x[5], packed["cu_seqlens"], cu, False, False)[2] is not None
+            out = kla.kla_chunk(*y[:5], 1e-6, h0=y[5], **packed)
+            return [*(t.detach() for t in out), *torch.autograd.grad(out, y, [d_o, d_hT])]
+    got = run(0)
+    by_hand = [*kla.kla_chunk_fwd(*x[:5], 1e-6, h0=x[5], **packed), *kla.kla_chunk_bwd(*x[:5], 1e-6, d_o, h0=x[5], d_hT=d_hT, **packed).values()]
+    for other in (by_hand, run(4), run(2), run(1)):
+        assert all(torch.equal(a, b) for a, b in zip(got, other))
 
 
 @pytest.mark.parametrize("N,T,H,dv", [(8, 70, 8, 128), (1, 4160, 2, 128), (2, 0, 2, 64)])

@@ -1,7 +1,8 @@
 """The bf16 scan with eight compute waves per workgroup (what batches of d_v >= 128 run where they save rounds of workgroups)
-and the scan order of packed batches, at the sizes where they can go wrong: one to three chunks, last chunks of 1, 63 and 64
-rows, both head widths, both slices of d_v = 256, empty sequences, more sequences than the order is built for.  The two-kernel
-form is asked for: some of these batches run the one-kernel form by themselves, which has neither."""
+and the scan order of packed batches (whose lengths give them two, eight, four and eight waves here), at the sizes where they
+can go wrong: one to three chunks, last chunks of 1, 63 and 64 rows, both head widths, both slices of d_v = 256, empty
+sequences, more sequences than the order is built for.  The two-kernel form is asked for: some of these batches run the
+one-kernel form by themselves, which has neither."""
 import numpy as np
 import pytest
 import torch
@@ -38,7 +39,8 @@ def test_eight_waves(kla, T, dk, dv, H):
     _check(kla, kla_inputs.chunk_inputs(8, T, H, dk, dv, seed=T + dv, h0_std=0.3, log_alpha_scale=0.1), normalize_q=T == 65)
 
 
-@pytest.mark.parametrize("lens,H,dv", [([70, 0, 200, 1, 64, 129, 0, 63, 300], 9, 256), ([(37 * i) % 75 for i in range(300)], 1, 64),
+@pytest.mark.parametrize("lens,H,dv", [([70, 0, 200, 1, 64, 129, 0, 63, 300], 9, 256),
+                                       ([70, 0, 200, 1, 64, 129, 0, 63, 300], 32, 256), ([(37 * i) % 75 for i in range(300)], 1, 64),
                                        ([(53 * i) % 131 for i in range(256)], 2, 128)])
 def test_packed_order(kla, lens, H, dv):
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32)
