@@ -141,9 +141,17 @@ def test_no_memory_to_save(kla, native, room):
             m.setattr(kla, "_native", kla._StepByStep)
         torch.cuda.synchronize()
         torch.cuda.empty_cache()
-        limit = torch.cuda.memory_reserved() + int(0.8 * keep if room == "plain" else keep + (2 << 20))
-        torch.cuda.set_per_process_memory_fraction(limit / total)
+        full = []                                        # what other tests hold may leave room in its segments: none of it counts
         try:
+            torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+            for mib in (1024, 256, 64, 16, 4, 1):
+                try:
+                    while True:
+                        full.append(torch.empty(mib << 20, dtype=torch.uint8, device="cuda"))
+                except torch.OutOfMemoryError:
+                    pass
+            limit = torch.cuda.memory_reserved() + int(0.8 * keep if room == "plain" else keep + (2 << 20))
+            torch.cuda.set_per_process_memory_fraction(limit / total)
             with torch.autograd.graph.saved_tensors_hooks(lambda t: kinds.append(t.dtype) or t, lambda t: t):
                 out = kla.kla_chunk(*y[:5], 1e-6, h0=y[5])
         finally:
