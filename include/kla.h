@@ -259,7 +259,8 @@ int kla_chunk_bwd_opts(const void *q, const void *k, const void *v,
  *                    cannot leave its intermediates (shapes whose forward runs as one kernel or in segments, batches without a
  *                    token, more than KLA_SAVED_MAX_BYTES, the plain kernels); the pair then returns KLA_ERR_SHAPE.
  *   workspace        of kla_chunk_bwd_saved: kla_chunk_bwd_saved_workspace_bytes(...)
- * The size arguments and opts have to be those of the forward.
+ * The size arguments, the offsets of a packed batch (on host and device) and opts have to be those of the forward: what it left
+ * behind is laid out by them.
  */
 #define KLA_SAVED_MAX_BYTES (1024u << 20)
 size_t kla_chunk_saved_bytes(int N, int T, int H, int dk, int dv, int chunk, kla_dtype dt,

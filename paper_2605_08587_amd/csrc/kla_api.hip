@@ -158,7 +158,7 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
     }
     p->seqs = {p->n_states, (T + 63) / 64, cu_host};
     // Up to 256 chains of sixteen columns each have a CU to themselves: the scan that shares a chain among the waves of one (8
-    // heads of 128 columns, 700 tokens: 18.7 against 20.9 us; 256 chains, 4 x 1000 tokens of 8 heads: 27.5 against 29.3; 384: 35.7
+    // heads of 128 columns, 700 tokens: 17.7 against 20.3 us; 256 chains, 4 x 1000 tokens of 8 heads: 26.6 against 28.8; 384: 35.7
     // against 26.0).  Same bits.
     p->rows = dt == KLA_BF16 && !p->tune.scan_waves && !p->tune.generic_scan && ((long)p->n_states * H + 7) / 8 * 8 * (dv / 16) <= 256;
     // The fused kernel (two compute waves per workgroup) keeps the per-chunk objects on chip and needs nothing of the

@@ -10,8 +10,8 @@
 // from memory into the registers of the one wave that uses them, three chunks ahead. What is left is the rate at which a CU takes
 // its 47 KB per step, 1 KB every 35 .. 40 cycles: steps of 0.8 us. (A form with 32 columns per workgroup, for up to 512 chains, was no
 // faster than the column split: 25.1 against 24.8 us for 4 x 700 tokens, 8 heads, d_v = 256.)
-// Measured, column split -> this, call with stage 1: 8 heads, d = 128: 200 tokens 14.6 -> 13.5 us, 700 20.9 -> 18.7, 4000 72.1 -> 64.3;
-// 4 x 1000 tokens (256 chains) 29.3 -> 27.5; leaving intermediates, 4000 tokens 83.4 -> 73.6.
+// Measured, column split -> this, call with stage 1: 8 heads, d = 128: 200 tokens 13.4 -> 12.3 us, 700 20.3 -> 17.7, 4000 72.8 -> 64.4;
+// 4 x 1000 tokens (256 chains) 28.8 -> 26.6; leaving intermediates, 4000 tokens 80.9 -> 73.1.
 #include "kla_bf16_ops.hpp"
 #include "kla_common.hpp"
 #include "kla_kernels.hpp"
