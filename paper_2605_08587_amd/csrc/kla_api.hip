@@ -401,14 +401,16 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     return KLA_OK;
 }
 
-// Compute waves of the bf16 sweeps: two (32 state columns) per workgroup once that still gives a workgroup per CU, four (64 columns)
+// Compute waves of the bf16 sweeps: one (16 state columns) per workgroup while every chain has a CU to itself (reverse sweep of 4 x 2000
+// tokens, 8 heads: 50 us with one, 54 with two); beyond that its workgroups would take two rounds, where those of two waves (32
+// columns) take one (5 x 2000, 320 chains: 87 us with one, 55 with two). Four (64 columns)
 // where that shortens the work of the busiest CU: their visits are about 1.15 times as long (call of 8 x 4096 tokens, 8 heads, one
 // round either way: 469 us with two, 511 us with four; 9 x 2000, two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347;
 // 40 x 1000, five rounds against three: 584, 520)
 int sweep_waves(const Plan& p, int H, int dv)
 {
     const long chains8 = ((long)p.n_states * H + 7) / 8 * 8;
-    if (chains8 * (dv / 32) < 192) return 1;
+    if (chains8 * (dv / 16) <= 256) return 1;
     return !p.tune.generic_bwd && dv >= 64 && busiest_cu(p.seqs, H, dv / 64) * 115 < busiest_cu(p.seqs, H, dv / 32) * 100 ? 4 : 2;
 }
 
@@ -480,7 +482,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             if (kla::launch_segment_scatter(d_hT, segG, N, H, dk, dv, G, st) != hipSuccess) return KLA_ERR_HIP;
             ba.seg_G = G; ba.seg_Lc = pl.base.seg_Lc;
             const long sc8 = ((long)N * G * H + 7) / 8 * 8;
-            const int wseg = (sc8 * (dv / 32) >= 192) ? 2 : 1;
+            const int wseg = sc8 * (dv / 16) > 256 ? 2 : 1;
             ba.h0 = segS;
             if (kla::launch_bwd_states_bf16(ba, dk, wseg, st) != hipSuccess) return KLA_ERR_HIP;
             ba.d_hT = segG; ba.dh0 = segB; ba.opts = opts | kla::kOptNoStore;

@@ -850,27 +850,33 @@ hipError_t launch_bwd_assemble_bf16(const BwdArgs<bf16_t>& a, int dk, long n_chu
     return hipGetLastError();
 }
 
-template <int DK, bool REV>
-static hipError_t launch_sweep_dk(const BwdArgs<bf16_t>& a, int waves, hipStream_t st)
+template <int DK, int NW, bool REV>
+static hipError_t launch_sweep(const BwdArgs<bf16_t>& a, hipStream_t st)
 {
     const int n_chains = (a.n_seq > 0 ? a.n_seq : (a.seg_G > 0 ? a.N * a.seg_G : a.N)) * a.H;
     if (n_chains == 0) return hipSuccess;
-    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * waves))));
-    if (waves == 1) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 1, REV>), grid, dim3(128 + (REV ? 64 : 0)), 0, st, a);
-    else if (waves == 2) hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 2, REV>), grid, dim3(192 + (REV ? 64 : 0)), 0, st, a);
-    else            hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, 4, REV>), grid, dim3(320 + (REV ? 64 : 0)), 0, st, a);
+    const dim3 grid((unsigned)(((n_chains + 7) / 8) * 8 * (a.dv_dim / (16 * NW))));
+    hipLaunchKernelGGL((bwd_sweep_bf16_kernel<DK, NW, REV>), grid, dim3(64 * NW + (REV ? 128 : 64)), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_states_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (waves != 1 && waves != 2 && waves != 4) return hipErrorInvalidValue;
-    return dk == 64 ? launch_sweep_dk<64, false>(a, waves, st) : launch_sweep_dk<128, false>(a, waves, st);
+    switch (waves) {
+        case 1: return dk == 64 ? launch_sweep<64, 1, false>(a, st) : launch_sweep<128, 1, false>(a, st);
+        case 2: return dk == 64 ? launch_sweep<64, 2, false>(a, st) : launch_sweep<128, 2, false>(a, st);
+        case 4: return dk == 64 ? launch_sweep<64, 4, false>(a, st) : launch_sweep<128, 4, false>(a, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 hipError_t launch_bwd_scan_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st)
 {
-    if (waves != 1 && waves != 2 && waves != 4) return hipErrorInvalidValue;
-    return dk == 64 ? launch_sweep_dk<64, true>(a, waves, st) : launch_sweep_dk<128, true>(a, waves, st);
+    switch (waves) {
+        case 1: return launch_bwd_rev_bf16(a, dk, st);
+        case 2: return dk == 64 ? launch_sweep<64, 2, true>(a, st) : launch_sweep<128, 2, true>(a, st);
+        case 4: return dk == 64 ? launch_sweep<64, 4, true>(a, st) : launch_sweep<128, 4, true>(a, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace kla

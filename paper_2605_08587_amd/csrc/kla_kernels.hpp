@@ -153,6 +153,8 @@ hipError_t launch_bwd_scan_f32(const BwdArgs<float>& a, int dk, int tiles, hipSt
 // bf16 specialisations of the two sweeps (copy wave, LDS ring, transposing reads: see kla_chunk_bwd_bf16.hip)
 hipError_t launch_bwd_states_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
 hipError_t launch_bwd_scan_bf16(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
+// the reverse sweep with a workgroup of four waves per 16 state columns (kla_chunk_rev_bf16.hip): what waves = 1 runs
+hipError_t launch_bwd_rev_bf16(const BwdArgs<bf16_t>& a, int dk, hipStream_t st);
 hipError_t launch_bwd_assemble_bf16(const BwdArgs<bf16_t>& a, int dk, long n_chunks, hipStream_t st);
 template <typename E> hipError_t launch_bwd_assemble(const BwdArgs<E>& a, int dk, long n_chunks, hipStream_t st);
 
