@@ -607,7 +607,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     sa.wsT = ia.wsT; sa.wsP = reinterpret_cast<E*>(ws + pl.base.off_P); sa.wsG = ia.wsG; sa.opts = 0u;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = ia.ktilde; sa.gc_vec = ia.gc;
     const long chains8 = ((long)pl.base.n_states * H + 7) / 8 * 8;
-    const int waves = (chains8 * (dv / 32) >= 192) ? 2 : 1;
+    const int waves = chains8 * (dv / 16) > 256 ? 2 : 1;
     if constexpr (sizeof(E) == 2) {
         if (!pl.base.tune.generic_scan)                  // else the plain kernel (A/B testing)
             return kla::launch_scan_bf16_diag(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
