@@ -351,13 +351,18 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
     constexpr int TE = 64 * LE * (int)sizeof(E), TG = 64 * LD * 4;
     constexpr int NSEG = 256 / CH, SROWS = 64 / NSEG;   // the running sums: 256 threads = CH channels x NSEG row segments
     constexpr int REC = ws_record_bytes<E>();
-    __shared__ __attribute__((aligned(16))) char area[2 * TE + TG > 3 * 64 * kLdm * 4 ? 2 * TE + TG : 3 * 64 * kLdm * 4];
+    // bf16: alpha itself too, for the pair sums (with fp32 rows a fourth table would leave room for two workgroups per CU; there it is
+    // formed from the running sums again)
+    constexpr bool AT = sizeof(E) == 2;
+    constexpr int TABLES = 2 * TE + TG + (AT ? 64 * CH * 4 : 0);
+    __shared__ __attribute__((aligned(16))) char area[TABLES > 3 * 64 * kLdm * 4 ? TABLES : 3 * 64 * kLdm * 4];
     __shared__ __attribute__((aligned(16))) float beta_s[64];
     __shared__ __attribute__((aligned(16))) float rq_s[64];      // 1/||q_i|| for the normalised read-out (Sec. 3.3), else 1
     __shared__ float segsum[NSEG][CH];
     const E* Kp = reinterpret_cast<const E*>(area);           // K rows (element type), later overlaid by Lm, Pm, Tm
     const E* Qp = reinterpret_cast<const E*>(area + TE);      // Q rows
     float* Gs = reinterpret_cast<float*>(area + 2 * TE);      // running sums of log2 alpha per channel
+    float* As = reinterpret_cast<float*>(area + 2 * TE + TG);
     float* Lm = reinterpret_cast<float*>(area);
     float* Pm = reinterpret_cast<float*>(area + 64 * kLdm * 4);
     float* Tm = reinterpret_cast<float*>(area + 2 * 64 * kLdm * 4);
@@ -435,29 +440,41 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
     floatx4 tkk[2], tqk[2];
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) { tkk[jb] = floatx4{0.f, 0.f, 0.f, 0.f}; tqk[jb] = tkk[jb]; }
-    // The MFMA jobs of phase 2a, two per wave: jobs 0..5 are the off-diagonal tiles (ti, tj); jobs 6 and 7 each take the
-    // lower-left 8x8 blocks of TWO diagonal tiles (2 (job - 6) and the next) in one 16x16 product - operand rows 0..7 belong
-    // to the first tile, rows 8..15 to the second, and the two off-diagonal 8x8 blocks of the result are not used.
-    // Per lane: the table row of its A operand row (ja), of its B operand row (jbr) and of the reference rows they are
-    // split at.
-    auto job_rows = [&](int job, int& ja, int& jbr, int& ea, int& eb) {
-        if (job < 6) {
-            const int ti = job < 1 ? 1 : (job < 3 ? 2 : 3);
-            const int tj = job < 1 ? 0 : (job < 3 ? job - 1 : job - 3);
-            ja = 16 * ti + r; jbr = 16 * tj + r; ea = eb = 16 * tj + 15;
+    // The MFMA jobs of phase 2a, two per wave: the six off-diagonal tiles (ti, tj), split at e = the last row before tile ti, so
+    // that the A operands do not depend on tj: waves 0 and 1 take two tiles of a row each and form them once; and two
+    // jobs of which each takes the lower-left 8x8 blocks of TWO diagonal tiles (2 d and the next) in one 16x16 product - operand rows
+    // 0..7 belong to the first tile, rows 8..15 to the second, and the two off-diagonal 8x8 blocks of the result are not used.
+    //     wave 0: (3,0) (3,1)    wave 1: (2,0) (2,1)    wave 2: (3,2), d = 0    wave 3: (1,0), d = 1
+    const bool same_a = wave < 2;
+    auto job_tile = [&](int jb, int& ti, int& tj) {          // (not of the two jobs on the diagonal: wave >= 2, jb = 1)
+        ti = wave == 1 ? 2 : (wave == 3 ? 1 : 3);
+        tj = wave == 2 ? 2 : (wave == 3 ? 0 : jb);
+    };
+    // Per lane: the table row of its A operand row (ja), of its B operand row (jbr) and of the reference row.
+    auto job_rows = [&](int jb, int r, int& ja, int& jbr, int& e) {
+        if (wave < 2 || jb == 0) {
+            int ti, tj;
+            job_tile(jb, ti, tj);
+            ja = 16 * ti + r; jbr = 16 * tj + r; e = 16 * ti - 1;
         } else {
-            const int t = 2 * (job - 6) + (r >> 3);      // the diagonal tile this lane's operand rows belong to
-            ja = 16 * t + 8 + (r & 7); jbr = 16 * t + (r & 7); ea = eb = 16 * t + 7;
+            const int t = 2 * (wave - 2) + (r >> 3);         // the diagonal tile this lane's operand rows belong to
+            ja = 16 * t + 8 + (r & 7); jbr = 16 * t + (r & 7); e = 16 * t + 7;
         }
     };
-    float pkk = 0.f, pqk = 0.f, pdg = 0.f;
-    int pi = 0, pj = 0;
-    if (tid < 224) {                                 // 8 blocks x 28 pairs with j < i
-        const int b8 = tid / 28, p = tid % 28;
-        int ii = 1;
-        while ((ii * (ii + 1)) / 2 <= p) ++ii;       // ii (ii - 1) / 2 <= p < ii (ii + 1) / 2
-        pi = 8 * b8 + ii; pj = 8 * b8 + p - (ii * (ii - 1)) / 2;
-    }
+    // The 8x8 blocks on the diagonal: a thread takes eight channels of a pass and, of one block, the pairs of two columns, j = m with
+    // the 7 - m rows below it and j = 7 - m with the m below that one: seven steps down the rows, k_j multiplied by alpha on
+    // the way, so a pair costs three operations per channel. (One pair per thread over all channels, gamma_i/gamma_j an exponential
+    // each, was a third of the kernel's instructions: with the running sums in registers,
+    // two shared A operands and the zeros of phase 2b only where they are read 137 -> 120 us for 4096 chunk-heads of d_k = 128, 4.5 TB/s.)
+    struct Pairs {
+        int cg8, m, b;                                       // channel group, column pair, first row of the block
+        __device__ __forceinline__ Pairs(int lane, int wave) : cg8(lane & 7), m((lane >> 3) & 3), b(8 * (2 * wave + (lane >> 5))) {}
+        __device__ __forceinline__ int row(int x) const { return b + x + 1 + (x < 7 - m ? m : 0); }      // i of step x
+        __device__ __forceinline__ int col(int x) const { return b + (x < 7 - m ? m : 7 - m); }          // j
+    };
+    float skk[7], sqk[7], sdg[2] = {0.f, 0.f};               // sdg: q_i . k_i of rows m and 7 - m
+#pragma unroll
+    for (int x = 0; x < 7; ++x) { skk[x] = 0.f; sqk[x] = 0.f; }
 
     float ksq[64 * PPH / 256];                       // this thread's share of ||k_row||^2, rows (tid + 256 it) / PPH
 #pragma unroll
@@ -488,8 +505,19 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
     };
     constexpr bool AHEAD = sizeof(E) == 2;           // fp32 rows are twice the registers: fetched pass by pass
     if constexpr (AHEAD) fetch(0);
+    float et[NKQ];                                   // of the rows whose norms this thread ends up with
+#pragma unroll
+    for (int it = 0; it < NKQ; ++it) {
+        const int x = tid + 256 * it, row = x / PPH;
+        et[it] = x % PPH == 0 && row < clen ? a.eta[(size_t)(tok0 + row) * a.H + h] : 0.f;
+    }
     for (int pass = 0; pass < NPASS; ++pass) {
         const int c0 = pass * CH;                    // first channel of this pass
+        // a lane index that the compiler cannot see through: the addresses of a pass are formed in it, not kept over all of them
+        int tv = threadIdx.x;
+        asm volatile("" : "+v"(tv));
+        const int tid = tv, lane = tid & 63, r = lane & 15, g = lane >> 4;
+        const Pairs pr(lane, wave);
         if (pass > 0) __syncthreads();               // the previous pass has read its tables
         if constexpr (!AHEAD) fetch(c0);
         // ---- phase 1: K, Q rows and log2 alpha of CH channels -> LDS (the squares of K summed for the key norms on the way)
@@ -509,20 +537,28 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
             const int x = tid + 256 * it, row = x / (CH / 4), c4 = x % (CH / 4);
             const float4 v = lad[it];
             const float s2 = 1.44269504088896341f;
-            *reinterpret_cast<float4*>(Gs + row * LD + 4 * c4) = make_float4(v.x * s2, v.y * s2, v.z * s2, v.w * s2);
+            const float4 l2 = make_float4(v.x * s2, v.y * s2, v.z * s2, v.w * s2);
+            *reinterpret_cast<float4*>(Gs + row * LD + 4 * c4) = l2;
+            if constexpr (AT)
+                *reinterpret_cast<float4*>(As + row * CH + 4 * (c4 ^ (row & 15))) =
+                    make_float4(__builtin_amdgcn_exp2f(l2.x), __builtin_amdgcn_exp2f(l2.y), __builtin_amdgcn_exp2f(l2.z), __builtin_amdgcn_exp2f(l2.w));
         }
         __syncthreads();
         {   // per channel: running sum over the tokens of the chunk, NSEG row segments side by side, then their offsets
             const int c = tid % CH, sg = tid / CH;
-            float acc = 0.f;
-            for (int i = sg * SROWS; i < (sg + 1) * SROWS; ++i) { acc += Gs[i * LD + c]; Gs[i * LD + c] = acc; }
-            segsum[sg][c] = acc;
+            float* col = Gs + sg * SROWS * LD + c;
+            float acc[SROWS];
+#pragma unroll
+            for (int i = 0; i < SROWS; ++i) acc[i] = col[i * LD];
+#pragma unroll
+            for (int i = 1; i < SROWS; ++i) acc[i] += acc[i - 1];
+            segsum[sg][c] = acc[SROWS - 1];
             __syncthreads();
             float base = 0.f;
             for (int s2 = 0; s2 < sg; ++s2) base += segsum[s2][c];
-            if (sg > 0)
-                for (int i = sg * SROWS; i < (sg + 1) * SROWS; ++i) Gs[i * LD + c] += base;
-            if (sg == NSEG - 1) a.gc[(size_t)blockIdx.x * DK + c0 + c] = __builtin_amdgcn_exp2f(base + acc);      // gamma_C
+#pragma unroll
+            for (int i = 0; i < SROWS; ++i) col[i * LD] = acc[i] + base;
+            if (sg == NSEG - 1) a.gc[(size_t)blockIdx.x * DK + c0 + c] = __builtin_amdgcn_exp2f(base + acc[SROWS - 1]);      // gamma_C
         }
         __syncthreads();
 
@@ -557,69 +593,89 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
         // (no barrier: phase 2a only reads the tables, like phase 1b)
 
         // ---- phase 2a: K K^T and Q K^T with the decay ratios inside the sums, the channels of this pass ---------
-        // (1) MFMA jobs, operands formed in registers from the tables: the six off-diagonal 16x16 tiles (ti > tj), split at
-        //     e = last row of tile tj, A row i = k_i (or q_i) o gamma_i/gamma_e, B row j = k_j o gamma_e/gamma_j; and of
-        //     each diagonal tile the lower-left 8x8 block, split at e = row 7 of the tile, the other rows of both operands
-        //     zero.  Every factor is <= 1.  Jobs 0..9 go to wave (job % 4).
-        // (2) the 8x8 blocks on the diagonal, one (i, j) pair per thread over all channels: gamma_i/gamma_j <= 1 directly.
+        // (1) MFMA jobs, operands formed in registers from the tables: A row i = k_i (or q_i) o gamma_i/gamma_e, B row
+        //     j = k_j o gamma_e/gamma_j, every factor <= 1.
+        // (2) the 8x8 blocks on the diagonal, pair by pair on the vector ALUs.
+#pragma unroll 1
+        for (int kp = 0; kp < CH / 32; ++kp) {
+            Slot<E> sk, sq;
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            const int job = wave + 4 * jb;
-            int ja, jbr, ea, eb;
-            job_rows(job, ja, jbr, ea, eb);
-            const float* gi = Gs + ja * LD;
-            const float* gj = Gs + jbr * LD;
-            const float* gea = Gs + ea * LD;
-            const float* geb = Gs + eb * LD;
-            const E* ki = Kp + ja * LE;
-            const E* qi = Qp + ja * LE;
-            const E* kj = Kp + jbr * LE;
-            for (int kp = 0; kp < CH / 32; ++kp) {
-                floatx4 ka[2], qa[2], kbv[2];
+            for (int jb = 0; jb < 2; ++jb) {
+                int ja, jbr, e;
+                job_rows(jb, r, ja, jbr, e);
+                const float* ge = Gs + e * LD;
+                if (jb == 0 || !same_a) {
+                    const float* gi = Gs + ja * LD;
+                    const E* ki = Kp + ja * LE;
+                    const E* qi = Qp + ja * LE;
+                    floatx4 ka[2], qa[2];
+#pragma unroll
+                    for (int blk = 0; blk < 2; ++blk) {
+                        const int c = 32 * kp + 16 * blk + 4 * g;
+                        const floatx4 gev = ld4f(ge + c), giv = ld4f(gi + c), kiv = ld4e(ki + c), qiv = ld4e(qi + c);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            const float up = __builtin_amdgcn_exp2f(giv[x] - gev[x]);      // gamma_i / gamma_e <= 1
+                            ka[blk][x] = kiv[x] * up; qa[blk][x] = qiv[x] * up;
+                        }
+                    }
+                    sk.q0 = acc_to_quad<E>(ka[0]); sk.q1 = acc_to_quad<E>(ka[1]);
+                    sq.q0 = acc_to_quad<E>(qa[0]); sq.q1 = acc_to_quad<E>(qa[1]);
+                }
+                const float* gj = Gs + jbr * LD;
+                const E* kj = Kp + jbr * LE;
+                floatx4 kbv[2];
 #pragma unroll
                 for (int blk = 0; blk < 2; ++blk) {
                     const int c = 32 * kp + 16 * blk + 4 * g;
-                    const floatx4 geav = ld4f(gea + c), gebv = ld4f(geb + c), giv = ld4f(gi + c), gjv = ld4f(gj + c);
-                    const floatx4 kiv = ld4e(ki + c), qiv = ld4e(qi + c), kjv = ld4e(kj + c);
+                    const floatx4 gev = ld4f(ge + c), gjv = ld4f(gj + c), kjv = ld4e(kj + c);
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const float up = __builtin_amdgcn_exp2f(giv[x] - geav[x]);      // gamma_i / gamma_e <= 1
-                        const float dn = __builtin_amdgcn_exp2f(gebv[x] - gjv[x]);      // gamma_e / gamma_j <= 1
-                        ka[blk][x] = kiv[x] * up; qa[blk][x] = qiv[x] * up; kbv[blk][x] = kjv[x] * dn;
-                    }
+                    for (int x = 0; x < 4; ++x) kbv[blk][x] = kjv[x] * __builtin_amdgcn_exp2f(gev[x] - gjv[x]);      // gamma_e / gamma_j <= 1
                 }
-                Slot<E> sk, sq;
-                sk.q0 = acc_to_quad<E>(ka[0]); sk.q1 = acc_to_quad<E>(ka[1]);
-                sq.q0 = acc_to_quad<E>(qa[0]); sq.q1 = acc_to_quad<E>(qa[1]);
                 const typename QuadT<E>::type b0 = acc_to_quad<E>(kbv[0]), b1 = acc_to_quad<E>(kbv[1]);
                 mma32<E>(tkk[jb], sk, b0, b1);
                 mma32<E>(tqk[jb], sq, b0, b1);
             }
         }
         if constexpr (AHEAD) { if (pass + 1 < NPASS) fetch(c0 + CH); }   // on their way during the pair sums
-        if (tid < 224) {
-            const float* gi = Gs + pi * LD; const float* gj = Gs + pj * LD;
-            const E* ki = Kp + pi * LE; const E* qi = Qp + pi * LE; const E* kj = Kp + pj * LE;
-#pragma unroll 2
-            for (int c = 0; c < CH; c += 4) {
-                const floatx4 giv = ld4f(gi + c), gjv = ld4f(gj + c);
-                const floatx4 kiv = ld4e(ki + c), qiv = ld4e(qi + c), kjv = ld4e(kj + c);
+#pragma unroll 1
+        for (int c4 = 0; c4 < 2; ++c4) {                 // this thread's channels: 4 cg8 .. + 3 and 32 more
+            const int c = 32 * c4 + 4 * pr.cg8;
+            floatx4 w = ld4e(Kp + (pr.b + pr.m) * LE + c);
+            const floatx4 k2 = ld4e(Kp + (pr.b + 7 - pr.m) * LE + c);
+            const floatx4 q1 = ld4e(Qp + (pr.b + pr.m) * LE + c), q2 = ld4e(Qp + (pr.b + 7 - pr.m) * LE + c);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) { sdg[0] += q1[x] * w[x]; sdg[1] += q2[x] * k2[x]; }
+            static_for<7>([&](auto sc) {
+                constexpr int st = sc;
+                const int i = pr.row(st);
+                if constexpr (st >= 4) { if (st == 7 - pr.m) w = k2; }
+                floatx4 al;
+                if constexpr (AT) al = ld4f(As + i * CH + 4 * ((8 * c4 + pr.cg8) ^ (i & 15)));
+                else {
+                    const floatx4 g1 = ld4f(Gs + i * LD + c), g0 = ld4f(Gs + (i - 1) * LD + c);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) al[x] = __builtin_amdgcn_exp2f(g1[x] - g0[x]);
+                }
+                const floatx4 kv = ld4e(Kp + i * LE + c), qv = ld4e(Qp + i * LE + c);
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    const float w = kjv[x] * __builtin_amdgcn_exp2f(giv[x] - gjv[x]);
-                    pkk += kiv[x] * w; pqk += qiv[x] * w;
+                    w[x] *= al[x];
+                    skk[st] += kv[x] * w[x]; sqk[st] += qv[x] * w[x];
                 }
-            }
-        }
-        if (tid < 64) {                                  // P_ii = q_i . k_i
-            const E* ki = Kp + tid * LE; const E* qi = Qp + tid * LE;
-            for (int c = 0; c < CH; c += 4) {
-                const floatx4 kiv = ld4e(ki + c), qiv = ld4e(qi + c);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) pdg += qiv[x] * kiv[x];
-            }
+            });
         }
     }
+    // over the eight threads of a block's column pair (exchange with lane ^ 1, ^ 2, then the mirror of eight lanes)
+    auto sum8 = [](float v) {
+        v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));     // quad_perm [1,0,3,2]
+        v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xf, 0xf, true));     // quad_perm [2,3,0,1]
+        v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, true));    // row_half_mirror
+        return v;
+    };
+#pragma unroll
+    for (int x = 0; x < 7; ++x) { skk[x] = sum8(skk[x]); sqk[x] = sum8(sqk[x]); }
+    sdg[0] = sum8(sdg[0]); sdg[1] = sum8(sdg[1]);
     // ---- beta of eq. (3) from the key norms (the PPH threads of a row sit in consecutive lanes)
 #pragma unroll
     for (int it = 0; it < 64 * PPH / 256; ++it) {
@@ -629,31 +685,31 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
 #pragma unroll
         for (int off = 1; off < PPH; off <<= 1) ss += __shfl_xor(ss, off, kWave);
         if (x % PPH == 0) {
-            const float et = row < clen ? a.eta[(size_t)(tok0 + row) * a.H + h] : 0.f;
-            beta_s[row] = (a.opts & kOptGdnBeta) ? et : kaczmarz_beta(et, ss, a.eps);
+            beta_s[row] = (a.opts & kOptGdnBeta) ? et[it] : kaczmarz_beta(et[it], ss, a.eps);
         }
     }
     __syncthreads();   // the tables are dead from here on; Lm, Pm, Tm overlay them
 
-    // ---- phase 2b: beta -> L and P, everything else zero ---------------------------------------------------------
-    for (int x = tid; x < 64 * 64; x += 256) {
-        const int i = x >> 6, j = x & 63;
-        Lm[i * kLdm + j] = 0.f; Pm[i * kLdm + j] = 0.f; Tm[i * kLdm + j] = 0.f;
+    // ---- phase 2b: beta -> L and P.  What is read besides the products must be zero: of P the diagonal tiles and the tiles (0,1) and
+    //      (2,3) to their right (tile-pairs are stored whole), of T' these two; of L only the strict lower triangle is read.
+    for (int x = tid; x < 512; x += 256) {
+        const int t = x >> 6, row = (x >> 2) & 15, c4 = x & 3;                                  // eight 16x16 tiles
+        const int ti = t < 4 ? t : (t & 1) * 2, tj = t < 4 ? t : ti + 1;
+        *reinterpret_cast<float4*>((t < 6 ? Pm : Tm) + (16 * ti + row) * kLdm + 16 * tj + 4 * c4) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
-        const int job = wave + 4 * jb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int il = 4 * g + e;                // row inside the product tile; its column is r
             int i, j; bool ok;
-            if (job < 6) {
-                const int ti = job < 1 ? 1 : (job < 3 ? 2 : 3);
-                const int tj = job < 1 ? 0 : (job < 3 ? job - 1 : job - 3);
+            if (wave < 2 || jb == 0) {
+                int ti, tj;
+                job_tile(jb, ti, tj);
                 i = 16 * ti + il; j = 16 * tj + r; ok = true;
             } else {                                 // the two diagonal 8x8 blocks of the product
-                const int t = 2 * (job - 6) + (il >> 3);
+                const int t = 2 * (wave - 2) + (il >> 3);
                 i = 16 * t + 8 + (il & 7); j = 16 * t + (r & 7); ok = (il >> 3) == (r >> 3);
             }
             if (ok) {
@@ -662,8 +718,16 @@ __global__ __launch_bounds__(256, 3) void intra_diag_kernel(IntraDiagArgs<E> a)
             }
         }
     }
-    if (tid < 224) { Lm[pi * kLdm + pj] = beta_s[pi] * pkk; Pm[pi * kLdm + pj] = pqk * rq_s[pi]; }
-    if (tid < 64) Pm[tid * kLdm + tid] = pdg * rq_s[tid];
+    const Pairs pr(lane, wave);
+    if (pr.cg8 == 0) {
+#pragma unroll
+        for (int x = 0; x < 7; ++x) {
+            const int i = pr.row(x), j = pr.col(x);
+            Lm[i * kLdm + j] = beta_s[i] * skk[x]; Pm[i * kLdm + j] = sqk[x] * rq_s[i];
+        }
+        Pm[(pr.b + pr.m) * (kLdm + 1)] = sdg[0] * rq_s[pr.b + pr.m];
+        Pm[(pr.b + 7 - pr.m) * (kLdm + 1)] = sdg[1] * rq_s[pr.b + 7 - pr.m];
+    }
     __syncthreads();
     invert_and_store<E, false>(Lm, Tm, Pm, beta_s, reinterpret_cast<char*>(a.wsT) + (size_t)blockIdx.x * REC, tid);
 }
