@@ -459,6 +459,10 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     ba.Y = reinterpret_cast<E*>(ws + pl.off_Y);
     ba.opts = opts;
     ba.seg_G = 0; ba.seg_Lc = 0;
+    // What the slices of a head all copy in the reverse sweep, K, Q, M^T and P^T: beyond some 144 MB (of a memory-side cache of 256, which
+    // the checkpoints, Y and dO go through too) it comes from HBM, and asking ahead shortens the copies' way (8 x 4096 tokens, 8
+    // heads: 143 -> 122 us; 7 x 4096, 161 MB: 130 -> 119); below, it is there already (8 x 3000, 135 MB: 90.3, 90.5; 8 x 2048: 63.7, 65.7).
+    ba.touch = (size_t)pl.base.n_chunks * H * (2 * 64 * dk * sizeof(E) + (size_t)2 * 384 * 8 * sizeof(E)) > ((size_t)144 << 20);
     if constexpr (sizeof(E) == 2) {
         if (fast && pl.base.seg_G > 1) {
             // Segment-parallel sweeps for a few long sequences (see kla_chunk_segments.hip).  Forward: maps of all

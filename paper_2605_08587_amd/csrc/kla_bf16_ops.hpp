@@ -52,6 +52,21 @@ __device__ __forceinline__ void dma16(const char* gbase_uniform, int lane_off, c
                  : "memory");
 }
 
+// One dword of one 128-byte line that all slices of a head will copy: the lines of two [64 x d_k] tiles (rows of RB bytes, `stride` apart,
+// from row `row0` of `rows` on) and the first `n_rec` lines at `rec`, counted through in this order; i: which.  A wave that has nothing
+// else to wait for asks for its slice's share some chunks ahead of the copies, which then find their lines in L2: a CU's
+// copies are in flight by the 64 KB, so what they take in per cycle falls with their latency.  The value is of no interest, but has to be
+// waited for (by the next call's caller) before its register is free.
+template <int RB> __device__ __forceinline__ uint32_t touch_line(const char* tile0, const char* tile1, size_t stride, int row0, int rows,
+                                                                 const char* rec, int n_rec, int i)
+{
+    constexpr int LPR = RB / 128, NL = 64 * LPR;
+    if (i >= 2 * NL + n_rec) return 0u;
+    const int l = i % NL;
+    const char* p = i < 2 * NL ? (i < NL ? tile0 : tile1) + (size_t)min(row0 + l / LPR, rows - 1) * stride + (l % LPR) * 128 : rec + (size_t)(i - 2 * NL) * 128;
+    return *reinterpret_cast<const uint32_t*>(p);
+}
+
 // s_waitcnt on the vector-memory counter only (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 template <int N> __device__ __forceinline__ void wait_vmcnt()
 {

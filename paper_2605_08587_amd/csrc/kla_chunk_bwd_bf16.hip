@@ -349,8 +349,21 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             // ---- the store wave: after the barrier that ends visit i, chunk_of(i) is complete in the staging area of
             //      parity i & 1, which the compute waves write again only in visit i + 2, behind the barrier this wave
             //      reaches next
+            //      Two chains: it also touches the lines of K, Q, M^T and P^T of the visit AHEAD later (a.touch: where these are more
+            //      than the memory-side cache holds on to).
+            constexpr int AHEAD = 4;
+            uint32_t seen[2] = {0u, 0u};
             __syncthreads();
             for (int i = 0; i < nch; ++i) {
+                if constexpr (NW == 2) {
+                    asm volatile("" ::"v"(seen[0]), "v"(seen[1]));
+                    if (a.touch && i + AHEAD < nch) {
+                        const int c = chunk_of(i + AHEAD);
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            seen[j] = touch_line<RB>(kbase, qbase, kq_row, 64 * c, len, tpbase + (size_t)c * a.H * REC + C::TPB, 2 * C::TPB / 128, (2 * slice + j) * 64 + lane);
+                    }
+                }
                 __syncthreads();
                 if (store) write_out(chunk_of(i), (i & 1) ? ost1 : ost0);
             }

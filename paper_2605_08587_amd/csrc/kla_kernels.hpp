@@ -145,6 +145,7 @@ template <typename E> struct BwdArgs {
     // segment, [N * seg_G][H][dk][dv].
     int seg_G, seg_Lc;
     const int* seq_order = nullptr;  // packed batches, see ScanArgs
+    bool touch = false;              // reverse sweep of two chains: lines asked for ahead of the copies (touch_line in kla_bf16_ops.hpp)
 };
 hipError_t launch_bwd_states(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);   // bf16, plain form
 hipError_t launch_bwd_scan(const BwdArgs<bf16_t>& a, int dk, int waves, hipStream_t st);
