@@ -495,7 +495,10 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         float* dst = wave == 0 ? eg_s : (wave == 1 ? ed_s : (wave == 2 ? beta_s : invden_s));
         dst[lane] = vec[tid];
         if (wave == 1) rq_s[lane] = vec[256 + lane];
-        if (wave == 0) g_s[lane] = lane < clen ? a.log_alpha[(size_t)(tok0 + lane) * a.H + h] : 0.f;
+        if (wave == 0) {                                 // g_i = log gamma_i, in units of log 2: the decay ratios below are exp2 of differences
+            const float la = lane < clen ? a.log_alpha[(size_t)(tok0 + lane) * a.H + h] : 0.f;
+            g_s[lane] = prefix_sum64(la, lane) * 1.44269504088896341f;
+        }
     }
 
     // ---- per-lane offsets ---------------------------------------------------------------------------
@@ -681,12 +684,6 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
             }
         }
     }
-    if (wave == 0) {                                 // g_i = log gamma_i
-        float x = g_s[lane];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_up(x, off, kWave); if (lane >= off) x += y; }
-        g_s[lane] = x * 1.44269504088896341f;        // in units of log 2: the decay ratios below are exp2 of differences
-    }
     {   // D_gamma dO S^T,  -D_gamma dX S^T (dX = B Y),  diag(gamma_C/gamma_i) U dS'^T
         const floatx4 egv = ld_f4(reinterpret_cast<const char*>(eg_s + 16 * wave + 4 * g));
         const floatx4 edv = ld_f4(reinterpret_cast<const char*>(ed_s + 16 * wave + 4 * g));
@@ -696,7 +693,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         for (int ct = 0; ct < KB; ++ct) { dQ[ct] = dQ[ct] * egq; dKr[ct] = dKr[ct] * ngb; dKw[ct] = dKw[ct] * edv; }
     }
     if ((r >> 2) == g) yx_s[16 * wave + r] = (r & 2) ? ((r & 1) ? YX[3] : YX[2]) : ((r & 1) ? YX[1] : YX[0]);
-    sdot = wave_sum(sdot);
+    sdot = wave_sum_rows(sdot);
     if (lane == 0) red_s[wave] = sdot;
     wait_vmcnt<0>();                                 // this wave's part of K and Q
     __syncthreads();                                 // the slab areas are dead from here on
@@ -733,7 +730,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
 #pragma unroll
         for (int e = 0; e < 4; ++e) zsum += rowmask[e] * dKw[ct][e] * kk[e];
     }
-    zsum = wave_sum(zsum);
+    zsum = wave_sum_rows(zsum);
     if (lane == 0) red_s[4 + wave] = zsum;
 
     floatx4 E2[KB];
@@ -802,11 +799,8 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int i = 16 * wave + 4 * g + e;
-        float db = dbr[e], dgv = dgr[e], dqv = dqr[e];
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            db += __shfl_xor(db, off, kWave); dgv += __shfl_xor(dgv, off, kWave); dqv += __shfl_xor(dqv, off, kWave);
-        }
+        float db = row_sum16(dbr[e]);
+        const float dgv = row_sum16(dgr[e]), dqv = row_sum16(dqr[e]);
         db += yx_s[i];
         if (r == 0) { dbeta_s[i] = db; dg_s[i] = rowmask[e] * (dgv + dqv); }
         cq[e] = -dqv * rq_s[i] * rq_s[i];
@@ -843,13 +837,13 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         }
     }
     if (wave == 0) {
-        float x = dg_s[lane];
-        if (lane == 63) x += eg_s[63] * (red_s[0] + red_s[1] + red_s[2] + red_s[3]) + (red_s[4] + red_s[5] + red_s[6] + red_s[7]);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_down(x, off, kWave); if (lane + off < 64) x += y; }
-        if (lane < clen) {
-            a.dlog_alpha[(size_t)(tok0 + lane) * a.H + h] = x;
-            a.deta[(size_t)(tok0 + lane) * a.H + h] = dbeta_s[lane] * invden_s[lane];
+        const int i = 63 - lane;                         // suffix sums: prefix sums from the last token on
+        float x = dg_s[i];
+        if (lane == 0) x += eg_s[63] * (red_s[0] + red_s[1] + red_s[2] + red_s[3]) + (red_s[4] + red_s[5] + red_s[6] + red_s[7]);
+        x = prefix_sum64(x, lane);
+        if (i < clen) {
+            a.dlog_alpha[(size_t)(tok0 + i) * a.H + h] = x;
+            a.deta[(size_t)(tok0 + i) * a.H + h] = dbeta_s[i] * invden_s[i];
         }
     }
 }

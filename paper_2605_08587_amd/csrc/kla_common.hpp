@@ -55,6 +55,33 @@ __device__ __forceinline__ float wave_sum(float x)
     return x;
 }
 
+// Sums by DPP moves, which stay on the vector ALU (a shuffle goes through LDS): over the 16 lanes of a row, in every lane; over
+// the wave, in every lane; and the inclusive prefix sum over the 64 lanes (shifts within rows, the rows joined through the scalar unit).
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)); }
+__device__ __forceinline__ float row_sum16(float x)
+{
+    x += dpp_mov<0xB1>(x);       // quad_perm [1,0,3,2]
+    x += dpp_mov<0x4E>(x);       // quad_perm [2,3,0,1]
+    x += dpp_mov<0x141>(x);      // row_half_mirror
+    x += dpp_mov<0x140>(x);      // row_mirror
+    return x;
+}
+__device__ __forceinline__ float lane_value(float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); }
+__device__ __forceinline__ float wave_sum_rows(float x)
+{
+    x = row_sum16(x);
+    return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
+}
+__device__ __forceinline__ float prefix_sum64(float x, int lane)
+{
+    x += dpp_mov<0x111>(x);      // row_shr:1, 2, 4, 8
+    x += dpp_mov<0x112>(x);
+    x += dpp_mov<0x114>(x);
+    x += dpp_mov<0x118>(x);
+    const float r0 = lane_value(x, 15), r1 = lane_value(x, 31), r2 = lane_value(x, 47);
+    return x + (lane < 16 ? 0.f : (lane < 32 ? r0 : (lane < 48 ? r0 + r1 : (r0 + r1) + r2)));
+}
+
 // Where a per-chunk workgroup works: global chunk index cg (sequences in order, chunks of 64 tokens counted from each
 // sequence's own first token) -> first token of the chunk and its length (64, or less for a ragged last chunk).
 // cu_seqlens / chunk_off (chunk_off[s] = number of chunks before sequence s) describe a packed batch; both NULL for a
