@@ -456,19 +456,17 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     constexpr int RB = DK * 2, PPR = DK / 8, RPB = 1024 / RB, NKB = 64 / RPB;      // [64 x d_k] tiles
     constexpr int RBA = 64, NAB = 4;                 // [64 tokens x 32 columns] slabs: 4 blocks of 16 rows of 64 bytes
     constexpr int TK = 64 * RB, TS = 32 * RB, NSB = TS / 1024, TA = 64 * RBA;
-    constexpr int kLd = 68, MB = 64 * kLd * 4;
+    constexpr int ORQ = RB + 16, MB = 64 * ORQ > 16384 ? 64 * ORQ : 16384;       // row stride and room of the dq / dk staging tiles
     // first phase, two buffers of one 32-column slab each: S^T | dS'^T | dO | U | Y | X (U is formed here, from T' and X)
     constexpr int OFF_S = 0, OFF_DS = TS, OFF_DO = 2 * TS, OFF_U = OFF_DO + TA, OFF_Y = OFF_U + TA, OFF_X = OFF_Y + TA;
     constexpr int SLAB = 2 * TS + 4 * TA;
     constexpr int PH1 = 2 * SLAB;
-    // second phase: K | Q | A o dP | D'.  K and Q are fetched into the first buffer while the last slab (always in the
-    // second one: d_v / 32 is even) is being used.
+    // second phase: K | Q | A o dP, D' | B D', the latter two areas also the staging tiles of dq and dk.  K and Q are fetched into the
+    // first buffer while the last slab (always in the second one: d_v / 32 is even) is being used.
     constexpr int OFF_K = 0, OFF_Q = TK, OFF_E1 = 2 * TK, OFF_DP = 2 * TK + MB;
     constexpr int PH2 = 2 * TK + 2 * MB;
     constexpr int BIG = PH1 > PH2 ? PH1 : PH2;
     static_assert(2 * TK <= SLAB, "the K and Q tiles fit one slab buffer");
-    constexpr int ORQ = RB + 16;                     // row stride of the dq / dk staging tiles (over A o dP and D')
-    static_assert(64 * ORQ <= MB, "staging tiles fit the fp32 matrices they replace");
     __shared__ __attribute__((aligned(1024))) char lds[BIG];
     __shared__ __attribute__((aligned(1024))) char tp_s[kTriPairs * 1024];       // T' of the chunk, as the record holds it
     __shared__ __attribute__((aligned(16))) float eg_s[64], ed_s[64], beta_s[64], invden_s[64], rq_s[64], g_s[64], yx_s[64],
@@ -580,7 +578,8 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     // ---- first phase: everything that contracts over d_v, 32 columns at a time.  The products of a slab take a quarter of a
     //      trip to memory, so a buffer is refilled as soon as every wave is done with it (one more barrier per slab), while
     //      the slab in the other one is still on its way; K and Q come behind the last slab.  12 sequences of 100 .. 2100 tokens,
-    //      8 heads, d_v = 256: assembly 151 -> 144 us; 8 x 4096 tokens, d_v = 128: 164 -> 156 (5.2 TB/s) -----------------
+    //      8 heads, d_v = 256: assembly 151 -> 144 us; 8 x 4096 tokens, d_v = 128: 164 -> 156. (With row sums by DPP and the
+    //      bf16 tiles of the second phase 133 and 150 us, 5.3 TB/s of its bytes.) -----------------
     const char* Sg = reinterpret_cast<const char*>(a.s_chk) + (size_t)blockIdx.x * DK * a.dv_dim * 2;
     const char* dSg = reinterpret_cast<const char*>(a.ds_chk) + (size_t)blockIdx.x * DK * a.dv_dim * 2;
     // X and Y of a whole chunk: slots, 4 KiB per slab; of a short one: rows (put_rows)
@@ -698,20 +697,36 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     wait_vmcnt<0>();                                 // this wave's part of K and Q
     __syncthreads();                                 // the slab areas are dead from here on
 
-    // ---- second phase: A o dP and D' = -A^- o (Y U^T) as fp32 matrices ------------------------------------------
-    float* E1 = reinterpret_cast<float*>(lds + OFF_E1);
-    float* Dp = reinterpret_cast<float*>(lds + OFF_DP);
-    static_for<4>([&](auto jt) {
-        const int j = 16 * jt + r;
-        const float gj = g_s[j];
+    // ---- second phase: A o dP, D' = -A^- o (Y U^T) and B D' as bf16 tiles of 512 bytes, tile (ti, tj) at 4 ti + tj, each as the
+    //      accumulators hold it: lane (r, g)'s quad is rows 4 g .. + 3 of column r, which is the A operand of the transposed
+    //      products as it lies and of the others through the transposing read. (As fp32 matrices they took 32 writes of one float, 24 to 48 reads
+    //      and the conversions per wave: 152.6 -> 150 us, 136.5 -> 133, one round of chunk-heads 15.6 -> 13.9.) Tiles right of the diagonal that a pair of tiles drags in are zero.
+    char* Et = lds + OFF_E1;
+    char* Dt = Et + 8192;
+    char* Bt = lds + OFF_DP;
+    static_assert(2 * 8192 <= MB, "the tiles fit where the fp32 staging tiles go");
+    {
+        const floatx4 gi = ld_f4(reinterpret_cast<const char*>(g_s + 16 * wave + 4 * g)), rqi = ld_f4(reinterpret_cast<const char*>(rq_s + 16 * wave + 4 * g)),
+                      bi = ld_f4(reinterpret_cast<const char*>(beta_s + 16 * wave + 4 * g));
+        static_for<4>([&](auto jt) {
+            if (jt <= (wave | 1)) {
+                const int j = 16 * jt + r;
+                const float gj = g_s[j];
+                floatx4 ev, dv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = 16 * wave + 4 * g + e;
-            const float dec = (jt <= wave && j <= i && i < clen) ? __builtin_amdgcn_exp2f(g_s[i] - gj) : 0.f;
-            E1[i * kLd + j] = dec * rq_s[i] * dP[jt][e];
-            Dp[i * kLd + j] = (j < i) ? -dec * N1[jt][e] : 0.f;
-        }
-    });
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 16 * wave + 4 * g + e;
+                    const float dec = (jt <= wave && j <= i && i < clen) ? __builtin_amdgcn_exp2f(gi[e] - gj) : 0.f;
+                    ev[e] = dec * rqi[e] * dP[jt][e];
+                    dv[e] = (j < i) ? -dec * N1[jt][e] : 0.f;
+                }
+                const int at = (4 * wave + jt) * 512 + lane * 8;
+                *reinterpret_cast<u32x2*>(Et + at) = to_quad(ev);
+                *reinterpret_cast<u32x2*>(Dt + at) = to_quad(dv);
+                *reinterpret_cast<u32x2*>(Bt + at) = to_quad(dv * bi);
+            }
+        });
+    }
     __syncthreads();
 
     // K and Q of this wave's rows as accumulator tiles: token 16 wave + 4 g + e, feature of (tile ct, lane r)
@@ -736,26 +751,22 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     floatx4 E2[KB];
 #pragma unroll
     for (int ct = 0; ct < KB; ++ct) E2[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int row_a = 16 * wave + r;
-    auto rows_slot = [&](const float* m, int jp, u32x2& q0, u32x2& q1) {
-        q0 = to_quad(ld_f4(reinterpret_cast<const char*>(m + row_a * kLd + 32 * jp + 4 * g)));
-        q1 = to_quad(ld_f4(reinterpret_cast<const char*>(m + row_a * kLd + 32 * jp + 16 + 4 * g)));
+    const int otr = (16 * c4 + 4 * g + a4) * 8;          // source of the transposing read: rows 4 c4 .. + 3 of column 4 g + a4
+    auto rows_slot = [&](const char* m, int jp, u32x2& q0, u32x2& q1) {      // rows 16 wave + r, columns 32 jp + (16 +) 4 g ..
+        const char* p = m + (4 * wave + 2 * jp) * 512 + otr;
+        q0 = lds_read_tr(p);
+        q1 = lds_read_tr(p + 512);
     };
-    auto cols_slot = [&](const float* m, const float* scale, int jp, u32x2& q0, u32x2& q1) {
-        floatx4 x0, x1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i0 = 32 * jp + 4 * g + e, i1 = i0 + 16;
-            x0[e] = m[i0 * kLd + row_a]; x1[e] = m[i1 * kLd + row_a];
-            if (scale) { x0[e] *= scale[i0]; x1[e] *= scale[i1]; }
-        }
-        q0 = to_quad(x0); q1 = to_quad(x1);
+    auto cols_slot = [&](const char* m, int jp, u32x2& q0, u32x2& q1) {      // column 16 wave + r, rows 32 jp + (16 +) 4 g ..
+        const char* p = m + (8 * jp + wave) * 512 + lane * 8;
+        q0 = *reinterpret_cast<const u32x2*>(p);
+        q1 = *reinterpret_cast<const u32x2*>(p + 4 * 512);
     };
     static_for<2>([&](auto jp) {
         if (jp <= (wave >> 1)) {
             u32x2 e0, e1, d0, d1;
-            rows_slot(E1, jp, e0, e1);
-            rows_slot(Dp, jp, d0, d1);
+            rows_slot(Et, jp, e0, e1);
+            rows_slot(Dt, jp, d0, d1);
 #pragma unroll
             for (int ct = 0; ct < KB; ++ct) {
                 u32x2 k0, k1;
@@ -766,8 +777,8 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
         }
         if (jp >= (wave >> 1)) {
             u32x2 e0, e1, d0, d1;
-            cols_slot(E1, nullptr, jp, e0, e1);
-            cols_slot(Dp, beta_s, jp, d0, d1);
+            cols_slot(Et, jp, e0, e1);
+            cols_slot(Bt, jp, d0, d1);
 #pragma unroll
             for (int ct = 0; ct < KB; ++ct) {
                 u32x2 k0, k1, q0, q1;
