@@ -499,13 +499,6 @@ __device__ __forceinline__ Slot<E> slot_from_cols(const float* m, const float* s
     Slot<E> s; s.q0 = acc_to_quad<E>(x0); s.q1 = acc_to_quad<E>(x1); return s;
 }
 
-__device__ __forceinline__ float row16_sum(float x)       // sum over the 16 lanes that share g
-{
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off, kWave);
-    return x;
-}
-
 }  // namespace
 
 template <typename E, int DK>
@@ -551,14 +544,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
         // Normalised read-out (Sec. 3.3): the rows of dO are scaled by 1/||q_i|| wherever they meet U or S, which makes
         // dQ' = diag(1/||q||) dL/d(q/||q||); dq_i = dQ'_i - (q_i . dQ'_i) q_i / ||q_i||^2 at the end.
         if (wave == 1) rq_s[lane] = vec[256 + lane];
-        if (wave == 0) g_s[lane] = lane < clen ? a.log_alpha[(size_t)(tok0 + lane) * a.H + h] : 0.f;
-    }
-    __syncthreads();
-    if (wave == 0) {                                 // g_i = log gamma_i
-        float x = g_s[lane];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_up(x, off, kWave); if (lane >= off) x += y; }
-        g_s[lane] = x;
+        if (wave == 0) g_s[lane] = prefix_sum64(lane < clen ? a.log_alpha[(size_t)(tok0 + lane) * a.H + h] : 0.f, lane);     // g_i = log gamma_i
     }
 
     floatx4 dQ[KB], dKr[KB], dKw[KB], dP[4], N1[4];
@@ -641,10 +627,10 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         float x = yx[it];
-        x += __shfl_xor(x, 1, kWave); x += __shfl_xor(x, 2, kWave); x += __shfl_xor(x, 4, kWave);
+        x += dpp_mov<0xB1>(x); x += dpp_mov<0x4E>(x); x += dpp_mov<0x141>(x);
         if ((tid & 7) == 0) yx_s[(tid + 256 * it) >> 3] = x;
     }
-    sdot = wave_sum(sdot);
+    sdot = wave_sum_rows(sdot);
     if (lane == 0) red_s[wave] = sdot;
     __syncthreads();                                 // the slab areas are dead from here on
 
@@ -699,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) zsum += dKw[ct][e] * kk[e];
     }
-    zsum = wave_sum(zsum);
+    zsum = wave_sum_rows(zsum);
     if (lane == 0) red_s[4 + wave] = zsum;
 
     floatx4 E2[KB];
@@ -750,9 +736,9 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int i = 16 * wave + 4 * g + e;
-        const float db = row16_sum(dbr[e]) + yx_s[i];
-        const float dqv = row16_sum(dqr[e]);
-        const float dgv = row16_sum(dgr[e]) + dqv;
+        const float db = row_sum16(dbr[e]) + yx_s[i];
+        const float dqv = row_sum16(dqr[e]);
+        const float dgv = row_sum16(dgr[e]) + dqv;
         if (r == 0) { dbeta_s[i] = db; dg_s[i] = dgv; }
         cq[e] = -dqv * rq_s[i] * rq_s[i];
         c5[e] = (a.opts & kOptGdnBeta) ? 0.f : -2.f * beta_s[i] * db * invden_s[i];   // beta = eta does not depend on k
@@ -778,13 +764,13 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_kernel(BwdArgs<E> a)
     if (wave == 0) {
         // g_C sits at row 63 (rows past the end of a ragged chunk carry log alpha = 0), and the gradient of the
         // outgoing state meets it through <dS', S'> = gamma_C <dS', S> + sum_i (gamma_C/gamma_i) k_i.(dS' U_i)
-        float x = dg_s[lane];
-        if (lane == 63) x += eg_s[63] * (red_s[0] + red_s[1] + red_s[2] + red_s[3]) + (red_s[4] + red_s[5] + red_s[6] + red_s[7]);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const float y = __shfl_down(x, off, kWave); if (lane + off < 64) x += y; }
-        if (lane < clen) {
-            a.dlog_alpha[(size_t)(tok0 + lane) * a.H + h] = x;
-            a.deta[(size_t)(tok0 + lane) * a.H + h] = dbeta_s[lane] * invden_s[lane];
+        const int i = 63 - lane;                         // suffix sums: prefix sums from the last token on
+        float x = dg_s[i];
+        if (lane == 0) x += eg_s[63] * (red_s[0] + red_s[1] + red_s[2] + red_s[3]) + (red_s[4] + red_s[5] + red_s[6] + red_s[7]);
+        x = prefix_sum64(x, lane);
+        if (i < clen) {
+            a.dlog_alpha[(size_t)(tok0 + i) * a.H + h] = x;
+            a.deta[(size_t)(tok0 + i) * a.H + h] = dbeta_s[i] * invden_s[i];
         }
     }
 }
