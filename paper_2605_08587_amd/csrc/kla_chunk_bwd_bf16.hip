@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
         const float gC = *reinterpret_cast<const float*>(st + C::OFF_EG + 63 * 4);
         u32x2 Sq[KB];
 #pragma unroll
-        for (int kt = 0; kt < KB; ++kt) { Sq[kt] = to_quad(S[kt]); S[kt] = S[kt] * gC; }
+        for (int kt = 0; kt < KB; ++kt) { Sq[kt] = to_quad(S[kt]); if constexpr (!REV) S[kt] = S[kt] * gC; }
         if (store) put_checkpoint<DK>(reinterpret_cast<char*>(REV ? a.ds_chk : a.s_chk) + ((size_t)(ch0 + c) * a.H + h) * a.dv_dim * RB,
                                       slice * NW + wave, Sq, r, g);
 
@@ -274,17 +274,18 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             u32x4 psl[kTriPairs];
 #pragma unroll
             for (int i = 0; i < kTriPairs; ++i) psl[i] = ld16(sq + lane * 16 + C::OFF_P + i * 1024);
-            // ---- dU = diag(gamma_C/gamma_i) K dS' + P^T dO   (P^T upper triangular)
+            // ---- dU = diag(gamma_C/gamma_i) K dS' + P^T dO   (P^T upper triangular; the order of the sums here and in the state
+            //      update is that of kla_chunk_rev_bf16.hip, to the last bit)
             floatx4 dU[4];
 #pragma unroll
-            for (int it = 0; it < 4; ++it) dU[it] = edv[it] * ks[it];
+            for (int it = 0; it < 4; ++it) dU[it] = floatx4{0.f, 0.f, 0.f, 0.f};
             mma_bf16(dU[0], psl[triu_pair(0, 0)], vq[0], vq[1]);
             mma_bf16(dU[1], psl[triu_pair(1, 0)], vq[0], vq[1]);
 #pragma unroll
             for (int it = 0; it < 4; ++it) mma_bf16(dU[it], psl[triu_pair(it, 1)], vq[2], vq[3]);
             u32x2 dUq[4];
 #pragma unroll
-            for (int it = 0; it < 4; ++it) dUq[it] = to_quad(dU[it]);
+            for (int it = 0; it < 4; ++it) dUq[it] = to_quad(edv[it] * ks[it] + dU[it]);
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 0, sq + C::OFF_Q, kt[0][t][0], kt[0][t][1]);
             // ---- Y = M^T dU
@@ -312,10 +313,13 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             }
             if (store) put_rows(reinterpret_cast<char*>(a.Y) + (size_t)(t0 + 64L * c) * v_row, v_row, a.dv_dim, h, slice * NW + wave, Yq, clen, r, g);
             // ---- dS = gamma_C dS' + Q^T D_gamma dO - K^T D_gamma dV
+            floatx4 inc[KB];
 #pragma unroll
-            for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[0][t][0], kt[0][t][1], gdOq[0], gdOq[1]);
+            for (int t = 0; t < KB; ++t) { inc[t] = floatx4{0.f, 0.f, 0.f, 0.f}; mma_bf16(inc[t], kt[0][t][0], kt[0][t][1], gdOq[0], gdOq[1]); }
 #pragma unroll
-            for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[1][t][0], kt[1][t][1], gdOq[2], gdOq[3]);
+            for (int t = 0; t < KB; ++t) mma_bf16(inc[t], kt[1][t][0], kt[1][t][1], gdOq[2], gdOq[3]);
+#pragma unroll
+            for (int t = 0; t < KB; ++t) S[t] = S[t] * gC + inc[t];
 #pragma unroll
             for (int t = 0; t < KB; ++t) ktslot(t, 0, st, kt[0][t][0], kt[0][t][1]);
 #pragma unroll

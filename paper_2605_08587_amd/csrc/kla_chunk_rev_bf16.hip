@@ -312,14 +312,15 @@ __global__ __launch_bounds__((64 * RevCfg<DK>::NWAVES)) void bwd_rev_bf16_kernel
         u32x4 tsl[kTriPairs];
 #pragma unroll
         for (int j = 0; j < kTriPairs; ++j) tsl[j] = ld16(st + C::OFF_M + j * 1024 + lane * 16);
-        floatx4 edv[4], ngb[4];                          // gamma_C/gamma_i; -gamma_i beta_i, zero past a ragged end
+        floatx4 edv[4], egv[4], bev[4];                  // gamma_C/gamma_i; gamma_i, zero past a ragged end; beta_i
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             edv[it] = ld_f4(pG + 256 + 64 * it);
-            ngb[it] = -(ld_f4(pG + 64 * it) * ld_f4(pG + 512 + 64 * it));
+            egv[it] = ld_f4(pG + 64 * it);
+            bev[it] = ld_f4(pG + 512 + 64 * it);
             if (clen < 64) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ngb[it][e] = (16 * it + 4 * g + e < clen) ? ngb[it][e] : 0.f;
+                for (int e = 0; e < 4; ++e) egv[it][e] = (16 * it + 4 * g + e < clen) ? egv[it][e] : 0.f;
             }
         }
         // ---- dU = diag(gamma_C/gamma_i) K dS' + P^T dO
@@ -342,7 +343,7 @@ __global__ __launch_bounds__((64 * RevCfg<DK>::NWAVES)) void bwd_rev_bf16_kernel
         // ---- dS = gamma_C dS' + Q^T D_gamma dO - K^T D_gamma dV
         u32x2 gdXq[4];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) gdXq[it] = to_quad(ngb[it] * Y[it]);
+        for (int it = 0; it < 4; ++it) gdXq[it] = to_quad(-(egv[it] * (Y[it] * bev[it])));
 #pragma unroll
         for (int t = 0; t < KB; ++t) mma_bf16(S[t], kt[0][t][0], kt[0][t][1], gdXq[0], gdXq[1]);
 #pragma unroll
