@@ -10,6 +10,7 @@
 // has anyway), and the wave that stores rows takes Y in fp32 and the checkpoint from the chain and does the scaling by beta, the
 // roundings and the transposition. The chain keeps K dS', Y and K^T D_gamma dV: a visit is 1.2 us instead of 1.5.
 // LDS: ring A, three stages (K, M^T, the vectors), feeds the chain; ring B, two stages (Q, P^T, the dO slice, the vectors), its helper.
+// The order of the sums is that of the wider sweeps, so the bits do not depend on the batch that a sequence comes in.
 // A second barrier in the visit, passed as soon as the chain and the store wave have read what they were handed, lets each of the
 // hand-over areas exist once.
 // Measured, one wave per chain -> this, 8 heads, d = 128: 3000 tokens 70 -> 57 us; 2 x 700 22.8 -> 18.6; 3 x 2000 (192 chains)
