@@ -3,16 +3,17 @@
 // from the environment; everything is enqueued on the caller's stream.
 #include <math.h>
 
-#include <algorithm>
-#include <functional>
 #include <mutex>
 
 #include "../../include/kla.h"
 #include "kla_kernels.hpp"
+#include "kla_widths.hpp"
 
 namespace {
 
 using kla::bf16_t;
+using kla::busiest_cu;
+using kla::Lengths;
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -51,9 +52,6 @@ bool parse_tune(unsigned opts, Tune* t)
     t->decode_nt = nt == 0 ? -1 : (int)nt - 1;
     return true;
 }
-
-// The sequences of a call, as far as the lengths of its sweeps go: n of them of NT chunks each, or (cu != NULL) packed.
-struct Lengths { int n, NT; const int32_t* cu; };
 
 struct Plan {
     long n_chunks;       // over all sequences
@@ -96,7 +94,6 @@ int plan_segments(int N, int NT, int H, int dv, int dt, int n_seq, const Tune& t
     return G;
 }
 
-long busiest_cu(const Lengths& seqs, int H, int slices);
 int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tune& tune);
 
 // Packed batches: the order in which the scans take the sequences, behind the n_seq + 1 chunk offsets.  More than
@@ -178,42 +175,6 @@ int make_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const int3
                (p->tune.fused ? forced <= 2 : pair && dv <= 128);
     if (p->fused) { p->total = 256; p->order_bytes = 0; }
     return KLA_OK;
-}
-
-// Chunk steps the busiest CU takes in a sweep of `slices` workgroups per (sequence, head), one at a time on a CU (a bf16
-// workgroup fills one with its LDS).  Equal lengths: rounds of workgroups times chunks.  A packed batch starts its workgroups
-// longest sequence first, each on the first CU to become free, so a second round of shorter ones costs less than a
-// round: that schedule is played through, for batches small enough that it matters.
-long busiest_cu(const Lengths& s, int H, int slices)
-{
-    constexpr int kCUs = 256;
-    if (!s.cu) return (((long)s.n * H + 7) / 8 * 8 * slices + kCUs - 1) / kCUs * (s.NT > 1 ? s.NT : 1);
-    const long per_seq = (long)H * slices;
-    long longest = 0, total = 0;
-    for (int i = 0; i < s.n; ++i) {
-        const long c = ((long)s.cu[i + 1] - s.cu[i] + 63) / 64;
-        longest = std::max(longest, c);
-        total += c;
-    }
-    if (s.n > 64 || s.n * per_seq > 4096) return std::max(longest, (total * per_seq + kCUs - 1) / kCUs);
-    int len[64];
-    for (int i = 0; i < s.n; ++i) len[i] = (s.cu[i + 1] - s.cu[i] + 63) / 64;
-    std::sort(len, len + s.n, std::greater<int>());
-    struct { long load; int n; } level[kCUs + 1] = {{0, kCUs}};   // CUs by load, least first
-    int k = 1;
-    for (int i = 0; i < s.n && len[i] > 0; ++i) {
-        for (long left = per_seq; left > 0;) {
-            const int m = (int)std::min<long>(left, level[0].n);
-            const long to = level[0].load + len[i];
-            left -= m;
-            if ((level[0].n -= m) == 0) std::copy(level + 1, level + k--, level);
-            int at = 0;
-            while (at < k && level[at].load < to) ++at;
-            if (at < k && level[at].load == to) level[at].n += m;
-            else { std::copy_backward(level + at, level + k, level + k + 1); ++k; level[at] = {to, m}; }
-        }
-    }
-    return level[k - 1].load;
 }
 
 int scan_waves(const Lengths& seqs, int H, int dv, int dt, bool saves, const Tune& tune)
@@ -401,19 +362,6 @@ int make_bwd_plan(int N, int T, int H, int dk, int dv, int chunk, int dt, const 
     return KLA_OK;
 }
 
-// Compute waves of the bf16 sweeps: one (16 state columns) per workgroup while every chain has a CU to itself (reverse sweep of 4 x 2000
-// tokens, 8 heads: 50 us with one, 54 with two); beyond that its workgroups would take two rounds, where those of two waves (32
-// columns) take one (5 x 2000, 320 chains: 87 us with one, 55 with two). Four (64 columns)
-// where that shortens the work of the busiest CU: their visits are about 1.15 times as long (call of 8 x 4096 tokens, 8 heads, one
-// round either way: 469 us with two, 511 us with four; 9 x 2000, two rounds against one: 305, 251; 8 x 2048, d_v = 256: 392, 347;
-// 40 x 1000, five rounds against three: 584, 520)
-int sweep_waves(const Plan& p, int H, int dv)
-{
-    const long chains8 = ((long)p.n_states * H + 7) / 8 * 8;
-    if (chains8 * (dv / 16) <= 256) return 1;
-    return !p.tune.generic_bwd && dv >= 64 && busiest_cu(p.seqs, H, dv / 64) * 115 < busiest_cu(p.seqs, H, dv / 32) * 100 ? 4 : 2;
-}
-
 template <typename E>
 int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log_alpha, const float* eta, float eps,
                    const float* h0, const void* d_o, const float* d_hT, void* dq, void* dk_, void* dv_,
@@ -499,7 +447,7 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
             return kla::launch_bwd_assemble_bf16(ba, dk, pl.base.n_chunks, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;
         }
     }
-    [[maybe_unused]] const int waves = sizeof(E) == 2 ? sweep_waves(pl.base, H, dv) : 0;
+    [[maybe_unused]] const int waves = sizeof(E) == 2 ? kla::sweep_waves(pl.base.seqs, H, dv, !pl.base.tune.generic_bwd) : 0;
     if constexpr (sizeof(E) == 2) {
         if (fast) {
             if (!have && kla::launch_bwd_states_bf16(ba, dk, waves, st) != hipSuccess) return KLA_ERR_HIP;
@@ -610,8 +558,7 @@ int chunk_fwd_diag_impl(const void* q, const void* k, const void* v, const float
     sa.N = N; sa.T = T; sa.NT = NT; sa.H = H; sa.dv = dv;
     sa.wsT = ia.wsT; sa.wsP = reinterpret_cast<E*>(ws + pl.base.off_P); sa.wsG = ia.wsG; sa.opts = 0u;
     sa.seg_G = 0; sa.seg_Lc = 0; sa.kt_src = ia.ktilde; sa.gc_vec = ia.gc;
-    const long chains8 = ((long)pl.base.n_states * H + 7) / 8 * 8;
-    const int waves = chains8 * (dv / 16) > 256 ? 2 : 1;
+    const int waves = kla::diag_scan_waves(pl.base.seqs, H, dk, dv);
     if constexpr (sizeof(E) == 2) {
         if (!pl.base.tune.generic_scan)                  // else the plain kernel (A/B testing)
             return kla::launch_scan_bf16_diag(sa, dk, waves, st) == hipSuccess ? KLA_OK : KLA_ERR_HIP;

@@ -1,5 +1,6 @@
-// bf16 reverse state sweep of the backward pass for batches of at most 256 chains of sixteen state columns, a CU for each (see
-// kla_chunk_bwd.hip for the algebra; kla_chunk_bwd_bf16.hip has the reverse sweep of two and four chains per workgroup):
+// bf16 reverse state sweep of the backward pass for batches of at most 256 chains of sixteen state columns, a CU for each, and packed ones
+// whose further chains are so short that they fit behind the others (kla_widths.hpp; kla_chunk_bwd.hip has the algebra,
+// kla_chunk_bwd_bf16.hip the reverse sweep of two and four chains per workgroup):
 //
 //     dU = P^T dO + diag(gamma_C/gamma_i) K dS',   Y = M^T dU,   dV = B Y,
 //     dS <- gamma_C dS' + Q^T D_gamma dO - K^T D_gamma dV;      leaves dS'_c, Y, dV and finally dh0.
