@@ -52,18 +52,19 @@ inline long busiest_cu(const Lengths& s, int H, int slices, int start = 0)
 
 // Whether a sweep with one wave per workgroup ends before one with two (32 columns), whose step is `step2` percent as long: while every
 // chain has a CU to itself, and for a packed batch so unequal that the second round fits behind the longest sequence. A
-// workgroup's start is worth about two steps (which decides for many short sequences).
+// workgroup's start is taken as three steps, which decides for short sequences (backward of {211, 186, 148, 128, 329, 346, 265, 82, 254}
+// tokens, d_k = d_v = 64, 8 heads, training step 52 us with two waves and 53 with one: 9 steps against 10, by two steps a tie).
 inline bool one_wave(const Lengths& s, int H, int dv, int step2)
 {
     const long chains8 = ((long)s.n * H + 7) / 8 * 8;
-    return chains8 * (dv / 16) <= 256 || busiest_cu(s, H, dv / 16, 2) * 100 <= busiest_cu(s, H, dv / 32, 2) * step2;
+    return chains8 * (dv / 16) <= 256 || busiest_cu(s, H, dv / 16, 3) * 100 <= busiest_cu(s, H, dv / 32, 3) * step2;
 }
 
 // Compute waves of the backward's bf16 sweeps: one, two or (where the kernel has them) four. Two against one: a step of the reverse
 // sweep is 1.1 (every CU busy) to 1.4 times as long, of the forward sweep 1.0 to 1.1. Whole backward, d_k = d_v = 128, 8 heads, with one and
 // with two: 4 x 2000 tokens (256 chains) 139 and 143 us; 5 x 2000 (two rounds against one) 201 and 159; packed {4000, 300, 300, 300,
-// 200} 168 and 203, {2500, 1200, 1000, 800, 600} 134 and 155, {2000, 1900, 1900, 1800, 300} (38 steps against 34) 145.5 and 145.1 (d_k =
-// d_v = 64, 16 heads: 138 and 136), {3000, 100} of 16 heads, d_v = 256 (53 against 49) 190 and 193; 4000 and 40 x 200 (76 against 65) 260
+// 200} 168 and 203, {2500, 1200, 1000, 800, 600} 134 and 155, {2000, 1900, 1900, 1800, 300} (40 steps against 35) 145.5 and 145.1 (d_k =
+// d_v = 64, 16 heads: 138 and 136), {3000, 100} of 16 heads, d_v = 256 (55 against 50) 190 and 193; 4000 and 40 x 200 (87 against 66) 260
 // and 256; 8000 and 70 x 100 392 and 420. (The forward sweep by itself, whose workgroups of one wave fit twice on a CU, goes the same
 // way: 5 x 2000 8 us longer with one, {4000, ..} 2 shorter.)
 // Four (64 columns) where that shortens the work of the busiest CU: their visits are about 1.15 times as long as with two (8 x 4096
@@ -76,8 +77,8 @@ inline int sweep_waves(const Lengths& s, int H, int dv, bool four)
 }
 
 // Compute waves of the per-channel scan (bf16). Whole call, d_k = 128, 8 heads, d_v = 128, with one and two: 5 x 2000 tokens 132 and 94 us,
-// packed {4000, 300, 300, 300, 200} 109 and 114, {2500, 1200, 1000, 800, 600} 90 and 93, {2000, 1800, 1700, 1600, 300} (34 steps
-// either way) 83 and 84, {2000, 1900, 1900, 1800, 300} (38 against 34) 87 and 84, {130, 70, 60, 30, 20} (6 against 5) 25.5 and 23.8.
+// packed {4000, 300, 300, 300, 200} 109 and 114, {2500, 1200, 1000, 800, 600} 90 and 93, {2000, 1800, 1700, 1600, 300} (36 steps
+// against 35) 83 and 84, {2000, 1900, 1900, 1800, 300} (40 against 35) 87 and 84, {130, 70, 60, 30, 20} (8 against 6) 25.5 and 23.8.
 // At d_k = 64 two are as fast at equal steps ({4000, 300, 300, 300, 200}, 16 heads, d_v = 64: 103 and 100; 8 heads, d_v = 128: 79 and 79).
 inline int diag_scan_waves(const Lengths& s, int H, int dk, int dv) { return one_wave(s, H, dv, dk == 128 ? 100 : 0) ? 1 : 2; }
 
