@@ -66,8 +66,9 @@ def _backward(kla, lens, H, dk, dv):
     _one_by_one(kla, run, lens, names, [d[m].cuda() for m in ("q", "k", "v", "log_alpha", "eta")] + [d_o], [d["h0"].cuda(), d_hT])
 
 
-# more than 256 chains: two waves per workgroup (second rounds of one would be longer), then one in two rounds (tests/test_sweep_widths.py)
+# more than 256 chains: two waves per workgroup (second rounds of one would be longer), four, one in two rounds (tests/test_sweep_widths.py)
 MANY = [([65, 64, 63, 1, 128], 8, 128), ([200, 190, 180, 170, 129], 8, 128), ([385, 321, 320, 449, 448], 8, 128), ([257, 256, 255, 193, 192, 250], 16, 64),
+        ([192, 129, 190, 65, 130, 191, 150, 180, 140], 8, 128),
         ([300, 64, 1, 130, 60], 8, 128), ([449, 100, 0, 64, 1, 127], 16, 64)]
 
 
@@ -75,6 +76,13 @@ MANY = [([65, 64, 63, 1, 128], 8, 128), ([200, 190, 180, 170, 129], 8, 128), ([3
 @pytest.mark.parametrize("dk", [64, 128])
 def test_same_bits_as_few_chains(kla, lens, H, dk, dv):
     _backward(kla, lens, H, dk, dv)
+
+
+@pytest.mark.parametrize("lens,dk", [([2304, 2241, 2303, 2250, 2277, 2299], 128), ([3584, 3583, 3521, 3550, 3577, 3530], 64)])
+def test_lines_asked_for_ahead(kla, lens, dk):
+    """More than 144 MB of K, Q, M^T and P^T under two waves per workgroup: the only sweep that touches lines ahead of its copies."""
+    assert 16 * sum((n + 63) // 64 for n in lens) * (2 * 64 * dk * 2 + 2 * 6144) > 144 << 20
+    _backward(kla, lens, 16, dk, 64)
 
 
 @pytest.mark.parametrize("lens,H,dv", MANY)

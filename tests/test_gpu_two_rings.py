@@ -30,7 +30,7 @@ def test_reverse_sweep(lens, H, dv):
         pytest.skip("no GPU")
     import paper_2605_08587_amd as kla
     # more than one round of workgroups of two waves, one of four
-    assert len(lens) * H * (dv // 64) <= 256 < len(lens) * H * (dv // 32) and H * (dv // 32) < 192
+    assert len(lens) * H * (dv // 64) <= 256 < len(lens) * H * (dv // 32) and (H + 7) // 8 * 8 * (dv // 16) <= 256
     off = [sum(lens[:i]) for i in range(len(lens) + 1)]
     cu = torch.tensor(off, dtype=torch.int32)
     d = kla_inputs.chunk_inputs(1, off[-1], H, 128, dv, seed=dv + off[-1], h0_std=0.3, n_h0=len(lens), log_alpha_scale=0.1)
