@@ -410,6 +410,9 @@ int chunk_bwd_impl(const void* q, const void* k, const void* v, const float* log
     // What the slices of a head all copy in the reverse sweep, K, Q, M^T and P^T: beyond some 144 MB (of a memory-side cache of 256, which
     // the checkpoints, Y and dO go through too) it comes from HBM, and asking ahead shortens the copies' way (8 x 4096 tokens, 8
     // heads: 143 -> 122 us; 7 x 4096, 161 MB: 130 -> 119); below, it is there already (8 x 3000, 135 MB: 90.3, 90.5; 8 x 2048: 63.7, 65.7).
+    // Whole backward, not asked and asked, 8 heads: 4 x 8192, d_v = 256 729 and 678 us; 16 x 2048, d_v = 64 (two slices, which ask for K and
+    // Q alone) 271 and 267; one sequence of 65536 in segments 1244 and 1224; d_k = 64: 16 x 4096, d_v = 64 408 and 402, 8 x 8192, d_v = 128
+    // 609 and 605.
     ba.touch = (size_t)pl.base.n_chunks * H * (2 * 64 * dk * sizeof(E) + (size_t)2 * 384 * 8 * sizeof(E)) > ((size_t)144 << 20);
     if constexpr (sizeof(E) == 2) {
         if (fast && pl.base.seg_G > 1) {

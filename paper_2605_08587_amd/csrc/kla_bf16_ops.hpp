@@ -54,8 +54,9 @@ __device__ __forceinline__ void dma16(const char* gbase_uniform, int lane_off, c
 
 // One dword of one 128-byte line that all slices of a head will copy: the lines of two [64 x d_k] tiles (rows of RB bytes, `stride` apart,
 // from row `row0` of `rows` on) and the first `n_rec` lines at `rec`, counted through in this order; i: which.  A wave that has nothing
-// else to wait for asks for its slice's share some chunks ahead of the copies, which then find their lines in L2: a CU's
-// copies are in flight by the 64 KB, so what they take in per cycle falls with their latency.  The value is of no interest, but has to be
+// else to wait for asks for 128 of them, slice s for 128 s .. 128 s + 127, some chunks ahead of the copies, which then find their lines in
+// L2: a CU's copies are in flight by the 64 KB, so what they take in per cycle falls with their latency.  (Where there are fewer slices
+// than lines by the 128, the last lines are nobody's.)  The value is of no interest, but has to be
 // waited for (by the next call's caller) before its register is free.
 template <int RB> __device__ __forceinline__ uint32_t touch_line(const char* tile0, const char* tile1, size_t stride, int row0, int rows,
                                                                  const char* rec, int n_rec, int i)

@@ -353,8 +353,9 @@ __global__ __launch_bounds__(64 * NW + (REV ? 128 : 64)) void bwd_sweep_bf16_ker
             // ---- the store wave: after the barrier that ends visit i, chunk_of(i) is complete in the staging area of
             //      parity i & 1, which the compute waves write again only in visit i + 2, behind the barrier this wave
             //      reaches next
-            //      Two chains: it also touches the lines of K, Q, M^T and P^T of the visit AHEAD later (a.touch: where these are more
-            //      than the memory-side cache holds on to).
+            //      Two chains: it also touches lines of K, Q, M^T and P^T of the visit AHEAD later (a.touch: where these are more
+            //      than the memory-side cache holds on to). At d_k = 128 the 352 lines are those of three slices; the two slices of
+            //      d_v = 64 ask for K and Q alone.  At d_k = 64 two slices ask for all 224.
             constexpr int AHEAD = 4;
             uint32_t seen[2] = {0u, 0u};
             __syncthreads();
@@ -708,7 +709,7 @@ __global__ __launch_bounds__(256, 2) void bwd_assemble_bf16_kernel(BwdArgs<bf16_
     char* Et = lds + OFF_E1;
     char* Dt = Et + 8192;
     char* Bt = lds + OFF_DP;
-    static_assert(2 * 8192 <= MB, "the tiles fit where the fp32 staging tiles go");
+    static_assert(2 * 8192 <= MB, "the tiles fit where the staging tiles of dq and dk go");
     {
         const floatx4 gi = ld_f4(reinterpret_cast<const char*>(g_s + 16 * wave + 4 * g)), rqi = ld_f4(reinterpret_cast<const char*>(rq_s + 16 * wave + 4 * g)),
                       bi = ld_f4(reinterpret_cast<const char*>(beta_s + 16 * wave + 4 * g));

@@ -84,8 +84,10 @@ __device__ __forceinline__ void write_tri(char* out, const float* m, const float
 
 // Phases 3-6 of the intra-chunk stage, shared by its variants: from L (strictly lower triangular, fp32, in Lm) and
 // the fp32 image of P (in Pm) to the record at `rec`: T' = (I + L)^{-1} B and P (forward), or T', M^T and P^T
-// (backward).  Tm receives (I + L)^{-1}; the strictly-upper tiles of Lm, Pm, Tm must be zero on entry.  Called by all
-// 256 threads after a barrier; contains barriers.
+// (backward).  Tm receives (I + L)^{-1}.  What must be zero on entry: the 16x16 tiles (0,1) and (2,3) of Pm and of Tm, and Pm above
+// the diagonal inside its diagonal tiles - the stored tile-pairs, of the matrix or of its transpose, take these in, and phase 5 those
+// two tiles of Tm.  The other upper tiles of both, and Lm on and above its diagonal, are not read and may hold anything.  Called by
+// all 256 threads after a barrier; contains barriers.
 template <typename E, bool BWD>
 __device__ __forceinline__ void invert_and_store(const float* Lm, float* Tm, const float* Pm, const float* beta_s, char* rec,
                                                  int tid)

@@ -1119,8 +1119,9 @@ __global__ __launch_bounds__((64 * Cfg<DK, NW, DG, FU>::NWAVES)) void scan_bf16_
             // its parity, which the compute waves write again only in step c + 2, behind the barrier this wave reaches
             // after the write-out
             // Diagonal gating, d_k = 128, four slices or more: it also touches the lines of K~, K+, Q+ and the record AHEAD chunks
-            // ahead (8 x 4096 tokens, 8 heads: scan 110.5 -> 102 us; 6 x 1500 39.6 -> 39.3, 4 x 1500 37.4 -> 36.5; d_k = d_v = 64, two slices:
-            // 32 -> 34.  K, T' and Q of the plain scans of four waves: 130 -> 155 for one 65K sequence, 95.5 -> 98 for a packed batch).
+            // ahead, 480 of them, so the first four slices do (8 x 4096 tokens, 8 heads: scan 110.5 -> 102 us; 6 x 1500 39.6 -> 39.3, 4 x 1500
+            // 37.4 -> 36.5; whole calls, d_v = 256: 4 x 4096 179 -> 161, 1 x 2000 58.6 -> 57.8, six packed of 300 .. 2000 94 -> 84; d_k = d_v =
+            // 64, two slices: 32 -> 34; d_k = 64, four and eight: 8 x 4096 168 -> 174, 4 x 4096 128 -> 130.  K, T' and Q of the plain scans of four waves: 130 -> 155 for one 65K sequence, 95.5 -> 98 for a packed batch).
             constexpr int AHEAD = 2;
             constexpr bool TOUCH = DG && DK == 128;
             uint32_t seen[2] = {0u, 0u};
